@@ -1,15 +1,17 @@
-"""ctypes binding of liblvlm.so: argument marshalling only.
+"""Binding of liblvlm.so: argument marshalling only.
 
 Every step of the path runs in the library's HIP kernels; this module turns
 torch tensors (used for device memory and streams) into the pointers, strides
-and plain structs of include/lvlm.h and raises on any non-zero status.  There
-is no fallback: if the shared library is missing the import fails.
+and plain structs of include/lvlm.h and raises on any non-zero status.  The
+calls of the path are native (csrc/torch_binding.cpp, built beside the
+library); the descriptors and helper calls here go through ctypes.  There is
+no fallback: if a shared library is missing the import fails.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
-from typing import Optional, Sequence
+from typing import Optional
 
 import torch
 
@@ -137,6 +139,22 @@ def _load():
 lib = _load()
 
 
+def _load_calls():
+    try:
+        from . import _torch_binding
+    except ImportError as e:
+        raise ImportError("the native side of the binding is missing or does not fit this torch: run "
+                          f"`python -c 'import __graft_entry__ as g; g.build()'` ({e})") from e
+    address = lambda name: C.cast(getattr(lib, name), C.c_void_p).value          # noqa: E731
+    _torch_binding.setup(LvlmError, *(address("lvlm_" + n) for n in (
+        "last_error", "workspace_bytes", "set_workspace", "score_tokens", "score_from_probs", "prefill_attn", "merge_compact",
+        "merge_similar", "kv_compress", "decode_attn", "decode_attn_static")))
+    return _torch_binding.ContextCalls
+
+
+_ContextCalls = _load_calls()
+
+
 def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else C.c_void_p(t.data_ptr())
 
@@ -161,7 +179,7 @@ def merge_weights(mode: int, m: int) -> torch.Tensor:
     return torch.tensor(list(out), dtype=torch.float32)
 
 
-class Context:
+class Context(_ContextCalls):
     """One lvlm_ctx plus a grow-only workspace tensor (device memory via torch)."""
 
     def __init__(self, device: int = 0):
@@ -170,10 +188,11 @@ class Context:
         if st:
             raise LvlmError(st, "lvlm_create")
         self.device = device
-        self._ws: Optional[torch.Tensor] = None
+        self._attach(self._h.value, device)
 
     def close(self):
         if self._h:
+            self._attach(0, self.device)
             lib.lvlm_destroy(self._h)
             self._h = C.c_void_p()
 
@@ -191,12 +210,6 @@ class Context:
         n = C.c_size_t()
         self._check(lib.lvlm_workspace_bytes(self._h, op, C.byref(desc), C.byref(n)))
         return n.value
-
-    def reserve(self, nbytes: int):
-        """Grows the attached workspace (never shrinks); call outside graph capture."""
-        if self._ws is None or self._ws.numel() < nbytes:
-            self._ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=f"cuda:{self.device}")
-            self._check(lib.lvlm_set_workspace(self._h, _ptr(self._ws), self._ws.numel()))
 
     def set_workspace(self, ws: Optional[torch.Tensor]):
         self._ws = ws
@@ -219,6 +232,9 @@ class Context:
         return {arr[i].name.decode(): (arr[i].calls, arr[i].total_ms, arr[i].min_ms, arr[i].max_ms)
                 for i in range(n.value)}
 
+    # score_tokens, score_from_probs, prefill_attn, merge_compact, merge_similar, kv_compress and decode_attn are
+    # native (csrc/torch_binding.cpp), with the argument names and defaults that help(Context) shows.
+
     # ---- step 1 ----
     def score_desc(self, q, k, *, q_pos0, img_begin, n_img, scale=None, causal=True, score_head=None) -> ScoreDesc:
         B, T, Hq, hd = q.shape
@@ -237,142 +253,6 @@ class Context:
         self._check(lib.lvlm_score_plan(self._h, C.byref(desc), C.byref(form)))
         return form.value
 
-    def score_tokens(self, q, k, *, q_pos0, img_begin, n_img, scale=None, causal=True, row_lse=None,
-                     score_head=None, score_mean=None, reserve=True):
-        """lvlm_score_tokens.  q [B,T,Hq,d], k [B,N,Hkv,d] -> (score_head [B,Hkv,n_img], score_mean [B,n_img])."""
-        d = self.score_desc(q, k, q_pos0=q_pos0, img_begin=img_begin, n_img=n_img, scale=scale, causal=causal,
-                            score_head=score_head)
-        if score_head is None:
-            score_head = torch.empty(d.B, d.Hkv, n_img, dtype=torch.float32, device=q.device)
-        if score_mean is None:
-            score_mean = torch.empty(d.B, n_img, dtype=torch.float32, device=q.device)
-        if reserve:
-            self.reserve(self.workspace_bytes(OP_SCORE, d))
-        self._check(lib.lvlm_score_tokens(self._h, _stream(), C.byref(d), _ptr(q), _ptr(k), _ptr(row_lse),
-                                          _ptr(score_head), _ptr(score_mean)))
-        return score_head, score_mean
-
-    def score_from_probs(self, probs, *, n_kv_heads, img_begin, n_img, score_head=None, score_mean=None, reserve=True):
-        """lvlm_score_from_probs.  probs [B,Hq,T,N] (softmax rows of the query rows to be summed) ->
-        (score_head [B,Hkv,n_img], score_mean [B,n_img])."""
-        B, Hq, T, N = probs.shape
-        assert probs.stride(3) == 1, "the key axis must be contiguous"
-        d = ProbsDesc(_DTYPE[probs.dtype], B, N, T, Hq, n_kv_heads, img_begin, n_img,
-                      probs.stride(0), probs.stride(1), probs.stride(2),
-                      0 if score_head is None else score_head.stride(0),
-                      0 if score_head is None else score_head.stride(1))
-        if score_head is None:
-            score_head = torch.empty(B, n_kv_heads, n_img, dtype=torch.float32, device=probs.device)
-        if score_mean is None:
-            score_mean = torch.empty(B, n_img, dtype=torch.float32, device=probs.device)
-        if reserve:
-            self.reserve(self.workspace_bytes(OP_SCORE_PROBS, d))
-        self._check(lib.lvlm_score_from_probs(self._h, _stream(), C.byref(d), _ptr(probs), _ptr(score_head),
-                                              _ptr(score_mean)))
-        return score_head, score_mean
-
-    def prefill_attn(self, q, k, v, *, scale=None, causal=True, n_text=0, img_begin=0, n_img=0, out=None, row_lse=None,
-                     score_head=None, score_mean=None, reserve=True):
-        """lvlm_prefill_attn.  q [B,N,Hq,d], k, v [B,N,Hkv,d] (any strides with a contiguous head vector) ->
-        (out [B,N,Hq,d], row_lse [B,Hq,N], score_head, score_mean); the scores (of the last n_text rows over
-        the image keys) only when n_text > 0, else None."""
-        B, N, Hq, hd = q.shape
-        Hkv = k.shape[2]
-        assert k.shape == (B, N, Hkv, hd) and v.shape == (B, N, Hkv, hd)
-        assert q.stride(3) == 1 and k.stride(3) == 1 and v.stride(3) == 1
-        if out is None:
-            out = torch.empty(B, N, Hq, hd, dtype=q.dtype, device=q.device)
-        if row_lse is None:
-            row_lse = torch.empty(B, Hq, N, dtype=torch.float32, device=q.device)
-        assert out.stride(3) == 1 and row_lse.is_contiguous()
-        if n_text > 0:
-            if score_head is None:
-                score_head = torch.empty(B, Hkv, n_img, dtype=torch.float32, device=q.device)
-            if score_mean is None:
-                score_mean = torch.empty(B, n_img, dtype=torch.float32, device=q.device)
-        dense = score_head is None or score_head.is_contiguous()
-        d = PrefillDesc(_DTYPE[q.dtype], B, N, Hq, Hkv, hd, int(causal), float(scale if scale is not None else hd ** -0.5),
-                        n_text, img_begin, n_img, q.stride(0), q.stride(1), q.stride(2), k.stride(0), k.stride(1),
-                        k.stride(2), v.stride(0), v.stride(1), v.stride(2), out.stride(0), out.stride(1), out.stride(2),
-                        0 if dense else score_head.stride(0), 0 if dense else score_head.stride(1))
-        if reserve:
-            self.reserve(self.workspace_bytes(OP_PREFILL_ATTN, d))
-        self._check(lib.lvlm_prefill_attn(self._h, _stream(), C.byref(d), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(row_lse),
-                                          _ptr(score_head), _ptr(score_mean)))
-        return out, row_lse, score_head, score_mean
-
-    # ---- steps 2-4 ----
-    @staticmethod
-    def _planes(planes: Sequence[torch.Tensor], outs: Sequence[torch.Tensor], rules: Sequence[int]):
-        arr = (Plane * len(planes))()
-        for i, (src, dst, rule) in enumerate(zip(planes, outs, rules)):
-            assert src.dim() == 3 and src.stride(2) == 1 and src.stride(1) == src.shape[2]
-            assert dst.stride(2) == 1 and dst.stride(1) == dst.shape[2]
-            arr[i] = Plane(src.data_ptr(), dst.data_ptr(), src.stride(0), dst.stride(0), src.shape[2],
-                           _DTYPE[src.dtype], rule, 0)
-        return arr
-
-    def merge_compact(self, planes, score_mean, *, img_begin, n_img, n_keep, w=None, rules=None, outs=None,
-                      keep_idx=None, merged_idx=None, reserve=True):
-        """lvlm_merge_compact.  planes: list of [B,N,row] tensors -> (outs, keep_idx, merged_idx)."""
-        B, N = planes[0].shape[0], planes[0].shape[1]
-        r = n_img - n_keep
-        rules = list(rules) if rules is not None else [RULE_WEIGHTED] * len(planes)
-        if outs is None:
-            outs = [torch.empty(B, N - r, p.shape[2], dtype=p.dtype, device=p.device) for p in planes]
-        dev = planes[0].device
-        if keep_idx is None:
-            keep_idx = torch.empty(B, max(n_keep - 1, 0) if r > 0 else n_img, dtype=torch.int32, device=dev)
-        if merged_idx is None:
-            merged_idx = torch.empty(B, r + 1 if r > 0 else 0, dtype=torch.int32, device=dev)
-        d = MergeDesc(B, N, img_begin, n_img, n_keep, len(planes))
-        arr = self._planes(planes, outs, rules)
-        if reserve:
-            self.reserve(self.workspace_bytes(OP_MERGE, MergeQuery(C.pointer(d), arr)))
-        self._check(lib.lvlm_merge_compact(self._h, _stream(), C.byref(d), _ptr(score_mean), _ptr(w), arr,
-                                           _ptr(keep_idx) if keep_idx.numel() else None,
-                                           _ptr(merged_idx) if merged_idx.numel() else None))
-        return outs, keep_idx, merged_idx
-
-    # ---- step 3b ----
-    def merge_similar(self, planes, score_mean, *, img_begin, n_img, n_keep, size=None, rules=None, outs=None,
-                      size_out=None, keep_idx=None, assign=None, reserve=True):
-        """lvlm_merge_similar.  planes: list of [B,N,row] tensors -> (outs, keep_idx, assign, size_out)."""
-        B, N = planes[0].shape[0], planes[0].shape[1]
-        r = n_img - n_keep
-        rules = list(rules) if rules is not None else [RULE_WEIGHTED] * len(planes)
-        dev = planes[0].device
-        if outs is None:
-            outs = [torch.empty(B, N - r, p.shape[2], dtype=p.dtype, device=p.device) for p in planes]
-        if keep_idx is None:
-            keep_idx = torch.empty(B, n_keep, dtype=torch.int32, device=dev)
-        if assign is None:
-            assign = torch.empty(B, n_img, dtype=torch.int32, device=dev)
-        if size_out is None:
-            size_out = torch.empty(B, n_keep, dtype=torch.float32, device=dev)
-        d = MergeDesc(B, N, img_begin, n_img, n_keep, len(planes))
-        arr = self._planes(planes, outs, rules)
-        if reserve:
-            self.reserve(self.workspace_bytes(OP_MERGE_SIMILAR, MergeQuery(C.pointer(d), arr)))
-        self._check(lib.lvlm_merge_similar(self._h, _stream(), C.byref(d), _ptr(score_mean), arr, _ptr(size),
-                                           _ptr(size_out), _ptr(keep_idx), _ptr(assign)))
-        return outs, keep_idx, assign, size_out
-
-    # ---- step 5 ----
-    def kv_compress(self, k_cache, v_cache, score, kind, orig_pos, length, *, mode, order=ORDER_STABLE,
-                    beta=0.995, budget=0, n_recent=0, len_bound=0, n_evicted=None, reserve=True, want_evicted=True):
-        """lvlm_kv_compress (in place).  Caches [B,Hkv,Lmax,d]; returns n_evicted [B,Hkv] (None if not wanted)."""
-        B, Hkv, Lmax, hd = k_cache.shape
-        assert k_cache.is_contiguous() and v_cache.is_contiguous() and score.is_contiguous()
-        d = KvDesc(_DTYPE[k_cache.dtype], B, Hkv, hd, Lmax, len_bound, mode, order, budget, n_recent, float(beta))
-        if n_evicted is None and want_evicted:
-            n_evicted = torch.empty(B, Hkv, dtype=torch.int32, device=k_cache.device)
-        if reserve:
-            self.reserve(self.workspace_bytes(OP_KV_COMPRESS, d))
-        self._check(lib.lvlm_kv_compress(self._h, _stream(), C.byref(d), _ptr(k_cache), _ptr(v_cache), _ptr(score),
-                                         _ptr(kind), _ptr(orig_pos), _ptr(length), _ptr(n_evicted)))
-        return n_evicted
-
     # ---- step 6 ----
     def decode_plan(self, desc: AttnDesc):
         """lvlm_decode_plan: (n_split, split_len, form); form 0 = one tile per wave, 1 = some wave has a second tile,
@@ -380,22 +260,3 @@ class Context:
         n, sl, form = C.c_int32(), C.c_int32(), C.c_int32()
         self._check(lib.lvlm_decode_plan(self._h, C.byref(desc), C.byref(n), C.byref(sl), C.byref(form)))
         return n.value, sl.value, form.value
-
-    def decode_attn(self, q, k_new, v_new, k_cache, v_cache, score, kind, orig_pos, length, *, scale=None,
-                    score_decay=1.0, new_kind=KIND_GENERATED, new_pos=0, len_bound=0, evict_budget=0, evict_recent=0,
-                    out=None, reserve=True, static_scratch=False):
-        """lvlm_decode_attn.  q [B,Hq,d], k_new/v_new [B,Hkv,d] or None -> out [B,Hq,d].
-        static_scratch: lvlm_decode_attn_static instead (the library's own fixed scratch array, no workspace)."""
-        B, Hq, hd = q.shape
-        _, Hkv, Lmax, _ = k_cache.shape
-        assert q.is_contiguous() and k_cache.is_contiguous() and v_cache.is_contiguous()
-        d = AttnDesc(_DTYPE[q.dtype], B, Hq, Hkv, hd, Lmax, len_bound, new_kind, new_pos,
-                     float(hd ** -0.5 if scale is None else scale), float(score_decay), evict_budget, evict_recent)
-        if out is None:
-            out = torch.empty_like(q)
-        if reserve and not static_scratch:
-            self.reserve(self.workspace_bytes(OP_DECODE_ATTN, d))
-        call = lib.lvlm_decode_attn_static if static_scratch else lib.lvlm_decode_attn
-        self._check(call(self._h, _stream(), C.byref(d), _ptr(q), _ptr(k_new), _ptr(v_new),
-                        _ptr(k_cache), _ptr(v_cache), _ptr(score), _ptr(kind), _ptr(orig_pos), _ptr(length), _ptr(out)))
-        return out

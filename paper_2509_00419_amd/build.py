@@ -1,13 +1,16 @@
-"""Builds liblvlm.so (the C-ABI library) in-tree with hipcc for gfx950."""
+"""Builds liblvlm.so (the C-ABI library) in-tree with hipcc for gfx950, and the native side of the torch binding."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "liblvlm.so")
+BINDING_PATH = os.path.join(HERE, "_torch_binding.so")
 SOURCES = ["api.hip", "score.hip", "merge.hip", "sim.hip", "kv.hip", "attn.hip", "prefill.hip", "scratch.hip", "probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -18,8 +21,20 @@ FLAGS = [
 ]
 
 
+def binding_command() -> list:
+    """The command that builds the native side of binding.py (host code only: torch tensors to the C ABI)."""
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+            "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",          # what the HIP and torch headers ask of a host compiler
+            "-I" + os.path.join(torch_dir, "include"), "-I" + os.path.join(torch_dir, "include/torch/csrc/api/include"),
+            "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "torch_binding.cpp"), "-o", BINDING_PATH, "-L" + os.path.join(torch_dir, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
 def build_library(verbose: bool = True) -> str:
-    """Compiles every source and links the shared library; returns its path."""
+    """Compiles every source, links the shared library and the torch binding; returns the library's path."""
     objs = []
     build_dir = os.path.join(HERE, "_build")
     os.makedirs(build_dir, exist_ok=True)
@@ -31,6 +46,10 @@ def build_library(verbose: bool = True) -> str:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    cmd = binding_command()
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    procs.append(("torch_binding.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     failed = False
     for src, p in procs:
         out, _ = p.communicate()
@@ -41,7 +60,7 @@ def build_library(verbose: bool = True) -> str:
         elif verbose and out:
             print(out)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("the compiler failed")
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     if verbose:
         print(" ".join(cmd), flush=True)
