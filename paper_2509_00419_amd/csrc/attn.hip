@@ -4,14 +4,11 @@
 //
 // The step streams K and V of every retained entry once; everything else is
 // arranged around that stream:
-//   attn_partial_kernel  grid (split, KV head, batch).  A wave takes 32 entries
-//       at a time.  K rows go straight from global memory into the A operand of
-//       a 32x32 MFMA (rows = entries, columns = the G query heads of the group,
-//       padded), V rows are loaded in their natural, fully coalesced layout.
-//       Softmax is online (fp32, log2 domain); the 32 x G probabilities pass
-//       through a wave-private LDS tile so that P.V can run on the vector ALUs
-//       against the natural V layout.  Each workgroup leaves (max, sum, o) of
-//       its split and, if importance is tracked, the raw logits of its entries.
+//   attn_partial_*_kernel  grid (split, KV head, batch).  A wave takes 32 entries
+//       at a time: bf16 on 16x16 MFMA tiles (entries x the group's query heads),
+//       fp32 on the vector ALUs.  Softmax is online (fp32, log2 domain).  Each
+//       workgroup leaves (max, sum, o) of its split and, if importance is
+//       tracked, the raw logits of its entries.
 //       The entry being appended is taken from k_new / v_new instead of the
 //       cache, so no workgroup depends on another one's write.
 //   attn_combine_kernel  folds the splits, writes the output rows, turns the
@@ -85,83 +82,63 @@ __device__ __forceinline__ bf16x8 pack_bf16x8(const float *p) {
     return __builtin_bit_cast(bf16x8, u);
 }
 
-template <int DT, int HD>
-struct TileRegs {
-    static constexpr int ROWB = HD * esize<DT>();
-    static constexpr int UPR = ROWB / 16;
-    static constexpr int KSUB = 64 / UPR;
-    static constexpr int VPL = 32 / KSUB;
-    HalfRow<DT, HD> kf;   // K rows as the MFMA A operand: lane = (entry l32, half hf)
-    uint4 vv[VPL];        // V rows in natural layout: lane = (unit lane % UPR, entry lane / UPR + KSUB * i)
-};
-
-template <int DT, int HD, int GP>
-__global__ __launch_bounds__(256) void attn_partial_kernel(AttnArgs a) {
-    constexpr int ES = esize<DT>();
-    constexpr int ROWB = HD * ES;
-    constexpr int NV = HalfRow<DT, HD>::NV;
+// fp32 variant, on the vector ALUs: the fp32 matrix instruction multiplies 16 or 32 head columns whatever the group holds,
+// and at its rate (64 cycles for 4096 flops) the padding, not memory, would bound the launch -- a group of one
+// head took 4096 cycles per 32 entries, 31 of 32 columns zero.  Here a tile of 32 entries costs some 450 cycles per query head.
+// Lane = (l16, kg): the 16 lanes of row group kg hold one K row and one V row per load instruction (fully coalesced),
+// lane l16 the channels 64 u + 4 l16 + c; instruction i of a tile brings entries 4 i + kg.  A logit is
+// G 4-channel products summed over the 16 lanes by four data-parallel moves, after which each of them has it and
+// weighs its own channels of the V row.  The four row groups see different entries and keep a sum and an output each;
+// they meet, like the four waves, at the end.
+// Measured (heads of 64 channels, fold included, 32x32 matrix instruction -> here): one head per group 4 x 257 entries
+// 12.4 -> 7.0 us, 64 x 4097 46 -> 26 us; four per group 8 x 2049 13.2 -> 10.6 us; eight per group, where the exponentials of
+// 64 logits per tile weigh most, 13.5 -> 14.2 us (of 128 channels 25.9 -> 23.2 us).
+template <int HD, int GP>
+__global__ __launch_bounds__(256) void attn_partial_f32_kernel(AttnArgs a) {
+    constexpr int ROWB = HD * 4;
     constexpr int UPR = ROWB / 16;        // 16-byte units per row
-    constexpr int KSUB = 64 / UPR;        // rows a wave covers with one load instruction
-    constexpr int VPL = 32 / KSUB;        // V units per lane per 32-entry tile
-    constexpr int NB = HD / 32;           // 32-row blocks of the transposed output
-    constexpr int VPITCH = ROWB + 16;     // LDS row pitch of the V tile: the two lane halves hit different banks
-    static_assert(UPR <= 64 && KSUB >= 1, "row too long for one wave");
-
-    __shared__ __attribute__((aligned(16))) char v_lds[4][32 * VPITCH];
-    __shared__ float wm[4][GP], wl[4][GP];
-    __shared__ __attribute__((aligned(16))) float wo[4][GP][HD];
+    constexpr int CU = HD / 64;           // units of a row per lane
+    __shared__ float wm[4][GP], wl[4][4][GP];
+    __shared__ __attribute__((aligned(16))) float wo[4][4][GP][HD];      // per wave and row group
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int hf = lane >> 5, l32 = lane & 31;
+    const int l16 = lane & 15, kg = lane >> 4;
     const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
     const int hg = b * a.Hkv + g;
     const long long cbase = (long long)hg * a.Lmax;
-    const char *kc = a.k + cbase * ROWB;
-    const char *vc = a.v + cbase * ROWB;
-    const int vunit = lane % UPR, vsub = lane / UPR;
+    const char *kc = a.k + cbase * ROWB + 16 * l16;
+    const char *vc = a.v + cbase * ROWB + 16 * l16;
     const int s_lo = split * a.split_len;
+    const int j_first = s_lo + 32 * wave;
 
+    float4 kf[8][CU], vf[8][CU];
     // Loads do not wait for the length: any slot below Lmax is readable, stale rows are masked later.
-    auto load_tile = [&](int j0, TileRegs<DT, HD> &t) {
-        const int jk = min(j0 + l32, a.Lmax - 1);
-        const char *ks = kc + (long long)jk * ROWB + hf * (ROWB / 2);
+    auto load = [&](float4 (&dst)[8][CU], const char *base, int j0) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) t.kf.v[i] = *reinterpret_cast<const uint4 *>(ks + 16 * i);
+        for (int i = 0; i < 8; ++i) {
+            const char *src = base + (long long)min(j0 + 4 * i + kg, a.Lmax - 1) * ROWB;
 #pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            const int jv = min(j0 + vsub + KSUB * i, a.Lmax - 1);
-            t.vv[i] = *reinterpret_cast<const uint4 *>(vc + (long long)jv * ROWB + 16 * vunit);
+            for (int u = 0; u < CU; ++u) dst[i][u] = *reinterpret_cast<const float4 *>(src + 256 * u);
         }
     };
-    TileRegs<DT, HD> cur;
-    const int j_first = s_lo + 32 * wave;
-    if (j_first < a.Lmax) load_tile(j_first, cur);
-
-    // query operand: column l32 of the product is head l32 of the group (zero beyond G)
-    HalfRow<DT, HD> qf;
-    if (l32 < a.G) {
-        const char *src = a.q + ((long long)b * a.Hq + g * a.G + l32) * ROWB + hf * (ROWB / 2);
+    if (j_first < a.Lmax) load(kf, kc, j_first);
+    float4 qf[GP][CU];
 #pragma unroll
-        for (int i = 0; i < NV; ++i) qf.v[i] = *reinterpret_cast<const uint4 *>(src + 16 * i);
-    } else {
+    for (int h = 0; h < GP; ++h) {
+        const char *src = a.q + ((long long)b * a.Hq + g * a.G + min(h, a.G - 1)) * ROWB + 16 * l16;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) qf.v[i] = make_uint4(0, 0, 0, 0);
+        for (int u = 0; u < CU; ++u) {
+            const float4 x = *reinterpret_cast<const float4 *>(src + 256 * u);
+            qf[h][u] = make_float4(x.x * a.scale_log2, x.y * a.scale_log2, x.z * a.scale_log2, x.w * a.scale_log2);
+        }
     }
-    // the entry being appended, in both operand layouts (split 0 also stores it into the cache)
-    HalfRow<DT, HD> kn_f;
-    uint4 vn_u = make_uint4(0, 0, 0, 0);
-    if (a.append) {
-        const char *kn = a.k_new + (long long)hg * ROWB;
-        const char *vn = a.v_new + (long long)hg * ROWB;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) kn_f.v[i] = *reinterpret_cast<const uint4 *>(kn + hf * (ROWB / 2) + 16 * i);
-        vn_u = *reinterpret_cast<const uint4 *>(vn + 16 * vunit);
-    }
+    if (j_first < a.Lmax) load(vf, vc, j_first);
 
     const HeadLen hl = head_len(a.len[hg], a.bound, a.append);
     const int L = hl.L, new_slot = hl.new_slot;
     const int s_hi = split == a.n_split - 1 ? L : min(L, s_lo + a.split_len);   // the last split takes the remainder
     if (split == 0) {
+        // the appended entry goes into the cache here; every reader below takes it from k_new / v_new
         if (new_slot >= 0) {
             if (tid < UPR)
                 *reinterpret_cast<uint4 *>(a.k + (cbase + new_slot) * ROWB + 16 * tid) =
@@ -180,128 +157,101 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnArgs a) {
         }
     }
 
-    float m_run = -INFINITY, l_run = 0.f;   // of head l32 (both lane halves hold the same value)
-    f32x16 oacc[NB];                        // O^T: rows = output channels of block nb, column = head l32
+    float m_run[GP], l_run[GP];             // maximum over the wave's entries, sum over this row group's
+    float4 o[GP][CU];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int h = 0; h < GP; ++h) {
+        m_run[h] = -INFINITY;
+        l_run[h] = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[nb][r] = 0.f;
-
-    char *vt = &v_lds[wave][0];
+        for (int u = 0; u < CU; ++u) o[h][u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
     for (int j0 = j_first; j0 < s_hi; j0 += 128) {
-        TileRegs<DT, HD> nxt = cur;     // always defined (a conditionally written local would live in scratch)
         const bool more = j0 + 128 < s_hi;
-        if (more) load_tile(j0 + 128, nxt);
-
-        // substitute the appended entry, zero the rows beyond the range (their V must not reach the MFMA)
+        // the appended entry comes from k_new / v_new; rows beyond the range must not reach the products
         if (j0 + 32 > s_hi || (new_slot >= j0 && new_slot < j0 + 32)) {
-            if (j0 + l32 == new_slot) cur.kf = kn_f;
 #pragma unroll
-            for (int i = 0; i < VPL; ++i) {
-                const int j = j0 + vsub + KSUB * i;
-                if (j == new_slot) cur.vv[i] = vn_u;
-                if (j >= s_hi) cur.vv[i] = make_uint4(0, 0, 0, 0);
-            }
-        }
-        // V tile to LDS in natural layout
+            for (int i = 0; i < 8; ++i) {
+                const int j = j0 + 4 * i + kg;
 #pragma unroll
-        for (int i = 0; i < VPL; ++i)
-            *reinterpret_cast<uint4 *>(vt + (vsub + KSUB * i) * VPITCH + 16 * vunit) = cur.vv[i];
-
-        // logits: rows = entries, columns = heads
-        f32x16 acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-        mma_tile<DT, HD>(acc, cur.kf, qf);
-
-        float tmax = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int j = j0 + acc_row(r, hf);
-            const float t = (j < s_hi) ? acc[r] * a.scale_log2 : -INFINITY;
-            acc[r] = t;
-            tmax = fmaxf(tmax, t);
-        }
-        tmax = fmaxf(tmax, other_half(tmax));
-        const float m_new = fmaxf(m_run, tmax);          // finite: the tile holds at least one entry
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-        // (rows of a tile beyond the range lie beyond the head's length, and the logit rows are whole tiles
-        // long: the four consecutive entries of a register quad go out as one 16-byte word, masked or not)
-        if (a.update_score && l32 < a.G) {
-            float *lg = a.logits + ((long long)hg * GP + l32) * a.Lcap + j0 + 4 * hf;
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-                *reinterpret_cast<float4 *>(lg + 8 * r4) =
-                    make_float4(acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]);
-        }
-        float p[16];
-        float psum = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            p[r] = __builtin_amdgcn_exp2f(acc[r] - m_new);
-            psum += p[r];
-        }
-        psum += other_half(psum);
-        l_run = l_run * alpha + psum;
-        m_run = m_new;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[nb][r] *= alpha;
-
-        // the V tile is private to this wave: order the LDS traffic, no workgroup barrier
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-        // O^T += V^T P^T on the matrix cores.  The contraction index is free, so it is numbered the way
-        // the probabilities already sit in this lane's registers: step s, slot i <-> entry
-        // 16 s + 8 (i/4) + 4 hf + i%4 (bf16) or entry acc_row(s, hf) (fp32).  V is read transposed from LDS.
-        if constexpr (DT == LVLM_BF16) {
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2) {
-                const bf16x8 pb = pack_bf16x8(&p[8 * s2]);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    uint32_t w[4];
-#pragma unroll
-                    for (int i2 = 0; i2 < 4; ++i2) {
-                        const int e0 = 16 * s2 + 8 * ((2 * i2) >> 2) + 4 * hf + ((2 * i2) & 3);
-                        const uint32_t lo = *reinterpret_cast<const uint16_t *>(vt + e0 * VPITCH + 2 * (32 * nb + l32));
-                        const uint32_t hi =
-                            *reinterpret_cast<const uint16_t *>(vt + (e0 + 1) * VPITCH + 2 * (32 * nb + l32));
-                        w[i2] = lo | (hi << 16);
+                for (int u = 0; u < CU; ++u) {
+                    if (j == new_slot) {
+                        kf[i][u] = *reinterpret_cast<const float4 *>(a.k_new + (long long)hg * ROWB + 16 * l16 + 256 * u);
+                        vf[i][u] = *reinterpret_cast<const float4 *>(a.v_new + (long long)hg * ROWB + 16 * l16 + 256 * u);
                     }
-                    const bf16x8 va = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
-                    oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb, oacc[nb], 0, 0, 0);
-                }
-            }
-        } else {
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) {
-                const int e0 = acc_row(s2, hf);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const float va = *reinterpret_cast<const float *>(vt + e0 * VPITCH + 4 * (32 * nb + l32));
-                    oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, p[s2], oacc[nb], 0, 0, 0);
+                    if (j >= s_hi) vf[i][u] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (more) cur = nxt;
+        float t[8][GP];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int h = 0; h < GP; ++h) {
+                float d = 0.f;
+#pragma unroll
+                for (int u = 0; u < CU; ++u) {
+                    d = fmaf(kf[i][u].x, qf[h][u].x, d);
+                    d = fmaf(kf[i][u].y, qf[h][u].y, d);
+                    d = fmaf(kf[i][u].z, qf[h][u].z, d);
+                    d = fmaf(kf[i][u].w, qf[h][u].w, d);
+                }
+                d += dpp_quad1(d);
+                d += dpp_quad2(d);
+                d += dpp_half_mirror(d);
+                d += dpp_row_mirror(d);
+                t[i][h] = (j0 + 4 * i + kg < s_hi) ? d : -INFINITY;
+            }
+        if (more) load(kf, kc, j0 + 128);
+        // (rows of a tile beyond the range lie beyond the head's length, and the logit rows are whole tiles long)
+        if (a.update_score) {
+#pragma unroll
+            for (int h = 0; h < GP; ++h) {
+                float x = t[0][h];
+#pragma unroll
+                for (int i = 1; i < 8; ++i) x = l16 == i ? t[i][h] : x;
+                if (h < a.G && l16 < 8) a.logits[((long long)hg * GP + h) * a.Lcap + j0 + 4 * l16 + kg] = x;
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < GP; ++h) {
+            float m_new = m_run[h];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m_new = fmaxf(m_new, t[i][h]);
+            m_new = fmaxf(m_new, other_row(m_new));
+            m_new = fmaxf(m_new, other_half(m_new));                 // finite: the tile holds at least one entry
+            const float alpha = __builtin_amdgcn_exp2f(m_run[h] - m_new);
+            float sum = 0.f;
+#pragma unroll
+            for (int u = 0; u < CU; ++u) {
+                o[h][u].x *= alpha; o[h][u].y *= alpha; o[h][u].z *= alpha; o[h][u].w *= alpha;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float p = __builtin_amdgcn_exp2f(t[i][h] - m_new);
+                sum += p;
+#pragma unroll
+                for (int u = 0; u < CU; ++u) {
+                    o[h][u].x = fmaf(p, vf[i][u].x, o[h][u].x);
+                    o[h][u].y = fmaf(p, vf[i][u].y, o[h][u].y);
+                    o[h][u].z = fmaf(p, vf[i][u].z, o[h][u].z);
+                    o[h][u].w = fmaf(p, vf[i][u].w, o[h][u].w);
+                }
+            }
+            l_run[h] = l_run[h] * alpha + sum;
+            m_run[h] = m_new;
+        }
+        if (more) load(vf, vc, j0 + 128);
     }
 
-    // ---- fold the four waves: lane (head l32 < G, half hf) holds 16 channels of every block
-    if (l32 < GP) {
+    // ---- fold the four waves and their row groups
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+    for (int h = 0; h < GP; ++h) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) wo[wave][l32][32 * nb + acc_row(r, hf)] = oacc[nb][r];
-        if (hf == 0) {
-            wm[wave][l32] = m_run;
-            wl[wave][l32] = l_run;
+        for (int u = 0; u < CU; ++u) *reinterpret_cast<float4 *>(&wo[wave][kg][h][64 * u + 4 * l16]) = o[h][u];
+        if (l16 == 0) {
+            wl[wave][kg][h] = l_run[h];
+            if (kg == 0) wm[wave][h] = m_run[h];
         }
     }
     __syncthreads();
@@ -312,22 +262,19 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(AttnArgs a) {
 #pragma unroll
         for (int w = 1; w < 4; ++w) mx = fmaxf(mx, wm[w][h]);
         const float ms = (mx == -INFINITY) ? 0.f : mx;
-        float sacc = 0.f;
+        float oacc = 0.f, lacc = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) sacc += wo[w][h][e] * __builtin_amdgcn_exp2f(wm[w][h] - ms);
-        po[idx] = sacc;
-    }
-    if (tid < GP) {
-        float mx = wm[0][tid];
-#pragma unroll
-        for (int w = 1; w < 4; ++w) mx = fmaxf(mx, wm[w][tid]);
-        const float ms = (mx == -INFINITY) ? 0.f : mx;
-        float sacc = 0.f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) sacc += wl[w][tid] * __builtin_amdgcn_exp2f(wm[w][tid] - ms);
-        float *pml = a.part_ml + (((long long)hg * a.n_split + split) * GP + tid) * 2;
-        pml[0] = mx;
-        pml[1] = sacc;
+        for (int w = 0; w < 4; ++w) {
+            const float wgt = __builtin_amdgcn_exp2f(wm[w][h] - ms);
+            oacc = fmaf((wo[w][0][h][e] + wo[w][1][h][e]) + (wo[w][2][h][e] + wo[w][3][h][e]), wgt, oacc);
+            lacc = fmaf((wl[w][0][h] + wl[w][1][h]) + (wl[w][2][h] + wl[w][3][h]), wgt, lacc);
+        }
+        po[idx] = oacc;
+        if (e == 0) {
+            float *pml = a.part_ml + (((long long)hg * a.n_split + split) * GP + h) * 2;
+            pml[0] = mx;
+            pml[1] = lacc;
+        }
     }
 }
 
@@ -918,7 +865,7 @@ void launch_both(const Prof &prof, const AttnArgs &a, int B, int len_bound) {
             LVLM_LAUNCH(prof, (attn_partial_bf16_kernel<HD, GP, false, false>), grid, dim3(256), 0, stream, a);
     }
     else
-        LVLM_LAUNCH(prof, (attn_partial_kernel<DT, HD, GP>), dim3(a.n_split, a.Hkv, B), dim3(256), 0, stream, a);
+        LVLM_LAUNCH(prof, (attn_partial_f32_kernel<HD, GP>), dim3(a.n_split, a.Hkv, B), dim3(256), 0, stream, a);
     prof.end();
     if (a.evict_budget > 0) {
         prof.begin("attn_combine_evict");

@@ -548,6 +548,17 @@ def test_decode_attn_shapes(ctx):
         _attn_case(ctx, torch.bfloat16, 2, 14, 2, 128, 1100, [1024, 37, 0, 700], seed)           # again and again
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 7, 8])
+def test_decode_attn_fp32_groups_and_tile_edges(ctx, G, d):
+    # every padded group size; one entry, tile and split edges, a second tile per wave, a remainder on the last split
+    lens = [0, 1, 3, 31, 32, 33, 127, 128, 129, 255, 256, 300]
+    _attn_case(ctx, torch.float32, 6, 2 * G, 2, d, 320, lens, 300 + G)
+    _attn_case(ctx, torch.float32, 1, 2 * G, 2, d, 400, [257, 256], 310 + G, len_bound=258)
+    if d == 64:
+        _attn_case(ctx, torch.float32, 128, 2 * G, 2, d, 300, [280 - i % 40 for i in range(256)], 320 + G)
+
+
 def test_decode_attn_heads_at_or_beyond_the_length_bound(ctx):
     """The lengths live on the device, so a head can break the caller's len_bound promise without the host seeing
     it (the fused eviction may find nothing to evict).  Such a head must be handled inside the bound: a full

@@ -204,6 +204,19 @@ def test_prefill_attn_random_shapes(ctx):
             assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5, case
 
 
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
+    (1, 1, 1, 1, 64, True), (2, 15, 4, 4, 64, True), (1, 16, 2, 1, 128, False), (1, 17, 4, 2, 64, True),
+    (1, 97, 3, 1, 128, True), (1, 128, 2, 2, 64, True), (1, 129, 2, 2, 64, False), (2, 161, 4, 1, 128, True),
+    (683, 33, 8, 4, 64, True), (700, 30, 12, 4, 128, True)])      # the last two: two 16-row blocks per workgroup
+def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causal):
+    fused, split = _qkv(B, N, Hq, Hkv, d, torch.float32, 500 + N, 2.0)
+    q, k, v = split(fused)
+    out, lse, _, _ = ctx.prefill_attn(*split(fused.to(DEV)), causal=causal)
+    o_out, o_lse = O.prefill_attn(f64(q), f64(k), f64(v), causal=causal, dtype="f32")
+    assert rel_err(out.cpu(), o_out) < 1e-5
+    assert np.abs(lse.cpu().numpy() - o_lse).max() < 1e-5 * max(1.0, np.abs(o_lse).max())
+
+
 def test_prefill_attn_rejects_bad_arguments(ctx):
     fused, split = _qkv(1, 64, 4, 2, 64, torch.bfloat16, 1)
     qd, kd, vd = split(fused.to(DEV))
