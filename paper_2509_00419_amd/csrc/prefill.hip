@@ -46,31 +46,347 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 }
 
 // bf16, matrix cores.  A workgroup of two waves owns 128 query rows of one head, 64 per wave as two 32-row
-// blocks held in registers as MFMA operands.  Keys and values go by in tiles of 32: the 128 threads fetch
-// the next tile while the current one is multiplied, K into LDS as it is (rows = keys), V turned around
-// (rows = channels, 32 keys each) in registers on the way in; one barrier per tile.  Per tile and block:
+// blocks held in registers as MFMA operands.  Keys and values go by in tiles of 32, K into LDS as it is (rows = keys),
+// V turned around (rows = channels, 32 keys each) in registers on the way in; one barrier per tile.  Per tile and block:
 // S^T = K Q^T (rows = keys, columns = queries), so a lane owns ONE query row and 16 of its logits -- the
-// online max and sum are lane-local but for one exchange with the other half-wave -- and the 16
+// max and sum are lane-local but for one exchange with the other half-wave -- and the 16
 // probabilities, rounded to bf16, are already laid out as the second operand of O^T += V^T P^T when the
 // keys inside V^T's rows are stored in the order the accumulator registers hold them.  Both blocks of a wave
-// use each K and V^T fragment read from LDS, which is what keeps LDS bandwidth (about 64 bytes a clock per
-// CU, measured) from bounding the kernel: one fragment read feeds two matrix instructions.
+// use each K and V^T fragment read from LDS.
 //
-// The kernel exists twice.  The FAST one fixes each row's reference maximum at the first tile (every row sees
+// There are two kernels.  The FAST one fixes each row's reference maximum at the first tile (every row sees
 // key 0 there) and never rescales: probabilities are exp2 of the distance to that reference, possibly far
-// above 1, which fp32 sums and bf16 operands carry at unchanged relative precision, and no vector instruction
-// touches the output accumulators inside the loop, so they stay in the accumulation registers (with the
-// rescaling branch in the loop the compiler copied all of them to vector registers and back on every tile).
+// above 1, which fp32 sums and bf16 operands carry at unchanged relative precision.
 // Should a logit rise more than 2^kRisk above its row's reference, the wave writes nothing and the workgroup
 // marks itself in `redo`; the SAFE
-// kernel, launched right after over the same grid, does the marked workgroups again with the textbook online
+// kernel, launched right after, does the marked workgroups again with the textbook online
 // softmax, whose reference follows the running maximum (lazily, in steps of 2^kLazy) and rescales sums and
-// accumulators when it moves.  Unmarked workgroups of the SAFE launch exit at once.
-template <int HD, bool SAFE>
+// accumulators when it moves.
+
+// Workgroup number -> (batch, head, query block); false: padding.  Numbers with the same remainder modulo 8 run on one
+// XCD.  The B * Hq heads, in memory order (heads of one KV head next to each other), are dealt to the 8 XCDs in
+// contiguous runs of equal length (+-1): heads that read the same keys and values mostly share an L2, and
+// every XCD gets the same load whatever the head counts.  Within an XCD the longest blocks (latest rows)
+// come first.
+struct PrefillBlock {
+    int b, h, g, q0;
+};
+__device__ __forceinline__ bool prefill_block(const PrefillArgs &a, int id, PrefillBlock &w) {
+    const int xcd = id & 7, seq = id >> 3;
+    const int NH = a.B * a.Hq;
+    const int qb = a.nqb - 1 - seq / a.heads_per_xcd;
+    const int head_first = (xcd * NH + 7) >> 3, head_end = ((xcd + 1) * NH + 7) >> 3;
+    const int bh = head_first + seq % a.heads_per_xcd;
+    if (bh >= head_end) return false;
+    w.b = bh / a.Hq;
+    w.h = bh % a.Hq;
+    w.g = w.h / a.G;
+    w.q0 = qb * 128;
+    return true;
+}
+
+// Position of key kk of a tile inside a V^T row: accumulator register r of half hf holds key
+// 8 (r / 4) + 4 hf + r % 4 of a 32-key tile, and the second product wants the 8 keys of registers
+// 8 t .. 8 t + 7 in one 16-byte word: word index 2 t + hf, inside it 4 (r / 4 % 2) + r % 4.  Four keys
+// 4 vkg .. 4 vkg + 3 stay together: they go to byte 32 (vkg / 4) + 16 (vkg % 2) + 8 (vkg / 2 % 2).
+__device__ __forceinline__ int vt_offset(int vkg) { return 32 * (vkg >> 2) + 16 * (vkg & 1) + 8 * ((vkg >> 1) & 1); }
+constexpr int kVtPitch = 80;            // V^T row: 32 keys x 2 bytes + 16
+// channels 2m (low halves of word c) and 2m + 1 (high halves) of a 16-byte unit, four keys (rows v0 .. v3) each
+__device__ __forceinline__ void vt_store(char *vd, int m, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3) {
+    uint2 lo, hi;
+    lo.x = __builtin_amdgcn_perm(v1, v0, 0x05040100u);
+    lo.y = __builtin_amdgcn_perm(v3, v2, 0x05040100u);
+    hi.x = __builtin_amdgcn_perm(v1, v0, 0x07060302u);
+    hi.y = __builtin_amdgcn_perm(v3, v2, 0x07060302u);
+    *reinterpret_cast<uint2 *>(vd + (2 * m) * kVtPitch) = lo;
+    *reinterpret_cast<uint2 *>(vd + (2 * m + 1) * kVtPitch) = hi;
+}
+
+// Did some probability of the wave's rows go beyond 2^kRisk (or to inf / NaN)?  Otherwise the sums stay below 2^kRisk
+// times the row length.
+__device__ __forceinline__ bool risky_sums(float l0, float l1) {
+    const float limit = __builtin_amdgcn_exp2f(kRisk) * 65536.f;
+    return __builtin_amdgcn_ballot_w64(!(l0 < limit) || !(l1 < limit)) != 0ull;
+}
+
+// Normalises and writes one 32-row block: lane (query l32, half hf) holds channels 32 cb + 8 (r / 4) + 4 hf + r % 4.
+template <int NCB>
+__device__ __forceinline__ void prefill_write(const PrefillArgs &a, const PrefillBlock &w, int row, int hf, float m_run,
+                                              float l_run, const f32x16 (&oacc)[NCB]) {
+    const float l_tot = l_run + other_half(l_run);
+    if (row >= a.N) return;
+    const float inv = 1.f / l_tot;
+    char *dst = a.out + (long long)w.b * a.osb + (long long)row * a.osn + (long long)w.h * a.osh + 8 * hf;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            uint2 u;
+            u.x = pack_bf16(oacc[cb][4 * r4 + 0] * inv, oacc[cb][4 * r4 + 1] * inv);
+            u.y = pack_bf16(oacc[cb][4 * r4 + 2] * inv, oacc[cb][4 * r4 + 3] * inv);
+            *reinterpret_cast<uint2 *>(dst + 64 * cb + 16 * r4) = u;
+        }
+    if (hf == 0) {
+        const float lse = m_run * a.scale + __logf(l_tot);
+        a.row_lse[((long long)w.b * a.Hq + w.h) * a.N + row] = lse;
+        if (a.lse_t && row >= a.N - a.T) a.lse_t[((long long)w.b * a.Hq + w.h) * a.T + (row - (a.N - a.T))] = lse;
+    }
+}
+
+// The FAST kernel.  The matrix pipe and the vector ALUs of a SIMD work side by side when a wave has independent
+// instructions for both (measured: 16 products with 4 fused multiply-adds or 2 exponentials behind each take the time
+// of the products alone), and one tile's products and softmax, which depend on each other, are about equally long.
+// So the loop is pipelined over three tiles: iteration t multiplies S(t+1) = K(t+1) Q and O += V(t-1) P(t-1)
+// while it turns S(t) into P(t).  It is cut into 32 slots of one product and one lane's work on one logit, the logit's
+// scaling, exponential and sum each a slot apart so that no slot waits for its own results; a scheduling barrier behind
+// each keeps the compiler from drawing the pieces apart again.  The LDS fragments of the second product are
+// read during the first, those of the next tile's first product during the second.  Staging (a ring of two K and two
+// V^T tiles; K(t+3) and V(t) go to LDS and the next ones are requested) goes with the first product, so that the barrier
+// at the end finds the LDS queue drained.  One wave per SIMD: the 128 output accumulators, two tiles of logits, the query
+// operands and the fragments take 426 registers.
+// The masks around the diagonal and at the end of the sequence are one compare and select per logit, in a second copy
+// of the iteration that only the last (up to four) tiles of a workgroup run through.
+// Addresses are a uniform base plus 32-bit offsets per thread (the host checks that a tile's rows span less than 2 GiB).
+// What bounds it: the power the chip allows (16512 tokens: 5.8 M cycles, the products 57 % of them, at 1.79 of 2.4 GHz;
+// the same call on zeros runs at 1390 TFLOP/s), then the masked tiles of short rows.  Measured against products and softmax
+// in turn: 16512 tokens, 48 heads 3.92 -> 3.13 ms (855 -> 1070 TFLOP/s), 8 x 1888 tokens, 32 heads 353 -> 298 us,
+// one sequence of 2176, 28 heads 90 -> 63 us.
 __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a) {
+    constexpr int HD = 128;
     constexpr int ROWB = HD * 2;
     constexpr int KP = ROWB + 16;           // K tile pitch: odd multiple of 16 bytes
-    constexpr int VP = 80;                  // V^T row: 32 keys x 2 bytes + 16
+    constexpr int VP = kVtPitch;
+    constexpr int NV = HD / 16;             // 16-byte words a lane holds of a row half = chunks of one product
+    constexpr int NCB = HD / 32;            // blocks of 32 channels
+    constexpr int UPR = ROWB / 16;          // 16-byte units per row
+    constexpr int KTPR = 128 / 32;          // threads per K row, four units each
+    __shared__ __attribute__((aligned(16))) char k_lds[2][32 * KP];
+    __shared__ __attribute__((aligned(16))) char v_lds[2][HD * VP];
+    __shared__ int bail_s[2];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform: conditions on it are scalar branches
+    const int hf = lane >> 5, l32 = lane & 31;
+    PrefillBlock w;
+    if (!prefill_block(a, blockIdx.x, w)) return;
+    const int wrow0 = w.q0 + 64 * wave;               // this wave's first row
+    const int kmax = a.causal ? min(a.N, w.q0 + 128) : a.N;
+    const int n_tiles = (kmax + 31) >> 5;
+    const int j_last = (n_tiles - 1) << 5;
+
+    // staging.  K: thread -> row krow, units kcu + KTPR x.  V: thread -> four keys 4 vkg .. 4 vkg + 3 of one
+    // 16-byte unit vcu (8 channels).  In the last tile rows past the end repeat the last row (masked later).
+    const int krow = tid / KTPR, kcu = tid % KTPR;
+    const int vkg = tid & 7, vcu = tid >> 3;
+    const unsigned ksn = (unsigned)a.ksn, vsn = (unsigned)a.vsn;
+    const int r_last = a.N - 1 - j_last;
+    const unsigned ko = krow * ksn + 16 * kcu, ko_e = min(krow, r_last) * ksn + 16 * kcu;
+    unsigned vo[4], vo_e[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        vo[x] = (4 * vkg + x) * vsn + 16 * vcu;
+        vo_e[x] = min(4 * vkg + x, r_last) * vsn + 16 * vcu;
+    }
+    const char *kbase = a.k + (long long)w.b * a.ksb + (long long)w.g * a.ksh;
+    const char *vbase = a.v + (long long)w.b * a.vsb + (long long)w.g * a.vsh;
+    auto k_unit = [&](int t, int x) {
+        const int tc = min(t, n_tiles - 1);
+        return *reinterpret_cast<const uint4 *>(kbase + (long long)(tc << 5) * a.ksn + (tc == n_tiles - 1 ? ko_e : ko) + 16 * KTPR * x);
+    };
+    auto v_unit = [&](int t, int x) {
+        const int tc = min(t, n_tiles - 1);
+        return *reinterpret_cast<const uint4 *>(vbase + (long long)(tc << 5) * a.vsn + (tc == n_tiles - 1 ? vo_e[x] : vo[x]));
+    };
+    char *const k_dst = &k_lds[0][krow * KP + 16 * kcu];
+    char *const v_dst = &v_lds[0][(8 * vcu) * VP + vt_offset(vkg)];
+    const char *const k_src = &k_lds[0][l32 * KP + 16 * hf];
+    const char *const v_src = &v_lds[0][l32 * VP + 16 * hf];
+    auto frag = [](const char *src) { return *reinterpret_cast<const uint4 *>(src); };
+
+    // ---- the first tiles, all loads at once
+    // (named registers: staging that is carried around the loop in arrays went to scratch memory)
+    uint4 ks0 = k_unit(0, 0), ks1 = k_unit(0, 1), ks2 = k_unit(0, 2), ks3 = k_unit(0, 3);
+    const uint4 t0 = k_unit(1, 0), t1 = k_unit(1, 1), t2 = k_unit(1, 2), t3 = k_unit(1, 3);
+    uint4 qf[2][NV];                        // lane (row l32 of block x, half hf) holds bytes 16 hf + 32 i of its row
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const char *src = a.q + (long long)w.b * a.qsb + (long long)min(wrow0 + 32 * x + l32, a.N - 1) * a.qsn +
+                          (long long)w.h * a.qsh + 16 * hf;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) qf[x][i] = *reinterpret_cast<const uint4 *>(src + 32 * i);
+    }
+    auto put_k = [&](char *dst, const uint4 &u0, const uint4 &u1, const uint4 &u2, const uint4 &u3) {
+        *reinterpret_cast<uint4 *>(dst) = u0;
+        *reinterpret_cast<uint4 *>(dst + 16 * KTPR) = u1;
+        *reinterpret_cast<uint4 *>(dst + 32 * KTPR) = u2;
+        *reinterpret_cast<uint4 *>(dst + 48 * KTPR) = u3;
+    };
+    put_k(k_dst, ks0, ks1, ks2, ks3);
+    ks0 = k_unit(2, 0), ks1 = k_unit(2, 1), ks2 = k_unit(2, 2), ks3 = k_unit(2, 3);
+    uint4 vs0 = v_unit(0, 0), vs1 = v_unit(0, 1), vs2 = v_unit(0, 2), vs3 = v_unit(0, 3);
+    put_k(k_dst + 32 * KP, t0, t1, t2, t3);
+    // V^T(-1) is zero: iteration 0 multiplies it with probabilities that are zero too
+    for (int x = tid; x < HD * VP / 16; x += 128) *reinterpret_cast<uint4 *>(&v_lds[1][16 * x]) = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+
+    f32x16 sa[2], sb[2];                    // logits of the even and the odd tiles
+    uint32_t pa[2][8], pb[2][8];            // probabilities of the odd and the even tiles (of the tile before the logits)
+    uint4 kf[NV], vf[NV];
+    f32x16 oacc[2][NCB];
+    float mb[2], m_run[2], l_run[2];
+    auto mfma = [](const uint4 &x, const uint4 &y, const f32x16 &c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
+    };
+    auto quad = [](const uint32_t (&p)[8], int h) { return make_uint4(p[4 * h], p[4 * h + 1], p[4 * h + 2], p[4 * h + 3]); };
+    // last visible key of this lane's row of block x, relative to key 4 hf of tile 0
+    int lim0[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) lim0[x] = (a.causal ? min(wrow0 + 32 * x + l32, a.N - 1) : a.N - 1) - 4 * hf;
+    auto hidden = [&](int r, int lim) { return 8 * (r >> 2) + (r & 3) > lim; };
+    f32x16 zero;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) kf[i] = frag(k_src + 32 * i);
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int x = 0; x < 2; ++x) sa[x] = mfma(kf[i], qf[x][i], i == 0 ? zero : sa[x]);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) kf[i] = frag(k_src + 32 * KP + 32 * i);
+    __syncthreads();
+    put_k(k_dst, ks0, ks1, ks2, ks3);
+    ks0 = k_unit(3, 0), ks1 = k_unit(3, 1), ks2 = k_unit(3, 2), ks3 = k_unit(3, 3);
+    // the reference of every row: its maximum over the first tile (key 0 is visible to every row)
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, hidden(r, lim0[x]) ? -INFINITY : sa[x][r]);
+        m_run[x] = half_max(mx);
+        mb[x] = -(m_run[x] * a.scale_log2);
+        l_run[x] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) pa[x][i] = 0;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) oacc[x][cb] = zero;
+    }
+    __syncthreads();
+
+    // iteration t: logits sin -> probabilities pout, products of the next logits into sout, probabilities pin of the
+    // tile before into the output
+    auto step = [&](int t, f32x16 (&sin)[2], f32x16 (&sout)[2], uint32_t (&pin)[2][8], uint32_t (&pout)[2][8], auto edge_tag) {
+        constexpr bool EDGE = decltype(edge_tag)::value;
+        const int buf = t & 1;
+        const char *vr = v_src + (buf ^ 1) * (HD * VP), *kr = k_src + buf * (32 * KP);
+        char *vw = v_dst + buf * (HD * VP), *kw = k_dst + (buf ^ 1) * (32 * KP);
+        const int tk = min(t + 4, n_tiles - 1), tv = min(t + 1, n_tiles - 1);
+        const char *kb = kbase + (long long)(tk << 5) * a.ksn, *vb = vbase + (long long)(tv << 5) * a.vsn;
+        const unsigned ok = tk == n_tiles - 1 ? ko_e : ko;
+        const int lim[2] = {lim0[0] - (t << 5), lim0[1] - (t << 5)};
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) asm volatile("" : "+a"(oacc[x][cb]));
+        asm volatile("" : "+a"(sin[0]), "+a"(sin[1]));
+        // softmax of logit el (block el / 16, register el % 16) in three stages, each a slot behind the one before
+        float e_arg[32], e_p[32];
+        auto stage_arg = [&](int el) {
+            float v = sin[el >> 4][el & 15];
+            if constexpr (EDGE) v = hidden(el & 15, lim[el >> 4]) ? -INFINITY : v;
+            e_arg[el] = fmaf(v, a.scale_log2, mb[el >> 4]);
+        };
+        auto stage_exp = [&](int el) { e_p[el] = __builtin_amdgcn_exp2f(e_arg[el]); };
+        auto stage_sum = [&](int el) {
+            l_run[el >> 4] += e_p[el];
+            if (el & 1) pout[el >> 4][(el & 15) >> 1] = pack_bf16(e_p[el - 1], e_p[el]);
+        };
+        stage_arg(0);
+#pragma unroll
+        for (int sl = 0; sl < 32; ++sl) {
+            const int c = (sl >> 1) & 7, x = sl & 1;         // step of the product, block
+            if (sl < 16) {
+                sout[x] = mfma(kf[c], qf[x][c], c == 0 ? zero : sout[x]);
+            } else {
+                oacc[x][c >> 1] = mfma(vf[c], quad(pin[x], c & 1), oacc[x][c >> 1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (sl < 16) {
+                if (x == 0) vf[c] = frag(vr + (32 * (c >> 1)) * VP + 32 * (c & 1));
+                // staging, behind the block-1 product of each step: K units in steps 0-3, V words in 4-7
+#define LVLM_K_UNIT(u)                                                          \
+    if (sl == 2 * u + 1) {                                                      \
+        *reinterpret_cast<uint4 *>(kw + 16 * KTPR * u) = ks##u;                 \
+        ks##u = *reinterpret_cast<const uint4 *>(kb + ok + 16 * KTPR * u);      \
+    }
+                LVLM_K_UNIT(0) LVLM_K_UNIT(1) LVLM_K_UNIT(2) LVLM_K_UNIT(3)
+#undef LVLM_K_UNIT
+                if (sl == 9) vt_store(vw, 0, vs0.x, vs1.x, vs2.x, vs3.x);
+                if (sl == 11) vt_store(vw, 1, vs0.y, vs1.y, vs2.y, vs3.y);
+                if (sl == 13) vt_store(vw, 2, vs0.z, vs1.z, vs2.z, vs3.z);
+                if (sl == 15) vt_store(vw, 3, vs0.w, vs1.w, vs2.w, vs3.w);
+            } else {
+                if (sl < 24) kf[sl - 16] = frag(kr + 32 * (sl - 16));
+                if (sl == 16) vs0 = *reinterpret_cast<const uint4 *>(vb + (tv == n_tiles - 1 ? vo_e[0] : vo[0]));
+                if (sl == 17) vs1 = *reinterpret_cast<const uint4 *>(vb + (tv == n_tiles - 1 ? vo_e[1] : vo[1]));
+                if (sl == 18) vs2 = *reinterpret_cast<const uint4 *>(vb + (tv == n_tiles - 1 ? vo_e[2] : vo[2]));
+                if (sl == 19) vs3 = *reinterpret_cast<const uint4 *>(vb + (tv == n_tiles - 1 ? vo_e[3] : vo[3]));
+            }
+            if (sl < 31) stage_arg(sl + 1);
+            stage_exp(sl);
+            if (sl > 0) stage_sum(sl - 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        stage_sum(31);
+        __syncthreads();
+    };
+    // tiles [0, t_whole) are seen whole by every row of the workgroup
+    const int t_whole = (a.causal ? min(w.q0, a.N) : a.N) >> 5;
+    int t = 0;
+    for (; t + 1 < t_whole; t += 2) {
+        step(t, sa, sb, pa, pb, std::false_type{});
+        step(t + 1, sb, sa, pb, pa, std::false_type{});
+    }
+    for (; t + 1 < n_tiles; t += 2) {
+        step(t, sa, sb, pa, pb, std::true_type{});
+        step(t + 1, sb, sa, pb, pa, std::true_type{});
+    }
+    if (t < n_tiles) {
+        step(t, sa, sb, pa, pb, std::true_type{});
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) pa[x][i] = pb[x][i];
+    }
+    // the last tile's probabilities
+    {
+        const char *vr = v_src + ((n_tiles - 1) & 1) * (HD * VP);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const uint4 f = frag(vr + (32 * (i >> 1)) * VP + 32 * (i & 1));
+#pragma unroll
+            for (int x = 0; x < 2; ++x) oacc[x][i >> 1] = mfma(f, quad(pa[x], i & 1), oacc[x][i >> 1]);
+        }
+    }
+    // A wave that saw the risk writes nothing, and the mark makes the SAFE kernel do the whole workgroup again.
+    const bool risky = risky_sums(l_run[0], l_run[1]);
+    if (lane == 0) bail_s[wave] = risky;
+    __syncthreads();
+    if (tid == 0) a.redo[blockIdx.x] = bail_s[0] | bail_s[1];
+    if (risky) return;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) prefill_write<NCB>(a, w, wrow0 + 32 * x + l32, hf, m_run[x], l_run[x], oacc[x]);
+}
+
+// One tile after the other, products and softmax in turn: the SAFE sweep (a rescale touches everything in flight, so
+// nothing is pipelined across tiles), and the FAST sweep for 64 channels, where the pipelined loop above has too few
+// products per logit to hide the softmax behind and two waves per SIMD -- 230 registers here, 300 there -- do
+// better (2 x 4000 tokens, 32 heads: 185 us here, 221 us pipelined).  Returns whether a FAST sweep has to be done again.
+template <int HD, bool SAFE>
+__device__ __forceinline__ bool prefill_plain_block(const PrefillArgs &a, const PrefillBlock &w) {
+    constexpr int ROWB = HD * 2;
+    constexpr int KP = ROWB + 16;           // K tile pitch: odd multiple of 16 bytes
+    constexpr int VP = kVtPitch;
     constexpr int NV = HD / 16;             // 16-byte words a lane holds of a row half
     constexpr int NCB = HD / 32;            // blocks of 32 channels
     constexpr int UPR = ROWB / 16;          // 16-byte units per row
@@ -82,22 +398,7 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform: conditions on it are scalar branches
     const int hf = lane >> 5, l32 = lane & 31;
-    // Workgroup id -> (batch, head, query block).  Ids with the same remainder modulo 8 run on one XCD.  The
-    // B * Hq heads, in memory order (heads of one KV head next to each other), are dealt to the 8 XCDs in
-    // contiguous runs of equal length (+-1): heads that read the same keys and values mostly share an L2, and
-    // every XCD gets the same load whatever the head counts.  Within an XCD the longest blocks (latest rows)
-    // come first.
-    const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-    const int NH = a.B * a.Hq;
-    const int qb = a.nqb - 1 - seq / a.heads_per_xcd;
-    const int head_first = (xcd * NH + 7) >> 3, head_end = ((xcd + 1) * NH + 7) >> 3;
-    const int bh = head_first + seq % a.heads_per_xcd;
-    if (bh >= head_end) return;
-    if constexpr (SAFE) {
-        if (a.redo[blockIdx.x] == 0) return;
-    }
-    const int b = bh / a.Hq, h = bh % a.Hq, g = h / a.G;
-    const int q0 = qb * 128;
+    const int b = w.b, h = w.h, g = w.g, q0 = w.q0;
     const int wrow0 = q0 + 64 * wave;                 // this wave's first row
     const int kmax = a.causal ? min(a.N, q0 + 128) : a.N;
     const int n_tiles = (kmax + 31) >> 5;
@@ -145,22 +446,7 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
             vs3 = *reinterpret_cast<const uint4 *>(vbase + (long long)min(jv + 3, a.N - 1) * a.vsn);
         }
     };
-    // Position of key kk of a tile inside a V^T row: accumulator register r of half hf holds key
-    // 8 (r / 4) + 4 hf + r % 4 of a 32-key tile, and the second product wants the 8 keys of registers
-    // 8 t .. 8 t + 7 in one 16-byte word: word index 2 t + hf, inside it 4 (r / 4 % 2) + r % 4.  Four keys
-    // 4 vkg .. 4 vkg + 3 stay together: they go to byte 32 (vkg / 4) + 16 (vkg % 2) + 8 (vkg / 2 % 2).
-    const int v_off = 32 * (vkg >> 2) + 16 * (vkg & 1) + 8 * ((vkg >> 1) & 1);
-    // channels 2m (low halves of word m) and 2m + 1 (high halves) of the unit, four keys each
-#define LVLM_VT(m, c)                                                                    \
-    {                                                                                    \
-        uint2 lo, hi;                                                                    \
-        lo.x = __builtin_amdgcn_perm(vs1.c, vs0.c, 0x05040100u);                         \
-        lo.y = __builtin_amdgcn_perm(vs3.c, vs2.c, 0x05040100u);                         \
-        hi.x = __builtin_amdgcn_perm(vs1.c, vs0.c, 0x07060302u);                         \
-        hi.y = __builtin_amdgcn_perm(vs3.c, vs2.c, 0x07060302u);                         \
-        *reinterpret_cast<uint2 *>(vd + (2 * m) * VP) = lo;                              \
-        *reinterpret_cast<uint2 *>(vd + (2 * m + 1) * VP) = hi;                          \
-    }
+    const int v_off = vt_offset(vkg);
     auto stash = [&](int buf) {
         uint4 *dst = reinterpret_cast<uint4 *>(&k_lds[buf][krow * KP + 16 * kcu]);
         dst[0] = ks0;
@@ -169,16 +455,15 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
         if constexpr (KUPT > 3) dst[3 * KTPR] = ks3;
         if (v_on) {
             char *vd = &v_lds[buf][(8 * vcu) * VP + v_off];
-            LVLM_VT(0, x) LVLM_VT(1, y) LVLM_VT(2, z) LVLM_VT(3, w)
+            vt_store(vd, 0, vs0.x, vs1.x, vs2.x, vs3.x);
+            vt_store(vd, 1, vs0.y, vs1.y, vs2.y, vs3.y);
+            vt_store(vd, 2, vs0.z, vs1.z, vs2.z, vs3.z);
+            vt_store(vd, 3, vs0.w, vs1.w, vs2.w, vs3.w);
         }
     };
-#undef LVLM_VT
 
-    __shared__ int bail_s[2];
     float m_run[2], l_run[2];
     f32x16 oacc[2][NCB];
-    bool risky = false;                     // FAST: some logit ran too far ahead of its row's reference (uniform per wave)
-    (void)risky;
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
         m_run[x] = -INFINITY;
@@ -327,40 +612,36 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
     const int t_whole = a.causal ? min(q0, a.N) >> 5 : a.N >> 5;
     for (int t = 0; t < t_whole; ++t) step(t, std::false_type{});
     for (int t = t_whole; t < n_tiles; ++t) step(t, std::true_type{});
-    // The FAST sweep runs to its end even when it has become useless (an exit from inside the loop makes the
-    // compiler copy the accumulators on every tile); a wave that saw the risk writes nothing, and the mark
-    // makes the SAFE kernel do the whole workgroup again.
-    if constexpr (!SAFE) {
-        // sums stay below 2^kRisk times the row length unless some probability went beyond 2^kRisk (or to inf / NaN)
-        const float limit = __builtin_amdgcn_exp2f(kRisk) * 65536.f;
-        risky = __builtin_amdgcn_ballot_w64(!(l_run[0] < limit) || !(l_run[1] < limit)) != 0ull;
-        if (lane == 0) bail_s[wave] = risky;
-        __syncthreads();
-        if (tid == 0) a.redo[blockIdx.x] = bail_s[0] | bail_s[1];
-        if (risky) return;
-    }
+    if (!SAFE && risky_sums(l_run[0], l_run[1])) return true;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) prefill_write<NCB>(a, w, wrow0 + 32 * x + l32, hf, m_run[x], l_run[x], oacc[x]);
+    return false;
+}
 
-    // normalise and write: lane (query l32, half hf) holds channels 32 cb + 8 (r / 4) + 4 hf + r % 4
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        const int row = wrow0 + 32 * x + l32;
-        const float l_tot = l_run[x] + __shfl_xor(l_run[x], 32);
-        if (row >= a.N) continue;
-        const float inv = 1.f / l_tot;
-        char *dst = a.out + (long long)b * a.osb + (long long)row * a.osn + (long long)h * a.osh + 8 * hf;
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                uint2 w;
-                w.x = pack_bf16(oacc[x][cb][4 * r4 + 0] * inv, oacc[x][cb][4 * r4 + 1] * inv);
-                w.y = pack_bf16(oacc[x][cb][4 * r4 + 2] * inv, oacc[x][cb][4 * r4 + 3] * inv);
-                *reinterpret_cast<uint2 *>(dst + 64 * cb + 16 * r4) = w;
-            }
-        if (hf == 0) {
-            const float lse = m_run[x] * a.scale + __logf(l_tot);
-            a.row_lse[((long long)b * a.Hq + h) * a.N + row] = lse;
-            if (a.lse_t && row >= a.N - a.T) a.lse_t[((long long)b * a.Hq + h) * a.T + (row - (a.N - a.T))] = lse;
+__global__ __launch_bounds__(128, 1) void prefill_attn_d64_kernel(PrefillArgs a) {
+    __shared__ int bail_s[2];
+    PrefillBlock w;
+    if (!prefill_block(a, blockIdx.x, w)) return;
+    const bool again = prefill_plain_block<64, false>(a, w);
+    if ((threadIdx.x & 63) == 0) bail_s[threadIdx.x >> 6] = again;
+    __syncthreads();
+    if (threadIdx.x == 0) a.redo[blockIdx.x] = bail_s[0] | bail_s[1];
+}
+
+// The SAFE kernel: the marked workgroups of a FAST one (or all of them, redo null); 512 workgroups, two to a compute
+// unit, look through the marks 64 at a time.
+template <int HD>
+__global__ __launch_bounds__(128, 1) void prefill_attn_safe_kernel(PrefillArgs a, int total) {
+    const int lane = threadIdx.x & 63;
+    for (long long id0 = blockIdx.x; id0 < total; id0 += 64ll * gridDim.x) {
+        const long long mine = id0 + (long long)lane * gridDim.x;
+        unsigned long long todo = __ballot(mine < total && (!a.redo || a.redo[mine] != 0));
+        while (todo) {
+            const int k = __ffsll((unsigned long long)todo) - 1;
+            todo &= todo - 1;
+            PrefillBlock w;
+            if (prefill_block(a, (int)(id0 + (long long)k * gridDim.x), w)) prefill_plain_block<HD, true>(a, w);
+            __syncthreads();
         }
     }
 }
@@ -588,12 +869,16 @@ hipError_t launch_prefill_attn(const Prof &prof, const lvlm_prefill_desc &d, con
     prof.begin("prefill_attn");
     if (d.dtype == LVLM_BF16) {
         const long long grid = (long long)a.heads_per_xcd * 8 * a.nqb;
+        // the FAST kernel addresses a tile's rows by 32-bit offsets; row strides beyond that leave all of it to the other
+        const bool fast = d.k_stride_n * es < (1ll << 26) && d.v_stride_n * es < (1ll << 26);
+        if (!fast) a.redo = nullptr;
+        const dim3 safe_grid((unsigned)(grid < 512 ? grid : 512));
         if (d.hd == 128) {
-            LVLM_LAUNCH(prof, (prefill_attn_bf16_kernel<128, false>), dim3((unsigned)grid), dim3(128), 0, stream, a);
-            LVLM_LAUNCH(prof, (prefill_attn_bf16_kernel<128, true>), dim3((unsigned)grid), dim3(128), 0, stream, a);
+            if (fast) LVLM_LAUNCH(prof, prefill_attn_bf16_kernel, dim3((unsigned)grid), dim3(128), 0, stream, a);
+            LVLM_LAUNCH(prof, prefill_attn_safe_kernel<128>, safe_grid, dim3(128), 0, stream, a, (int)grid);
         } else {
-            LVLM_LAUNCH(prof, (prefill_attn_bf16_kernel<64, false>), dim3((unsigned)grid), dim3(128), 0, stream, a);
-            LVLM_LAUNCH(prof, (prefill_attn_bf16_kernel<64, true>), dim3((unsigned)grid), dim3(128), 0, stream, a);
+            if (fast) LVLM_LAUNCH(prof, prefill_attn_d64_kernel, dim3((unsigned)grid), dim3(128), 0, stream, a);
+            LVLM_LAUNCH(prof, prefill_attn_safe_kernel<64>, safe_grid, dim3(128), 0, stream, a, (int)grid);
         }
     } else {
         // one block of 16 rows per workgroup; two (each K and V operand feeds two products, 64 bytes of L2 traffic per
