@@ -511,15 +511,12 @@ def kernel_work(ctx, lv, w, layers, dec_lens, moved, merge="rank", per_layer=Fal
             if merge == "similar":
                 rowb, n_img, outside = w.hidden * e + 3 * 4, en["n_img"], N - en["n_img"]
                 add("sim_gemm", "mfma", 2.0 * B * r * en["merge_to"] * w.hidden)
-                add("sim_rank", "hbm", 8.0 * B * n_img)
-                add("sim_rank2", "hbm", 8.0 * B * n_img)
+                # scores in, ranks out; every image row in, its norm out (one launch)
+                add("sim_rank", "hbm", B * n_img * (8.0 + w.hidden * e + 4.0))
                 add("sim_index", "hbm", 8.0 * B * n_img)
                 add("sim_order", "hbm", 8.0 * B * n_img)
-                add("sim_assign", "hbm", 8.0 * B * n_img)
-                add("sim_norm", "hbm", B * n_img * (w.hidden * e + 4.0))            # every image row in, its norm out
-                add("sim_merge", "hbm", B * (n_img + en["merge_to"]) * rowb)        # image rows in, dominant rows out
-                if outside > 0:
-                    add("sim_copy", "hbm", 2.0 * B * outside * rowb)
+                # image rows in, dominant rows out; the rows outside the span from old to new place
+                add("sim_merge", "hbm", B * (n_img + en["merge_to"] + 2.0 * outside) * rowb)
             else:
                 add("merge_rank", "hbm", 8.0 * B * en["n_img"])             # scores in, ranks out
                 add("merge_index", "hbm", 8.0 * B * en["n_img"])            # ranks in, index lists out

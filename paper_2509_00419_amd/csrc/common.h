@@ -63,9 +63,8 @@ struct MergeWs {
 MergeWs merge_ws(const lvlm_merge_desc &d, const lvlm_plane *planes);
 
 struct SimWs {
-    size_t rank, dom_of, keep_idx, rest_idx, inv_norm, pbest_val, pbest_idx, assign, key, rank2, order, sorted, total;
+    size_t rank, dom_of, keep_idx, rest_idx, inv_norm, best, assign, rank2, order, owner, sorted, total;
     int tile;      // rows of dominant (and of other) tokens per workgroup tile of the similarity product
-    int NB;        // blocks of `tile` dominant tokens
 };
 SimWs sim_ws(const lvlm_merge_desc &d);
 
@@ -120,7 +119,29 @@ struct Prof {
 // ---- launches (defined in the .hip files; all asynchronous on `stream`) ----
 // scratch: rank_scratch_bytes(n, B) bytes for the sorted blocks of long sequences, or null (counting at any length)
 size_t rank_scratch_bytes(int n, int B);
-void launch_rank(const Prof &prof, const float *score, int32_t *rank, int n, int B, void *scratch);
+// norm: 1 / |row| of these rows on the side, in the same launch (null: none)
+struct NormJob {
+    const char *src;        // row 0 of sequence 0; rows of row_bytes (a multiple of 16)
+    long long stride_b;     // bytes from sequence to sequence
+    float *inv_norm;        // [B, n]
+    int row_bytes, dtype, n;
+};
+void launch_rank(const Prof &prof, const float *score, int32_t *rank, int n, int B, void *scratch, const NormJob *norm = nullptr);
+// Which dominant token every other token joined, and what the similarity merge makes of it: the tokens ordered by
+// (owner, index), the dominant ones behind.
+struct OwnerJob {
+    const int32_t *dom_of;              // [B, n]  p >= 0: dominant position; -(q+1): q-th other token
+    const unsigned long long *best;     // [B, r]  (order-preserving key of the cosine, ~dominant position); 0: none comparable
+    int32_t *order, *owner, *assign;    // [B, n]  token and owner of every place, owner of every token
+    int r;
+#if defined(__HIPCC__)
+    __device__ __forceinline__ int joined(int b, int d) const {
+        const unsigned long long w = best[(long long)b * r - d - 1];
+        return w == 0ull ? 0 : (int)(0xffffffffu - (uint32_t)w);
+    }
+#endif
+};
+void launch_owner_order(const Prof &prof, const OwnerJob &owners, int32_t *rank, int n, int B, void *scratch);
 hipError_t launch_score(const Prof &prof, const lvlm_score_desc &d, const ScoreWs &w, char *ws,
                         const void *q, const void *k, const float *row_lse, float *score_head,
                         float *score_mean);

@@ -34,24 +34,94 @@ constexpr int kGatherWgs = 1536;   // workgroups the gather launch aims for (six
 constexpr int kRankTile = 8192;   // keys staged in LDS per step of the rank kernel (32 KB)
 constexpr int kRankBlock = 64;    // tokens ranked by one workgroup (one per lane; the 16 waves split the keys)
 
+// What is ranked: descending 32-bit keys of the n tokens of a sequence, ties by ascending index.
+//   ByScore   the scores; rank[j] is the result
+//   ByOwner   (similarity merge) the tokens that joined dominant position p get key ~p, the dominant ones 0, so that the
+//             order is (owner, index) with the dominant tokens behind; order, owner and assign are the result
+template <class KEY>
 struct RankArgs {
-    const float *score;   // [B, n]
-    int32_t *rank;        // [B, n]
-    int n;
+    KEY key;
+    int32_t *rank;                  // [B, n]
+    unsigned long long *sorted;     // [B, n_blocks, 1024]  (long sequences)
+    int n, n_blocks;
+    int rank_wgs;                   // workgroups of the launch that rank; the rest take rows of `norm`
+    NormJob norm;
 };
+
+struct ByScore {
+    const float *score;      // [B, n]
+    __device__ __forceinline__ uint32_t at(int b, int n, int i) const { return score_key(score[(long long)b * n + i]); }
+    static constexpr bool kOrder = false;
+    __device__ __forceinline__ void put(int, int, int, int) const {}
+};
+
+struct ByOwner {
+    OwnerJob o;
+    __device__ __forceinline__ uint32_t at(int b, int n, int i) const {
+        const int d = o.dom_of[(long long)b * n + i];
+        return d >= 0 ? 0u : ~(uint32_t)o.joined(b, d);
+    }
+    static constexpr bool kOrder = true;
+    __device__ __forceinline__ void put(int b, int n, int j, int place) const {
+        const int d = o.dom_of[(long long)b * n + j];
+        const int pos = d >= 0 ? d : o.joined(b, d);
+        o.assign[(long long)b * n + j] = pos;
+        o.order[(long long)b * n + place] = j;
+        o.owner[(long long)b * n + place] = pos;
+    }
+};
+
+// 1 / |row| of 16 rows (one per wave).  The job rides along in a ranking launch: it needs nothing from the ranks and
+// streams from memory while the ranking workgroups count.
+__device__ __forceinline__ void norm_rows(const NormJob &w, int wg, int b) {
+    const int lane = threadIdx.x & 63, j = wg * 16 + (threadIdx.x >> 6);
+    if (j >= w.n) return;
+    const char *row = w.src + (long long)b * w.stride_b + (long long)j * w.row_bytes;
+    const int units = w.row_bytes / 16;
+    float s = 0.f;
+    for (int u0 = 0; u0 < units; u0 += 8 * 64) {
+        uint4 v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const int u = u0 + 64 * x + lane;
+            v[x] = u < units ? *reinterpret_cast<const uint4 *>(row + 16ll * u) : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const uint32_t d[4] = {v[x].x, v[x].y, v[x].z, v[x].w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (w.dtype == LVLM_BF16) {
+                    const float lo = __uint_as_float(d[i] << 16), hi = __uint_as_float(d[i] & 0xffff0000u);
+                    s = fmaf(lo, lo, s);
+                    s = fmaf(hi, hi, s);
+                } else {
+                    const float e = __uint_as_float(d[i]);
+                    s = fmaf(e, e, s);
+                }
+            }
+        }
+    }
+    s = wave_sum(s);
+    if (lane == 0) w.inv_norm[(long long)b * w.n + j] = s > 0.f ? 1.0f / sqrtf(s) : 1.0f;
+}
 
 // rank[j] = #{i : key_i > key_j, or key_i == key_j and i < j}.  A workgroup ranks 64 tokens: every wave
 // holds the same 64 tokens (one per lane) and counts over its own sixteenth of the staged keys, read
 // from LDS as broadcast 128-bit words; the sixteen counts are added through LDS.
-__global__ __launch_bounds__(1024) void rank_kernel(RankArgs a) {
+template <class KEY>
+__global__ __launch_bounds__(1024) void rank_kernel(RankArgs<KEY> a) {
     __shared__ __attribute__((aligned(16))) uint32_t keys[kRankTile];
     __shared__ int cnt_lds[16][kRankBlock];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.y;
+    if ((int)blockIdx.x >= a.rank_wgs) {
+        norm_rows(a.norm, blockIdx.x - a.rank_wgs, b);
+        return;
+    }
     const int j0 = blockIdx.x * kRankBlock;
     const int j = j0 + lane;
-    const float *score = a.score + (long long)b * a.n;
-    const uint32_t kj = j < a.n ? score_key(score[j]) : 0u;
+    const uint32_t kj = j < a.n ? a.key.at(b, a.n, j) : 0u;
     int cnt = 0;
     for (int t0 = 0; t0 < a.n; t0 += kRankTile) {
         const int tile_n = min(kRankTile, a.n - t0);
@@ -61,7 +131,7 @@ __global__ __launch_bounds__(1024) void rank_kernel(RankArgs a) {
             const int i = t0 + x;
             // Padding sits above every real index, so it only ever meets the ">" rule (or the full
             // rule with i > j): the lowest key can never precede anything.
-            keys[x] = i < a.n ? score_key(score[i]) : 0u;
+            keys[x] = i < a.n ? a.key.at(b, a.n, i) : 0u;
         }
         __syncthreads();
         const int x_lo = wave * share, x_hi = min(kRankTile, x_lo + share);
@@ -93,7 +163,8 @@ __global__ __launch_bounds__(1024) void rank_kernel(RankArgs a) {
         int tot = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) tot += cnt_lds[w][lane];
-        a.rank[(long long)b * a.n + j] = tot;
+        if constexpr (KEY::kOrder) a.key.put(b, a.n, j, tot);
+        else a.rank[(long long)b * a.n + j] = tot;
     }
 }
 
@@ -111,27 +182,24 @@ constexpr int kSortBlock = 1024;
 constexpr int kSortMinTokens = 4096;
 constexpr int kSortStage = 8;        // sorted blocks held in LDS at a time (64 KB)
 
-__device__ __forceinline__ unsigned long long order_word(float score, int idx) {
-    return ((unsigned long long)score_key(score) << 32) | (unsigned long long)(0xffffffffu - (uint32_t)idx);
+__device__ __forceinline__ unsigned long long order_word(uint32_t key, int idx) {
+    return ((unsigned long long)key << 32) | (unsigned long long)(0xffffffffu - (uint32_t)idx);
 }
-
-struct SortArgs {
-    const float *score;             // [B, n]
-    unsigned long long *sorted;     // [B, n_blocks, 1024]
-    int32_t *rank;                  // [B, n]
-    int n, n_blocks;
-};
 
 // 64 tokens per workgroup (one per lane, the same in all 16 waves); wave w counts over words 64 w .. 64 w + 63 of
 // the tokens' own block, read from LDS as broadcast 128-bit pairs.
-__global__ __launch_bounds__(1024) void rank_block_kernel(SortArgs a) {
+template <class KEY>
+__global__ __launch_bounds__(1024) void rank_block_kernel(RankArgs<KEY> a) {
     __shared__ __attribute__((aligned(16))) unsigned long long words[kSortBlock];
     __shared__ int cnt_lds[16][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.y;
+    if ((int)blockIdx.x >= a.rank_wgs) {
+        norm_rows(a.norm, blockIdx.x - a.rank_wgs, b);
+        return;
+    }
     const int j0 = blockIdx.x * 64, j = j0 + lane;
     const int blk = j0 / kSortBlock, r0 = blk * kSortBlock;
-    const float *score = a.score + (long long)b * a.n;
     unsigned long long *out = a.sorted + ((long long)b * a.n_blocks + blk) * kSortBlock;
     if (j0 >= a.n) {                              // nothing but padding here (uniform over the workgroup)
         if (wave == 0) out[j - r0] = 0ull;
@@ -139,9 +207,9 @@ __global__ __launch_bounds__(1024) void rank_block_kernel(SortArgs a) {
     }
     {
         const int i = r0 + tid;
-        words[tid] = i < a.n ? order_word(score[i], i) : 0ull;
+        words[tid] = i < a.n ? order_word(a.key.at(b, a.n, i), i) : 0ull;
     }
-    const unsigned long long mine = j < a.n ? order_word(score[j], j) : 0ull;
+    const unsigned long long mine = j < a.n ? order_word(a.key.at(b, a.n, j), j) : 0ull;
     __syncthreads();
     int cnt = 0;
 #pragma unroll 8
@@ -165,12 +233,13 @@ __global__ __launch_bounds__(1024) void rank_block_kernel(SortArgs a) {
     }
 }
 
-__global__ __launch_bounds__(256) void rank_search_kernel(SortArgs a) {
+template <class KEY>
+__global__ __launch_bounds__(256) void rank_search_kernel(RankArgs<KEY> a) {
     __shared__ __attribute__((aligned(16))) unsigned long long words[kSortStage * kSortBlock];
     const int tid = threadIdx.x;
     const int b = blockIdx.y;
     const int j = blockIdx.x * 256 + tid;
-    const unsigned long long mine = j < a.n ? order_word(a.score[(long long)b * a.n + j], j) : ~0ull;
+    const unsigned long long mine = j < a.n ? order_word(a.key.at(b, a.n, j), j) : ~0ull;
     const uint4 *src = reinterpret_cast<const uint4 *>(a.sorted + (long long)b * a.n_blocks * kSortBlock);
     int rank = 0;
     {
@@ -201,10 +270,18 @@ __global__ __launch_bounds__(256) void rank_search_kernel(SortArgs a) {
         for (int bb = 0; bb < kSortStage; ++bb) rank += pos[bb] + (words[bb * kSortBlock + pos[bb]] > mine ? 1 : 0);   // place 1023 itself
     }
     if (j < a.n) {
-        if (gridDim.z == 1) a.rank[(long long)b * a.n + j] = rank;
-        else atomicAdd(&a.rank[(long long)b * a.n + j], rank);
+        if (gridDim.z > 1) atomicAdd(&a.rank[(long long)b * a.n + j], rank);
+        else if constexpr (KEY::kOrder) a.key.put(b, a.n, j, rank);
+        else a.rank[(long long)b * a.n + j] = rank;
     }
 }
+
+// the order from ranks that several workgroups added up
+__global__ __launch_bounds__(256) void rank_order_kernel(RankArgs<ByOwner> a) {
+    const int j = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+    if (j < a.n) a.key.put(b, a.n, j, a.rank[(long long)b * a.n + j]);
+}
+
 
 struct IndexArgs {
     const int32_t *rank;
@@ -443,25 +520,42 @@ size_t rank_scratch_bytes(int n, int B) {
     return (size_t)B * ((n + kSortBlock - 1) / kSortBlock) * kSortBlock * sizeof(unsigned long long);
 }
 
-void launch_rank(const Prof &prof, const float *score, int32_t *rank, int n, int B, void *scratch) {
+namespace {
+template <class KEY>
+void launch_rank_by(const Prof &prof, const KEY &key, int32_t *rank, int n, int B, void *scratch, const NormJob *norm) {
     hipStream_t stream = prof.stream;
+    RankArgs<KEY> a{};
+    a.key = key;
+    a.rank = rank;
+    a.n = n;
+    int norm_wgs = 0;
+    if (norm) {
+        a.norm = *norm;
+        norm_wgs = (norm->n + 15) / 16;
+    }
     if (scratch && n >= kSortMinTokens) {
-        SortArgs sa{};
-        sa.score = score;
-        sa.sorted = static_cast<unsigned long long *>(scratch);
-        sa.rank = rank;
-        sa.n = n;
-        sa.n_blocks = (n + kSortBlock - 1) / kSortBlock;
-        LVLM_LAUNCH(prof, rank_block_kernel, dim3(sa.n_blocks * (kSortBlock / 64), B), dim3(1024), 0, stream, sa);
-        LVLM_LAUNCH(prof, rank_search_kernel, dim3((n + 255) / 256, B, (sa.n_blocks + kSortStage - 1) / kSortStage), dim3(256), 0,
-                    stream, sa);
+        a.sorted = static_cast<unsigned long long *>(scratch);
+        a.n_blocks = (n + kSortBlock - 1) / kSortBlock;
+        a.rank_wgs = a.n_blocks * (kSortBlock / 64);
+        const int z = (a.n_blocks + kSortStage - 1) / kSortStage;
+        LVLM_LAUNCH(prof, rank_block_kernel<KEY>, dim3(a.rank_wgs + norm_wgs, B), dim3(1024), 0, stream, a);
+        LVLM_LAUNCH(prof, rank_search_kernel<KEY>, dim3((n + 255) / 256, B, z), dim3(256), 0, stream, a);
+        if constexpr (KEY::kOrder) {
+            if (z > 1) LVLM_LAUNCH(prof, rank_order_kernel, dim3((n + 255) / 256, B), dim3(256), 0, stream, a);
+        }
         return;
     }
-    RankArgs ra{};
-    ra.score = score;
-    ra.rank = rank;
-    ra.n = n;
-    LVLM_LAUNCH(prof, rank_kernel, dim3((n + kRankBlock - 1) / kRankBlock, B), dim3(1024), 0, stream, ra);
+    a.rank_wgs = (n + kRankBlock - 1) / kRankBlock;
+    LVLM_LAUNCH(prof, rank_kernel<KEY>, dim3(a.rank_wgs + norm_wgs, B), dim3(1024), 0, stream, a);
+}
+}  // namespace
+
+void launch_rank(const Prof &prof, const float *score, int32_t *rank, int n, int B, void *scratch, const NormJob *norm) {
+    launch_rank_by(prof, ByScore{score}, rank, n, B, scratch, norm);
+}
+
+void launch_owner_order(const Prof &prof, const OwnerJob &owners, int32_t *rank, int n, int B, void *scratch) {
+    launch_rank_by(prof, ByOwner{owners}, rank, n, B, scratch, nullptr);
 }
 
 MergeWs merge_ws(const lvlm_merge_desc &d, const lvlm_plane *planes) {

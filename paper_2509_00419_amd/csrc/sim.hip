@@ -3,17 +3,16 @@
 // other token joins the dominant token it is most similar to (cosine of the rows of plane 0) and each
 // dominant token becomes the size-weighted mean of its cluster.
 //
-//   rank_kernel (merge.hip)  ranks by score                     -> dominant = rank < n_keep
+//   rank_kernel (merge.hip)  ranks by score -> dominant = rank < n_keep; in the same launch 1 / |row| of every image token
 //   sim_index_kernel         positions of dominant tokens, list of the others (both ascending)
-//   sim_norm_kernel          1 / |row| of every image token
 //   sim_gemm_kernel          the one dense contraction of the path: (dominant x others) dot products on
-//                            the matrix cores, 128 x 128 tile per workgroup, with the arg-max over the
-//                            dominant axis taken in the epilogue (nothing of the similarity matrix is stored)
-//   sim_assign_kernel        folds the per-block arg-maxima; emits the assignment and a sort key
-//   rank_kernel + sim_order_kernel   tokens ordered by (assignment, index): each cluster is a contiguous,
+//                            the matrix cores, with the arg-max over the dominant axis taken in the epilogue (nothing
+//                            of the similarity matrix is stored): one 64-bit atomic maximum per other token and tile of
+//                            (cosine, lower position first), so the result does not depend on who comes first
+//   rank_kernel              tokens ordered by (dominant position joined, index): each cluster is a contiguous,
 //                            index-ordered segment, so the sums below run in a fixed order
-//   sim_merge_kernel         one workgroup per dominant token and column block: size-weighted mean
-//   sim_copy_kernel          rows outside the image span
+//   sim_merge_kernel         one workgroup per dominant token: size-weighted mean of its cluster; further workgroups
+//                            copy the rows outside the image span
 #include <limits.h>
 
 #include "common.h"
@@ -25,7 +24,6 @@ namespace {
 
 struct SimArgs {
     PlaneDev plane[LVLM_MAX_PLANES];
-    const float *score;
     const float *size_in;   // [B, n] or null (all ones)
     float *size_out;        // [B, n_keep] or null
     int32_t *rank;          // [B, n]
@@ -33,78 +31,59 @@ struct SimArgs {
     int32_t *keep_idx;      // [B, n_keep]
     int32_t *rest_idx;      // [B, r]
     float *inv_norm;        // [B, n]
-    float *pbest_val;       // [B, NB, r]
-    int32_t *pbest_idx;     // [B, NB, r]
+    unsigned long long *best;   // [B, r]  (key of the cosine, ~dominant position)
     int32_t *assign;        // [B, n]
-    float *key;             // [B, n]
-    int32_t *rank2;         // [B, n]
-    int32_t *order;         // [B, n]
-    int B, N, img_begin, n, n_keep, r, NB, n_planes;
+    int32_t *order;         // [B, n]   other tokens by (assignment, index), then the dominant ones
+    int32_t *owner;         // [B, n]   assignment of order[s]
+    int B, N, img_begin, n, n_keep, r, n_planes;
 };
 
 // ---- dominant positions and the list of the other tokens, both in ascending index ----
+// One workgroup per 4096 tokens of a sequence (thread t holds four of them); it counts the dominant tokens in front of
+// its chunk itself, all loads in flight together, so the chunks need nothing from each other.
+constexpr int kSimChunk = 4096;
 __global__ __launch_bounds__(1024) void sim_index_kernel(SimArgs a) {
-    __shared__ int wave_cnt[16];
-    __shared__ int base_s;
+    __shared__ int wave_tot[16], wave_before[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.x;
+    const int b = blockIdx.y, s0 = blockIdx.x * kSimChunk, j0 = s0 + 4 * tid;
     const int32_t *rank = a.rank + (long long)b * a.n;
-    if (tid == 0) base_s = 0;
-    __syncthreads();
-    for (int j0 = 0; j0 < a.n; j0 += 1024) {
-        const int j = j0 + tid;
-        const bool dom = j < a.n && rank[j] < a.n_keep;
-        const unsigned long long bal = __ballot(dom);
-        if (lane == 0) wave_cnt[wave] = __popcll(bal);
-        __syncthreads();
-        int p = base_s + __popcll(bal & ((1ull << lane) - 1ull));
-        int tot = 0;
-        for (int w = 0; w < 16; ++w) {
-            p += w < wave ? wave_cnt[w] : 0;
-            tot += wave_cnt[w];
-        }
-        if (j < a.n) {
-            if (dom) {
-                a.dom_of[(long long)b * a.n + j] = p;
-                a.keep_idx[(long long)b * a.n_keep + p] = j;
-            } else {
-                const int q = j - p;              // tokens before j that are not dominant
-                a.dom_of[(long long)b * a.n + j] = -(q + 1);
-                a.rest_idx[(long long)b * a.r + q] = j;
-            }
-        }
-        __syncthreads();
-        if (tid == 0) base_s += tot;
-        __syncthreads();
-    }
-}
-
-// ---- 1 / |row| of every image token of plane 0 (one wave per token) ----
-template <int DT>
-__global__ __launch_bounds__(256) void sim_norm_kernel(SimArgs a) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int j = blockIdx.x * 4 + wave, b = blockIdx.y;
-    if (j >= a.n) return;
-    const PlaneDev &p = a.plane[0];
-    const char *row = p.src + (long long)b * p.src_stride_b + (long long)(a.img_begin + j) * p.row_bytes;
-    float s = 0.f;
-    for (int u = lane; u < p.row_bytes / 16; u += 64) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(row + 16 * u);
-        const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+    bool dom[4];
+    int cnt = 0, before = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (DT == LVLM_BF16) {
-                const float lo = __uint_as_float(d[i] << 16), hi = __uint_as_float(d[i] & 0xffff0000u);
-                s = fmaf(lo, lo, s);
-                s = fmaf(hi, hi, s);
-            } else {
-                const float x = __uint_as_float(d[i]);
-                s = fmaf(x, x, s);
-            }
+    for (int e = 0; e < 4; ++e) {
+        dom[e] = j0 + e < a.n && rank[min(j0 + e, a.n - 1)] < a.n_keep;
+        cnt += dom[e];
+    }
+#pragma unroll 4
+    for (int i = tid; i < s0; i += 1024) before += rank[i] < a.n_keep;
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (lane >= o) incl += t;
+        before += __shfl_xor(before, o);
+    }
+    if (lane == 63) wave_tot[wave] = incl;
+    if (lane == 0) wave_before[wave] = before;
+    __syncthreads();
+    int p = incl - cnt;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) p += wave_before[w] + (w < wave ? wave_tot[w] : 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int j = j0 + e;
+        if (j >= a.n) continue;
+        if (dom[e]) {
+            a.dom_of[(long long)b * a.n + j] = p;
+            a.keep_idx[(long long)b * a.n_keep + p] = j;
+            ++p;
+        } else {
+            const int q = j - p;              // tokens before j that are not dominant
+            a.dom_of[(long long)b * a.n + j] = -(q + 1);
+            a.rest_idx[(long long)b * a.r + q] = j;
+            a.best[(long long)b * a.r + q] = 0ull;
         }
     }
-    s = wave_sum(s);
-    if (lane == 0) a.inv_norm[(long long)b * a.n + j] = s > 0.f ? 1.0f / sqrtf(s) : 1.0f;
 }
 
 // ---- dot products dominant x others on the matrix cores, arg-max over the dominant axis ----
@@ -139,7 +118,7 @@ __global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int hf = lane >> 5, l32 = lane & 31;
-    const int wn = wave % NWN, wm = wave / NWN;
+    const int wn = wave % NWN, wm = __builtin_amdgcn_readfirstlane(wave / NWN);
     // tile of this workgroup
     const int NBt = (a.n_keep + TM - 1) / TM, MBt = (a.r + TN - 1) / TN;
     constexpr int RUN = kSimGN * kSimGM;
@@ -281,47 +260,12 @@ __global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
                     v = bv[w][i];
                     ix = bi[w][i];
                 }
-            const long long o = ((long long)b * a.NB + nb) * a.r + q;
-            a.pbest_val[o] = v;
-            a.pbest_idx[o] = ix;
+            if (ix != INT_MAX)
+                atomicMax(&a.best[(long long)b * a.r + q],
+                          ((unsigned long long)score_key(v) << 32) | (unsigned long long)(0xffffffffu - (uint32_t)ix));
         }
     }
 #undef LVLM_SIM8
-}
-
-// ---- fold the dominant blocks; assignment of every token and the key that sorts tokens by it ----
-__global__ __launch_bounds__(256) void sim_assign_kernel(SimArgs a) {
-    const int j = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
-    if (j >= a.n) return;
-    const int d = a.dom_of[(long long)b * a.n + j];
-    int pos;
-    float key;
-    if (d >= 0) {
-        pos = d;
-        key = -1.0e9f;          // dominant tokens sort behind every cluster member
-    } else {
-        const int q = -d - 1;
-        float best_v = -INFINITY;
-        pos = INT_MAX;
-        for (int nb = 0; nb < a.NB; ++nb) {
-            const long long o = ((long long)b * a.NB + nb) * a.r + q;
-            const float v = a.pbest_val[o];
-            const int i = a.pbest_idx[o];
-            if (v > best_v || (v == best_v && i < pos)) {
-                best_v = v;
-                pos = i;
-            }
-        }
-        if (pos == INT_MAX) pos = 0;
-        key = -(float)pos;      // exact: positions are far below 2^24
-    }
-    a.assign[(long long)b * a.n + j] = pos;
-    a.key[(long long)b * a.n + j] = key;
-}
-
-__global__ __launch_bounds__(256) void sim_order_kernel(SimArgs a) {
-    const int j = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
-    if (j < a.n) a.order[(long long)b * a.n + a.rank2[(long long)b * a.n + j]] = j;
 }
 
 // ---- size-weighted mean of each cluster ----
@@ -347,99 +291,133 @@ __device__ __forceinline__ void store_mean(char *dst, const Acc<DT, UB> &acc, fl
     }
 }
 
-template <int DT, int UB>
-__device__ __forceinline__ void merge_plane(const SimArgs &a, const PlaneDev &p, int b, int i, int lo, int hi) {
+// Units unit0, unit0 + 256, ... of one plane's row of dominant position i (token ji), NU at a time.  `members` holds the
+// cluster's first 64 other tokens, one per lane; up to four of their rows are in flight together.
+template <int DT, int UB, int NU>
+__device__ __forceinline__ void merge_plane(const SimArgs &a, const PlaneDev &p, int b, int i, int ji, int lo, int n_mem,
+                                            int members) {
     using U = typename Unit<UB>::type;
-    const int unit = blockIdx.y * 256 + threadIdx.x;
-    if (unit >= p.row_bytes / UB) return;
-    const char *img = p.src + (long long)b * p.src_stride_b + (long long)a.img_begin * p.row_bytes + (long long)unit * UB;
-    char *dst = p.dst + (long long)b * p.dst_stride_b + (long long)(a.img_begin + i) * p.row_bytes + (long long)unit * UB;
-    const int ji = a.keep_idx[(long long)b * a.n_keep + i];
-    const U own = *reinterpret_cast<const U *>(img + (long long)ji * p.row_bytes);
-    if (p.rule != LVLM_RULE_WEIGHTED || DT == LVLM_I32) {
-        *reinterpret_cast<U *>(dst) = own;
+    const int units = p.row_bytes / UB;
+    const char *img0 = p.src + (long long)b * p.src_stride_b + (long long)a.img_begin * p.row_bytes;
+    char *dst0 = p.dst + (long long)b * p.dst_stride_b + (long long)(a.img_begin + i) * p.row_bytes;
+    const bool weighted = p.rule == LVLM_RULE_WEIGHTED && DT != LVLM_I32;
+    const float *size = a.size_in ? a.size_in + (long long)b * a.n : nullptr;
+    // whole waves in and out of the loop: lanes without a unit still hand out member indices
+    for (int w0 = threadIdx.x & ~63; w0 < units; w0 += 256 * NU) {
+        const int u0 = w0 + (threadIdx.x & 63);
+        int off[NU];                            // byte offset of the unit in a row (a repeat past the end, not stored)
+#pragma unroll
+        for (int x = 0; x < NU; ++x) off[x] = min(u0 + 256 * x, units - 1) * UB;
+        U own[NU];
+#pragma unroll
+        for (int x = 0; x < NU; ++x) own[x] = *reinterpret_cast<const U *>(img0 + (long long)ji * p.row_bytes + off[x]);
+        if (!weighted) {
+#pragma unroll
+            for (int x = 0; x < NU; ++x)
+                if (u0 + 256 * x < units) *reinterpret_cast<U *>(dst0 + off[x]) = own[x];
+            continue;
+        }
+        if constexpr (DT != LVLM_I32) {
+            Acc<DT, UB> acc[NU];
+            float tot = size ? size[ji] : 1.0f;
+#pragma unroll
+            for (int x = 0; x < NU; ++x) {
+#pragma unroll
+                for (int e = 0; e < Acc<DT, UB>::NE; ++e) acc[x].v[e] = 0.f;
+                accumulate<DT, UB>(acc[x], own[x], tot);
+            }
+            int mem = members;
+            for (int s0 = 0; s0 < n_mem; s0 += 4) {          // cluster members in ascending index
+                if ((s0 & 63) == 0 && s0 > 0) mem = a.order[(long long)b * a.n + min(lo + s0 + (int)(threadIdx.x & 63), a.n - 1)];
+                U val[4][NU];
+                float w[4];
+#pragma unroll
+                for (int y = 0; y < 4; ++y) {
+                    const int t = __builtin_amdgcn_readlane(mem, (min(s0 + y, n_mem - 1)) & 63);
+                    w[y] = size ? size[t] : 1.0f;
+#pragma unroll
+                    for (int x = 0; x < NU; ++x) val[y][x] = *reinterpret_cast<const U *>(img0 + (long long)t * p.row_bytes + off[x]);
+                }
+#pragma unroll
+                for (int y = 0; y < 4; ++y) {
+                    if (s0 + y >= n_mem) break;
+#pragma unroll
+                    for (int x = 0; x < NU; ++x) accumulate<DT, UB>(acc[x], val[y][x], w[y]);
+                    tot += w[y];
+                }
+            }
+#pragma unroll
+            for (int x = 0; x < NU; ++x)
+                if (u0 + 256 * x < units) store_mean<DT, UB>(dst0 + off[x], acc[x], 1.0f / tot);
+            if (size && a.size_out && threadIdx.x == 0 && u0 == 0) a.size_out[(long long)b * a.n_keep + i] = tot;
+        }
+    }
+}
+
+// One row of every plane from its old place to its new one.
+__device__ __forceinline__ void copy_row(const SimArgs &a, int b, int from, int to) {
+    for (int pi = 0; pi < a.n_planes; ++pi) {
+        const PlaneDev &p = a.plane[pi];
+        const char *s = p.src + (long long)b * p.src_stride_b + (long long)from * p.row_bytes;
+        char *d = p.dst + (long long)b * p.dst_stride_b + (long long)to * p.row_bytes;
+        for (int byte = threadIdx.x * p.unit_bytes; byte < p.row_bytes; byte += 256 * p.unit_bytes) {
+            if (p.unit_bytes == 16) *reinterpret_cast<uint4 *>(d + byte) = *reinterpret_cast<const uint4 *>(s + byte);
+            else if (p.unit_bytes == 4) *reinterpret_cast<uint32_t *>(d + byte) = *reinterpret_cast<const uint32_t *>(s + byte);
+            else *reinterpret_cast<uint16_t *>(d + byte) = *reinterpret_cast<const uint16_t *>(s + byte);
+        }
+    }
+}
+
+// nothing removed: every row stays where it is
+__global__ __launch_bounds__(256) void sim_copy_kernel(SimArgs a) { copy_row(a, blockIdx.y, blockIdx.x, blockIdx.x); }
+
+// One workgroup per dominant position, every plane and column in it; workgroups past them copy the rows outside the
+// image span.  The tokens assigned to position i form the
+// segment [lo, lo + n) of the sorted order; its two ends are found by all waves at once, 64 probes of the owners a
+// round (two rounds up to 4096 other tokens, three up to 262144) instead of one thread's bisection, whose chain of some
+// 20 pairs of dependent loads per workgroup was the time of the kernel.  Bound by memory: 8 x 1263 clusters of 4096 bf16
+// channels (213 MB) 72 -> 33 us.
+__global__ __launch_bounds__(256) void sim_merge_kernel(SimArgs a) {
+    const int i = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63;
+    if (i >= a.n_keep) {
+        const int o = i - a.n_keep;                  // o-th row outside the image span
+        copy_row(a, b, o < a.img_begin ? o : o + a.n, o < a.img_begin ? o : o + a.n_keep);
         return;
     }
-    if constexpr (DT != LVLM_I32) {
-        const float *size = a.size_in ? a.size_in + (long long)b * a.n : nullptr;
-        const int32_t *order = a.order + (long long)b * a.n;
-        Acc<DT, UB> acc;
-#pragma unroll
-        for (int e = 0; e < Acc<DT, UB>::NE; ++e) acc.v[e] = 0.f;
-        float tot = size ? size[ji] : 1.0f;
-        accumulate<DT, UB>(acc, own, tot);
-        for (int s = lo; s < hi; ++s) {          // cluster members in ascending index
-            const int t = order[s];
-            const float st = size ? size[t] : 1.0f;
-            accumulate<DT, UB>(acc, *reinterpret_cast<const U *>(img + (long long)t * p.row_bytes), st);
-            tot += st;
-        }
-        store_mean<DT, UB>(dst, acc, 1.0f / tot);
-        if (size && blockIdx.y == 0 && threadIdx.x == 0 && (int)blockIdx.z < a.B && a.size_out)
-            a.size_out[(long long)b * a.n_keep + i] = tot;
+    const int32_t *order = a.order + (long long)b * a.n, *owner = a.owner + (long long)b * a.n;
+    const int ji = a.keep_idx[(long long)b * a.n_keep + i];
+    // owners below i, and below i + 1, among the r other tokens: each lies in a range [base, base + len)
+    int lo = 0, hi = 0, len_lo = a.r, len_hi = a.r;
+    while (len_lo > 0 || len_hi > 0) {
+        const int st_lo = (len_lo + 65) / 65, st_hi = (len_hi + 65) / 65;      // probes base + step * (lane + 1) - 1
+        const int p_lo = lo + st_lo * (lane + 1) - 1, p_hi = hi + st_hi * (lane + 1) - 1;
+        const int o_lo = owner[min(p_lo, a.n - 1)], o_hi = owner[min(p_hi, a.n - 1)];
+        const int c_lo = __popcll(__ballot(len_lo > 0 && st_lo * (lane + 1) <= len_lo && o_lo < i));
+        const int c_hi = __popcll(__ballot(len_hi > 0 && st_hi * (lane + 1) <= len_hi && o_hi < i + 1));
+        // c probes are below: the end lies in the step behind the last of them, whose own last place is no candidate
+        const int rest_lo = len_lo - c_lo * st_lo, rest_hi = len_hi - c_hi * st_hi;
+        lo += c_lo * st_lo;
+        hi += c_hi * st_hi;
+        len_lo = max(0, min(st_lo - 1, rest_lo));
+        len_hi = max(0, min(st_hi - 1, rest_hi));
     }
-}
-
-__global__ __launch_bounds__(256) void sim_merge_kernel(SimArgs a) {
-    __shared__ int s_lo, s_hi;
-    const int i = blockIdx.x;
-    const int pi = blockIdx.z / a.B, b = blockIdx.z % a.B;
-    const PlaneDev &p = a.plane[pi];
-    if ((int)blockIdx.y >= p.col_blocks) return;
-    if (threadIdx.x == 0) {
-        // the tokens assigned to dominant position i form the segment [lo, hi) of the sorted order
-        const int32_t *order = a.order + (long long)b * a.n;
-        const int32_t *assign = a.assign + (long long)b * a.n;
-        int lo = 0, hi = a.r;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (assign[order[mid]] >= i) hi = mid; else lo = mid + 1;
+    const int n_mem = hi - lo;
+    const int members = order[min(lo + lane, a.n - 1)];
+    // sizes of all-ones clusters are written here (the weighted path writes them when sizes are given)
+    if (threadIdx.x == 0 && a.size_out && a.size_in == nullptr) a.size_out[(long long)b * a.n_keep + i] = (float)(1 + n_mem);
+    for (int pi = 0; pi < a.n_planes; ++pi) {
+        const PlaneDev &p = a.plane[pi];
+        if (p.dtype == LVLM_BF16) {
+            if (p.unit_bytes == 16) merge_plane<LVLM_BF16, 16, 2>(a, p, b, i, ji, lo, n_mem, members);
+            else if (p.unit_bytes == 4) merge_plane<LVLM_BF16, 4, 1>(a, p, b, i, ji, lo, n_mem, members);
+            else merge_plane<LVLM_BF16, 2, 1>(a, p, b, i, ji, lo, n_mem, members);
+        } else if (p.dtype == LVLM_F32) {
+            if (p.unit_bytes == 16) merge_plane<LVLM_F32, 16, 2>(a, p, b, i, ji, lo, n_mem, members);
+            else merge_plane<LVLM_F32, 4, 1>(a, p, b, i, ji, lo, n_mem, members);
+        } else {
+            if (p.unit_bytes == 16) merge_plane<LVLM_I32, 16, 1>(a, p, b, i, ji, lo, n_mem, members);
+            else merge_plane<LVLM_I32, 4, 1>(a, p, b, i, ji, lo, n_mem, members);
         }
-        s_lo = lo;
-        hi = a.r;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (assign[order[mid]] >= i + 1) hi = mid; else lo = mid + 1;
-        }
-        s_hi = lo;
-        // sizes of all-ones clusters are written here (the weighted path writes them when sizes are given)
-        if (pi == 0 && blockIdx.y == 0 && a.size_out && a.size_in == nullptr)
-            a.size_out[(long long)b * a.n_keep + i] = (float)(1 + s_hi - s_lo);
-    }
-    __syncthreads();
-    const int lo = s_lo, hi = s_hi;
-    if (p.dtype == LVLM_BF16) {
-        if (p.unit_bytes == 16) merge_plane<LVLM_BF16, 16>(a, p, b, i, lo, hi);
-        else if (p.unit_bytes == 4) merge_plane<LVLM_BF16, 4>(a, p, b, i, lo, hi);
-        else merge_plane<LVLM_BF16, 2>(a, p, b, i, lo, hi);
-    } else if (p.dtype == LVLM_F32) {
-        if (p.unit_bytes == 16) merge_plane<LVLM_F32, 16>(a, p, b, i, lo, hi);
-        else merge_plane<LVLM_F32, 4>(a, p, b, i, lo, hi);
-    } else {
-        if (p.unit_bytes == 16) merge_plane<LVLM_I32, 16>(a, p, b, i, lo, hi);
-        else merge_plane<LVLM_I32, 4>(a, p, b, i, lo, hi);
-    }
-}
-
-// ---- rows outside the image span (or every row when nothing is removed) ----
-struct CopyArgs {
-    PlaneDev plane[LVLM_MAX_PLANES];
-    int B, n_rows, split, src_shift, dst_shift;   // row ro >= split reads ro + src_shift, writes ro + dst_shift
-};
-
-__global__ __launch_bounds__(256) void sim_copy_kernel(CopyArgs a) {
-    const int pi = blockIdx.z / a.B, b = blockIdx.z % a.B;
-    const PlaneDev &p = a.plane[pi];
-    const long long byte = ((long long)blockIdx.y * 256 + threadIdx.x) * p.unit_bytes;
-    if (byte >= p.row_bytes) return;
-    for (int ro = blockIdx.x; ro < a.n_rows; ro += gridDim.x) {
-        const int rs = ro < a.split ? ro : ro + a.src_shift;
-        const int rd = ro < a.split ? ro : ro + a.dst_shift;
-        const char *s = p.src + (long long)b * p.src_stride_b + (long long)rs * p.row_bytes + byte;
-        char *d = p.dst + (long long)b * p.dst_stride_b + (long long)rd * p.row_bytes + byte;
-        if (p.unit_bytes == 16) *reinterpret_cast<uint4 *>(d) = *reinterpret_cast<const uint4 *>(s);
-        else if (p.unit_bytes == 4) *reinterpret_cast<uint32_t *>(d) = *reinterpret_cast<const uint32_t *>(s);
-        else *reinterpret_cast<uint16_t *>(d) = *reinterpret_cast<const uint16_t *>(s);
     }
 }
 
@@ -460,7 +438,6 @@ SimWs sim_ws(const lvlm_merge_desc &d) {
     const int r = d.n_img - d.n_keep;
     // the large tile shape once it still gives every CU two workgroups
     w.tile = ((long long)d.B * ((d.n_keep + 255) / 256) * ((r + 255) / 256) >= 512) ? 256 : 128;
-    w.NB = (d.n_keep + w.tile - 1) / w.tile;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
@@ -472,12 +449,11 @@ SimWs sim_ws(const lvlm_merge_desc &d) {
     w.keep_idx = take((size_t)d.B * d.n_keep * 4);
     w.rest_idx = take((size_t)d.B * (r > 0 ? r : 1) * 4);
     w.inv_norm = take(n * 4);
-    w.pbest_val = take((size_t)d.B * w.NB * (r > 0 ? r : 1) * 4);
-    w.pbest_idx = take((size_t)d.B * w.NB * (r > 0 ? r : 1) * 4);
+    w.best = take((size_t)d.B * (r > 0 ? r : 1) * 8);
     w.assign = take(n * 4);
-    w.key = take(n * 4);
     w.rank2 = take(n * 4);
     w.order = take(n * 4);
+    w.owner = take(n * 4);
     w.sorted = take(rank_scratch_bytes(d.n_img, d.B));     // sorted blocks of the two rankings, used in turn
     w.total = off;
     return w;
@@ -489,14 +465,7 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     hipStream_t stream = prof.stream;
     const int r = d.n_img - d.n_keep;
     SimArgs a{};
-    CopyArgs c{};
-    int col_blocks = 1;
-    for (int i = 0; i < d.n_planes; ++i) {
-        a.plane[i] = make_plane_dev(planes[i]);
-        c.plane[i] = a.plane[i];
-        if (a.plane[i].col_blocks > col_blocks) col_blocks = a.plane[i].col_blocks;
-    }
-    a.score = score_mean;
+    for (int i = 0; i < d.n_planes; ++i) a.plane[i] = make_plane_dev(planes[i]);
     a.size_in = size_in;
     a.size_out = size_out;
     a.rank = reinterpret_cast<int32_t *>(ws + w.rank);
@@ -504,45 +473,38 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     a.keep_idx = keep_idx ? keep_idx : reinterpret_cast<int32_t *>(ws + w.keep_idx);
     a.rest_idx = reinterpret_cast<int32_t *>(ws + w.rest_idx);
     a.inv_norm = reinterpret_cast<float *>(ws + w.inv_norm);
-    a.pbest_val = reinterpret_cast<float *>(ws + w.pbest_val);
-    a.pbest_idx = reinterpret_cast<int32_t *>(ws + w.pbest_idx);
+    a.best = reinterpret_cast<unsigned long long *>(ws + w.best);
     a.assign = assign ? assign : reinterpret_cast<int32_t *>(ws + w.assign);
-    a.key = reinterpret_cast<float *>(ws + w.key);
-    a.rank2 = reinterpret_cast<int32_t *>(ws + w.rank2);
     a.order = reinterpret_cast<int32_t *>(ws + w.order);
-    a.B = d.B; a.N = d.N; a.img_begin = d.img_begin; a.n = d.n_img; a.n_keep = d.n_keep; a.r = r; a.NB = w.NB;
+    a.owner = reinterpret_cast<int32_t *>(ws + w.owner);
+    a.B = d.B; a.N = d.N; a.img_begin = d.img_begin; a.n = d.n_img; a.n_keep = d.n_keep; a.r = r;
     a.n_planes = d.n_planes;
-    c.B = d.B;
 
     if (r == 0) {
         a.keep_idx = keep_idx;
         a.assign = assign;
-        c.n_rows = d.N; c.split = d.N; c.src_shift = 0; c.dst_shift = 0;
         prof.begin("sim_copy");
-        LVLM_LAUNCH(prof, sim_copy_kernel, dim3(d.N < 2048 ? d.N : 2048, col_blocks, d.B * d.n_planes), dim3(256), 0,
-                           stream, c);
+        LVLM_LAUNCH(prof, sim_copy_kernel, dim3(d.N, d.B), dim3(256), 0, stream, a);
         prof.end();
         if (keep_idx || assign || size_out)
             LVLM_LAUNCH(prof, sim_identity_kernel, dim3((d.n_img + 255) / 256, d.B), dim3(256), 0, stream, a);
         return hipGetLastError();
     }
 
-    const dim3 per_token((d.n_img + 255) / 256, d.B);
+    NormJob norm{};
+    norm.src = a.plane[0].src + (long long)d.img_begin * a.plane[0].row_bytes;
+    norm.stride_b = a.plane[0].src_stride_b;
+    norm.inv_norm = a.inv_norm;
+    norm.row_bytes = a.plane[0].row_bytes; norm.dtype = planes[0].dtype; norm.n = d.n_img;
     prof.begin("sim_rank");
-    launch_rank(prof, score_mean, a.rank, d.n_img, d.B, ws + w.sorted);
+    launch_rank(prof, score_mean, a.rank, d.n_img, d.B, ws + w.sorted, &norm);
     prof.end();
     prof.begin("sim_index");
-    LVLM_LAUNCH(prof, sim_index_kernel, dim3(d.B), dim3(1024), 0, stream, a);
-    prof.end();
-    prof.begin("sim_norm");
-    if (planes[0].dtype == LVLM_BF16)
-        LVLM_LAUNCH(prof, sim_norm_kernel<LVLM_BF16>, dim3((d.n_img + 3) / 4, d.B), dim3(256), 0, stream, a);
-    else
-        LVLM_LAUNCH(prof, sim_norm_kernel<LVLM_F32>, dim3((d.n_img + 3) / 4, d.B), dim3(256), 0, stream, a);
+    LVLM_LAUNCH(prof, sim_index_kernel, dim3((d.n_img + kSimChunk - 1) / kSimChunk, d.B), dim3(1024), 0, stream, a);
     prof.end();
     prof.begin("sim_gemm");
     {
-        const long long tiles = (long long)d.B * w.NB * ((r + w.tile - 1) / w.tile);
+        const long long tiles = (long long)d.B * ((d.n_keep + w.tile - 1) / w.tile) * ((r + w.tile - 1) / w.tile);
         constexpr int run = kSimGN * kSimGM;
         const dim3 ggrid((unsigned)(((tiles + run - 1) / run + 7) / 8 * 8 * run));
         const bool bf = planes[0].dtype == LVLM_BF16;
@@ -560,26 +522,14 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
 #undef LVLM_GEMM
     }
     prof.end();
-    prof.begin("sim_assign");
-    LVLM_LAUNCH(prof, sim_assign_kernel, per_token, dim3(256), 0, stream, a);
-    prof.end();
-    prof.begin("sim_rank2");
-    launch_rank(prof, a.key, a.rank2, d.n_img, d.B, ws + w.sorted);
-    prof.end();
+    OwnerJob oj{};
+    oj.dom_of = a.dom_of; oj.best = a.best; oj.order = a.order; oj.owner = a.owner; oj.assign = a.assign; oj.r = r;
     prof.begin("sim_order");
-    LVLM_LAUNCH(prof, sim_order_kernel, per_token, dim3(256), 0, stream, a);
+    launch_owner_order(prof, oj, reinterpret_cast<int32_t *>(ws + w.rank2), d.n_img, d.B, ws + w.sorted);
     prof.end();
     prof.begin("sim_merge");
-    LVLM_LAUNCH(prof, sim_merge_kernel, dim3(d.n_keep, col_blocks, d.B * d.n_planes), dim3(256), 0, stream, a);
+    LVLM_LAUNCH(prof, sim_merge_kernel, dim3(d.n_keep + d.N - d.n_img, d.B), dim3(256), 0, stream, a);
     prof.end();
-    const int outside = d.N - d.n_img;
-    if (outside > 0) {
-        c.n_rows = outside; c.split = d.img_begin; c.src_shift = d.n_img; c.dst_shift = d.n_keep;
-        prof.begin("sim_copy");
-        LVLM_LAUNCH(prof, sim_copy_kernel, dim3(outside < 2048 ? outside : 2048, col_blocks, d.B * d.n_planes),
-                           dim3(256), 0, stream, c);
-        prof.end();
-    }
     return hipGetLastError();
 }
 

@@ -1028,6 +1028,15 @@ def test_merge_similar(ctx):
     _similar_case(ctx, torch.bfloat16, 1, 2, 4500, 2, 64, 1200, 108, clusters=16)               # ranks by sorted blocks
 
 
+@pytest.mark.parametrize("n_img,n_keep,clusters,with_size", [
+    (66, 65, 0, True), (66, 1, 0, False), (65, 64, 3, True), (130, 64, 2, False),   # owner search: one other token, 65, 66
+    (4096, 3000, 3, False), (4097, 1, 0, True), (4400, 80, 2, True),                # chunk and block edges, hundreds per cluster
+    (8192, 8000, 0, False), (8300, 3900, 40, True)])                                # one and two groups of sorted blocks
+def test_merge_similar_cluster_bounds_and_long_rankings(ctx, n_img, n_keep, clusters, with_size):
+    _similar_case(ctx, torch.float32 if n_img < 200 else torch.bfloat16, 1, 3, n_img, 4, 40, n_keep, 600 + n_img,
+                  clusters=clusters, with_size=with_size)
+
+
 # --------------------------------------------------------------------------- seeded random shapes, every entry point
 def _random_lens(rng, n, Lmax, lo=0):
     edges = [127, 128, 129, 159, 160, 161, 255, 256, 257, 1023, 1024, 1025]
