@@ -64,7 +64,6 @@ MergeWs merge_ws(const lvlm_merge_desc &d, const lvlm_plane *planes);
 
 struct SimWs {
     size_t rank, dom_of, keep_idx, rest_idx, inv_norm, best, assign, rank2, order, owner, sorted, total;
-    int tile;      // rows of dominant (and of other) tokens per workgroup tile of the similarity product
 };
 SimWs sim_ws(const lvlm_merge_desc &d);
 

@@ -36,6 +36,7 @@ struct SimArgs {
     int32_t *order;         // [B, n]   other tokens by (assignment, index), then the dominant ones
     int32_t *owner;         // [B, n]   assignment of order[s]
     int B, N, img_begin, n, n_keep, r, n_planes;
+    int run;                // consecutive tiles of the similarity product an XCD takes at a time
 };
 
 // ---- dominant positions and the list of the other tokens, both in ascending index ----
@@ -87,43 +88,58 @@ __global__ __launch_bounds__(1024) void sim_index_kernel(SimArgs a) {
 }
 
 // ---- dot products dominant x others on the matrix cores, arg-max over the dominant axis ----
-// Workgroup tile: TM dominant rows x TN other rows, NWN x NWM waves, each owning TR x TC tiles of 32 x 32.
-// Two shapes are built: 256 x 256 with eight waves of 128 x 64 (large problems: per tile product it moves
-// a third less through LDS than the small shape, and half as much from L2) and 128 x 128 with four waves of
-// 64 x 64 (more workgroups when the problem is small).  Rows are gathered by index; the contraction runs
-// over 128-byte slices of the rows, double buffered in LDS with the next slice's global loads in flight
-// (named scalars: they are carried around the loop).  One slice is eight 16-byte units per row and every
-// thread stages four units of the dominant and four of the other rows.
+// Workgroup tile: 128 dominant rows x 128 other rows, each wave 64 x 32 TC of it.  Rows are gathered by index; the
+// contraction runs over 128-byte slices of the rows, which go from memory straight into a ring of LDS buffers (the
+// direct loads need no staging registers and no LDS store instructions).  One wait and one barrier per slice: a
+// wave waits for its own share of slice k, the barrier makes that everybody's share and at the same time frees
+// the buffer of slice k-1 for slice k + RING - 1.  The direct loads are written out as assembly because the compiler,
+// which cannot tell the ring's buffers apart, would wait for all of them before every LDS read; the waits that take
+// its place are counted by hand: every wave issues the same number of loads for every slice (repeats of the last
+// one past the end).
+// A direct load fills 1024 consecutive LDS bytes lane by lane, so rows cannot be padded apart; instead the
+// eight 16-byte units of row R lie in the order u ^ (R / 2 % 8), chosen by the address each lane reads from: the sixteen
+// lanes an LDS read serves at a time then hit sixteen different bank groups (no conflicts counted).
+// What bounds a workgroup is the time a slice takes to arrive, so there are two forms:
+//   up to 256 tiles (one per compute unit): a ring of four slices, eight waves, the loads of a slice spread over the
+//       products (a compute unit takes 16 cycles per direct load: all of a slice's at once hold the products up)
+//   more: a ring of two and four waves, so that two workgroups share a compute unit and cover each other's waits; the
+//       loads go out first
+// (wider slices than 64 bytes: half a cache line each time fetched every line twice.  256 x 128 and 256 x 256 tiles, which
+// load less per product, leave the last turn of workgroups emptier and came out even or behind.)
+// Measured (staging through registers and LDS stores, with the 128- and 256-row tiles it had -> this): 300 x 276 tokens of
+// 3584 channels 45 -> 28 us; 8 x 1263 x 529 of 4096 79 -> 59 us (its rows alone, once from memory: 22 us); 5091 x 11293
+// of 6144 700 -> 650 us = 1085 TFLOP/s.
 //
 // Tiles are numbered block by block (blocks of GN x GM tiles, ragged at the edges, batch rows one after the
-// other) and handed out in runs of GN * GM consecutive numbers, run j to XCD j % 8 (workgroups reach the
+// other) and handed out in runs of consecutive numbers, run j to XCD j % 8 (workgroups reach the
 // XCDs round-robin by id).  The workgroups resident on an XCD at the same time are then neighbours that
 // sweep the contraction axis together: a row slice fetched into that XCD's L2 serves up to GM (dominant
-// rows) or GN (other rows) of them, and every XCD gets the same number of tiles to within one run.
-constexpr int kSimGN = 8, kSimGM = 4;
+// rows) or GN (other rows) of them.  A run is an eighth of the tiles where that is what an XCD can hold at a time (64):
+// every XCD gets one stretch and fetches few rows that another one fetches too; else GN * GM.
+constexpr int kSimTile = 128, kSimGN = 8, kSimGM = 4;
 
-template <int DT, int NWN, int NWM, int TR, int TC, bool RAGGED>
-__global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
-    constexpr int NT = 64 * NWN * NWM;
-    constexpr int TM = NWN * TR * 32, TN = NWM * TC * 32;
+__device__ __attribute__((aligned(16))) const uint32_t kSimZero[4] = {0, 0, 0, 0};     // what lies beyond the end of a row
+
+template <int DT, int NWM, int RING, bool RAGGED>
+__global__ __launch_bounds__(128 * NWM) void sim_gemm_kernel(SimArgs a) {
+    constexpr int NWN = 2, NW = NWN * NWM, NT = 64 * NW;
+    constexpr int TM = kSimTile, TN = kSimTile, TR = TM / NWN / 32, TC = TN / NWM / 32;
     constexpr int SB = 128;              // bytes of one slice of a row
-    constexpr int PITCH = SB + 16;       // slice + 16 bytes: spreads the rows over the LDS banks
-    constexpr int RPI = NT / 8;          // rows one load instruction of the workgroup covers
-    constexpr int UA = TM / RPI, UB = TN / RPI;      // staging units per thread: rows srow + RPI j of each operand
-    __shared__ __attribute__((aligned(16))) char a_lds[2][TM * PITCH];
-    __shared__ __attribute__((aligned(16))) char b_lds[2][TN * PITCH];
+    constexpr int UPS = SB / 16, RPL = 64 / UPS;     // 16-byte units of a row's slice, rows per direct load
+    constexpr int SLOT = (TM + TN) * SB; // the dominant rows, then the others
+    constexpr int DPW = (TM + TN) / RPL / NW;        // direct loads per wave and slice
+    __shared__ __attribute__((aligned(1024))) char ring[RING * SLOT];
     __shared__ float invn[TM];
     __shared__ float bv[NWN][TN];
     __shared__ int bi[NWN][TN];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hf = lane >> 5, l32 = lane & 31;
-    const int wn = wave % NWN, wm = __builtin_amdgcn_readfirstlane(wave / NWN);
+    const int wn = wave % NWN, wm = wave / NWN;
     // tile of this workgroup
     const int NBt = (a.n_keep + TM - 1) / TM, MBt = (a.r + TN - 1) / TN;
-    constexpr int RUN = kSimGN * kSimGM;
     const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-    int t = ((seq / RUN) * 8 + xcd) * RUN + seq % RUN;
+    int t = ((seq / a.run) * 8 + xcd) * a.run + seq % a.run;
     if (t >= a.B * NBt * MBt) return;
     const int b = t / (NBt * MBt);
     t -= b * NBt * MBt;
@@ -139,42 +155,41 @@ __global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
     const PlaneDev &p = a.plane[0];
     const int32_t *keep = a.keep_idx + (long long)b * a.n_keep;
     const int32_t *rest = a.rest_idx + (long long)b * a.r;
-    const int srow = tid >> 3, su = tid & 7;        // staging: rows srow + RPI j (j < 4), unit su of the slice
-    // Addresses are a uniform base (batch row, slice) plus a per-thread 32-bit byte offset (row, unit) that
-    // never changes: the slice loop then needs no vector instruction per load -- on this chip matrix and
-    // vector instructions do not overlap, so every one of them is time taken from the matrix cores.  The
-    // offsets fit: the image rows of one batch row span less than 2 GiB (checked on the host).
+    // Direct load x of this wave: rows 8 (wave DPW + x) .. + 7 of the slot, lane -> row lane / 8, place lane % 8.
+    // Addresses are a uniform base (batch row, slice) plus a per-thread 32-bit byte offset (row, unit) that never
+    // changes.  The offsets fit: the image rows of one batch row span less than 2 GiB (checked on the host).
     const char *img = p.src + (long long)b * p.src_stride_b + (long long)a.img_begin * p.row_bytes;
-    // (named scalars below, not arrays: values carried around the slice loop must stay in registers)
-    static_assert(UA <= 8 && UB <= 8, "staging registers are written out for up to eight units");
-#define LVLM_SIM8(M) M(0) M(1) M(2) M(3) M(4) M(5) M(6) M(7)
-#define LVLM_DECL(j)                                                                                        \
-    const unsigned oa##j = j < UA ? keep[min(nb * TM + srow + RPI * j, a.n_keep - 1)] * p.row_bytes + 16 * su : 0; \
-    const unsigned ob##j = j < UB ? rest[min(mb * TN + srow + RPI * j, a.r - 1)] * p.row_bytes + 16 * su : 0;      \
-    uint4 sa##j, sb##j;      /* written by load before store reads them */
-    LVLM_SIM8(LVLM_DECL)
-#undef LVLM_DECL
+    auto place = [](int row) { return (row >> 1) & 7; };
+    static_assert(DPW % 2 == 0, "rows 8 x .. of a wave: bit 3 of a row's number is that of x");
+    auto unit_of = [&](int x) { return (lane % UPS) ^ place(RPL * x + lane / UPS); };
+    unsigned off[DPW];
+#pragma unroll
+    for (int x = 0; x < DPW; ++x) {
+        const int R = RPL * (wave * DPW + x) + lane / UPS;
+        const int row = R < TM ? keep[min(nb * TM + R, a.n_keep - 1)] : rest[min(mb * TN + R - TM, a.r - 1)];
+        off[x] = (unsigned)row * (unsigned)p.row_bytes + 16 * unit_of(x);
+    }
     for (int i = tid; i < TM; i += NT) invn[i] = a.inv_norm[(long long)b * a.n + keep[min(nb * TM + i, a.n_keep - 1)]];
     const int nk = (p.row_bytes + SB - 1) / SB;      // the last slice may be partial: zero-filled
-
-    // RAGGED: rows that are not a whole number of slices; units of the last slice beyond the row read as zero
-    auto load = [&](int k) {
-        const char *base = img + SB * k;             // uniform
-        const bool in = !RAGGED || p.row_bytes - SB * k - 16 * su >= 16;
-        const uint4 z = make_uint4(0, 0, 0, 0);
-#define LVLM_LD(j)                                                                              \
-        if constexpr (j < UA) sa##j = in ? *reinterpret_cast<const uint4 *>(base + oa##j) : z;  \
-        if constexpr (j < UB) sb##j = in ? *reinterpret_cast<const uint4 *>(base + ob##j) : z;
-        LVLM_SIM8(LVLM_LD)
-#undef LVLM_LD
-    };
-    auto store = [&](int buf) {
-        char *da = &a_lds[buf][srow * PITCH + 16 * su], *db = &b_lds[buf][srow * PITCH + 16 * su];
-#define LVLM_ST(j)                                                                      \
-        if constexpr (j < UA) *reinterpret_cast<uint4 *>(da + j * RPI * PITCH) = sa##j;  \
-        if constexpr (j < UB) *reinterpret_cast<uint4 *>(db + j * RPI * PITCH) = sb##j;
-        LVLM_SIM8(LVLM_ST)
-#undef LVLM_ST
+    const unsigned ring0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)ring + 1024 * DPW * wave;
+    // direct loads [lo, hi) of slice k (the last slice again past the end) into slot k % RING
+    auto fetch = [&](int k, int lo, int hi) {
+        const char *base = img + SB * min(k, nk - 1);             // uniform
+        const unsigned dst = ring0 + (unsigned)(k % RING) * SLOT;
+#pragma unroll
+        for (int x = 0; x < DPW; ++x) {
+            if (x < lo || x >= hi) continue;
+            if constexpr (RAGGED) {
+                const bool in = p.row_bytes - SB * min(k, nk - 1) - 16 * unit_of(x) >= 16;
+                const char *src = in ? base + off[x] : reinterpret_cast<const char *>(kSimZero);
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(dst + 1024 * x)
+                             : "memory", "m0");
+            } else {
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off[x]), "s"(base),
+                             "s"(dst + 1024 * x)
+                             : "memory", "m0");
+            }
+        }
     };
 
     f32x16 acc[TR][TC];
@@ -185,38 +200,50 @@ __global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[nd][nr][r] = 0.f;
 
-    load(0);
-    store(0);
-    load(min(1, nk - 1));
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < RING - 1; ++k) fetch(k, 0, DPW);
+    // contraction step i of lane half hf takes unit NS hf + i of a row's slice
+    constexpr int NS = UPS / 2;
+    int uo[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) uo[i] = l32 * SB + 16 * ((NS * hf + i) ^ place(l32));
+    const char *const ar = ring + wn * (TR * 32 * SB), *const br = ring + TM * SB + wm * (TC * 32 * SB);
     for (int k = 0; k < nk; ++k) {
-        store((k + 1) & 1);                      // slice k+1 (a harmless repeat after the last one)
-        load(min(k + 2, nk - 1));
-        const int buf = k & 1;
-        const char *ar = &a_lds[buf][(wn * TR * 32 + l32) * PITCH + (SB / 2) * hf];
-        const char *br = &b_lds[buf][(wm * TC * 32 + l32) * PITCH + (SB / 2) * hf];
-        // one contraction step (16 bytes per lane and tile row) at a time: TR + TC operand words, TR x TC products
+        // all but the RING - 2 youngest slices' loads of this wave have landed: slice k is complete when everybody is here
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(DPW * (RING - 2)) : "memory");
+        if constexpr (RING == 2) fetch(k + RING - 1, 0, DPW);
+        const int at = (k % RING) * SLOT;
+        uint4 fa[NS][TR], fb[NS][TC];
 #pragma unroll
-        for (int i = 0; i < SB / 32; ++i) {
-            uint4 fa[TR], fb[TC];
+        for (int i = 0; i < NS; ++i) {
 #pragma unroll
-            for (int t = 0; t < TR; ++t) fa[t] = *reinterpret_cast<const uint4 *>(ar + t * 32 * PITCH + 16 * i);
+            for (int t2 = 0; t2 < TR; ++t2) fa[i][t2] = *reinterpret_cast<const uint4 *>(ar + at + uo[i] + t2 * 32 * SB);
 #pragma unroll
-            for (int t = 0; t < TC; ++t) fb[t] = *reinterpret_cast<const uint4 *>(br + t * 32 * PITCH + 16 * i);
+            for (int t2 = 0; t2 < TC; ++t2) fb[i][t2] = *reinterpret_cast<const uint4 *>(br + at + uo[i] + t2 * 32 * SB);
+        }
+        if constexpr (RING > 2) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
 #pragma unroll
             for (int nd = 0; nd < TR; ++nd)
 #pragma unroll
                 for (int nr = 0; nr < TC; ++nr) {
                     if constexpr (DT == LVLM_BF16) {
-                        mfma_one<DT>(acc[nd][nr], fa[nd], fb[nr], 0);      // rows = dominant, cols = others
+                        mfma_one<DT>(acc[nd][nr], fa[i][nd], fb[i][nr], 0);      // rows = dominant, cols = others
                     } else {
 #pragma unroll
-                        for (int cpt = 0; cpt < 4; ++cpt) mfma_one<DT>(acc[nd][nr], fa[nd], fb[nr], cpt);
+                        for (int cpt = 0; cpt < 4; ++cpt) mfma_one<DT>(acc[nd][nr], fa[i][nd], fb[i][nr], cpt);
                     }
                 }
+            if constexpr (RING > 2) {
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(k + RING - 1, DPW * i / NS, DPW * (i + 1) / NS);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-        __syncthreads();
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // no load may land after the workgroup has left its LDS
+    __syncthreads();
 
     // arg-max over the dominant rows: lane-local over its TR x 16 registers, then the other lane half, then
     // the NWN waves that share the columns.  Larger cosine wins; equal cosines go to the lower position.
@@ -265,7 +292,6 @@ __global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
                           ((unsigned long long)score_key(v) << 32) | (unsigned long long)(0xffffffffu - (uint32_t)ix));
         }
     }
-#undef LVLM_SIM8
 }
 
 // ---- size-weighted mean of each cluster ----
@@ -436,8 +462,6 @@ SimWs sim_ws(const lvlm_merge_desc &d) {
     SimWs w{};
     const size_t n = (size_t)d.B * d.n_img;
     const int r = d.n_img - d.n_keep;
-    // the large tile shape once it still gives every CU two workgroups
-    w.tile = ((long long)d.B * ((d.n_keep + 255) / 256) * ((r + 255) / 256) >= 512) ? 256 : 128;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         const size_t at = off;
@@ -504,20 +528,19 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     prof.end();
     prof.begin("sim_gemm");
     {
-        const long long tiles = (long long)d.B * ((d.n_keep + w.tile - 1) / w.tile) * ((r + w.tile - 1) / w.tile);
-        constexpr int run = kSimGN * kSimGM;
-        const dim3 ggrid((unsigned)(((tiles + run - 1) / run + 7) / 8 * 8 * run));
+        const long long tiles = (long long)d.B * ((d.n_keep + kSimTile - 1) / kSimTile) * ((r + kSimTile - 1) / kSimTile);
+        const long long per_xcd = (tiles + 7) / 8;
+        a.run = (int)(per_xcd <= 64 ? per_xcd : kSimGN * kSimGM);
+        const dim3 ggrid((unsigned)(((tiles + a.run - 1) / a.run + 7) / 8 * 8 * a.run));
         const bool bf = planes[0].dtype == LVLM_BF16;
         const bool ragged = (planes[0].row_elems * (bf ? 2 : 4)) % 128 != 0;
-#define LVLM_GEMM(DT, NWN, NWM, TR, TC)                                                                              \
-    if (ragged)                                                                                                      \
-        LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, NWN, NWM, TR, TC, true>), ggrid, dim3(64 * NWN * NWM), 0, stream, a);  \
-    else                                                                                                             \
-        LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, NWN, NWM, TR, TC, false>), ggrid, dim3(64 * NWN * NWM), 0, stream, a)
-        if (w.tile == 256) {
-            if (bf) { LVLM_GEMM(LVLM_BF16, 2, 4, 4, 2); } else { LVLM_GEMM(LVLM_F32, 2, 4, 4, 2); }
+#define LVLM_GEMM(DT, NWM, RING)                                                                                  \
+    if (ragged) LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, NWM, RING, true>), ggrid, dim3(128 * NWM), 0, stream, a);   \
+    else LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, NWM, RING, false>), ggrid, dim3(128 * NWM), 0, stream, a)
+        if (tiles <= 256) {
+            if (bf) { LVLM_GEMM(LVLM_BF16, 4, 4); } else { LVLM_GEMM(LVLM_F32, 4, 4); }
         } else {
-            if (bf) { LVLM_GEMM(LVLM_BF16, 2, 2, 2, 2); } else { LVLM_GEMM(LVLM_F32, 2, 2, 2, 2); }
+            if (bf) { LVLM_GEMM(LVLM_BF16, 2, 2); } else { LVLM_GEMM(LVLM_F32, 2, 2); }
         }
 #undef LVLM_GEMM
     }
