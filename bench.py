@@ -493,7 +493,9 @@ def kernel_work(ctx, lv, w, layers, dec_lens, moved, merge="rank", per_layer=Fal
         n_img = layers[last]["n_img"]
         N, gb = w.n_sys + n_img + T, (last - first + 1) * B
         form = score_form(ctx, lv, w, N, n_img, gb)
-        if form != 0:
+        # form 0 with few query rows and no normalisers given is one launch too (include/lvlm.h, lvlm_score_plan)
+        rows = not given_lse and N <= 4096 and gb * H * -(-(Hq // H * T) // 16) <= 768 and not (w.dtype == "f32" and d == 128)
+        if form != 0 or rows:
             launches = 2 if form == 3 and not given_lse else 1               # form 3: one launch per sweep
             add("score_single", "mfma", 2.0 * gb * T * ((0 if given_lse else N) + n_img) * d * Hq, launches=launches)
             if form == 3 and not given_lse:

@@ -792,6 +792,219 @@ __global__ __launch_bounds__(256, (DT == LVLM_F32 && HD == 128) ? 2 : 4) void sc
     if (jb < je) sweep(jb, je, true, std::true_type{});
 }
 
+// ---- few query rows: the logits of a chunk over ALL keys in registers, one sweep -------------------------
+// A workgroup of eight waves owns 16 query rows of one (batch, KV head) pair.  Wave w takes the 16-key tiles w, w + 8,
+// ... (NTW of them at most) and keeps every logit -- 4 registers per tile -- so the keys are read and multiplied once
+// where the other forms do it twice: the wave's own row maxima and sums, one exchange of them through LDS, and the
+// exponentials already taken are scaled to probabilities and summed down the rows.  Nothing but the chunk's column sums
+// leaves the workgroup.
+// A tile goes from memory straight into one of four LDS buffers of the wave (direct loads of whole rows: as operands, lane
+// = key, they would cost the memory pipeline a cycle per lane), three tiles ahead; no barrier, a wave waits for its own.
+// The 16-byte units of row R lie in the order u ^ R (256-byte rows; u ^ R / 2 for 128), so that the sixteen lanes an LDS read
+// serves at a time hit sixteen bank groups.  The loads are assembly for the reason given at the similarity product: the
+// compiler would wait for all buffers.
+// Operand lane = (l16, kg): contraction step i of lane group kg is bytes 64 i + 16 kg of a row; the result holds key l16 of a
+// 16-key block for query rows 4 kg + r.
+// What bounds it: launch and start-up (5.4 us for 200 keys), then a compute unit's rate of taking in the keys.
+constexpr int kRowsWaves = 8;
+template <int DT, int HD, int NTW>
+__global__ __launch_bounds__(64 * kRowsWaves) void score_rows_kernel(ScoreArgs a) {
+    constexpr int ES = esize<DT>();
+    constexpr int ROWB = HD * ES, UPR = ROWB / 16;
+    constexpr int NW = ROWB / 64;           // 16-byte words per lane of a row
+    constexpr int NWV = kRowsWaves, STEP = 16 * NWV, RING = 4;
+    constexpr int TB = 16 * ROWB;           // bytes of a tile
+    constexpr int DPT = TB / 1024, RPL = 1024 / ROWB;      // direct loads per tile, rows per load
+    static_assert(ROWB == 128 || ROWB == 256, "the swizzle is for these row lengths");
+    __shared__ __attribute__((aligned(1024))) char tile[NWV][RING][TB];
+    __shared__ __attribute__((aligned(16))) float wm[NWV][16], wl[NWV][16];      // [wave][row]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kg = lane >> 4;
+    // all chunks of one (batch, KV head) pair on one XCD (ids with the same remainder modulo 8)
+    const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+    const int pair = (seq / a.rs) * 8 + xcd, c = seq % a.rs;
+    if (pair >= a.B * a.Hkv) return;
+    const int b = pair / a.Hkv, g = pair % a.Hkv;
+    const int GT = a.G * a.T;
+    const long long rowbase = ((long long)b * a.Hq + (long long)g * a.G) * a.T;
+    auto div_t = [&](int rho) -> int { return a.T == 1 ? rho : (int)__umulhi((unsigned)rho, a.t_magic); };
+
+    const int key_lo = a.img_begin, key_hi = a.img_begin + a.n_img;
+    // with the normalisers given only the image keys are needed
+    const int j_lo = a.row_lse ? key_lo : 0, j_hi = a.row_lse ? key_hi : a.N;
+    const int jw = j_lo + 16 * wave;
+    const int n_t = jw < j_hi ? (j_hi - 1 - jw) / STEP + 1 : 0;     // this wave's tiles
+    const char *kbase = a.k + ((long long)b * a.ksb + (long long)g * a.ksh) * ES;
+    auto place = [](int row) { return ROWB == 256 ? row & 15 : (row >> 1) & 7; };
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)&tile[wave][0][0];
+    const unsigned ksb = (unsigned)(a.ksn * ES);          // (the host checks that a tile's rows span less than 2 GiB)
+    unsigned off[DPT], off_last[DPT];       // of this lane's units in a tile; in a tile that ends past the last row
+    const int r_last = (j_hi - 1 - jw) & (STEP - 1);      // last row inside this wave's last tile (>= 15: a whole one)
+#pragma unroll
+    for (int x = 0; x < DPT; ++x) {
+        const int row = RPL * x + lane / UPR, u = 16 * ((lane % UPR) ^ place(row));
+        off[x] = row * ksb + u;
+        off_last[x] = min(row, r_last) * ksb + u;
+    }
+    auto fetch = [&](int t) {               // tile t of this wave (the last one again past the end)
+        const int tc = min(t, n_t - 1), j0 = jw + STEP * tc;
+        const char *base = kbase + (long long)j0 * a.ksn * ES;
+        const unsigned dst = lds0 + (unsigned)(t % RING) * TB;
+        auto go = [&](const unsigned (&o)[DPT]) {
+#pragma unroll
+            for (int x = 0; x < DPT; ++x)
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(o[x]), "s"(base), "s"(dst + 1024u * x)
+                             : "memory", "m0");
+        };
+        if (j0 + 16 <= j_hi) go(off);
+        else go(off_last);
+    };
+    uint4 qf[NW];                           // row l16 of the chunk (rows past the last one repeat it; they weigh nothing)
+    {
+        const int rho = min(c * 16 + l16, GT - 1), hl = div_t(rho), i = rho - hl * a.T;
+        const char *src = a.q + ((long long)b * a.qsb + (long long)i * a.qst + (long long)(g * a.G + hl) * a.qsh) * ES + 16 * kg;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) qf[x] = *reinterpret_cast<const uint4 *>(src + 64 * x);
+    }
+    if (n_t > 0) {
+#pragma unroll
+        for (int t = 0; t < RING - 1; ++t) fetch(t);
+    }
+    int pos[4];                             // of rows 4 kg + r
+    float given[4];
+    bool real[4];
+    int pos_min = INT_MAX;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int rho = c * 16 + 4 * kg + r, rc = min(rho, GT - 1);
+        real[r] = rho < GT;
+        pos[r] = a.causal ? a.q_pos0 + rc - div_t(rc) * a.T : INT_MAX;
+        given[r] = a.row_lse ? a.row_lse[rowbase + rc] * kLog2e : 0.f;
+        pos_min = min(pos_min, pos[r]);
+    }
+    // earliest position of the chunk's rows (uniform): tiles at or before it need no mask
+    pos_min = min(pos_min, __float_as_int(swap_rows(__int_as_float(pos_min))));
+    pos_min = __builtin_amdgcn_readfirstlane(min(pos_min, __float_as_int(swap_halves(__int_as_float(pos_min)))));
+
+    static_assert(NTW % 4 == 0, "column sums go four tiles at a time");
+    f32x4 s[NTW];
+    float m[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+        const int j0 = jw + STEP * t;
+        if (t < n_t) {
+            fetch(t + RING - 1);            // (past the last tile: its last row again; the wait counts on these loads)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DPT * (RING - 1)) : "memory");
+            uint4 kf[NW];
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+                kf[i] = *reinterpret_cast<const uint4 *>(&tile[wave][t % RING][l16 * ROWB + 16 * ((4 * i + kg) ^ place(l16))]);
+            f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                if constexpr (DT == LVLM_BF16) {
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qf[i]), __builtin_bit_cast(bf16x8, kf[i]),
+                                                                  acc, 0, 0, 0);
+                } else {
+                    const uint32_t qw[4] = {qf[i].x, qf[i].y, qf[i].z, qf[i].w}, kw[4] = {kf[i].x, kf[i].y, kf[i].z, kf[i].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qw[e]), __uint_as_float(kw[e]), acc, 0, 0, 0);
+                }
+            }
+            if (j0 + 16 > j_hi || j0 + 15 > pos_min) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (j0 + l16 >= j_hi || j0 + l16 > pos[r]) acc[r] = -INFINITY;
+            }
+            s[t] = acc;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m[r] = fmaxf(m[r], acc[r]);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no load may land after the workgroup has left its LDS
+    // the wave's row maxima (log2 domain), exponentials relative to them and their sums
+    auto row_red = [](float v, auto op) {      // over the 16 lanes of the row group
+        v = op(v, dpp_quad1(v));
+        v = op(v, dpp_quad2(v));
+        v = op(v, dpp_half_mirror(v));
+        return op(v, dpp_row_mirror(v));
+    };
+    auto maxf = [](float x, float y) { return fmaxf(x, y); };
+    auto addf = [](float x, float y) { return x + y; };
+    float ref[4], l[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        m[r] = row_red(m[r], maxf) * a.scale_log2;        // scale > 0 (checked on the host)
+        ref[r] = m[r] == -INFINITY ? 0.f : m[r];
+        l[r] = 0.f;
+    }
+#pragma unroll
+    for (int t = 0; t < NTW; ++t) {
+        if (t < n_t) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[t][r] = __builtin_amdgcn_exp2f(fmaf(s[t][r], a.scale_log2, -ref[r]));
+                l[r] += s[t][r];
+            }
+        }
+    }
+    float f[4];                             // exponential -> probability
+    if (a.row_lse) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f[r] = real[r] ? __builtin_amdgcn_exp2f(ref[r] - given[r]) : 0.f;
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) l[r] = row_red(l[r], addf);
+        if (l16 == 0) {
+            *reinterpret_cast<float4 *>(&wm[wave][4 * kg]) = make_float4(m[0], m[1], m[2], m[3]);
+            *reinterpret_cast<float4 *>(&wl[wave][4 * kg]) = make_float4(l[0], l[1], l[2], l[3]);
+        }
+        __syncthreads();
+        // lane l16 takes wave l16's share of rows 4 kg + r (twice over: lanes 8 .. 15 repeat 0 .. 7, with sums of zero)
+        const int wj = l16 & (NWV - 1);
+        const float4 m4 = *reinterpret_cast<const float4 *>(&wm[wj][4 * kg]), l4 = *reinterpret_cast<const float4 *>(&wl[wj][4 * kg]);
+        const float mj[4] = {m4.x, m4.y, m4.z, m4.w}, lj[4] = {l4.x, l4.y, l4.z, l4.w};
+        const bool mine = l16 < NWV;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float mx = row_red(mj[r], maxf);
+            const float ms = mx == -INFINITY ? 0.f : mx;
+            const float tot = row_red(mine ? lj[r] * __builtin_amdgcn_exp2f(mj[r] - ms) : 0.f, addf);
+            // no visible key, or a padding row: contributes nothing
+            f[r] = real[r] && tot > 0.f ? __builtin_amdgcn_exp2f(ref[r] - ms) / tot : 0.f;
+        }
+    }
+    // column sums of the image keys: over the lane's four rows, then over the row groups -- four tiles at a time, each
+    // exchange leaving half of them with every lane: row group kg ends with tile t + kg
+    float *out = a.colpart + (((long long)c * a.B + b) * a.Hkv + g) * a.n_img;
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    auto fold16 = [](float x, float y) {       // lanes of even rows of 16: x of rows 2k and 2k + 1; of odd rows: y
+        const u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r.x) + __uint_as_float(r.y);
+    };
+    auto fold32 = [](float x, float y) {       // lanes 0-31: x of both halves; lanes 32-63: y
+        const u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r.x) + __uint_as_float(r.y);
+    };
+#pragma unroll
+    for (int t = 0; t < NTW; t += 4) {
+        if (t < n_t) {
+            float x[4];
+#pragma unroll
+            for (int y = 0; y < 4; ++y) {
+                x[y] = s[t + y][0] * f[0];
+#pragma unroll
+                for (int r = 1; r < 4; ++r) x[y] = fmaf(s[t + y][r], f[r], x[y]);
+            }
+            const float v = fold32(fold16(x[0], x[1]), fold16(x[2], x[3]));
+            const int j = jw + STEP * (t + kg) + l16;
+            if (t + kg < n_t && j >= key_lo && j < key_hi) out[j - key_lo] = v;
+        }
+    }
+}
+
 // Fold the per-block, per-wave (max, sum) pairs of each row into a log2-domain LSE.  Eight lanes share a
 // row: each folds every eighth pair online, then the eight partial (max, sum) states are merged.
 __global__ __launch_bounds__(256) void score_lse_kernel(const float *part_m, const float *part_l, float *lse2,
@@ -822,48 +1035,44 @@ __global__ __launch_bounds__(256) void score_lse_kernel(const float *part_m, con
 }
 
 // score_head[b][g][j] = (sum over row splits of the column sums) / G;  score_mean[b][j] = mean over g.
-// Four heads x eight splits are loaded together so that the loads overlap; more splits take more rounds
-// (a fixed summation order either way).
-constexpr int kMaxRowSplit = 8;
-
-__global__ __launch_bounds__(256) void score_finalize_kernel(ScoreArgs a) {
-    const int j = blockIdx.x * 256 + threadIdx.x;
+// A chain of latencies (launch, one round of loads, two barriers), so the parts of a column are spread over threads:
+// thread (column, slot of four heads, slot of four parts) sums every fourth part of every fourth head, eight loads in
+// flight; the sixteen slots meet in LDS in a fixed order.
+__global__ __launch_bounds__(1024) void score_finalize_kernel(ScoreArgs a) {
+    __shared__ float part[4][4][64];        // [part slot][head slot][column]
+    __shared__ float mean_s[4][64];
+    const int col = threadIdx.x & 63, hs = (threadIdx.x >> 6) & 3, ps = threadIdx.x >> 8;
+    const int j = blockIdx.x * 64 + col, jc = min(j, a.n_img - 1);
     const int b = blockIdx.y;
-    if (j >= a.n_img) return;
     const float inv_g = 1.0f / (float)a.G;
     const long long split_stride = (long long)a.B * a.Hkv * a.n_img;
-    float mean = 0.f;
+    float mean = 0.f;                       // of this head slot's heads (part slot 0)
     for (int g0 = 0; g0 < a.Hkv; g0 += 4) {
-        float tot[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int r0 = 0; r0 < a.rs; r0 += kMaxRowSplit) {
-            float v[4][kMaxRowSplit];
+        const int g = g0 + hs;
+        float tot = 0.f;
+        if (g < a.Hkv) {
+            const float *src = a.colpart + ((long long)b * a.Hkv + g) * a.n_img + jc;
+            for (int r0 = ps; r0 < a.rs; r0 += 32) {
+                float v[8];
 #pragma unroll
-            for (int gg = 0; gg < 4; ++gg)
+                for (int x = 0; x < 8; ++x) v[x] = r0 + 4 * x < a.rs ? src[(r0 + 4 * x) * split_stride] : 0.f;
 #pragma unroll
-                for (int r = 0; r < kMaxRowSplit; ++r) {
-                    const bool on = g0 + gg < a.Hkv && r0 + r < a.rs;
-                    const int gc = min(g0 + gg, a.Hkv - 1), rc = min(r0 + r, a.rs - 1);
-                    const float x = a.colpart[rc * split_stride + ((long long)b * a.Hkv + gc) * a.n_img + j];
-                    v[gg][r] = on ? x : 0.f;
-                }
-#pragma unroll
-            for (int gg = 0; gg < 4; ++gg) {
-                float s = 0.f;
-#pragma unroll
-                for (int r = 0; r < kMaxRowSplit; ++r) s += v[gg][r];
-                tot[gg] += s;
+                for (int x = 0; x < 8; ++x) tot += v[x];
             }
         }
-#pragma unroll
-        for (int gg = 0; gg < 4; ++gg) {
-            if (g0 + gg >= a.Hkv) break;
-            float s = tot[gg];
-            s *= inv_g;
-            a.score_head[(long long)b * a.shb + (long long)(g0 + gg) * a.shh + j] = s;
+        if (g0) __syncthreads();
+        part[ps][hs][col] = tot;
+        __syncthreads();
+        if (ps == 0 && g < a.Hkv) {
+            const float s = ((part[0][hs][col] + part[1][hs][col]) + (part[2][hs][col] + part[3][hs][col])) * inv_g;
+            if (j < a.n_img) a.score_head[(long long)b * a.shb + (long long)g * a.shh + j] = s;
             mean += s;
         }
     }
-    a.score_mean[(long long)b * a.n_img + j] = mean / (float)a.Hkv;
+    if (ps == 0) mean_s[hs][col] = mean;
+    __syncthreads();
+    if (threadIdx.x < 64 && j < a.n_img)
+        a.score_mean[(long long)b * a.n_img + j] = ((mean_s[0][col] + mean_s[1][col]) + (mean_s[2][col] + mean_s[3][col])) / (float)a.Hkv;
 }
 
 // ---- scores from probabilities the caller already holds ---------------------------------------------
@@ -958,9 +1167,29 @@ __global__ __launch_bounds__(256) void probs_colsum_vec_kernel(ProbsArgs a, int 
 }
 
 template <int DT, int HD, int KPW>
-void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool single, bool shared_tiles) {
+void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool single, bool shared_tiles, int rows) {
     hipStream_t stream = prof.stream;
     constexpr int BN = 4 * KPW * 32;
+    constexpr bool can_rows = !(DT == LVLM_F32 && HD == 128);
+    if (rows && can_rows) {
+        const int n_t = ((need_lse ? a.N : a.n_img) + 16 * kRowsWaves - 1) / (16 * kRowsWaves);      // tiles per wave
+        ScoreArgs r = a;
+        r.rs = rows;
+        const dim3 grid((a.B * a.Hkv + 7) / 8 * 8 * rows), wg(64 * kRowsWaves);
+        prof.begin("score_single");
+        if constexpr (can_rows) {
+            if (n_t <= 4) LVLM_LAUNCH(prof, (score_rows_kernel<DT, HD, 4>), grid, wg, 0, stream, r);
+            else if (n_t <= 8) LVLM_LAUNCH(prof, (score_rows_kernel<DT, HD, 8>), grid, wg, 0, stream, r);
+            else if (n_t <= 16) LVLM_LAUNCH(prof, (score_rows_kernel<DT, HD, 16>), grid, wg, 0, stream, r);
+            else if (n_t <= 24) LVLM_LAUNCH(prof, (score_rows_kernel<DT, HD, 24>), grid, wg, 0, stream, r);
+            else LVLM_LAUNCH(prof, (score_rows_kernel<DT, HD, 32>), grid, wg, 0, stream, r);
+        }
+        prof.end();
+        prof.begin("score_finalize");
+        LVLM_LAUNCH(prof, score_finalize_kernel, dim3((a.n_img + 63) / 64, a.B), dim3(1024), 0, stream, r);
+        prof.end();
+        return;
+    }
     if (single) {
         prof.begin("score_single");
         if (shared_tiles && a.n_seg > 1) {
@@ -985,7 +1214,7 @@ void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool sin
                                a);
         prof.end();
         prof.begin("score_finalize");
-        LVLM_LAUNCH(prof, score_finalize_kernel, dim3((a.n_img + 255) / 256, a.B), dim3(256), 0, stream, a);
+        LVLM_LAUNCH(prof, score_finalize_kernel, dim3((a.n_img + 63) / 64, a.B), dim3(1024), 0, stream, a);
         prof.end();
         return;
     }
@@ -1005,7 +1234,7 @@ void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool sin
     LVLM_LAUNCH(prof, (score_pass_kernel<DT, HD, KPW, 1>), grid1, dim3(256), 0, stream, a);
     prof.end();
     prof.begin("score_finalize");
-    LVLM_LAUNCH(prof, score_finalize_kernel, dim3((a.n_img + 255) / 256, a.B), dim3(256), 0, stream, a);
+    LVLM_LAUNCH(prof, score_finalize_kernel, dim3((a.n_img + 63) / 64, a.B), dim3(1024), 0, stream, a);
     prof.end();
 }
 
@@ -1063,7 +1292,7 @@ hipError_t launch_score_probs(const Prof &prof, const lvlm_probs_desc &d, const 
     a.shh = dense ? d.n_img : d.sh_stride_h;
     a.shb = dense ? (long long)d.Hkv * d.n_img : d.sh_stride_b;
     prof.begin("score_finalize");
-    LVLM_LAUNCH(prof, score_finalize_kernel, dim3((d.n_img + 255) / 256, d.B), dim3(256), 0, prof.stream, a);
+    LVLM_LAUNCH(prof, score_finalize_kernel, dim3((d.n_img + 63) / 64, d.B), dim3(1024), 0, prof.stream, a);
     prof.end();
     return hipGetLastError();
 }
@@ -1081,7 +1310,7 @@ ScoreWs score_ws(const lvlm_score_desc &d) {
     const long long wgs = (long long)d.B * d.Hkv * w.nkb;
     int rs = (int)((kRowSplitWgs + wgs - 1) / wgs);
     if (rs > (n_chunks + 1) / 2) rs = (n_chunks + 1) / 2;
-    if (rs > 8) rs = 8;            // kMaxRowSplit of the finalize kernel
+    if (rs > 8) rs = 8;            // (parts the finalize kernel has to add up)
     if (rs < 1) rs = 1;
     w.cps = (n_chunks + rs - 1) / rs;
     w.rs = (n_chunks + w.cps - 1) / w.cps;
@@ -1128,13 +1357,24 @@ ScoreWs score_ws(const lvlm_score_desc &d) {
         w.rs = n_chunks;
         w.cps = 1;
     }
+    // Few query rows: 16 of them per workgroup, the logits over all keys in registers.  A turn of 256 workgroups
+    // takes 4.2 us + 3.1 us per 1000 keys of 256 bytes.  Against the one-launch form of short sequences (whose workgroups
+    // read the keys twice, but for 32 rows) that wins while one turn holds all of it, against the two-pass kernels with their
+    // fold up to three turns: one sequence of 7B heads (112 workgroups) 700 keys 15.0 -> 11.1 us, 2176 keys 21.1 -> 15.5 us,
+    // two of them 28.7 -> 15.9 us, four (two turns) 38.8 -> 26.1 us; 768 workgroups x 2000 keys 41.7 -> 36.8 us; but two
+    // turns of 1000 keys 18.5 -> 19.9 us against the one-launch form.
+    const int n16 = (d.Hq / d.Hkv * d.T + 15) / 16;
+    const long long turns = ((long long)d.B * d.Hkv * n16 + 255) / 256;
+    w.rows = !w.shared_tiles && !(d.dtype == LVLM_F32 && d.hd == 128) && d.N <= 16 * kRowsWaves * 32 && d.scale > 0.f &&
+                     d.k_stride_n * (d.dtype == LVLM_BF16 ? 2 : 4) < (1ll << 26) && turns <= (w.single ? 1 : 3)
+                 ? n16 : 0;
     const size_t rows = (size_t)d.B * d.Hq * d.T;
     w.part_m = 0;
     const size_t n_part = (size_t)w.nkb * 4 > (size_t)w.key_segs ? (size_t)w.nkb * 4 : (size_t)w.key_segs;
     w.part_l = align_up(w.part_m + rows * n_part * sizeof(float), 256);
     w.lse2 = align_up(w.part_l + rows * n_part * sizeof(float), 256);
     w.colpart = align_up(w.lse2 + rows * sizeof(float), 256);
-    w.total = align_up(w.colpart + (size_t)w.rs * d.B * d.Hkv * d.n_img * sizeof(float), 256);
+    w.total = align_up(w.colpart + (size_t)(w.rs > w.rows ? w.rs : w.rows) * d.B * d.Hkv * d.n_img * sizeof(float), 256);
     return w;
 }
 
@@ -1164,16 +1404,17 @@ hipError_t launch_score(const Prof &prof, const lvlm_score_desc &d, const ScoreW
     a.shb = dense ? (long long)d.Hkv * d.n_img : d.sh_stride_b;
     const bool need_lse = row_lse == nullptr;
     const bool wide = w.block_keys == 256;
+    const int rows = need_lse || w.single ? w.rows : 0;      // (with the normalisers given one short pass is all there is)
     if (d.dtype == LVLM_BF16 && d.hd == 128) {
-        if (wide) launch_passes<LVLM_BF16, 128, 2>(prof, a, need_lse, w.single, w.shared_tiles);
-        else launch_passes<LVLM_BF16, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles);
+        if (wide) launch_passes<LVLM_BF16, 128, 2>(prof, a, need_lse, w.single, w.shared_tiles, rows);
+        else launch_passes<LVLM_BF16, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);
     } else if (d.dtype == LVLM_BF16 && d.hd == 64) {
-        if (wide) launch_passes<LVLM_BF16, 64, 2>(prof, a, need_lse, w.single, w.shared_tiles);
-        else launch_passes<LVLM_BF16, 64, 1>(prof, a, need_lse, w.single, w.shared_tiles);
+        if (wide) launch_passes<LVLM_BF16, 64, 2>(prof, a, need_lse, w.single, w.shared_tiles, rows);
+        else launch_passes<LVLM_BF16, 64, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);
     } else if (d.dtype == LVLM_F32 && d.hd == 128) {
-        launch_passes<LVLM_F32, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles);
+        launch_passes<LVLM_F32, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);
     } else {
-        launch_passes<LVLM_F32, 64, 1>(prof, a, need_lse, w.single, w.shared_tiles);
+        launch_passes<LVLM_F32, 64, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);
     }
     return hipGetLastError();
 }

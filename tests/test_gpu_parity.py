@@ -109,6 +109,30 @@ def test_score_tokens_keys_in_runs(ctx, B, T, Hq, Hkv, n_sys, n_img):
     assert rel_err(sh2.cpu(), osh) < 1e-5 and rel_err(sm2.cpu(), osm) < 1e-5
 
 
+@pytest.mark.parametrize("dtype,B,T,Hq,Hkv,d,n_sys,n_img,causal,scale", [
+    (torch.bfloat16, 1, 1, 1, 1, 128, 0, 1, True, None),            # one row, two keys
+    (torch.bfloat16, 1, 3, 5, 1, 128, 2, 107, True, None),          # 15 rows, 112 keys: the last wave has no tile
+    (torch.bfloat16, 2, 8, 6, 3, 64, 1, 120, False, None),          # 16 rows, 129 keys: one tile more than one per wave
+    (torch.bfloat16, 1, 17, 4, 4, 128, 0, 495, True, None),         # 17 rows, exactly four tiles per wave
+    (torch.bfloat16, 1, 17, 4, 4, 128, 0, 496, True, None),         # ... and one key more
+    (torch.float32, 1, 40, 4, 2, 64, 7, 1990, True, None),          # 80 rows, masked tiles ahead of the first rows
+    (torch.bfloat16, 1, 33, 14, 2, 128, 5, 3000, True, 0.3),        # peaky rows
+    (torch.bfloat16, 3, 64, 28, 4, 128, 0, 4032, True, None),       # the longest: 4096 keys, two turns of workgroups
+    (torch.bfloat16, 1, 9, 4, 2, 64, 3, 200, True, 0.0)])           # all logits equal (the other kernels' case)
+def test_score_tokens_few_query_rows(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img, causal, scale):
+    N = n_sys + n_img + T
+    q, k = _rand((B, T, Hq, d), dtype, 21), _rand((B, N, Hkv, d), dtype, 22)
+    kw = dict(q_pos0=n_sys + n_img, img_begin=n_sys, n_img=n_img, causal=causal, scale=scale)
+    sh, sm = ctx.score_tokens(q.to(DEV), k.to(DEV), **kw)
+    osh, osm = O.score_tokens(f64(q), f64(k), **kw)
+    assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
+    # query rows inside the key range: some keys hidden from every row, some rows that see a handful
+    kw.update(q_pos0=0, causal=True)
+    sh, sm = ctx.score_tokens(q.to(DEV), k.to(DEV), **kw)
+    osh, osm = O.score_tokens(f64(q), f64(k), **kw)
+    assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
+
+
 @pytest.mark.parametrize("N", [300, 1300])      # one launch for both passes / the two-pass kernels
 def test_score_tokens_mask_inside_span_and_strided_inputs(ctx, N):
     # query rows start INSIDE the scored span (all-rows reading): the causal mask bites in pass 1 too;
