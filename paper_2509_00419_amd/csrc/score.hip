@@ -953,7 +953,7 @@ __global__ __launch_bounds__(64 * kRowsWaves) void score_rows_kernel(ScoreArgs a
     float f[4];                             // exponential -> probability
     if (a.row_lse) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) f[r] = real[r] ? __builtin_amdgcn_exp2f(ref[r] - given[r]) : 0.f;
+        for (int r = 0; r < 4; ++r) f[r] = real[r] && m[r] > -INFINITY ? __builtin_amdgcn_exp2f(ref[r] - given[r]) : 0.f;
     } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r) l[r] = row_red(l[r], addf);
@@ -972,8 +972,9 @@ __global__ __launch_bounds__(64 * kRowsWaves) void score_rows_kernel(ScoreArgs a
             const float mx = row_red(mj[r], maxf);
             const float ms = mx == -INFINITY ? 0.f : mx;
             const float tot = row_red(mine ? lj[r] * __builtin_amdgcn_exp2f(mj[r] - ms) : 0.f, addf);
-            // no visible key, or a padding row: contributes nothing
-            f[r] = real[r] && tot > 0.f ? __builtin_amdgcn_exp2f(ref[r] - ms) / tot : 0.f;
+            // a padding row, or no key of this wave visible: contributes nothing (without a maximum of the wave's own the
+            // factor would be exp2(-ms), infinite for a row of very negative logits)
+            f[r] = real[r] && m[r] > -INFINITY && tot > 0.f ? __builtin_amdgcn_exp2f(ref[r] - ms) / tot : 0.f;
         }
     }
     // column sums of the image keys: over the lane's four rows, then over the row groups -- four tiles at a time, each

@@ -133,6 +133,24 @@ def test_score_tokens_few_query_rows(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img,
     assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
 
 
+@pytest.mark.parametrize("given", [False, True])
+def test_score_tokens_few_rows_very_negative_logits(ctx, given):
+    # logits around -200 and rows that see only the first keys: most waves see none, and no factor of theirs may overflow
+    B, T, H, d, N = 1, 16, 4, 64, 600
+    q, k = _rand((B, T, H, d), torch.float32, 31), _rand((B, N, H, d), torch.float32, 32)
+    q[..., 0], k[..., 0] = 16.0, -100.0
+    kw = dict(q_pos0=0, img_begin=0, n_img=N)
+    lse = None
+    if given:
+        s = torch.einsum("bthd,bnhd->bhtn", q.double(), k.double()) * d ** -0.5
+        s = s.masked_fill(torch.arange(N)[None, :] > torch.arange(T)[:, None], -math.inf)
+        lse = torch.logsumexp(s, dim=-1).float()
+    sh, sm = ctx.score_tokens(q.to(DEV), k.to(DEV), row_lse=None if lse is None else lse.to(DEV), **kw)
+    osh, osm = O.score_tokens(f64(q), f64(k), **kw)
+    tol = 4 * 200 * 2.0 ** -23        # a few roundings of a logit of that size in fp32
+    assert rel_err(sh.cpu(), osh) < tol and rel_err(sm.cpu(), osm) < tol
+
+
 @pytest.mark.parametrize("N", [300, 1300])      # one launch for both passes / the two-pass kernels
 def test_score_tokens_mask_inside_span_and_strided_inputs(ctx, N):
     # query rows start INSIDE the scored span (all-rows reading): the causal mask bites in pass 1 too;
