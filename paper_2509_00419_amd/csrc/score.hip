@@ -894,6 +894,8 @@ __global__ __launch_bounds__(64 * kRowsWaves) void score_rows_kernel(ScoreArgs a
     for (int t = 0; t < NTW; ++t) {
         const int j0 = jw + STEP * t;
         if (t < n_t) {
+            // the buffer about to be written is the one read for tile t - 1: those reads have to be back
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             fetch(t + RING - 1);            // (past the last tile: its last row again; the wait counts on these loads)
             asm volatile("s_waitcnt vmcnt(%0)" ::"n"(DPT * (RING - 1)) : "memory");
             uint4 kf[NW];

@@ -209,8 +209,9 @@ __global__ __launch_bounds__(128 * NWM) void sim_gemm_kernel(SimArgs a) {
     for (int i = 0; i < NS; ++i) uo[i] = l32 * SB + 16 * ((NS * hf + i) ^ place(l32));
     const char *const ar = ring + wn * (TR * 32 * SB), *const br = ring + TM * SB + wm * (TC * 32 * SB);
     for (int k = 0; k < nk; ++k) {
-        // all but the RING - 2 youngest slices' loads of this wave have landed: slice k is complete when everybody is here
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(DPW * (RING - 2)) : "memory");
+        // all but the RING - 2 youngest slices' loads of this wave have landed: slice k is complete when everybody is here;
+        // and this wave's reads of slice k - 1 are back, whose slot is written next
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(DPW * (RING - 2)) : "memory");
         if constexpr (RING == 2) fetch(k + RING - 1, 0, DPW);
         const int at = (k % RING) * SLOT;
         uint4 fa[NS][TR], fb[NS][TC];
