@@ -1078,6 +1078,60 @@ __global__ __launch_bounds__(1024) void score_finalize_kernel(ScoreArgs a) {
         a.score_mean[(long long)b * a.n_img + j] = ((mean_s[0][col] + mean_s[1][col]) + (mean_s[2][col] + mean_s[3][col])) / (float)a.Hkv;
 }
 
+// The same where a thread per column already fills the chip: no exchange, a workgroup reads 1 KB runs, four heads x eight
+// parts of a thread's loads in flight.
+__global__ __launch_bounds__(256) void score_finalize_wide_kernel(ScoreArgs a) {
+    constexpr int PARTS = 8;
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    const int b = blockIdx.y;
+    if (j >= a.n_img) return;
+    const float inv_g = 1.0f / (float)a.G;
+    const long long split_stride = (long long)a.B * a.Hkv * a.n_img;
+    float mean = 0.f;
+    for (int g0 = 0; g0 < a.Hkv; g0 += 4) {
+        float tot[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int r0 = 0; r0 < a.rs; r0 += PARTS) {
+            float v[4][PARTS];
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg)
+#pragma unroll
+                for (int r = 0; r < PARTS; ++r) {
+                    const bool on = g0 + gg < a.Hkv && r0 + r < a.rs;
+                    const int gc = min(g0 + gg, a.Hkv - 1), rc = min(r0 + r, a.rs - 1);
+                    const float x = a.colpart[rc * split_stride + ((long long)b * a.Hkv + gc) * a.n_img + j];
+                    v[gg][r] = on ? x : 0.f;
+                }
+#pragma unroll
+            for (int gg = 0; gg < 4; ++gg) {
+                float s = 0.f;
+#pragma unroll
+                for (int r = 0; r < PARTS; ++r) s += v[gg][r];
+                tot[gg] += s;
+            }
+        }
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg) {
+            if (g0 + gg >= a.Hkv) break;
+            float s = tot[gg];
+            s *= inv_g;
+            a.score_head[(long long)b * a.shb + (long long)(g0 + gg) * a.shh + j] = s;
+            mean += s;
+        }
+    }
+    a.score_mean[(long long)b * a.n_img + j] = mean / (float)a.Hkv;
+}
+
+// The first form up to one turn of the chip (two 1024-thread workgroups a compute unit).  A second turn costs more than
+// the shorter chains give: 12 sequences x 5091 columns x 8 heads of 24 parts (47 MB, 960 workgroups) 13.6 us against 10.8
+// us; one sequence's columns of 48 parts each 4.7 us against 9.6 us.
+void launch_finalize(const Prof &prof, const ScoreArgs &a) {
+    const dim3 grid((a.n_img + 63) / 64, a.B);
+    prof.begin("score_finalize");
+    if ((long long)grid.x * grid.y <= 512) LVLM_LAUNCH(prof, score_finalize_kernel, grid, dim3(1024), 0, prof.stream, a);
+    else LVLM_LAUNCH(prof, score_finalize_wide_kernel, dim3((a.n_img + 255) / 256, a.B), dim3(256), 0, prof.stream, a);
+    prof.end();
+}
+
 // ---- scores from probabilities the caller already holds ---------------------------------------------
 // Workgroup (column block, row group c): thread j sums probs[b][g*G + hl][i][img_begin + j] over the 32
 // rows rho = hl*T + i of group c (neighbouring threads read neighbouring columns), all 32 loads in flight;
@@ -1188,9 +1242,7 @@ void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool sin
             else LVLM_LAUNCH(prof, (score_rows_kernel<DT, HD, 32>), grid, wg, 0, stream, r);
         }
         prof.end();
-        prof.begin("score_finalize");
-        LVLM_LAUNCH(prof, score_finalize_kernel, dim3((a.n_img + 63) / 64, a.B), dim3(1024), 0, stream, r);
-        prof.end();
+        launch_finalize(prof, r);
         return;
     }
     if (single) {
@@ -1216,9 +1268,7 @@ void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool sin
             LVLM_LAUNCH(prof, (score_small_kernel<DT, HD, 4>), dim3((a.B * a.Hkv + 7) / 8 * 8 * a.rs), dim3(256), 0, stream,
                                a);
         prof.end();
-        prof.begin("score_finalize");
-        LVLM_LAUNCH(prof, score_finalize_kernel, dim3((a.n_img + 63) / 64, a.B), dim3(1024), 0, stream, a);
-        prof.end();
+        launch_finalize(prof, a);
         return;
     }
     if (need_lse) {
@@ -1236,9 +1286,7 @@ void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool sin
     prof.begin("score_pass1");
     LVLM_LAUNCH(prof, (score_pass_kernel<DT, HD, KPW, 1>), grid1, dim3(256), 0, stream, a);
     prof.end();
-    prof.begin("score_finalize");
-    LVLM_LAUNCH(prof, score_finalize_kernel, dim3((a.n_img + 63) / 64, a.B), dim3(1024), 0, stream, a);
-    prof.end();
+    launch_finalize(prof, a);
 }
 
 }  // namespace
@@ -1294,9 +1342,7 @@ hipError_t launch_score_probs(const Prof &prof, const lvlm_probs_desc &d, const 
     const bool dense = d.sh_stride_b == 0 && d.sh_stride_h == 0;
     a.shh = dense ? d.n_img : d.sh_stride_h;
     a.shb = dense ? (long long)d.Hkv * d.n_img : d.sh_stride_b;
-    prof.begin("score_finalize");
-    LVLM_LAUNCH(prof, score_finalize_kernel, dim3((d.n_img + 63) / 64, d.B), dim3(1024), 0, prof.stream, a);
-    prof.end();
+    launch_finalize(prof, a);
     return hipGetLastError();
 }
 

@@ -151,6 +151,18 @@ def test_score_tokens_few_rows_very_negative_logits(ctx, given):
     assert rel_err(sh.cpu(), osh) < tol and rel_err(sm.cpu(), osm) < tol
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,n_img", [
+    (32, 5, 5, 5, 1024),          # 512 workgroups of the fold: the last shape with the parts spread over threads
+    (27, 5, 5, 5, 1217),          # 540: a thread per column, one head beyond four, a last workgroup of 193 columns
+    (40, 90, 21, 3, 849)])        # 560, 20 parts: a second round of loads
+def test_score_fold_of_many_columns(ctx, B, T, Hq, Hkv, n_img):
+    q, k = _rand((B, T, Hq, 64), torch.bfloat16, 41), _rand((B, n_img + T, Hkv, 64), torch.bfloat16, 42)
+    kw = dict(q_pos0=n_img, img_begin=0, n_img=n_img)
+    sh, sm = ctx.score_tokens(q.to(DEV), k.to(DEV), **kw)
+    osh, osm = O.score_tokens(f64(q), f64(k), **kw)
+    assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
+
+
 @pytest.mark.parametrize("N", [300, 1300])      # one launch for both passes / the two-pass kernels
 def test_score_tokens_mask_inside_span_and_strided_inputs(ctx, N):
     # query rows start INSIDE the scored span (all-rows reading): the causal mask bites in pass 1 too;
