@@ -118,6 +118,31 @@ def test_prefill_attn_config5_shape_sampled_group(ctx):
     assert torch.isfinite(lse).all()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_prefill_attn_row_sums_of_long_rows(ctx, d):
+    """Sixteen thousand keys of which few weigh much (unit noise plus three times a salience): small probabilities must
+    not drop out of a row's sum.  A tile's probabilities are summed on their own before they meet the running sum, some
+    N / 32 + 16 additions a lane; one by one into the running sum they leave the normalisers about 4e-6 too low
+    (rms 4.2e-6), tile by tile without a bias (rms of the sum 2e-7).  The bounds: the sum's logarithm, the reference's
+    product and their total are each rounded at a magnitude below 16, at most 9.5e-7 apiece and 0.6e-6 in rms, and do not
+    lean to a side."""
+    N, rows = 16512, 512
+    g = torch.Generator().manual_seed(23)
+    q, k, v = (torch.randn(1, N, 1, d, generator=g) for _ in range(3))
+    u = torch.zeros(d)
+    u[0] = 1.0
+    k += 3.0 * d ** 0.25 * torch.randn(1, N, 1, 1, generator=g) * u
+    q[..., 0] = d ** 0.25
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    _, lse, _, _ = ctx.prefill_attn(q.to(DEV), k.to(DEV), v.to(DEV))
+    s = (q[0, N - rows:, 0].double() @ k[0, :, 0].double().T) * d ** -0.5
+    s = s.masked_fill(torch.arange(N)[None, :] > torch.arange(N - rows, N)[:, None], float("-inf"))
+    ref = torch.logsumexp(s, dim=1)
+    assert float(ref.abs().max()) < 24.0
+    err = lse[0, 0, N - rows:].cpu().double() - ref
+    assert abs(float(err.mean())) < 1e-6 and float(err.pow(2).mean().sqrt()) < 2e-6
+
+
 def test_prefill_attn_logits_far_above_the_first_tile(ctx):
     """Rows whose later logits exceed everything in the first 32 keys by far more than fp32 can hold as a
     probability ratio (natural-log distance 120): the kernel that fixes its reference at the first tile must
