@@ -376,9 +376,23 @@ __device__ __forceinline__ void merge_plane(const SimArgs &a, const PlaneDev &p,
 #pragma unroll
             for (int x = 0; x < NU; ++x)
                 if (u0 + 256 * x < units) store_mean<DT, UB>(dst0 + off[x], acc[x], 1.0f / tot);
-            if (size && a.size_out && threadIdx.x == 0 && u0 == 0) a.size_out[(long long)b * a.n_keep + i] = tot;
         }
     }
+}
+
+// Size of the cluster of token ji: its own and its members' sizes added in ascending index, the order of the weighted means
+// (one wave, 64 members a round).
+__device__ __forceinline__ float cluster_size(const SimArgs &a, int b, int ji, int lo, int n_mem, int members) {
+    const float *size = a.size_in + (long long)b * a.n;
+    const int lane = threadIdx.x & 63;
+    float tot = size[ji];
+    for (int s0 = 0; s0 < n_mem; s0 += 64) {
+        const int mem = s0 ? a.order[(long long)b * a.n + min(lo + s0 + lane, a.n - 1)] : members;
+        const float w = size[mem];
+        const int cnt = min(64, n_mem - s0);
+        for (int t = 0; t < cnt; ++t) tot += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), t));
+    }
+    return tot;
 }
 
 // One row of every plane from its old place to its new one.
@@ -430,8 +444,10 @@ __global__ __launch_bounds__(256) void sim_merge_kernel(SimArgs a) {
     }
     const int n_mem = hi - lo;
     const int members = order[min(lo + lane, a.n - 1)];
-    // sizes of all-ones clusters are written here (the weighted path writes them when sizes are given)
-    if (threadIdx.x == 0 && a.size_out && a.size_in == nullptr) a.size_out[(long long)b * a.n_keep + i] = (float)(1 + n_mem);
+    if (a.size_out && threadIdx.x < 64) {      // (here, not with the means: every plane may be one whose rows are only kept)
+        const float tot = a.size_in ? cluster_size(a, b, ji, lo, n_mem, members) : (float)(1 + n_mem);
+        if (lane == 0) a.size_out[(long long)b * a.n_keep + i] = tot;
+    }
     for (int pi = 0; pi < a.n_planes; ++pi) {
         const PlaneDev &p = a.plane[pi];
         if (p.dtype == LVLM_BF16) {

@@ -1082,6 +1082,23 @@ def test_merge_similar(ctx):
     _similar_case(ctx, torch.bfloat16, 1, 2, 4500, 2, 64, 1200, 108, clusters=16)               # ranks by sorted blocks
 
 
+@pytest.mark.parametrize("n_img,n_keep,clusters", [(200, 60, 5), (700, 2, 2), (40, 39, 0)])
+def test_merge_similar_sizes_of_planes_that_are_only_kept(ctx, n_img, n_keep, clusters):
+    """Cluster sizes are an output of their own: planes whose rows are all kept (no weighted plane) change nothing about
+    them.  Whole sizes up to 3 sum without rounding, clusters of one, of a few and of more than 64 members among them."""
+    g = torch.Generator().manual_seed(n_img)
+    hid = torch.randn(1, n_img + 3, 64, generator=g)
+    if clusters:
+        centres = torch.randn(clusters, 64, generator=g)
+        hid[0, 2:2 + n_img] = centres[torch.randint(0, clusters, (n_img,), generator=g)] + 0.1 * hid[0, 2:2 + n_img]
+    score, size = torch.rand(1, n_img, generator=g), torch.randint(1, 4, (1, n_img), generator=g).float()
+    size_out = torch.full((1, n_keep), -7.0, device=DEV)
+    _, _, assign, got = ctx.merge_similar([hid.to(DEV)], score.to(DEV), img_begin=2, n_img=n_img, n_keep=n_keep,
+                                          rules=[lv.RULE_TOP], size=size.to(DEV), size_out=size_out)
+    want = torch.zeros(n_keep).scatter_add_(0, assign[0].cpu().long(), size[0])
+    assert torch.equal(got[0].cpu(), want)
+
+
 @pytest.mark.parametrize("n_img,n_keep,clusters,with_size", [
     (66, 65, 0, True), (66, 1, 0, False), (65, 64, 3, True), (130, 64, 2, False),   # owner search: one other token, 65, 66
     (4096, 3000, 3, False), (4097, 1, 0, True), (4400, 80, 2, True),                # chunk and block edges, hundreds per cluster
