@@ -1121,13 +1121,20 @@ __global__ __launch_bounds__(256) void score_finalize_wide_kernel(ScoreArgs a) {
     a.score_mean[(long long)b * a.n_img + j] = mean / (float)a.Hkv;
 }
 
-// The first form up to one turn of the chip (two 1024-thread workgroups a compute unit).  A second turn costs more than
-// the shorter chains give: 12 sequences x 5091 columns x 8 heads of 24 parts (47 MB, 960 workgroups) 13.6 us against 10.8
-// us; one sequence's columns of 48 parts each 4.7 us against 9.6 us.
+// Which of the two, by what each thread of the wide form has to do in turn: a round of loads for every four heads and
+// eight parts.  From three rounds on, with more parts than one round holds, the shorter chains of the 1024-thread form win;
+// below that three quarters of its threads find no part and its two barriers per four heads are a loss (the whole
+// call, 1024-thread form against wide, up to 256 workgroups of the former: 4 heads 1-3 parts +0.2 to +0.5 us, 4-8 parts
+// +0.5 to +0.8, 12-16 +0.1, 24 -0.5, 48 -1.9 us; 8 heads 1-2 parts +0.1, 4-8 +0.5, 12 -0.7, 24 -1.7, 48 -4.5 us).
+// And up to one turn of the chip, two such workgroups a compute unit (8 heads of 12 parts at 257-512 workgroups: even); a second
+// turn costs more than the shorter chains give: 12 sequences x 5091 columns x 8 heads of 24 parts (47 MB, 960
+// workgroups) 13.6 us against 10.8 us.
 void launch_finalize(const Prof &prof, const ScoreArgs &a) {
     const dim3 grid((a.n_img + 63) / 64, a.B);
+    const int rounds = ((a.Hkv + 3) / 4) * ((a.rs + 7) / 8);
     prof.begin("score_finalize");
-    if ((long long)grid.x * grid.y <= 512) LVLM_LAUNCH(prof, score_finalize_kernel, grid, dim3(1024), 0, prof.stream, a);
+    if (a.rs > 8 && rounds > 2 && (long long)grid.x * grid.y <= 512)
+        LVLM_LAUNCH(prof, score_finalize_kernel, grid, dim3(1024), 0, prof.stream, a);
     else LVLM_LAUNCH(prof, score_finalize_wide_kernel, dim3((a.n_img + 255) / 256, a.B), dim3(256), 0, prof.stream, a);
     prof.end();
 }

@@ -151,6 +151,20 @@ def test_score_tokens_few_rows_very_negative_logits(ctx, given):
     assert rel_err(sh.cpu(), osh) < tol and rel_err(sm.cpu(), osm) < tol
 
 
+@pytest.mark.parametrize("Hkv,rows,n_img,B", [
+    (4, 512, 70, 1), (4, 513, 70, 1),             # 16 and 17 parts of 32 rows: two and three rounds of the wide form
+    (5, 256, 130, 2), (5, 257, 130, 2),           # 8 and 9 parts, five heads: no more parts than a round holds, and one more
+    (9, 32, 64, 1), (1, 801, 1, 3),               # one part of nine heads; 26 parts of a single column
+    (4, 513, 64, 512), (4, 513, 64, 513)])        # the last workgroup count of the spread form, and one more
+def test_score_fold_forms(ctx, Hkv, rows, n_img, B):
+    """The fold of the column sums at the edges of the rule that picks its form (parts, heads, workgroups)."""
+    g = torch.Generator(device=DEV).manual_seed(rows + n_img)
+    p = torch.rand(B, Hkv, rows, n_img, generator=g, device=DEV)
+    sh, sm = ctx.score_from_probs(p, n_kv_heads=Hkv, img_begin=0, n_img=n_img)
+    ref = p.cpu().double().sum(dim=2)
+    assert rel_err(sh.cpu(), ref) < 1e-5 and rel_err(sm.cpu(), ref.mean(dim=1)) < 1e-5
+
+
 @pytest.mark.parametrize("B,T,Hq,Hkv,n_img", [
     (32, 5, 5, 5, 1024),          # 512 workgroups of the fold: the last shape with the parts spread over threads
     (27, 5, 5, 5, 1217),          # 540: a thread per column, one head beyond four, a last workgroup of 193 columns
