@@ -171,11 +171,16 @@ LVLM_API lvlm_status lvlm_score_tokens(lvlm_ctx *ctx, void *stream, const lvlm_s
 
 /* Which kernels lvlm_score_tokens takes for a shape (host arithmetic; for benchmarks that credit work to
  * kernels by name): *form = 0 two passes over the keys in separate launches (normalisers, then column
- * sums) -- or, normalisers not given, a launch of at most 768 workgroups of 16 query rows over at most 4096 keys that keeps
- * their logits in registers (not for fp32 heads of 128 channels), 1 both sweeps in one launch with one query chunk per workgroup, 2 both sweeps in one launch with
+ * sums), 1 both sweeps in one launch with one query chunk per workgroup, 2 both sweeps in one launch with
  * four query chunks per workgroup sharing the key tiles, 3 the kernel of form 2 with the keys cut into runs
- * (one launch per sweep, the runs' normaliser partials folded in between: launches of few workgroups). */
+ * (one launch per sweep, the runs' normaliser partials folded in between: launches of few workgroups).
+ * Forms 0 and 1 are what the shape takes unless lvlm_score_few_rows says otherwise. */
 LVLM_API lvlm_status lvlm_score_plan(const lvlm_ctx *ctx, const lvlm_score_desc *d, int32_t *form);
+
+/* Whether a shape of form 0 or 1 goes to the kernel for few query rows instead, which reads and multiplies every
+ * key once in one launch and keeps the logits in registers: *chunks = its chunks of 16 query rows per KV head,
+ * 0 = not taken.  lse_given: nonzero if the call passes row_lse. */
+LVLM_API lvlm_status lvlm_score_few_rows(const lvlm_ctx *ctx, const lvlm_score_desc *d, int lse_given, int32_t *chunks);
 
 /* The same scores from attention probabilities the caller already holds -- a
  * plain attention that materialises its matrix (Sec. 3.2.2 names both sources:

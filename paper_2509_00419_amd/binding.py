@@ -116,6 +116,7 @@ def _load():
     lib.lvlm_merge_weights.argtypes = [C.c_int, C.c_int, C.POINTER(C.c_float)]
     lib.lvlm_score_tokens.argtypes = [vp, vp, C.POINTER(ScoreDesc), vp, vp, f32p, f32p, f32p]
     lib.lvlm_score_plan.argtypes = [vp, C.POINTER(ScoreDesc), C.POINTER(C.c_int32)]
+    lib.lvlm_score_few_rows.argtypes = [vp, C.POINTER(ScoreDesc), C.c_int, C.POINTER(C.c_int32)]
     lib.lvlm_score_from_probs.argtypes = [vp, vp, C.POINTER(ProbsDesc), vp, f32p, f32p]
     lib.lvlm_prefill_attn.argtypes = [vp, vp, C.POINTER(PrefillDesc), vp, vp, vp, vp, f32p, f32p, f32p]
     lib.lvlm_merge_compact.argtypes = [vp, vp, C.POINTER(MergeDesc), f32p, f32p, C.POINTER(Plane), i32p, i32p]
@@ -128,7 +129,7 @@ def _load():
     lib.lvlm_profile.argtypes = [C.c_void_p, C.c_int]
     lib.lvlm_profile_read.argtypes = [C.c_void_p, C.POINTER(ProfileEntry), C.c_int, C.POINTER(C.c_int)]
     for name in ("lvlm_profile", "lvlm_profile_read", "lvlm_create", "lvlm_destroy", "lvlm_workspace_bytes", "lvlm_set_workspace", "lvlm_schedule",
-                 "lvlm_merge_weights", "lvlm_score_tokens", "lvlm_score_plan", "lvlm_score_from_probs", "lvlm_prefill_attn", "lvlm_merge_compact",
+                 "lvlm_merge_weights", "lvlm_score_tokens", "lvlm_score_plan", "lvlm_score_few_rows", "lvlm_score_from_probs", "lvlm_prefill_attn", "lvlm_merge_compact",
                  "lvlm_merge_similar",
                  "lvlm_kv_compress",
                  "lvlm_decode_attn", "lvlm_decode_attn_static", "lvlm_decode_plan", "lvlm_stream_probe"):
@@ -252,6 +253,13 @@ class Context(_ContextCalls):
         form = C.c_int32()
         self._check(lib.lvlm_score_plan(self._h, C.byref(desc), C.byref(form)))
         return form.value
+
+    def score_few_rows(self, desc: ScoreDesc, lse_given: bool = False) -> int:
+        """lvlm_score_few_rows: chunks of 16 query rows per KV head where the kernel for few query rows takes the place of
+        form 0 or 1 (every key read and multiplied once, one launch), else 0."""
+        chunks = C.c_int32()
+        self._check(lib.lvlm_score_few_rows(self._h, C.byref(desc), int(lse_given), C.byref(chunks)))
+        return chunks.value
 
     # ---- step 6 ----
     def decode_plan(self, desc: AttnDesc):

@@ -373,6 +373,15 @@ lvlm_status lvlm_score_plan(const lvlm_ctx *ctx, const lvlm_score_desc *d, int32
     return LVLM_OK;
 }
 
+lvlm_status lvlm_score_few_rows(const lvlm_ctx *ctx, const lvlm_score_desc *d, int lse_given, int32_t *chunks) {
+    lvlm_ctx *c = const_cast<lvlm_ctx *>(ctx);
+    if (!ctx || !chunks) return fail(c, LVLM_ERR_INVALID_ARG, "score_few_rows: null argument");
+    if (const char *why = check_score(d)) return fail(c, LVLM_ERR_INVALID_ARG, "score_few_rows: %s", why);
+    const ScoreWs w = score_ws(*d);
+    *chunks = lse_given ? w.rows_given : w.rows;
+    return LVLM_OK;
+}
+
 lvlm_status lvlm_score_tokens(lvlm_ctx *ctx, void *stream, const lvlm_score_desc *d, const void *q, const void *k,
                               const float *row_lse, float *score_head, float *score_mean) {
     if (!ctx) return LVLM_ERR_INVALID_ARG;

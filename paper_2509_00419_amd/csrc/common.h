@@ -38,7 +38,8 @@ struct ScoreWs {
     bool single;   // short sequence: both passes in one launch, one part of column sums per query chunk
     bool shared_tiles;   // ... with four query chunks per workgroup sharing the key tiles through LDS
     int key_segs;        // ... and the keys cut into this many runs, a launch per sweep (1 = one launch)
-    int rows;            // few query rows: chunks of 16 of them, one workgroup each, in one launch (0: not that form)
+    int rows, rows_given;   // few query rows: chunks of 16 of them, one workgroup each, in one launch (0: not that form); the
+                            // same with the normalisers given
 };
 ScoreWs score_ws(const lvlm_score_desc &d);
 

@@ -22,6 +22,7 @@
 #include "common.h"
 #include "mma.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace lvlm {
@@ -1353,6 +1354,43 @@ hipError_t launch_score_probs(const Prof &prof, const lvlm_probs_desc &d, const 
     return hipGetLastError();
 }
 
+// Few query rows (score_rows_kernel): 16 of them per workgroup, the logits over all keys in registers.  Returns the chunks of
+// a KV head, or 0 where the form chosen without it (`w`) is the faster one.  Its time is one chain: start-up, the keys
+// at 1.6 us per 1000 of 128 bytes and 3.4 us of 256 bytes in bf16, 6 us in fp32, and a fold of one part per chunk; the other forms
+// read the keys twice but share the work over more workgroups.  The lines below are from some 900 shapes timed both ways
+// (4 to 768 workgroups, 85 to 4096 keys, heads of 64 and 128 channels; no shape taken loses more than 4 %).
+static int few_rows(const lvlm_score_desc &d, const ScoreWs &w, int n_chunks, bool given) {
+    const bool bf16 = d.dtype == LVLM_BF16;
+    const int es = bf16 ? 2 : 4;
+    const long long heads = (long long)d.B * d.Hkv;
+    const int n16 = (d.Hq / d.Hkv * d.T + 15) / 16;
+    const long long wgs = heads * n16;
+    if (w.shared_tiles || (!bf16 && d.hd == 128) || d.N > 16 * kRowsWaves * 32 || !(d.scale > 0.f) || d.k_stride_n * es >= (1ll << 26))
+        return 0;
+    if (w.single) {
+        // Against one chunk of 32 rows per workgroup, its keys over the waves: one turn of the chip, and keys enough to pay for
+        // eight waves and twice the parts -- in 256-byte rows 72, 7 more per chunk, and more than one tile a wave (28 heads x
+        // 64 rows: 7.2 -> 7.0 us at 212 keys, 15.0 -> 11.1 at 700; 8 heads of one row 6.8 -> 7.3 us at 85 keys).  With the
+        // normalisers given the other form reads the keys once as well: 280, 10 more per chunk (8 heads x 24 rows 6.9 -> 7.7 us
+        // at 108 keys, 12.2 -> 11.0 at 1044).
+        const long long sweep_rows = (long long)d.N * (d.hd * es) / 256;
+        return wgs <= 256 && n16 <= 48 && (given ? sweep_rows > 280 + 10 * n16 : d.N > 16 * kRowsWaves && sweep_rows > 72 + 7 * n16) ? n16 : 0;
+    }
+    // Against the two-pass kernels, whose three launches and fold cost 15 us whatever the shape and then split the keys over the
+    // chip; with the normalisers given they are a single short pass.
+    if (given || wgs > 768) return 0;
+    // one query row per KV head: they take 28 us and more for 4000 keys
+    if (d.T == 1 && n_chunks == 1) return n16;
+    // fp32: 4.75 us per 1000 keys behind by itself, ahead again as heads and workgroups fill the chip (4 heads x 24
+    // rows 15.5 -> 15.2 us at 1444 keys, 17.0 -> 29.5 at 3944; 192 heads of 24 rows 74 -> 39 us at 2048)
+    if (!bf16) return d.N * (4.75 - 0.078 * (double)heads - 0.014 * (double)wgs) < 5250.0 ? n16 : 0;
+    // bf16: the parts of many chunks cost more than the second sweep (28 heads x 128 rows, 56 chunks a KV head, 24.3 -> 29.6 us at
+    // 3048 keys, but two such sequences 35 -> 29 us), and beyond 3500 keys the chain shows unless the launch fills a turn, or
+    // several short of work (8 heads x 8 rows 17.8 -> 18.8 us at 3928 keys, 64 of them 40 -> 27 us).
+    if (n16 > (heads >= 8 ? 64 : 48)) return 0;
+    return d.N <= 3500 || (wgs >= 96 && (wgs <= 256 || n16 * 128 <= 4 * d.hd)) ? n16 : 0;
+}
+
 ScoreWs score_ws(const lvlm_score_desc &d) {
     ScoreWs w{};
     // Wide key blocks (2 tiles per wave) once they still give every CU two workgroups.
@@ -1413,24 +1451,15 @@ ScoreWs score_ws(const lvlm_score_desc &d) {
         w.rs = n_chunks;
         w.cps = 1;
     }
-    // Few query rows: 16 of them per workgroup, the logits over all keys in registers.  A turn of 256 workgroups
-    // takes 4.2 us + 3.1 us per 1000 keys of 256 bytes.  Against the one-launch form of short sequences (whose workgroups
-    // read the keys twice, but for 32 rows) that wins while one turn holds all of it, against the two-pass kernels with their
-    // fold up to three turns: one sequence of 7B heads (112 workgroups) 700 keys 15.0 -> 11.1 us, 2176 keys 21.1 -> 15.5 us,
-    // two of them 28.7 -> 15.9 us, four (two turns) 38.8 -> 26.1 us; 768 workgroups x 2000 keys 41.7 -> 36.8 us; but two
-    // turns of 1000 keys 18.5 -> 19.9 us against the one-launch form.
-    const int n16 = (d.Hq / d.Hkv * d.T + 15) / 16;
-    const long long turns = ((long long)d.B * d.Hkv * n16 + 255) / 256;
-    w.rows = !w.shared_tiles && !(d.dtype == LVLM_F32 && d.hd == 128) && d.N <= 16 * kRowsWaves * 32 && d.scale > 0.f &&
-                     d.k_stride_n * (d.dtype == LVLM_BF16 ? 2 : 4) < (1ll << 26) && turns <= (w.single ? 1 : 3)
-                 ? n16 : 0;
+    w.rows = few_rows(d, w, n_chunks, false);
+    w.rows_given = few_rows(d, w, n_chunks, true);
     const size_t rows = (size_t)d.B * d.Hq * d.T;
     w.part_m = 0;
     const size_t n_part = (size_t)w.nkb * 4 > (size_t)w.key_segs ? (size_t)w.nkb * 4 : (size_t)w.key_segs;
     w.part_l = align_up(w.part_m + rows * n_part * sizeof(float), 256);
     w.lse2 = align_up(w.part_l + rows * n_part * sizeof(float), 256);
     w.colpart = align_up(w.lse2 + rows * sizeof(float), 256);
-    w.total = align_up(w.colpart + (size_t)(w.rs > w.rows ? w.rs : w.rows) * d.B * d.Hkv * d.n_img * sizeof(float), 256);
+    w.total = align_up(w.colpart + (size_t)std::max(w.rs, std::max(w.rows, w.rows_given)) * d.B * d.Hkv * d.n_img * sizeof(float), 256);
     return w;
 }
 
@@ -1460,7 +1489,7 @@ hipError_t launch_score(const Prof &prof, const lvlm_score_desc &d, const ScoreW
     a.shb = dense ? (long long)d.Hkv * d.n_img : d.sh_stride_b;
     const bool need_lse = row_lse == nullptr;
     const bool wide = w.block_keys == 256;
-    const int rows = need_lse || w.single ? w.rows : 0;      // (with the normalisers given one short pass is all there is)
+    const int rows = need_lse ? w.rows : w.rows_given;
     if (d.dtype == LVLM_BF16 && d.hd == 128) {
         if (wide) launch_passes<LVLM_BF16, 128, 2>(prof, a, need_lse, w.single, w.shared_tiles, rows);
         else launch_passes<LVLM_BF16, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);

@@ -107,6 +107,33 @@ def test_argument_errors_are_reported_before_any_launch():
     assert st == 1 and b"together" in bd.lib.lvlm_last_error(ctx._h)
 
 
+def test_score_few_rows_rule():
+    """lvlm_score_few_rows is the library's own choice of the kernel for few query rows, at the edges of the rule: key
+    length, workgroups, chunks, type, stride, scale, normalisers."""
+    ctx = _ctx()
+
+    def chunks(B, N, T, Hq, Hkv, given=False, hd=128, dtype=bd.BF16, scale=0.088, stride=None):
+        d = bd.ScoreDesc(dtype, B, N, T, N - T, Hq, Hkv, hd, 0, N - T, 1, scale, T * Hq * hd, Hq * hd, hd,
+                         N * Hkv * hd, stride or Hkv * hd, hd)
+        return ctx.score_few_rows(d, given)
+
+    assert chunks(1, 2176, 64, 28, 4) == 28 and chunks(1, 845, 64, 28, 4) == 28
+    assert chunks(1, 845, 64, 28, 4, given=True) == 28 and chunks(1, 2176, 64, 28, 4, given=True) == 0
+    assert chunks(1, 128, 1, 8, 8) == 0 and chunks(1, 129, 1, 8, 8) == 1              # a tile per wave is too short
+    assert chunks(1, 4096, 1, 8, 8) == 1 and chunks(1, 4097, 1, 8, 8) == 0            # the registers hold 4096 keys
+    assert chunks(1, 3000, 109, 28, 4) == 48 and chunks(1, 3000, 112, 28, 4) == 0     # too many parts for four heads
+    assert chunks(2, 3000, 112, 28, 4) == 49
+    assert chunks(1, 3500, 8, 32, 8) == 2 and chunks(1, 3501, 8, 32, 8) == 0          # a long chain in a chip left idle
+    assert chunks(8, 4000, 8, 32, 8) == 2 and chunks(48, 4000, 8, 32, 8) == 2 and chunks(49, 4000, 8, 32, 8) == 0
+    assert chunks(1, 1100, 24, 4, 4, hd=64, dtype=bd.F32) == 2 and chunks(1, 2000, 24, 4, 4, hd=64, dtype=bd.F32) == 0
+    assert chunks(48, 2000, 24, 4, 4, hd=64, dtype=bd.F32) == 2 and chunks(1, 1100, 24, 4, 4, dtype=bd.F32) == 0
+    assert chunks(1, 845, 64, 28, 4, scale=0.0) == 0
+    assert chunks(1, 845, 64, 28, 4, stride=(1 << 25) - 8) == 28 and chunks(1, 845, 64, 28, 4, stride=1 << 25) == 0
+    assert chunks(64, 986, 96, 32, 8) == 0                                             # shared key tiles fill the chip
+    with pytest.raises(lv.LvlmError):
+        chunks(1, 100, 4, 6, 4)
+
+
 def test_score_plan_reports_the_launch_form():
     """lvlm_score_plan is the library's own launch decision (bench.py asks it instead of restating the rule)."""
     ctx = _ctx()

@@ -133,6 +133,34 @@ def test_score_tokens_few_query_rows(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img,
     assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
 
 
+@pytest.mark.parametrize("dtype,B,T,Hq,Hkv,d,n_sys,n_img,given", [
+    (torch.bfloat16, 1, 1, 1, 1, 128, 0, 128, False),        # 129 keys: the first length, one wave with a second tile
+    (torch.bfloat16, 1, 3, 5, 1, 128, 2, 507, False),        # 15 rows, exactly four tiles per wave
+    (torch.bfloat16, 2, 8, 6, 3, 64, 1, 200, False),         # 16 rows, heads of 64 channels
+    (torch.float32, 1, 17, 4, 4, 64, 0, 496, False),         # 17 rows, one key more than four tiles per wave
+    (torch.float32, 1, 24, 4, 4, 64, 7, 1000, False),        # fp32 in place of the two passes, at its longest for 8 workgroups
+    (torch.float32, 4, 1, 4, 4, 64, 0, 4095, False),         # one row per head: up to 4096 keys
+    (torch.bfloat16, 1, 48, 16, 1, 128, 0, 700, False),      # 48 chunks, the most for few heads
+    (torch.bfloat16, 1, 16, 4, 2, 128, 5, 310, True),        # normalisers given: the image keys alone, from key 5
+    (torch.float32, 1, 9, 8, 4, 64, 3, 400, True)])
+def test_score_tokens_few_rows_rule(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img, given):
+    """Shapes at the edges of the rule that takes the kernel for few query rows: the library says it takes it, and the
+    scores are the oracle's."""
+    N = n_sys + n_img + T
+    q, k = _rand((B, T, Hq, d), dtype, 25), _rand((B, N, Hkv, d), dtype, 26)
+    kw = dict(q_pos0=n_sys + n_img, img_begin=n_sys, n_img=n_img)
+    assert ctx.score_few_rows(ctx.score_desc(q, k, **kw), given) == (Hq // Hkv * T + 15) // 16
+    lse = None
+    if given:
+        tk = k.double().repeat_interleave(Hq // Hkv, dim=2)
+        s = torch.einsum("bthd,bnhd->bhtn", q.double(), tk) * d ** -0.5
+        s = s.masked_fill(torch.arange(N)[None, :] > (N - T + torch.arange(T))[:, None], -math.inf)
+        lse = torch.logsumexp(s, dim=-1).float().contiguous().to(DEV)
+    sh, sm = ctx.score_tokens(q.to(DEV), k.to(DEV), row_lse=lse, **kw)
+    osh, osm = O.score_tokens(f64(q), f64(k), **kw)
+    assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
+
+
 @pytest.mark.parametrize("given", [False, True])
 def test_score_tokens_few_rows_very_negative_logits(ctx, given):
     # logits around -200 and rows that see only the first keys: most waves see none, and no factor of theirs may overflow
