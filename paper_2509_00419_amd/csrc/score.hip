@@ -1358,7 +1358,8 @@ hipError_t launch_score_probs(const Prof &prof, const lvlm_probs_desc &d, const 
 // a KV head, or 0 where the form chosen without it (`w`) is the faster one.  Its time is one chain: start-up, the keys
 // at 1.6 us per 1000 of 128 bytes and 3.4 us of 256 bytes in bf16, 6 us in fp32, and a fold of one part per chunk; the other forms
 // read the keys twice but share the work over more workgroups.  The lines below are from some 900 shapes timed both ways
-// (4 to 768 workgroups, 85 to 4096 keys, heads of 64 and 128 channels; no shape taken loses more than 4 %).
+// (4 to 768 workgroups, 85 to 4096 keys, heads of 64 and 128 channels), and 240 more of 22 to 130 chunks a KV head.  All chunks of
+// a head run on one XCD, so with few heads the chunks beyond its 32 compute units wait, and their parts lengthen the fold.
 static int few_rows(const lvlm_score_desc &d, const ScoreWs &w, int n_chunks, bool given) {
     const bool bf16 = d.dtype == LVLM_BF16;
     const int es = bf16 ? 2 : 4;
@@ -1372,9 +1373,11 @@ static int few_rows(const lvlm_score_desc &d, const ScoreWs &w, int n_chunks, bo
         // eight waves and twice the parts -- in 256-byte rows 72, 7 more per chunk, and more than one tile a wave (28 heads x
         // 64 rows: 7.2 -> 7.0 us at 212 keys, 15.0 -> 11.1 at 700; 8 heads of one row 6.8 -> 7.3 us at 85 keys).  With the
         // normalisers given the other form reads the keys once as well: 280, 10 more per chunk (8 heads x 24 rows 6.9 -> 7.7 us
-        // at 108 keys, 12.2 -> 11.0 at 1044).
+        // at 108 keys, 12.2 -> 11.0 at 1044).  Chunks: 40 (of 5 heads 42 cost 16.9 -> 17.8 us at 818 keys, 40 still 18.85
+        // -> 18.6), with the normalisers given 32, a compute unit each (30: 15.1 -> 12.8 us, 42: 12.1 -> 16.0, 48 in fp32 15.7 -> 19.6).
         const long long sweep_rows = (long long)d.N * (d.hd * es) / 256;
-        return wgs <= 256 && n16 <= 48 && (given ? sweep_rows > 280 + 10 * n16 : d.N > 16 * kRowsWaves && sweep_rows > 72 + 7 * n16) ? n16 : 0;
+        if (wgs > 256 || n16 > (given ? 32 : 40)) return 0;
+        return (given ? sweep_rows > 280 + 10 * n16 : d.N > 16 * kRowsWaves && sweep_rows > 72 + 7 * n16) ? n16 : 0;
     }
     // Against the two-pass kernels, whose three launches and fold cost 15 us whatever the shape and then split the keys over the
     // chip; with the normalisers given they are a single short pass.
@@ -1382,12 +1385,15 @@ static int few_rows(const lvlm_score_desc &d, const ScoreWs &w, int n_chunks, bo
     // one query row per KV head: they take 28 us and more for 4000 keys
     if (d.T == 1 && n_chunks == 1) return n16;
     // fp32: 4.75 us per 1000 keys behind by itself, ahead again as heads and workgroups fill the chip (4 heads x 24
-    // rows 15.5 -> 15.2 us at 1444 keys, 17.0 -> 29.5 at 3944; 192 heads of 24 rows 74 -> 39 us at 2048)
+    // rows 15.5 -> 15.2 us at 1444 keys, 17.0 -> 29.5 at 3944; 192 heads of 24 rows 74 -> 39 us at 2048).  More than two chunks a
+    // compute unit of the few XCDs that have a head fill nothing (4 heads: 97 chunks 36 -> 43 us at 954 keys, 75 chunks 56 ->
+    // 65 us at 2729, but 106 chunks 36 -> 32 us at 487; 5 heads of 89 chunks 46 -> 37 us at 1009)
+    if (!bf16 && heads <= 4 && n16 > 64 && d.N > 650) return 0;
     if (!bf16) return d.N * (4.75 - 0.078 * (double)heads - 0.014 * (double)wgs) < 5250.0 ? n16 : 0;
     // bf16: the parts of many chunks cost more than the second sweep (28 heads x 128 rows, 56 chunks a KV head, 24.3 -> 29.6 us at
-    // 3048 keys, but two such sequences 35 -> 29 us), and beyond 3500 keys the chain shows unless the launch fills a turn, or
+    // 3048 keys, 2 heads of 48 chunks 18.1 -> 21.5 us at 1463, but two such sequences 35 -> 29 us), and beyond 3500 keys the chain shows unless the launch fills a turn, or
     // several short of work (8 heads x 8 rows 17.8 -> 18.8 us at 3928 keys, 64 of them 40 -> 27 us).
-    if (n16 > (heads >= 8 ? 64 : 48)) return 0;
+    if (n16 > (heads >= 8 ? 64 : 40)) return 0;
     return d.N <= 3500 || (wgs >= 96 && (wgs <= 256 || n16 * 128 <= 4 * d.hd)) ? n16 : 0;
 }
 

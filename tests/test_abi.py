@@ -121,7 +121,13 @@ def test_score_few_rows_rule():
     assert chunks(1, 845, 64, 28, 4, given=True) == 28 and chunks(1, 2176, 64, 28, 4, given=True) == 0
     assert chunks(1, 128, 1, 8, 8) == 0 and chunks(1, 129, 1, 8, 8) == 1              # a tile per wave is too short
     assert chunks(1, 4096, 1, 8, 8) == 1 and chunks(1, 4097, 1, 8, 8) == 0            # the registers hold 4096 keys
-    assert chunks(1, 3000, 109, 28, 4) == 48 and chunks(1, 3000, 112, 28, 4) == 0     # too many parts for four heads
+    assert chunks(1, 3000, 91, 28, 4) == 40 and chunks(1, 3000, 92, 28, 4) == 0       # too many parts for four heads
+    assert chunks(1, 880, 80, 8, 1) == 40 and chunks(1, 880, 81, 8, 1) == 0            # ... against the short form
+    assert chunks(1, 1000, 64, 8, 1, given=True) == 32 and chunks(1, 1000, 65, 8, 1, given=True) == 0
+    f32 = dict(hd=64, dtype=bd.F32)
+    assert chunks(1, 1500, 256, 16, 4, **f32) == 64 and chunks(1, 1500, 257, 16, 4, **f32) == 0
+    assert chunks(1, 650, 400, 16, 4, **f32) == 100 and chunks(1, 651, 400, 16, 4, **f32) == 0
+    assert chunks(1, 1000, 320, 20, 5, **f32) == 80
     assert chunks(2, 3000, 112, 28, 4) == 49
     assert chunks(1, 3500, 8, 32, 8) == 2 and chunks(1, 3501, 8, 32, 8) == 0          # a long chain in a chip left idle
     assert chunks(8, 4000, 8, 32, 8) == 2 and chunks(48, 4000, 8, 32, 8) == 2 and chunks(49, 4000, 8, 32, 8) == 0

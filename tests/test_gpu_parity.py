@@ -140,7 +140,9 @@ def test_score_tokens_few_query_rows(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img,
     (torch.float32, 1, 17, 4, 4, 64, 0, 496, False),         # 17 rows, one key more than four tiles per wave
     (torch.float32, 1, 24, 4, 4, 64, 7, 1000, False),        # fp32 in place of the two passes, at its longest for 8 workgroups
     (torch.float32, 4, 1, 4, 4, 64, 0, 4095, False),         # one row per head: up to 4096 keys
-    (torch.bfloat16, 1, 48, 16, 1, 128, 0, 700, False),      # 48 chunks, the most for few heads
+    (torch.bfloat16, 1, 40, 16, 1, 128, 0, 700, False),      # 40 chunks, the most for few heads
+    (torch.float32, 1, 260, 16, 4, 64, 0, 390, False),       # 65 fp32 chunks of four heads: up to 650 keys
+    (torch.bfloat16, 1, 32, 16, 1, 128, 3, 830, True),       # 32 chunks with the normalisers given
     (torch.bfloat16, 1, 16, 4, 2, 128, 5, 310, True),        # normalisers given: the image keys alone, from key 5
     (torch.float32, 1, 9, 8, 4, 64, 3, 400, True)])
 def test_score_tokens_few_rows_rule(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img, given):
