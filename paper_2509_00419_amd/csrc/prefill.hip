@@ -158,7 +158,6 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
     constexpr int VP = kVtPitch;
     constexpr int NV = HD / 16;             // 16-byte words a lane holds of a row half = chunks of one product
     constexpr int NCB = HD / 32;            // blocks of 32 channels
-    constexpr int UPR = ROWB / 16;          // 16-byte units per row
     constexpr int KTPR = 128 / 32;          // threads per K row, four units each
     __shared__ __attribute__((aligned(16))) char k_lds[2][32 * KP];
     __shared__ __attribute__((aligned(16))) char v_lds[2][HD * VP];
@@ -828,6 +827,179 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a)
     }
 }
 
+// fp32 where whole turns of the chip share their tiles (launch_prefill_attn has the rule), on the fp32 matrix instruction of
+// 32 x 32 x 2: the products of a 32 x 32 tile cost as much as above, but a K or V value read once serves 32 rows instead of 16 and the
+// four waves of a workgroup read the same tile, so it is the matrix instructions that bound it and not the reading.
+// A workgroup of four waves owns 128 query rows of one head, one 32-row block per wave, its rows held as an MFMA
+// operand.  K and V tiles of 32 keys go through LDS as they are (rows = keys), fetched one tile ahead by the 256
+// threads, one barrier per tile.  S^T = K Q^T (rows = keys, columns = queries): a lane owns one query row and 16
+// of its logits; the textbook online softmax (the reference follows the running maximum, sums and accumulators
+// are rescaled when it moves).  For O^T += V^T P^T the contraction of one instruction is two keys, one per
+// half-wave: exactly the two keys the two halves hold in the same accumulator register, so register r of the
+// probabilities is the second operand as it stands and the first is V[that key][channel] read from the tile.
+template <int HD>
+__global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(PrefillArgs a) {
+    constexpr int ROWB = HD * 4;
+    constexpr int KP = ROWB + 16;           // tile pitch: odd multiple of 16 bytes
+    constexpr int NV = HalfRow<LVLM_F32, HD>::NV;
+    constexpr int NCB = HD / 32;
+    constexpr int UPR = ROWB / 16;          // 16-byte units per row
+    constexpr int UPT = 32 * UPR / 256;     // units per thread and tile (2 or 4)
+    constexpr int TPR = UPR / UPT;          // threads per row
+    __shared__ __attribute__((aligned(16))) char k_lds[2][32 * KP];
+    __shared__ __attribute__((aligned(16))) char v_lds[2][32 * KP];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hf = lane >> 5, l32 = lane & 31;
+    const int qb = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;      // longest blocks first
+    const int g = h / a.G;
+    const int q0 = qb * 128, blk0 = q0 + 32 * wave;
+    const int row = blk0 + l32;
+    const int kmax = a.causal ? min(a.N, q0 + 128) : a.N;
+    const int n_tiles = (kmax + 31) >> 5;
+
+    HalfRow<LVLM_F32, HD> qa;               // lane (row l32, half hf): bytes 16 hf + 32 i of its row
+    {
+        const char *src = a.q + (long long)b * a.qsb + (long long)min(row, a.N - 1) * a.qsn + (long long)h * a.qsh + 16 * hf;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) qa.v[i] = *reinterpret_cast<const uint4 *>(src + 32 * i);
+    }
+    const int srow = tid / TPR, scu = tid % TPR;
+    const char *kbase = a.k + (long long)b * a.ksb + (long long)g * a.ksh + 16 * scu;
+    const char *vbase = a.v + (long long)b * a.vsb + (long long)g * a.vsh + 16 * scu;
+    uint4 ks0 = make_uint4(0, 0, 0, 0), ks1 = ks0, ks2 = ks0, ks3 = ks0, vs0 = ks0, vs1 = ks0, vs2 = ks0, vs3 = ks0;
+    auto fetch = [&](int j0) {              // rows past the end repeat the last row (masked later)
+        const long long r = min(j0 + srow, a.N - 1);
+        const uint4 *ksrc = reinterpret_cast<const uint4 *>(kbase + r * a.ksn);
+        const uint4 *vsrc = reinterpret_cast<const uint4 *>(vbase + r * a.vsn);
+        ks0 = ksrc[0], vs0 = vsrc[0];
+        ks1 = ksrc[TPR], vs1 = vsrc[TPR];
+        if constexpr (UPT > 2) {
+            ks2 = ksrc[2 * TPR], vs2 = vsrc[2 * TPR];
+            ks3 = ksrc[3 * TPR], vs3 = vsrc[3 * TPR];
+        }
+    };
+    auto stash = [&](int buf) {
+        uint4 *kd = reinterpret_cast<uint4 *>(&k_lds[buf][srow * KP + 16 * scu]);
+        uint4 *vd = reinterpret_cast<uint4 *>(&v_lds[buf][srow * KP + 16 * scu]);
+        kd[0] = ks0, vd[0] = vs0;
+        kd[TPR] = ks1, vd[TPR] = vs1;
+        if constexpr (UPT > 2) {
+            kd[2 * TPR] = ks2, vd[2 * TPR] = vs2;
+            kd[3 * TPR] = ks3, vd[3 * TPR] = vs3;
+        }
+    };
+
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x16 oacc[NCB];
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[cb][r] = 0.f;
+
+    fetch(0);
+    stash(0);
+    __syncthreads();
+    for (int t = 0; t < n_tiles; ++t) {
+        const int j0 = t << 5, buf = t & 1;
+        fetch(min(j0 + 32, (n_tiles - 1) << 5));
+        if (!a.causal || j0 <= blk0 + 31) {                       // the block sees some key of the tile
+            HalfRow<LVLM_F32, HD> kf;
+            {
+                const char *src = &k_lds[buf][l32 * KP + 16 * hf];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) kf.v[i] = *reinterpret_cast<const uint4 *>(src + 32 * i);
+            }
+            f32x16 s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.f;
+            mma_tile<LVLM_F32, HD>(s, kf, qa);                    // rows = keys, columns = queries
+            if ((a.causal && j0 + 31 > blk0) || j0 + 32 > a.N) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int j = j0 + acc_row(r, hf);
+                    if ((a.causal && j > row) || j >= a.N) s[r] = -INFINITY;
+                }
+            }
+            float mx = s[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+            mx = fmaxf(mx, other_half(mx));                       // finite: key j0 <= blk0 is visible to every row
+            const float m_new = fmaxf(m_run, mx);
+            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * a.scale_log2);   // first tile: 0
+            const float mb = m_new * a.scale_log2;
+            float p[16], sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                p[r] = __builtin_amdgcn_exp2f(fmaf(s[r], a.scale_log2, -mb));
+                sum += p[r];
+            }
+            l_run = l_run * alpha + sum;
+            m_run = m_new;
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[cb][r] *= alpha;
+                // register r of the two half-waves: keys acc_row(r, 0) and acc_row(r, 1) -- the two keys one
+                // instruction contracts
+                const char *vsrc = &v_lds[buf][4 * (32 * cb + l32)];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float vv = *reinterpret_cast<const float *>(vsrc + acc_row(r, hf) * KP);
+                    oacc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv, p[r], oacc[cb], 0, 0, 0);
+                }
+            }
+        }
+        if (t + 1 < n_tiles) stash(buf ^ 1);
+        __syncthreads();
+    }
+
+    const float l_tot = l_run + other_half(l_run);
+    if (row >= a.N) return;
+    const float inv = 1.f / l_tot;
+    // lane (query l32, half hf) holds channels 32 cb + 8 (r / 4) + 4 hf + r % 4
+    float *dst = reinterpret_cast<float *>(a.out + (long long)b * a.osb + (long long)row * a.osn + (long long)h * a.osh) + 4 * hf;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+            *reinterpret_cast<float4 *>(dst + 32 * cb + 8 * r4) =
+                make_float4(oacc[cb][4 * r4 + 0] * inv, oacc[cb][4 * r4 + 1] * inv, oacc[cb][4 * r4 + 2] * inv,
+                            oacc[cb][4 * r4 + 3] * inv);
+    if (hf == 0) {
+        const float lse = m_run * a.scale + __logf(l_tot);
+        a.row_lse[((long long)b * a.Hq + h) * a.N + row] = lse;
+        if (a.lse_t && row >= a.N - a.T) a.lse_t[((long long)b * a.Hq + h) * a.T + (row - (a.N - a.T))] = lse;
+    }
+}
+
+// Whether the fp32 kernel that shares its tiles is the faster one, from 680 shapes timed both ways (1 to 960 heads, 20 to
+// 4288 tokens).  It works in turns of 256 workgroups of 128 rows, each as long as its longest block: it needs turns that are
+// nearly full, and under a causal mask few blocks, or the longest ones are waited for (the other kernel's 16-row blocks
+// level that out).  Heads of 64 channels: where the four waves of the other kernel have equally many tiles (all but, of few
+// blocks), it reads less per product -- 256 heads x 384 tokens 95 -> 64 us, 512 heads x 128 tokens 45 -> 28 us, but 128 heads x 800 causal 144 -> 167 us.  Of 128
+// channels the other kernel is bound by reading K and V, and loses from three quarters of a turn on while the work is
+// small: 256 heads x 128 tokens 57 -> 31 us, 512 heads x 256 290 -> 189 us, 384 of 94 tokens 57 -> 43 us.
+bool f32_shares_tiles(const lvlm_prefill_desc &d) {
+    const long long heads = (long long)d.B * d.Hq, nqb = (d.N + 127) / 128, wgs = heads * nqb;
+    const int tiles = (d.N + 31) / 32, n16 = (d.N + 15) / 16;
+    if (tiles < 2 && d.hd == 64) return false;
+    if (d.causal && nqb > 5) return false;
+    const double fill = (double)wgs / (double)((wgs + 255) / 256 * 256);
+    // tiles a wave of the other kernel takes in turn, over its blocks of 16 rows; tiles a workgroup of this one takes
+    long long in_turn = 0, shared = 0;
+    if (d.causal) {
+        for (int x = 0; x < n16; ++x) in_turn += ((x < n16 - 1 ? 16 * x + 16 : d.N) + 127) / 128;
+        for (int x = 0; x < nqb; ++x) shared += (x < nqb - 1 ? 4 * (x + 1) : tiles);
+    } else {
+        in_turn = (long long)n16 * ((tiles + 3) / 4);
+        shared = nqb * tiles;
+    }
+    if (d.hd == 64) return fill > 0.9 && (double)(4 * in_turn) > (nqb <= 3 ? 6.7 : 7.8) * (double)shared;
+    return fill > 0.9 || (fill > (d.causal ? 0.78 : 0.71) && heads * in_turn <= 36 * 256);
+}
+
 }  // namespace
 
 PrefillWs prefill_ws(const lvlm_prefill_desc &d) {
@@ -884,6 +1056,10 @@ hipError_t launch_prefill_attn(const Prof &prof, const lvlm_prefill_desc &d, con
             if (fast) LVLM_LAUNCH(prof, prefill_attn_d64_kernel, dim3((unsigned)grid), dim3(128), 0, stream, a);
             LVLM_LAUNCH(prof, prefill_attn_safe_kernel<64>, safe_grid, dim3(128), 0, stream, a, (int)grid);
         }
+    } else if (f32_shares_tiles(d)) {
+        const dim3 grid((unsigned)a.nqb, (unsigned)d.Hq, (unsigned)d.B);
+        if (d.hd == 128) LVLM_LAUNCH(prof, prefill_attn_f32_shared_kernel<128>, grid, dim3(256), 0, stream, a);
+        else LVLM_LAUNCH(prof, prefill_attn_f32_shared_kernel<64>, grid, dim3(256), 0, stream, a);
     } else {
         // one block of 16 rows per workgroup; two (each K and V operand feeds two products, 64 bytes of L2 traffic per
         // product instead of 128) once that still leaves many rounds of the chip: it is 3-4 % faster from about

@@ -232,7 +232,7 @@ def test_prefill_attn_random_shapes(ctx):
 @pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
     (1, 1, 1, 1, 64, True), (2, 15, 4, 4, 64, True), (1, 16, 2, 1, 128, False), (1, 17, 4, 2, 64, True),
     (1, 97, 3, 1, 128, True), (1, 128, 2, 2, 64, True), (1, 129, 2, 2, 64, False), (2, 161, 4, 1, 128, True),
-    (683, 33, 8, 4, 64, True), (700, 30, 12, 4, 128, True)])      # the last two: two 16-row blocks per workgroup
+    (683, 33, 8, 4, 64, True), (1, 385, 24, 4, 128, True)])       # two 16-row blocks per workgroup; nearly three quarters of a turn
 def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causal):
     fused, split = _qkv(B, N, Hq, Hkv, d, torch.float32, 500 + N, 2.0)
     q, k, v = split(fused)
@@ -240,6 +240,26 @@ def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causa
     o_out, o_lse = O.prefill_attn(f64(q), f64(k), f64(v), causal=causal, dtype="f32")
     assert rel_err(out.cpu(), o_out) < 1e-5
     assert np.abs(lse.cpu().numpy() - o_lse).max() < 1e-5 * max(1.0, np.abs(o_lse).max())
+
+
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
+    (64, 50, 4, 4, 64, True), (64, 64, 4, 2, 64, False), (32, 125, 8, 4, 64, True), (64, 128, 4, 1, 64, False),   # one block, one turn
+    (32, 250, 4, 4, 64, False), (32, 250, 4, 4, 64, True), (16, 510, 4, 4, 64, True), (8, 610, 26, 2, 64, True),  # up to five blocks
+    (64, 1, 4, 4, 128, True), (64, 31, 4, 4, 128, False), (47, 33, 4, 2, 128, True), (32, 129, 4, 1, 128, True),  # 188 of 256 places
+    (16, 500, 4, 4, 128, False), (8, 640, 7, 1, 128, True),
+    (100, 643, 4, 2, 128, True)])                  # six blocks: sixteen-row blocks again, two per workgroup
+def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal):
+    """fp32 launches of whole turns of the chip: the kernel whose four waves share their tiles, at the edges of its rule, of
+    its 128-row blocks and of its 32-key tiles.  Sampled sequences against the oracle, every row written."""
+    fused, split = _qkv(B, N, Hq, Hkv, d, torch.float32, 700 + N, 2.0)
+    out = torch.full((B, N, Hq, d), float("nan"), device=DEV)
+    out, lse, _, _ = ctx.prefill_attn(*split(fused.to(DEV)), causal=causal, out=out)
+    assert torch.isfinite(out).all() and torch.isfinite(lse).all()
+    pick = [0, B // 2, B - 1]
+    q, k, v = (x[pick] for x in split(fused))
+    o_out, o_lse = O.prefill_attn(f64(q), f64(k), f64(v), causal=causal, dtype="f32")
+    assert rel_err(out[pick].cpu(), o_out) < 1e-5
+    assert np.abs(lse[pick].cpu().numpy() - o_lse).max() < 1e-5 * max(1.0, np.abs(o_lse).max())
 
 
 def test_prefill_attn_rejects_bad_arguments(ctx):
