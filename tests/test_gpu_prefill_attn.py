@@ -195,6 +195,55 @@ def test_prefill_attn_far_logits_in_the_middle_of_a_long_row(ctx):
     assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
 
 
+@pytest.mark.parametrize("B,N,Hq,Hkv,d", [
+    (1, 200, 3, 1, 64), (1, 200, 11, 1, 128),     # heads that do not fill the eight XCDs: padding workgroups, a mark each
+    (16, 250, 32, 2, 64), (16, 250, 32, 2, 128),  # 1024 workgroups: one mark each, every place of the chip redoes blocks in turn
+    (35, 500, 16, 2, 64), (35, 500, 16, 2, 128),  # 2240: five marks a workgroup, several of them set
+    (1376, 300, 8, 1, 64)])                       # 33024: more than 64 marks a workgroup, a second round
+def test_prefill_attn_many_far_logits(ctx, B, N, Hq, Hkv, d):
+    """Every query block of two sequences out of three sees later logits far beyond the reference of its first tile (natural-log
+    distance 120), so that workgroups of the fallback kernel have several marked blocks to redo, one after the other."""
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    q, k, v = (torch.randn(B, N, h, d, generator=g, device=DEV) for h in (Hq, Hkv, Hkv))
+    a = (60.0 * d ** 0.5) ** 0.5
+    far = (torch.arange(B, device=DEV) % 3 != 1).float()[:, None, None]
+    q, k = 0.05 * q, 0.05 * k
+    q[..., 0] = a * far
+    k[..., 0] = a * far
+    k[:, :32, :, 0] = -a * far
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    out = torch.full((B, N, Hq, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    out, lse, _, _ = ctx.prefill_attn(q, k, v, out=out)
+    assert torch.isfinite(out).all() and torch.isfinite(lse).all()
+    pick = sorted({0, B // 2, B - 1, max(B - 2, 0)})
+    o_out, o_lse = O.prefill_attn(f64(q[pick].cpu()), f64(k[pick].cpu()), f64(v[pick].cpu()), dtype="bf16")
+    assert rel_err(out[pick].float().cpu(), o_out) < 2e-2
+    assert np.abs(lse[pick].cpu().numpy() - o_lse).max() < 1e-5 * np.abs(o_lse).max()
+
+
+@pytest.mark.parametrize("d,which", [(64, "k"), (128, "v"), (128, "kv")])
+def test_prefill_attn_rows_64_mib_apart(ctx, d, which):
+    """Row strides of 64 MiB, beyond the 32-bit offsets inside a tile of the kernels that pipeline or share tiles: attention
+    and scores of such rows go to the kernels with 64-bit addresses (a whole and a ragged tile, 2.6 GB apart)."""
+    N, T, H, step = 40, 6, 2, 1 << 25
+    g = torch.Generator().manual_seed(d)
+    q, k, v = (torch.randn(1, N, H, d, generator=g).bfloat16() for _ in range(3))
+
+    def apart(x):
+        t = torch.empty((N - 1) * step + H * d, dtype=torch.bfloat16, device=DEV).as_strided((1, N, H, d), (N * step, step, d, 1))
+        return t.copy_(x.to(DEV))
+    kd, vd = (apart(x) if c in which else x.to(DEV) for c, x in (("k", k), ("v", v)))
+    out, lse, sh, sm = ctx.prefill_attn(q.to(DEV), kd, vd, n_text=T, img_begin=3, n_img=30)
+    o_out, o_lse = O.prefill_attn(f64(q), f64(k), f64(v), dtype="bf16")
+    assert rel_err(out.float().cpu(), o_out) < 2e-2
+    assert np.abs(lse.cpu().numpy() - o_lse).max() < 1e-5 * np.abs(o_lse).max()
+    kw = dict(q_pos0=N - T, img_begin=3, n_img=30)
+    osh, osm = O.score_tokens(f64(q[:, N - T:]), f64(k), **kw)
+    assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
+    sh, sm = ctx.score_tokens(q[:, N - T:].to(DEV), kd, **kw)
+    assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5
+
+
 def test_prefill_attn_random_shapes(ctx):
     """Seeded sweep over small shapes: lengths around the tile and block edges, head counts and groups (G = 1 ... 7),
     both head dimensions and dtypes, with and without the mask, any number of instruction rows, any image span,
@@ -232,7 +281,7 @@ def test_prefill_attn_random_shapes(ctx):
 @pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
     (1, 1, 1, 1, 64, True), (2, 15, 4, 4, 64, True), (1, 16, 2, 1, 128, False), (1, 17, 4, 2, 64, True),
     (1, 97, 3, 1, 128, True), (1, 128, 2, 2, 64, True), (1, 129, 2, 2, 64, False), (2, 161, 4, 1, 128, True),
-    (683, 33, 8, 4, 64, True), (1, 385, 24, 4, 128, True)])       # two 16-row blocks per workgroup; nearly three quarters of a turn
+    (683, 33, 8, 4, 64, True), (1, 385, 24, 4, 128, True)])       # two 16-row blocks per workgroup; a chip a third full
 def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causal):
     fused, split = _qkv(B, N, Hq, Hkv, d, torch.float32, 500 + N, 2.0)
     q, k, v = split(fused)
@@ -245,7 +294,7 @@ def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causa
 @pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
     (64, 50, 4, 4, 64, True), (64, 64, 4, 2, 64, False), (32, 125, 8, 4, 64, True), (64, 128, 4, 1, 64, False),   # one block, one turn
     (32, 250, 4, 4, 64, False), (32, 250, 4, 4, 64, True), (16, 510, 4, 4, 64, True), (8, 610, 26, 2, 64, True),  # up to five blocks
-    (64, 1, 4, 4, 128, True), (64, 31, 4, 4, 128, False), (47, 33, 4, 2, 128, True), (32, 129, 4, 1, 128, True),  # 188 of 256 places
+    (64, 1, 4, 4, 128, True), (64, 31, 4, 4, 128, False), (50, 33, 4, 2, 128, True), (32, 129, 4, 1, 128, True),  # 200 of 256 places
     (16, 500, 4, 4, 128, False), (8, 640, 7, 1, 128, True),
     (100, 643, 4, 2, 128, True)])                  # six blocks: sixteen-row blocks again, two per workgroup
 def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal):
