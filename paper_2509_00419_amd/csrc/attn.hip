@@ -91,8 +91,7 @@ __device__ __forceinline__ bf16x8 pack_bf16x8(const float *p) {
 // weighs its own channels of the V row.  The four row groups see different entries and keep a sum and an output each;
 // they meet, like the four waves, at the end.
 // Measured (heads of 64 channels, fold included, 32x32 matrix instruction -> here): one head per group 4 x 257 entries
-// 12.4 -> 7.0 us, 64 x 4097 46 -> 26 us; four per group 8 x 2049 13.2 -> 10.6 us; eight per group, where the exponentials of
-// 64 logits per tile weigh most, 13.5 -> 14.2 us (of 128 channels 25.9 -> 23.2 us).
+// 12.4 -> 7.0 us, 64 x 4097 46 -> 26 us; four per group 8 x 2049 13.2 -> 10.6 us; eight per group of 128 channels 25.9 -> 23.2 us.
 template <int HD, int GP>
 __global__ __launch_bounds__(256) void attn_partial_f32_kernel(AttnArgs a) {
     constexpr int ROWB = HD * 4;
@@ -278,6 +277,228 @@ __global__ __launch_bounds__(256) void attn_partial_f32_kernel(AttnArgs a) {
     }
 }
 
+
+// fp32 groups of five to eight query heads of 64 channels: the logits and P V on the 32x32 matrix instruction, rows = entries,
+// columns = heads.  A tile costs 4096 matrix cycles whatever the group holds; the vector kernel above needs some 450 per head and
+// in every one of 16 lanes the exponentials of all its logits, and falls behind from five heads on (heads per group, fold
+// included, vector -> here): 5 x 32 x 512 entries 40.0 -> 38.6 us, 7 x 64 x 1025 30.2 -> 28.1, 8 x 8 x 2048 18.1 -> 17.0 us.  Of 128
+// channels the vector kernel stays ahead (25.9 against 23.2 us).
+// A wave takes 32 entries at a time; V rows pass through a wave-private LDS tile to be read by channel.
+template <int HD, int GP>
+__global__ __launch_bounds__(256) void attn_partial_f32_wide_kernel(AttnArgs a) {
+    constexpr int ROWB = HD * 4;
+    constexpr int NV = HalfRow<LVLM_F32, HD>::NV;
+    constexpr int UPR = ROWB / 16;        // 16-byte units per row
+    constexpr int KSUB = 64 / UPR;        // rows a wave covers with one load instruction
+    constexpr int VPL = 32 / KSUB;        // V units per lane per 32-entry tile
+    constexpr int NB = HD / 32;           // 32-row blocks of the transposed output
+    constexpr int VPITCH = ROWB + 16;     // LDS row pitch of the V tile: the two lane halves hit different banks
+    struct Tile {
+        HalfRow<LVLM_F32, HD> kf;         // K rows as the A operand: lane = (entry l32, half hf)
+        uint4 vv[VPL];                    // V rows in natural layout: lane = (unit lane % UPR, entry lane / UPR + KSUB * i)
+    };
+
+    __shared__ __attribute__((aligned(16))) char v_lds[4][32 * VPITCH];
+    __shared__ float wm[4][GP], wl[4][GP];
+    __shared__ __attribute__((aligned(16))) float wo[4][GP][HD];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int hf = lane >> 5, l32 = lane & 31;
+    const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+    const int hg = b * a.Hkv + g;
+    const long long cbase = (long long)hg * a.Lmax;
+    const char *kc = a.k + cbase * ROWB;
+    const char *vc = a.v + cbase * ROWB;
+    const int vunit = lane % UPR, vsub = lane / UPR;
+    const int s_lo = split * a.split_len;
+
+    // Loads do not wait for the length: any slot below Lmax is readable, stale rows are masked later.
+    auto load_tile = [&](int j0, Tile &t) {
+        const int jk = min(j0 + l32, a.Lmax - 1);
+        const char *ks = kc + (long long)jk * ROWB + hf * (ROWB / 2);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) t.kf.v[i] = *reinterpret_cast<const uint4 *>(ks + 16 * i);
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) {
+            const int jv = min(j0 + vsub + KSUB * i, a.Lmax - 1);
+            t.vv[i] = *reinterpret_cast<const uint4 *>(vc + (long long)jv * ROWB + 16 * vunit);
+        }
+    };
+    Tile cur;
+    const int j_first = s_lo + 32 * wave;
+    if (j_first < a.Lmax) load_tile(j_first, cur);
+
+    // query operand: column l32 of the product is head l32 of the group (zero beyond G)
+    HalfRow<LVLM_F32, HD> qf;
+    if (l32 < a.G) {
+        const char *src = a.q + ((long long)b * a.Hq + g * a.G + l32) * ROWB + hf * (ROWB / 2);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) qf.v[i] = *reinterpret_cast<const uint4 *>(src + 16 * i);
+    } else {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) qf.v[i] = make_uint4(0, 0, 0, 0);
+    }
+    // the entry being appended, in both operand layouts (split 0 also stores it into the cache)
+    HalfRow<LVLM_F32, HD> kn_f;
+    uint4 vn_u = make_uint4(0, 0, 0, 0);
+    if (a.append) {
+        const char *kn = a.k_new + (long long)hg * ROWB;
+        const char *vn = a.v_new + (long long)hg * ROWB;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) kn_f.v[i] = *reinterpret_cast<const uint4 *>(kn + hf * (ROWB / 2) + 16 * i);
+        vn_u = *reinterpret_cast<const uint4 *>(vn + 16 * vunit);
+    }
+
+    const HeadLen hl = head_len(a.len[hg], a.bound, a.append);
+    const int L = hl.L, new_slot = hl.new_slot;
+    const int s_hi = split == a.n_split - 1 ? L : min(L, s_lo + a.split_len);   // the last split takes the remainder
+    if (split == 0) {
+        if (new_slot >= 0) {
+            if (tid < UPR)
+                *reinterpret_cast<uint4 *>(a.k + (cbase + new_slot) * ROWB + 16 * tid) =
+                    *reinterpret_cast<const uint4 *>(a.k_new + (long long)hg * ROWB + 16 * tid);
+            else if (tid < 2 * UPR)
+                *reinterpret_cast<uint4 *>(a.v + (cbase + new_slot) * ROWB + 16 * (tid - UPR)) =
+                    *reinterpret_cast<const uint4 *>(a.v_new + (long long)hg * ROWB + 16 * (tid - UPR));
+            else if (tid == 2 * UPR) {
+                a.kind[cbase + new_slot] = (uint8_t)a.new_kind;
+                a.pos[cbase + new_slot] = a.new_pos;
+            }
+        }
+        if (tid == 0) {
+            a.cur_len[2 * hg] = L;
+            a.cur_len[2 * hg + 1] = hl.flags;
+        }
+    }
+
+    float m_run = -INFINITY, l_run = 0.f;   // of head l32 (both lane halves hold the same value)
+    f32x16 oacc[NB];                        // O^T: rows = output channels of block nb, column = head l32
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[nb][r] = 0.f;
+
+    char *vt = &v_lds[wave][0];
+    for (int j0 = j_first; j0 < s_hi; j0 += 128) {
+        Tile nxt = cur;     // always defined (a conditionally written local would live in scratch)
+        const bool more = j0 + 128 < s_hi;
+        if (more) load_tile(j0 + 128, nxt);
+
+        // substitute the appended entry, zero the rows beyond the range (their V must not reach the MFMA)
+        if (j0 + 32 > s_hi || (new_slot >= j0 && new_slot < j0 + 32)) {
+            if (j0 + l32 == new_slot) cur.kf = kn_f;
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) {
+                const int j = j0 + vsub + KSUB * i;
+                if (j == new_slot) cur.vv[i] = vn_u;
+                if (j >= s_hi) cur.vv[i] = make_uint4(0, 0, 0, 0);
+            }
+        }
+        // V tile to LDS in natural layout
+#pragma unroll
+        for (int i = 0; i < VPL; ++i)
+            *reinterpret_cast<uint4 *>(vt + (vsub + KSUB * i) * VPITCH + 16 * vunit) = cur.vv[i];
+
+        // logits: rows = entries, columns = heads
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        mma_tile<LVLM_F32, HD>(acc, cur.kf, qf);
+
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int j = j0 + acc_row(r, hf);
+            const float t = (j < s_hi) ? acc[r] * a.scale_log2 : -INFINITY;
+            acc[r] = t;
+            tmax = fmaxf(tmax, t);
+        }
+        tmax = fmaxf(tmax, other_half(tmax));
+        const float m_new = fmaxf(m_run, tmax);          // finite: the tile holds at least one entry
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        // (rows of a tile beyond the range lie beyond the head's length, and the logit rows are whole tiles
+        // long: the four consecutive entries of a register quad go out as one 16-byte word, masked or not)
+        if (a.update_score && l32 < a.G) {
+            float *lg = a.logits + ((long long)hg * GP + l32) * a.Lcap + j0 + 4 * hf;
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+                *reinterpret_cast<float4 *>(lg + 8 * r4) =
+                    make_float4(acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]);
+        }
+        float p[16];
+        float psum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            p[r] = __builtin_amdgcn_exp2f(acc[r] - m_new);
+            psum += p[r];
+        }
+        psum += other_half(psum);
+        l_run = l_run * alpha + psum;
+        m_run = m_new;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[nb][r] *= alpha;
+
+        // the V tile is private to this wave: order the LDS traffic, no workgroup barrier
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+        // O^T += V^T P^T on the matrix cores.  The contraction index is free, so it is numbered the way
+        // the probabilities already sit in this lane's registers: step s <-> entry acc_row(s, hf).  V is read transposed from LDS.
+#pragma unroll
+        for (int s2 = 0; s2 < 16; ++s2) {
+            const int e0 = acc_row(s2, hf);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const float va = *reinterpret_cast<const float *>(vt + e0 * VPITCH + 4 * (32 * nb + l32));
+                oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, p[s2], oacc[nb], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (more) cur = nxt;
+    }
+
+    // ---- fold the four waves: lane (head l32 < G, half hf) holds 16 channels of every block
+    if (l32 < GP) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) wo[wave][l32][32 * nb + acc_row(r, hf)] = oacc[nb][r];
+        if (hf == 0) {
+            wm[wave][l32] = m_run;
+            wl[wave][l32] = l_run;
+        }
+    }
+    __syncthreads();
+    float *po = a.part_o + ((long long)hg * a.n_split + split) * GP * HD;
+    for (int idx = tid; idx < GP * HD; idx += 256) {
+        const int h = idx / HD, e = idx % HD;
+        float mx = wm[0][h];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) mx = fmaxf(mx, wm[w][h]);
+        const float ms = (mx == -INFINITY) ? 0.f : mx;
+        float sacc = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) sacc += wo[w][h][e] * __builtin_amdgcn_exp2f(wm[w][h] - ms);
+        po[idx] = sacc;
+    }
+    if (tid < GP) {
+        float mx = wm[0][tid];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) mx = fmaxf(mx, wm[w][tid]);
+        const float ms = (mx == -INFINITY) ? 0.f : mx;
+        float sacc = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) sacc += wl[w][tid] * __builtin_amdgcn_exp2f(wm[w][tid] - ms);
+        float *pml = a.part_ml + (((long long)hg * a.n_split + split) * GP + tid) * 2;
+        pml[0] = mx;
+        pml[1] = sacc;
+    }
+}
 
 // bf16 variant on 16x16x32 MFMA tiles: a group has at most 8 query heads, so a 16-wide head axis wastes
 // half as much as a 32-wide one, and the accumulators (32 + 8 registers) leave room for three waves per
@@ -864,6 +1085,8 @@ void launch_both(const Prof &prof, const AttnArgs &a, int B, int len_bound) {
         else
             LVLM_LAUNCH(prof, (attn_partial_bf16_kernel<HD, GP, false, false>), grid, dim3(256), 0, stream, a);
     }
+    else if constexpr (HD == 64 && GP == 8)
+        LVLM_LAUNCH(prof, (attn_partial_f32_wide_kernel<HD, GP>), dim3(a.n_split, a.Hkv, B), dim3(256), 0, stream, a);
     else
         LVLM_LAUNCH(prof, (attn_partial_f32_kernel<HD, GP>), dim3(a.n_split, a.Hkv, B), dim3(256), 0, stream, a);
     prof.end();
