@@ -36,6 +36,7 @@ struct SimArgs {
     int32_t *order;         // [B, n]   other tokens by (assignment, index), then the dominant ones
     int32_t *owner;         // [B, n]   assignment of order[s]
     int B, N, img_begin, n, n_keep, r, n_planes;
+    int size_plane;         // the weighted plane whose means also write size_out; -1: none
     int run;                // consecutive tiles of the similarity product an XCD takes at a time
 };
 
@@ -318,11 +319,12 @@ __device__ __forceinline__ void store_mean(char *dst, const Acc<DT, UB> &acc, fl
     }
 }
 
-// Units unit0, unit0 + 256, ... of one plane's row of dominant position i (token ji), NU at a time.  `members` holds the
+// One plane's row of dominant position i (token ji), 256 NU units a turn, thread t taking units t, t + 256, ... of it; the
+// workgroups of a cluster (gridDim.z) take the turns of all planes in rotation, and this one lets `wait` of them pass.  `members` holds the
 // cluster's first 64 other tokens, one per lane; up to four of their rows are in flight together.
-template <int DT, int UB, int NU>
+template <int DT, int UB, int NU, bool SHARED>
 __device__ __forceinline__ void merge_plane(const SimArgs &a, const PlaneDev &p, int b, int i, int ji, int lo, int n_mem,
-                                            int members) {
+                                            int members, int &wait) {
     using U = typename Unit<UB>::type;
     const int units = p.row_bytes / UB;
     const char *img0 = p.src + (long long)b * p.src_stride_b + (long long)a.img_begin * p.row_bytes;
@@ -330,7 +332,16 @@ __device__ __forceinline__ void merge_plane(const SimArgs &a, const PlaneDev &p,
     const bool weighted = p.rule == LVLM_RULE_WEIGHTED && DT != LVLM_I32;
     const float *size = a.size_in ? a.size_in + (long long)b * a.n : nullptr;
     // whole waves in and out of the loop: lanes without a unit still hand out member indices
-    for (int w0 = threadIdx.x & ~63; w0 < units; w0 += 256 * NU) {
+    for (int t0 = 0; t0 < units; t0 += 256 * NU) {
+        if constexpr (SHARED) {
+            if (wait > 0) {
+                --wait;
+                continue;
+            }
+            wait = gridDim.z - 1;
+        }
+        const int w0 = t0 + (threadIdx.x & ~63);
+        if (w0 >= units) continue;
         const int u0 = w0 + (threadIdx.x & 63);
         int off[NU];                            // byte offset of the unit in a row (a repeat past the end, not stored)
 #pragma unroll
@@ -376,6 +387,7 @@ __device__ __forceinline__ void merge_plane(const SimArgs &a, const PlaneDev &p,
 #pragma unroll
             for (int x = 0; x < NU; ++x)
                 if (u0 + 256 * x < units) store_mean<DT, UB>(dst0 + off[x], acc[x], 1.0f / tot);
+            if (u0 == 0 && &p == &a.plane[0] + a.size_plane) a.size_out[(long long)b * a.n_keep + i] = tot;
         }
     }
 }
@@ -409,18 +421,24 @@ __device__ __forceinline__ void copy_row(const SimArgs &a, int b, int from, int 
     }
 }
 
+// (1792 tokens -> n_keep, eight planes of 4096 and seven times 1024 channels; all of a cluster in one workgroup -> shared: 1 cluster
+// 2964 -> 430 us, 8 clusters 464 -> 103, 64 clusters 123 -> 65 us)
+constexpr int kSimMergeWgs = 512;
+
 // nothing removed: every row stays where it is
 __global__ __launch_bounds__(256) void sim_copy_kernel(SimArgs a) { copy_row(a, blockIdx.y, blockIdx.x, blockIdx.x); }
 
-// One workgroup per dominant position, every plane and column in it; workgroups past them copy the rows outside the
-// image span.  The tokens assigned to position i form the
+// One workgroup per dominant position, every plane and column in it, or (SHARED) gridDim.z of them; workgroups past
+// them copy the rows outside the image span.  The tokens assigned to position i form the
 // segment [lo, lo + n) of the sorted order; its two ends are found by all waves at once, 64 probes of the owners a
 // round (two rounds up to 4096 other tokens, three up to 262144) instead of one thread's bisection, whose chain of some
 // 20 pairs of dependent loads per workgroup was the time of the kernel.  Bound by memory: 8 x 1263 clusters of 4096 bf16
 // channels (213 MB) 72 -> 33 us.
+template <bool SHARED>
 __global__ __launch_bounds__(256) void sim_merge_kernel(SimArgs a) {
     const int i = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63;
     if (i >= a.n_keep) {
+        if (SHARED && blockIdx.z) return;
         const int o = i - a.n_keep;                  // o-th row outside the image span
         copy_row(a, b, o < a.img_begin ? o : o + a.n, o < a.img_begin ? o : o + a.n_keep);
         return;
@@ -444,22 +462,24 @@ __global__ __launch_bounds__(256) void sim_merge_kernel(SimArgs a) {
     }
     const int n_mem = hi - lo;
     const int members = order[min(lo + lane, a.n - 1)];
-    if (a.size_out && threadIdx.x < 64) {      // (here, not with the means: every plane may be one whose rows are only kept)
+    // sizes the means do not write: those of all-ones clusters, and those of a call whose planes are all only kept
+    if (a.size_out && a.size_plane < 0 && (!SHARED || blockIdx.z == 0) && threadIdx.x < 64) {
         const float tot = a.size_in ? cluster_size(a, b, ji, lo, n_mem, members) : (float)(1 + n_mem);
         if (lane == 0) a.size_out[(long long)b * a.n_keep + i] = tot;
     }
+    int wait = blockIdx.z;
     for (int pi = 0; pi < a.n_planes; ++pi) {
         const PlaneDev &p = a.plane[pi];
         if (p.dtype == LVLM_BF16) {
-            if (p.unit_bytes == 16) merge_plane<LVLM_BF16, 16, 2>(a, p, b, i, ji, lo, n_mem, members);
-            else if (p.unit_bytes == 4) merge_plane<LVLM_BF16, 4, 1>(a, p, b, i, ji, lo, n_mem, members);
-            else merge_plane<LVLM_BF16, 2, 1>(a, p, b, i, ji, lo, n_mem, members);
+            if (p.unit_bytes == 16) merge_plane<LVLM_BF16, 16, 2, SHARED>(a, p, b, i, ji, lo, n_mem, members, wait);
+            else if (p.unit_bytes == 4) merge_plane<LVLM_BF16, 4, 1, SHARED>(a, p, b, i, ji, lo, n_mem, members, wait);
+            else merge_plane<LVLM_BF16, 2, 1, SHARED>(a, p, b, i, ji, lo, n_mem, members, wait);
         } else if (p.dtype == LVLM_F32) {
-            if (p.unit_bytes == 16) merge_plane<LVLM_F32, 16, 2>(a, p, b, i, ji, lo, n_mem, members);
-            else merge_plane<LVLM_F32, 4, 1>(a, p, b, i, ji, lo, n_mem, members);
+            if (p.unit_bytes == 16) merge_plane<LVLM_F32, 16, 2, SHARED>(a, p, b, i, ji, lo, n_mem, members, wait);
+            else merge_plane<LVLM_F32, 4, 1, SHARED>(a, p, b, i, ji, lo, n_mem, members, wait);
         } else {
-            if (p.unit_bytes == 16) merge_plane<LVLM_I32, 16, 1>(a, p, b, i, ji, lo, n_mem, members);
-            else merge_plane<LVLM_I32, 4, 1>(a, p, b, i, ji, lo, n_mem, members);
+            if (p.unit_bytes == 16) merge_plane<LVLM_I32, 16, 1, SHARED>(a, p, b, i, ji, lo, n_mem, members, wait);
+            else merge_plane<LVLM_I32, 4, 1, SHARED>(a, p, b, i, ji, lo, n_mem, members, wait);
         }
     }
 }
@@ -520,6 +540,9 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     a.owner = reinterpret_cast<int32_t *>(ws + w.owner);
     a.B = d.B; a.N = d.N; a.img_begin = d.img_begin; a.n = d.n_img; a.n_keep = d.n_keep; a.r = r;
     a.n_planes = d.n_planes;
+    a.size_plane = -1;
+    for (int i = d.n_planes - 1; i >= 0 && size_in && size_out; --i)
+        if (a.plane[i].rule == LVLM_RULE_WEIGHTED && a.plane[i].dtype != LVLM_I32) a.size_plane = i;
 
     if (r == 0) {
         a.keep_idx = keep_idx;
@@ -568,7 +591,20 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     launch_owner_order(prof, oj, reinterpret_cast<int32_t *>(ws + w.rank2), d.n_img, d.B, ws + w.sorted);
     prof.end();
     prof.begin("sim_merge");
-    LVLM_LAUNCH(prof, sim_merge_kernel, dim3(d.n_keep + d.N - d.n_img, d.B), dim3(256), 0, stream, a);
+    // Few clusters are large ones, and a workgroup's time is its chain of members, once per turn (plane, 512 units of it): the turns
+    // go to workgroups of their own until kSimMergeWgs of them walk a chain.
+    long long turns = 0;
+    for (int i = 0; i < d.n_planes; ++i) {
+        const PlaneDev &p = a.plane[i];
+        const int units = p.row_bytes / p.unit_bytes, per_turn = 256 * (p.unit_bytes == 16 && p.dtype != LVLM_I32 ? 2 : 1);
+        turns += (units + per_turn - 1) / per_turn;
+    }
+    const long long clusters = (long long)d.n_keep * d.B;
+    long long share = kSimMergeWgs / clusters;
+    share = share < 1 ? 1 : (share > turns ? turns : share);
+    const dim3 mgrid(d.n_keep + d.N - d.n_img, d.B, (unsigned)share);
+    if (share > 1) LVLM_LAUNCH(prof, sim_merge_kernel<true>, mgrid, dim3(256), 0, stream, a);
+    else LVLM_LAUNCH(prof, sim_merge_kernel<false>, mgrid, dim3(256), 0, stream, a);
     prof.end();
     return hipGetLastError();
 }

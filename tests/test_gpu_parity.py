@@ -1061,7 +1061,8 @@ def test_degenerate_sizes(ctx):
 # --------------------------------------------------------------------------- step 3b: similarity merge
 def _similar_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed, clusters=0, with_size=True, extra=True,
                   identical=False):
-    """GPU dominant set must equal the oracle's; each GPU assignment must be an arg-max of the oracle's
+    """extra: two more planes, or the widths of more weighted planes.
+    GPU dominant set must equal the oracle's; each GPU assignment must be an arg-max of the oracle's
     fp64 cosines up to 1e-5 (exactly the oracle's choice wherever its margin is larger than that); merged
     values are checked against the oracle's merge under the GPU's assignment."""
     N = n_sys + n_img + n_txt
@@ -1078,7 +1079,10 @@ def _similar_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed, clusters=
     score = torch.rand(B, n_img, generator=g)
     size = torch.randint(1, 4, (B, n_img), generator=g).float() if with_size else None
     planes, rules, dts = [hid], [lv.RULE_WEIGHTED], ["bf16" if dtype == torch.bfloat16 else "f32"]
-    if extra:
+    if isinstance(extra, tuple):
+        planes += [_rand((B, N, x), dtype, seed + x) for x in extra]
+        rules, dts = rules * len(planes), dts * len(planes)
+    elif extra:
         planes += [_rand((B, N, 24), dtype, seed + 1), torch.arange(B * N, dtype=torch.int32).view(B, N, 1)]
         rules += [lv.RULE_WEIGHTED, lv.RULE_TOP]
         dts += [dts[0], "f32"]
@@ -1124,6 +1128,17 @@ def test_merge_similar(ctx):
     _similar_case(ctx, torch.bfloat16, 1, 1, 500, 1, 128, 130, 106, identical=True)              # all ties
     _similar_case(ctx, torch.bfloat16, 1, 2, 150, 2, 72, 40, 107, clusters=4)                    # 144-byte rows: partial slice
     _similar_case(ctx, torch.bfloat16, 1, 2, 4500, 2, 64, 1200, 108, clusters=16)               # ranks by sorted blocks
+
+
+@pytest.mark.parametrize("dtype,B,n_img,n_keep,C,widths", [
+    (torch.bfloat16, 1, 300, 1, 4104, (6, 7, 520)),          # one cluster: a workgroup for every turn of 512 units (or 256 of 4 bytes)
+    (torch.bfloat16, 2, 300, 3, 64, (4096, 4104, 1030, 9)),
+    (torch.float32, 1, 200, 2, 2052, (3, 1025, 8, 8, 8, 8, 8)),
+    (torch.bfloat16, 1, 500, 171, 64, (64, 8200)),           # two workgroups a cluster for four turns
+    (torch.bfloat16, 1, 600, 256, 4104, (24,)),              # the last count of clusters that are shared, and one more
+    (torch.bfloat16, 1, 600, 257, 4104, (24,))])
+def test_merge_similar_planes_shared_between_workgroups(ctx, dtype, B, n_img, n_keep, C, widths):
+    _similar_case(ctx, dtype, B, 2, n_img, 3, C, n_keep, 900 + n_img + n_keep, clusters=3, extra=widths)
 
 
 @pytest.mark.parametrize("n_img,n_keep,clusters", [(200, 60, 5), (700, 2, 2), (40, 39, 0)])
