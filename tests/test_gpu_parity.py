@@ -1141,6 +1141,18 @@ def test_merge_similar_planes_shared_between_workgroups(ctx, dtype, B, n_img, n_
     _similar_case(ctx, dtype, B, 2, n_img, 3, C, n_keep, 900 + n_img + n_keep, clusters=3, extra=widths)
 
 
+@pytest.mark.parametrize("dtype,B,n_img,n_keep,C", [
+    (torch.bfloat16, 1, 4400, 2200, 256),     # 324 tiles, four whole slices of 128 bytes
+    (torch.bfloat16, 1, 4400, 2200, 200),     # ... and the fourth partial
+    (torch.bfloat16, 8, 1792, 1263, 328),     # 400 tiles over eight sequences, six slices, the last partial
+    (torch.bfloat16, 4, 2000, 1000, 192),     # 256 tiles: the last count of the form with four slots
+    (torch.float32, 1, 4400, 2200, 72),       # fp32, three slices, the last partial
+    (torch.float32, 1, 4400, 2200, 96)])      # fp32, three whole slices
+def test_merge_similar_products_of_several_slices(ctx, dtype, B, n_img, n_keep, C):
+    """More tiles than compute units: two slots and two workgroups a unit, whose slots are refilled and read again here."""
+    _similar_case(ctx, dtype, B, 1, n_img, 2, C, n_keep, 800 + C, clusters=0, extra=False)
+
+
 @pytest.mark.parametrize("n_img,n_keep,clusters", [(200, 60, 5), (700, 2, 2), (40, 39, 0)])
 def test_merge_similar_sizes_of_planes_that_are_only_kept(ctx, n_img, n_keep, clusters):
     """Cluster sizes are an output of their own: planes whose rows are all kept (no weighted plane) change nothing about
