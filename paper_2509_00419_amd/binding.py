@@ -10,6 +10,7 @@ no fallback: if a shared library is missing the import fails.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional
 
@@ -18,6 +19,7 @@ import torch
 HERE = os.path.dirname(os.path.abspath(__file__))
 # the in-tree build, or another build of the same sources named by LVLM_LIBRARY (e.g. one with a sanitized host side)
 LIB_PATH = os.environ.get("LVLM_LIBRARY") or os.path.join(HERE, "liblvlm.so")
+TORCH_BINDING_PATH = os.environ.get("LVLM_TORCH_BINDING")       # ... and of the extension module beside it
 
 # ---- enums (include/lvlm.h) ----
 BF16, F32, I32 = 0, 1, 2
@@ -142,7 +144,12 @@ lib = _load()
 
 def _load_calls():
     try:
-        from . import _torch_binding
+        if TORCH_BINDING_PATH:
+            spec = importlib.util.spec_from_file_location(__package__ + "._torch_binding", TORCH_BINDING_PATH)
+            _torch_binding = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(_torch_binding)
+        else:
+            from . import _torch_binding
     except ImportError as e:
         raise ImportError("the native side of the binding is missing or does not fit this torch: run "
                           f"`python -c 'import __graft_entry__ as g; g.build()'` ({e})") from e

@@ -21,15 +21,15 @@ FLAGS = [
 ]
 
 
-def binding_command() -> list:
+def binding_command(out: str = BINDING_PATH, flags: tuple = ("-O2",)) -> list:
     """The command that builds the native side of binding.py (host code only: torch tensors to the C ABI)."""
     torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
     rocm = os.path.dirname(os.path.dirname(HIPCC))
-    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+    return [os.environ.get("CXX", "g++"), *flags, "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
             "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",          # what the HIP and torch headers ask of a host compiler
             "-I" + os.path.join(torch_dir, "include"), "-I" + os.path.join(torch_dir, "include/torch/csrc/api/include"),
             "-I" + os.path.join(rocm, "include"), "-I" + sysconfig.get_paths()["include"],
-            os.path.join(CSRC, "torch_binding.cpp"), "-o", BINDING_PATH, "-L" + os.path.join(torch_dir, "lib"),
+            os.path.join(CSRC, "torch_binding.cpp"), "-o", out, "-L" + os.path.join(torch_dir, "lib"),
             "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 
@@ -68,10 +68,10 @@ def build_library(verbose: bool = True) -> str:
     return LIB_PATH
 
 
-def build_host_sanitized(out_dir: str) -> str:
+def build_host_sanitized(out_dir: str) -> tuple:
     """The same sources with the HOST side under the undefined-behaviour sanitizer in trap mode (no runtime library:
     undefined behaviour in the library's host code ends the process with an illegal-instruction signal).  The device
-    code is compiled as always, at -O1.  Returns the path of the library written into out_dir."""
+    code is compiled as always, at -O1.  Returns the paths of the library and of the torch binding written into out_dir."""
     os.makedirs(out_dir, exist_ok=True)
     flags = [f for f in FLAGS if f != "-O3"] + ["-O1", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host",
                                                 "-fsanitize-trap=undefined"]
@@ -81,13 +81,16 @@ def build_host_sanitized(out_dir: str) -> str:
         procs.append((src, subprocess.Popen([HIPCC, *flags, "-c", os.path.join(CSRC, src), "-o", obj],
                                             stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    binding = os.path.join(out_dir, "_torch_binding.so")
+    cmd = binding_command(binding, ("-O1", "-fsanitize=undefined", "-fno-sanitize=vptr", "-fsanitize-undefined-trap-on-error"))
+    procs.append(("torch_binding.cpp", subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+            raise RuntimeError(f"the compiler failed on {src}:\n{out}")
     lib = os.path.join(out_dir, "liblvlm_ubsan.so")
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs], check=True)
-    return lib
+    return lib, binding
 
 
 if __name__ == "__main__":
