@@ -120,6 +120,7 @@ def test_score_tokens_keys_in_runs(ctx, B, T, Hq, Hkv, n_sys, n_img):
     (torch.bfloat16, 3, 64, 28, 4, 128, 0, 4032, True, None),       # the longest: 4096 keys, two turns of workgroups
     (torch.bfloat16, 1, 9, 4, 2, 64, 3, 200, True, 0.0)])           # all logits equal (the other kernels' case)
 def test_score_tokens_few_query_rows(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img, causal, scale):
+    # (few rows over lengths at the edges of tiles and waves, whichever kernel takes them: the rule has a test of its own)
     N = n_sys + n_img + T
     q, k = _rand((B, T, Hq, d), dtype, 21), _rand((B, N, Hkv, d), dtype, 22)
     kw = dict(q_pos0=n_sys + n_img, img_begin=n_sys, n_img=n_img, causal=causal, scale=scale)
@@ -196,9 +197,9 @@ def test_score_fold_forms(ctx, Hkv, rows, n_img, B):
 
 
 @pytest.mark.parametrize("B,T,Hq,Hkv,n_img", [
-    (32, 5, 5, 5, 1024),          # 512 workgroups of the fold: the last shape with the parts spread over threads
-    (27, 5, 5, 5, 1217),          # 540: a thread per column, one head beyond four, a last workgroup of 193 columns
-    (40, 90, 21, 3, 849)])        # 560, 20 parts: a second round of loads
+    (32, 5, 5, 5, 1024),          # a thread per column, one part of five heads, whole workgroups of columns
+    (27, 5, 5, 5, 1217),          # ... a last workgroup of 193 columns
+    (40, 90, 21, 3, 849)])        # 20 parts: a second round of loads
 def test_score_fold_of_many_columns(ctx, B, T, Hq, Hkv, n_img):
     q, k = _rand((B, T, Hq, 64), torch.bfloat16, 41), _rand((B, n_img + T, Hkv, 64), torch.bfloat16, 42)
     kw = dict(q_pos0=n_img, img_begin=0, n_img=n_img)
