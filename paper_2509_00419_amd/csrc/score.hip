@@ -822,10 +822,13 @@ __global__ __launch_bounds__(64 * kRowsWaves) void score_rows_kernel(ScoreArgs a
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
-    // all chunks of one (batch, KV head) pair on one XCD (ids with the same remainder modulo 8)
-    const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-    const int pair = (seq / a.rs) * 8 + xcd, c = seq % a.rs;
-    if (pair >= a.B * a.Hkv) return;
+    // (batch, KV head, chunk) triples in memory order, an eighth of them to every XCD (ids with the same remainder modulo 8): the
+    // chunks of a pair mostly share an L2, and no XCD gets more than another whatever the heads (with all chunks of a pair on one
+    // XCD: one head of 37 chunks x 2632 keys 26.9 us, 18 heads of 13 x 242 keys 13.1; evenly 15.6 and 9.3)
+    const int total = a.B * a.Hkv * a.rs, per_xcd = (total + 7) >> 3;
+    const int item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (item >= total) return;
+    const int pair = item / a.rs, c = item % a.rs;
     const int b = pair / a.Hkv, g = pair % a.Hkv;
     const int GT = a.G * a.T;
     const long long rowbase = ((long long)b * a.Hq + (long long)g * a.G) * a.T;
@@ -1240,7 +1243,7 @@ void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool sin
         const int n_t = ((need_lse ? a.N : a.n_img) + 16 * kRowsWaves - 1) / (16 * kRowsWaves);      // tiles per wave
         ScoreArgs r = a;
         r.rs = rows;
-        const dim3 grid((a.B * a.Hkv + 7) / 8 * 8 * rows), wg(64 * kRowsWaves);
+        const dim3 grid((a.B * a.Hkv * rows + 7) / 8 * 8), wg(64 * kRowsWaves);
         prof.begin("score_single");
         if constexpr (can_rows) {
             if (n_t <= 4) LVLM_LAUNCH(prof, (score_rows_kernel<DT, HD, 4>), grid, wg, 0, stream, r);
@@ -1357,44 +1360,37 @@ hipError_t launch_score_probs(const Prof &prof, const lvlm_probs_desc &d, const 
 // Few query rows (score_rows_kernel): 16 of them per workgroup, the logits over all keys in registers.  Returns the chunks of
 // a KV head, or 0 where the form chosen without it (`w`) is the faster one.  Its time is one chain: start-up, the keys
 // at 1.6 us per 1000 of 128 bytes and 3.4 us of 256 bytes in bf16, 6 us in fp32, and a fold of one part per chunk; the other forms
-// read the keys twice but share the work over more workgroups.  The lines below are from some 900 shapes timed both ways
-// (4 to 768 workgroups, 85 to 4096 keys, heads of 64 and 128 channels), and 240 more of 22 to 130 chunks a KV head.  All chunks of
-// a head run on one XCD, so with few heads the chunks beyond its 32 compute units wait, and their parts lengthen the fold.
+// read the keys twice but share the work over more workgroups.  The lines below are from 800 shapes timed both ways (1 to 768
+// workgroups, 1 to 130 chunks a head, 65 to 4096 keys, heads of 64 and 128 channels): the rule is 0.4 % from the faster
+// form on average and no shape taken loses more than 5 % (other form -> this one in what follows).
 static int few_rows(const lvlm_score_desc &d, const ScoreWs &w, int n_chunks, bool given) {
     const bool bf16 = d.dtype == LVLM_BF16;
-    const int es = bf16 ? 2 : 4;
+    const int row_bytes = d.hd * (bf16 ? 2 : 4);
     const long long heads = (long long)d.B * d.Hkv;
     const int n16 = (d.Hq / d.Hkv * d.T + 15) / 16;
     const long long wgs = heads * n16;
-    if (w.shared_tiles || (!bf16 && d.hd == 128) || d.N > 16 * kRowsWaves * 32 || !(d.scale > 0.f) || d.k_stride_n * es >= (1ll << 26))
+    if (w.shared_tiles || (!bf16 && d.hd == 128) || d.N > 16 * kRowsWaves * 32 || !(d.scale > 0.f) ||
+        d.k_stride_n * (bf16 ? 2 : 4) >= (1ll << 26))
         return 0;
     if (w.single) {
-        // Against one chunk of 32 rows per workgroup, its keys over the waves: one turn of the chip, and keys enough to pay for
-        // eight waves and twice the parts -- in 256-byte rows 72, 7 more per chunk, and more than one tile a wave (28 heads x
-        // 64 rows: 7.2 -> 7.0 us at 212 keys, 15.0 -> 11.1 at 700; 8 heads of one row 6.8 -> 7.3 us at 85 keys).  With the
-        // normalisers given the other form reads the keys once as well: 280, 10 more per chunk (8 heads x 24 rows 6.9 -> 7.7 us
-        // at 108 keys, 12.2 -> 11.0 at 1044).  Chunks: 40 (of 5 heads 42 cost 16.9 -> 17.8 us at 818 keys, 40 still 18.85
-        // -> 18.6), with the normalisers given 32, a compute unit each (30: 15.1 -> 12.8 us, 42: 12.1 -> 16.0, 48 in fp32 15.7 -> 19.6).
-        const long long sweep_rows = (long long)d.N * (d.hd * es) / 256;
-        if (wgs > 256 || n16 > (given ? 32 : 40)) return 0;
-        return (given ? sweep_rows > 280 + 10 * n16 : d.N > 16 * kRowsWaves && sweep_rows > 72 + 7 * n16) ? n16 : 0;
+        // Against one chunk of 32 rows per workgroup: one turn of the chip, and in bf16 keys enough to pay for eight waves and twice
+        // the parts, 27 KB of them (3 heads of 13 chunks, 64 channels, 6.9 -> 7.7 us at 187 keys; 28 heads x 64 rows 15.0 -> 11.1
+        // at 700).  fp32 always (8 heads of one row 9.2 -> 8.6 us at 86 keys).  With the normalisers given the other form reads
+        // the image keys once as well: 82 KB of them, 33 KB in fp32 (12 heads of 12 chunks, 64 channels, 7.0 -> 7.9 us at 202 keys, 8
+        // heads x 96 rows, 128 channels, 12.0 -> 10.0 at 931; fp32 8 heads x 32 rows 13.9 -> 11.7 at 611).
+        if (wgs > 256) return 0;
+        if (given) return (long long)d.n_img * row_bytes > 256 * (bf16 ? 320 : 130) ? n16 : 0;
+        return !bf16 || (long long)d.N * row_bytes > 256 * 105 ? n16 : 0;
     }
     // Against the two-pass kernels, whose three launches and fold cost 15 us whatever the shape and then split the keys over the
     // chip; with the normalisers given they are a single short pass.
     if (given || wgs > 768) return 0;
     // one query row per KV head: they take 28 us and more for 4000 keys
     if (d.T == 1 && n_chunks == 1) return n16;
-    // fp32: 4.75 us per 1000 keys behind by itself, ahead again as heads and workgroups fill the chip (4 heads x 24
-    // rows 15.5 -> 15.2 us at 1444 keys, 17.0 -> 29.5 at 3944; 192 heads of 24 rows 74 -> 39 us at 2048).  More than two chunks a
-    // compute unit of the few XCDs that have a head fill nothing (4 heads: 97 chunks 36 -> 43 us at 954 keys, 75 chunks 56 ->
-    // 65 us at 2729, but 106 chunks 36 -> 32 us at 487; 5 heads of 89 chunks 46 -> 37 us at 1009)
-    if (!bf16 && heads <= 4 && n16 > 64 && d.N > 650) return 0;
-    if (!bf16) return d.N * (4.75 - 0.078 * (double)heads - 0.014 * (double)wgs) < 5250.0 ? n16 : 0;
-    // bf16: the parts of many chunks cost more than the second sweep (28 heads x 128 rows, 56 chunks a KV head, 24.3 -> 29.6 us at
-    // 3048 keys, 2 heads of 48 chunks 18.1 -> 21.5 us at 1463, but two such sequences 35 -> 29 us), and beyond 3500 keys the chain shows unless the launch fills a turn, or
-    // several short of work (8 heads x 8 rows 17.8 -> 18.8 us at 3928 keys, 64 of them 40 -> 27 us).
-    if (n16 > (heads >= 8 ? 64 : 40)) return 0;
-    return d.N <= 3500 || (wgs >= 96 && (wgs <= 256 || n16 * 128 <= 4 * d.hd)) ? n16 : 0;
+    // the chain of a few workgroups over long sequences (2 heads of 4 chunks, 128 channels, 17.5 -> 18.4 us at 3980 keys, 23 heads of
+    // one 39 -> 27; fp32 one head 17.4 -> 22.8 us at 2709 keys, 14 chunks of 6 heads 31.8 -> 26.0 at 2936)
+    if (bf16) return d.hd == 64 || d.N <= 3500 || wgs >= 16 ? n16 : 0;
+    return d.N <= 2050 || heads >= 8 || wgs >= 64 ? n16 : 0;
 }
 
 ScoreWs score_ws(const lvlm_score_desc &d) {

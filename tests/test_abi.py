@@ -117,22 +117,21 @@ def test_score_few_rows_rule():
                          N * Hkv * hd, stride or Hkv * hd, hd)
         return ctx.score_few_rows(d, given)
 
+    f32 = dict(hd=64, dtype=bd.F32)
     assert chunks(1, 2176, 64, 28, 4) == 28 and chunks(1, 845, 64, 28, 4) == 28
     assert chunks(1, 845, 64, 28, 4, given=True) == 28 and chunks(1, 2176, 64, 28, 4, given=True) == 0
-    assert chunks(1, 128, 1, 8, 8) == 0 and chunks(1, 129, 1, 8, 8) == 1              # a tile per wave is too short
+    assert chunks(1, 105, 1, 8, 8) == 0 and chunks(1, 106, 1, 8, 8) == 1              # bf16: keys enough for eight waves
+    assert chunks(1, 210, 1, 8, 8, hd=64) == 0 and chunks(1, 211, 1, 8, 8, hd=64) == 1 and chunks(1, 70, 1, 8, 8, **f32) == 1
+    assert chunks(1, 384, 64, 8, 1, given=True) == 0 and chunks(1, 385, 64, 8, 1, given=True) == 32      # image keys alone
+    assert chunks(1, 194, 64, 8, 1, given=True, **f32) == 0 and chunks(1, 195, 64, 8, 1, given=True, **f32) == 32
+    assert chunks(4, 240, 32, 32, 8) == 8 and chunks(4, 240, 33, 32, 8) == 0          # one turn against the short form
     assert chunks(1, 4096, 1, 8, 8) == 1 and chunks(1, 4097, 1, 8, 8) == 0            # the registers hold 4096 keys
-    assert chunks(1, 3000, 91, 28, 4) == 40 and chunks(1, 3000, 92, 28, 4) == 0       # too many parts for four heads
-    assert chunks(1, 880, 80, 8, 1) == 40 and chunks(1, 880, 81, 8, 1) == 0            # ... against the short form
-    assert chunks(1, 1000, 64, 8, 1, given=True) == 32 and chunks(1, 1000, 65, 8, 1, given=True) == 0
-    f32 = dict(hd=64, dtype=bd.F32)
-    assert chunks(1, 1500, 256, 16, 4, **f32) == 64 and chunks(1, 1500, 257, 16, 4, **f32) == 0
-    assert chunks(1, 650, 400, 16, 4, **f32) == 100 and chunks(1, 651, 400, 16, 4, **f32) == 0
-    assert chunks(1, 1000, 320, 20, 5, **f32) == 80
-    assert chunks(2, 3000, 112, 28, 4) == 49
-    assert chunks(1, 3500, 8, 32, 8) == 2 and chunks(1, 3501, 8, 32, 8) == 0          # a long chain in a chip left idle
-    assert chunks(8, 4000, 8, 32, 8) == 2 and chunks(48, 4000, 8, 32, 8) == 2 and chunks(49, 4000, 8, 32, 8) == 0
-    assert chunks(1, 1100, 24, 4, 4, hd=64, dtype=bd.F32) == 2 and chunks(1, 2000, 24, 4, 4, hd=64, dtype=bd.F32) == 0
-    assert chunks(48, 2000, 24, 4, 4, hd=64, dtype=bd.F32) == 2 and chunks(1, 1100, 24, 4, 4, dtype=bd.F32) == 0
+    assert chunks(2, 3000, 384, 28, 4, hd=64) == 0 and chunks(1, 3000, 438, 28, 4, hd=64) == 192      # 768 workgroups, and more
+    assert chunks(1, 3500, 8, 32, 8) == 2 and chunks(1, 4000, 8, 32, 8) == 2          # 16 workgroups
+    assert chunks(1, 3500, 8, 28, 4) == 4 and chunks(1, 3501, 8, 12, 4) == 0 and chunks(1, 3501, 8, 12, 4, hd=64) == 2
+    assert chunks(1, 2050, 24, 4, 4, **f32) == 2 and chunks(1, 2051, 24, 4, 4, **f32) == 0 and chunks(2, 2051, 24, 4, 4, **f32) == 2
+    assert chunks(1, 2051, 256, 4, 4, **f32) == 16 and chunks(1, 2051, 240, 4, 4, **f32) == 0
+    assert chunks(1, 1100, 24, 4, 4, dtype=bd.F32) == 0                                # fp32 heads of 128 channels
     assert chunks(1, 845, 64, 28, 4, scale=0.0) == 0
     assert chunks(1, 845, 64, 28, 4, stride=(1 << 25) - 8) == 28 and chunks(1, 845, 64, 28, 4, stride=1 << 25) == 0
     assert chunks(64, 986, 96, 32, 8) == 0                                             # shared key tiles fill the chip

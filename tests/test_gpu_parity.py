@@ -135,17 +135,21 @@ def test_score_tokens_few_query_rows(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img,
 
 
 @pytest.mark.parametrize("dtype,B,T,Hq,Hkv,d,n_sys,n_img,given", [
-    (torch.bfloat16, 1, 1, 1, 1, 128, 0, 128, False),        # 129 keys: the first length, one wave with a second tile
+    (torch.bfloat16, 1, 1, 1, 1, 128, 0, 105, False),        # 106 keys: the first length, the last wave without a tile
+    (torch.bfloat16, 1, 1, 1, 1, 128, 0, 128, False),        # 129 keys: one wave with a second tile
+    (torch.float32, 2, 2, 3, 3, 64, 0, 14, False),           # fp32 at any length: one tile, seven waves without
     (torch.bfloat16, 1, 3, 5, 1, 128, 2, 507, False),        # 15 rows, exactly four tiles per wave
-    (torch.bfloat16, 2, 8, 6, 3, 64, 1, 200, False),         # 16 rows, heads of 64 channels
+    (torch.bfloat16, 2, 8, 6, 3, 64, 1, 202, False),         # 16 rows, heads of 64 channels
     (torch.float32, 1, 17, 4, 4, 64, 0, 496, False),         # 17 rows, one key more than four tiles per wave
     (torch.float32, 1, 24, 4, 4, 64, 7, 1000, False),        # fp32 in place of the two passes, at its longest for 8 workgroups
     (torch.float32, 4, 1, 4, 4, 64, 0, 4095, False),         # one row per head: up to 4096 keys
-    (torch.bfloat16, 1, 40, 16, 1, 128, 0, 700, False),      # 40 chunks, the most for few heads
-    (torch.float32, 1, 260, 16, 4, 64, 0, 390, False),       # 65 fp32 chunks of four heads: up to 650 keys
+    (torch.bfloat16, 1, 37, 16, 1, 128, 0, 700, False),      # one head of 37 chunks: five an XCD, the last two have one and none
+    (torch.bfloat16, 6, 68, 9, 3, 128, 1, 139, False),       # 18 heads of 13 chunks, 30 an XCD: heads split between XCDs
+    (torch.bfloat16, 1, 292, 28, 4, 64, 0, 1900, False),     # 512 workgroups of 128 chunks a head
+    (torch.float32, 1, 260, 16, 4, 64, 0, 790, False),       # 65 fp32 chunks of four heads
     (torch.bfloat16, 1, 32, 16, 1, 128, 3, 830, True),       # 32 chunks with the normalisers given
-    (torch.bfloat16, 1, 16, 4, 2, 128, 5, 310, True),        # normalisers given: the image keys alone, from key 5
-    (torch.float32, 1, 9, 8, 4, 64, 3, 400, True)])
+    (torch.bfloat16, 1, 16, 4, 2, 128, 5, 321, True),        # normalisers given: the image keys alone, from key 5
+    (torch.float32, 1, 9, 8, 4, 64, 3, 131, True)])
 def test_score_tokens_few_rows_rule(ctx, dtype, B, T, Hq, Hkv, d, n_sys, n_img, given):
     """Shapes at the edges of the rule that takes the kernel for few query rows: the library says it takes it, and the
     scores are the oracle's."""
