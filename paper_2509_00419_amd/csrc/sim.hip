@@ -36,7 +36,7 @@ struct SimArgs {
     int32_t *order;         // [B, n]   other tokens by (assignment, index), then the dominant ones
     int32_t *owner;         // [B, n]   assignment of order[s]
     int B, N, img_begin, n, n_keep, r, n_planes;
-    int size_plane;         // the weighted plane whose means also write size_out; -1: none
+    bool sizes_apart;       // sizes are given and no weighted plane's means would write size_out
     int run;                // consecutive tiles of the similarity product an XCD takes at a time
 };
 
@@ -387,7 +387,7 @@ __device__ __forceinline__ void merge_plane(const SimArgs &a, const PlaneDev &p,
 #pragma unroll
             for (int x = 0; x < NU; ++x)
                 if (u0 + 256 * x < units) store_mean<DT, UB>(dst0 + off[x], acc[x], 1.0f / tot);
-            if (u0 == 0 && &p == &a.plane[0] + a.size_plane) a.size_out[(long long)b * a.n_keep + i] = tot;
+            if (size && a.size_out && threadIdx.x == 0 && u0 == 0) a.size_out[(long long)b * a.n_keep + i] = tot;   // (every such plane the same)
         }
     }
 }
@@ -462,10 +462,14 @@ __global__ __launch_bounds__(256) void sim_merge_kernel(SimArgs a) {
     }
     const int n_mem = hi - lo;
     const int members = order[min(lo + lane, a.n - 1)];
-    // sizes the means do not write: those of all-ones clusters, and those of a call whose planes are all only kept
-    if (a.size_out && a.size_plane < 0 && (!SHARED || blockIdx.z == 0) && threadIdx.x < 64) {
-        const float tot = a.size_in ? cluster_size(a, b, ji, lo, n_mem, members) : (float)(1 + n_mem);
-        if (lane == 0) a.size_out[(long long)b * a.n_keep + i] = tot;
+    // sizes of all-ones clusters are written here (the weighted means write them when sizes are given)
+    if (threadIdx.x == 0 && a.size_out && a.size_in == nullptr) a.size_out[(long long)b * a.n_keep + i] = (float)(1 + n_mem);
+    if constexpr (SHARED) {
+        // (a call whose planes are all only kept takes this form: in the other the code alone cost 2 % of the launch)
+        if (a.sizes_apart && blockIdx.z == 0 && threadIdx.x < 64) {
+            const float tot = cluster_size(a, b, ji, lo, n_mem, members);
+            if (lane == 0) a.size_out[(long long)b * a.n_keep + i] = tot;
+        }
     }
     int wait = blockIdx.z;
     for (int pi = 0; pi < a.n_planes; ++pi) {
@@ -540,9 +544,9 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     a.owner = reinterpret_cast<int32_t *>(ws + w.owner);
     a.B = d.B; a.N = d.N; a.img_begin = d.img_begin; a.n = d.n_img; a.n_keep = d.n_keep; a.r = r;
     a.n_planes = d.n_planes;
-    a.size_plane = -1;
-    for (int i = d.n_planes - 1; i >= 0 && size_in && size_out; --i)
-        if (a.plane[i].rule == LVLM_RULE_WEIGHTED && a.plane[i].dtype != LVLM_I32) a.size_plane = i;
+    a.sizes_apart = size_in && size_out;
+    for (int i = 0; i < d.n_planes; ++i)
+        if (a.plane[i].rule == LVLM_RULE_WEIGHTED && a.plane[i].dtype != LVLM_I32) a.sizes_apart = false;
 
     if (r == 0) {
         a.keep_idx = keep_idx;
@@ -603,7 +607,7 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     long long share = kSimMergeWgs / clusters;
     share = share < 1 ? 1 : (share > turns ? turns : share);
     const dim3 mgrid(d.n_keep + d.N - d.n_img, d.B, (unsigned)share);
-    if (share > 1) LVLM_LAUNCH(prof, sim_merge_kernel<true>, mgrid, dim3(256), 0, stream, a);
+    if (share > 1 || a.sizes_apart) LVLM_LAUNCH(prof, sim_merge_kernel<true>, mgrid, dim3(256), 0, stream, a);
     else LVLM_LAUNCH(prof, sim_merge_kernel<false>, mgrid, dim3(256), 0, stream, a);
     prof.end();
     return hipGetLastError();
