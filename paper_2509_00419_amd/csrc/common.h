@@ -175,6 +175,17 @@ hipError_t attn_static_scratch(int device, char **ptr, size_t *bytes);
 // ---- device helpers ----
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
+// A load of something that passes through once and should not take up a cache.
+template <class T>
+__device__ __forceinline__ T load_once(const T *p) {
+    if constexpr (sizeof(T) == 16) {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const u4 *>(p)));
+    } else {
+        return __builtin_nontemporal_load(p);
+    }
+}
+
 // round-to-nearest-even; NaN stays NaN
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     uint32_t u = __float_as_uint(f);

@@ -28,7 +28,9 @@
 namespace lvlm {
 namespace {
 
+constexpr int kGatherRows = 8;     // rows per batch (all of a batch's loads are in flight together)
 constexpr int kGatherWgs = 1536;   // workgroups the gather launch aims for (six per compute unit)
+constexpr long long kGatherCached = 256ll << 20;       // bytes of source rows that the memory-side cache can hold
 
 
 constexpr int kRankTile = 8192;   // keys staged in LDS per step of the rank kernel (32 KB)
@@ -381,17 +383,17 @@ struct GatherArgs {
 // of a batch of RB rows are loaded unconditionally (indices clamped into range), so the loads of many
 // rows are in flight at once; then kept rows are stored and every row is multiplied by its weight (zero
 // unless it is merged) and accumulated.
-template <int DT, int UB>
-__device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev &p, int pi, int b) {
+template <int DT, int UB, int TEAMS, bool ONCE>
+__device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev &p, int pi, int b, float (*other)[256]) {
     using U = typename Unit<UB>::type;
-    constexpr int RB = 8;   // rows per batch (all of a batch's loads are in flight together)
+    constexpr int RB = kGatherRows;
     const int tid = threadIdx.x;
     const int tpr = 1 << p.tpr_log2;
-    const int group = tid >> p.tpr_log2;
-    const int groups = 256 >> p.tpr_log2;
-    const int sub = blockIdx.x * groups + group;
+    const int chunks = 256 >> p.tpr_log2;                 // of rows, per workgroup
+    const int team = tid >> 8;                            // a chunk's batches of rows go to the teams in turn
+    const int sub = blockIdx.x * chunks + ((tid & 255) >> p.tpr_log2);
     const int row_units = p.row_bytes / UB;
-    if (sub >= p.n_sub || (int)blockIdx.y >= p.col_blocks) return;
+    if ((int)blockIdx.x * chunks >= p.n_sub || (int)blockIdx.y >= p.col_blocks) return;      // uniform
     const int unit_raw = blockIdx.y * 256 + (tid & (tpr - 1));
     const bool active = unit_raw < row_units;
     const int unit = active ? unit_raw : row_units - 1;
@@ -399,12 +401,12 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
     const char *src = p.src + (long long)b * p.src_stride_b + (long long)unit * UB;
     char *dst = p.dst + (long long)b * p.dst_stride_b + (long long)unit * UB;
     const int n_lo = sub * a.rows_per_sub;
-    const int n_hi = min(a.N, n_lo + a.rows_per_sub);
+    const int n_hi = min(a.N, n_lo + a.rows_per_sub);     // (a chunk past the last one has no rows)
     if (a.dst_of == nullptr) {
         // nothing is removed (kernel-uniform case): plain row copy
         if (active) {
 #pragma unroll 4
-            for (int n = n_lo; n < n_hi; ++n)
+            for (int n = n_lo + team; n < n_hi; n += TEAMS)
                 *reinterpret_cast<U *>(dst + (long long)n * p.row_bytes) =
                     *reinterpret_cast<const U *>(src + (long long)n * p.row_bytes);
         }
@@ -419,7 +421,7 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
 #pragma unroll
     for (int i = 0; i < Acc<DT, UB>::NE; ++i) acc.v[i] = 0.f;
 
-    for (int n0 = n_lo; n0 < n_hi; n0 += RB) {
+    for (int n0 = n_lo + team * RB; n0 < n_hi; n0 += TEAMS * RB) {
         // all loads of the batch first (clamped row / token indices keep every address valid) ...
         U val[RB];
         int code[RB];
@@ -428,7 +430,8 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
         for (int x = 0; x < RB; ++x) {
             const int n = min(n0 + x, n_hi - 1);
             const int j = min(max(n - a.img_begin, 0), a.n_img - 1);
-            val[x] = *reinterpret_cast<const U *>(src + (long long)n * p.row_bytes);
+            const U *at = reinterpret_cast<const U *>(src + (long long)n * p.row_bytes);
+            val[x] = ONCE ? load_once(at) : *at;
             code[x] = dst_of[j];
             wk[x] = wgt[j];
         }
@@ -450,8 +453,19 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
         }
     }
     if constexpr (DT != LVLM_I32) {
-        if (weighted && active) {
-            constexpr int NE = Acc<DT, UB>::NE;
+        if (!weighted) return;                                       // uniform
+        constexpr int NE = Acc<DT, UB>::NE;
+        if constexpr (TEAMS > 1) {
+            if (team) {
+#pragma unroll
+                for (int i = 0; i < NE; ++i) other[i][tid & 255] = acc.v[i];
+            }
+            __syncthreads();
+            if (team) return;
+#pragma unroll
+            for (int i = 0; i < NE; ++i) acc.v[i] += other[i][tid];
+        }
+        if (active && sub < p.n_sub) {
             float *out = a.partial + (((long long)b * a.n_planes + pi) * a.n_sub_max + sub) * a.max_row_elems +
                          (long long)unit * NE;
 #pragma unroll
@@ -460,7 +474,18 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
     }
 }
 
-__global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
+// What bounds it: HBM.  A thread keeps the eight loads of a batch in flight and then waits for them, so the chip is kept
+// busy by the workgroups resident beside each other; a second team of 256 threads on the same chunk doubles them at the
+// same number of partial sums (half as many rows per chunk instead: 20 MB more of them to write and read).  One team -> two:
+// 16384 -> 5091 rows of 12 KB 53 -> 46 us (267 MB, 5.8 TB/s; the whole call 90.4 -> 83), 8 x 3000 -> 1000 rows of 12 KB in
+// three planes 119 -> 112, 2 x 10000 -> 5000 rows of 7 KB 79 -> 70; chunks too short for two batches keep one team (2048 ->
+// 1000 rows of 7 KB 22.9 -> 26.4 us with two).
+// ONCE: loads past the caches, for planes that outgrow the 256 MB cache in front of the memory: they would only push each
+// other out of it (305 MB: the call 112 -> 100 us; 353 MB: 150 -> 129); smaller ones may still lie there since they were
+// written (64 MB 39 -> 45 us, 203 MB 83 -> 85 with such loads).
+template <int TEAMS, bool ONCE>
+__global__ __launch_bounds__(256 * TEAMS) void gather_kernel(GatherArgs a) {
+    __shared__ float other[TEAMS > 1 ? 8 : 1][256];       // the second team's sums
     const int pi = blockIdx.z / a.B, b = blockIdx.z % a.B;
     // (selected by comparison: indexing the argument array with a run-time value would copy it to scratch)
     PlaneDev p = a.plane[0];
@@ -468,15 +493,15 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
     for (int i = 1; i < LVLM_MAX_PLANES; ++i)
         if (pi == i) p = a.plane[i];
     if (p.dtype == LVLM_BF16) {
-        if (p.unit_bytes == 16) gather_plane<LVLM_BF16, 16>(a, p, pi, b);
-        else if (p.unit_bytes == 4) gather_plane<LVLM_BF16, 4>(a, p, pi, b);
-        else gather_plane<LVLM_BF16, 2>(a, p, pi, b);
+        if (p.unit_bytes == 16) gather_plane<LVLM_BF16, 16, TEAMS, ONCE>(a, p, pi, b, other);
+        else if (p.unit_bytes == 4) gather_plane<LVLM_BF16, 4, TEAMS, ONCE>(a, p, pi, b, other);
+        else gather_plane<LVLM_BF16, 2, TEAMS, ONCE>(a, p, pi, b, other);
     } else if (p.dtype == LVLM_F32) {
-        if (p.unit_bytes == 16) gather_plane<LVLM_F32, 16>(a, p, pi, b);
-        else gather_plane<LVLM_F32, 4>(a, p, pi, b);
+        if (p.unit_bytes == 16) gather_plane<LVLM_F32, 16, TEAMS, ONCE>(a, p, pi, b, other);
+        else gather_plane<LVLM_F32, 4, TEAMS, ONCE>(a, p, pi, b, other);
     } else {
-        if (p.unit_bytes == 16) gather_plane<LVLM_I32, 16>(a, p, pi, b);
-        else gather_plane<LVLM_I32, 4>(a, p, pi, b);
+        if (p.unit_bytes == 16) gather_plane<LVLM_I32, 16, TEAMS, ONCE>(a, p, pi, b, other);
+        else gather_plane<LVLM_I32, 4, TEAMS, ONCE>(a, p, pi, b, other);
     }
 }
 
@@ -602,6 +627,7 @@ hipError_t launch_merge(const Prof &prof, const lvlm_merge_desc &d, const MergeW
 
     int grid_x = 1, grid_y = 1;
     bool any_weighted = false;
+    long long source_bytes = 0;
     for (int i = 0; i < d.n_planes; ++i) {
         PlaneDev &p = g.plane[i];
         p = make_plane_dev(planes[i]);
@@ -611,6 +637,7 @@ hipError_t launch_merge(const Prof &prof, const lvlm_merge_desc &d, const MergeW
         if (gx > grid_x) grid_x = gx;
         if (p.col_blocks > grid_y) grid_y = p.col_blocks;
         any_weighted |= p.rule == LVLM_RULE_WEIGHTED;
+        source_bytes += (long long)d.B * d.N * p.row_bytes;
     }
 
     if (r > 0) {
@@ -632,7 +659,10 @@ hipError_t launch_merge(const Prof &prof, const lvlm_merge_desc &d, const MergeW
         prof.end();
     }
     prof.begin("merge_gather");
-    LVLM_LAUNCH(prof, gather_kernel, dim3(grid_x, grid_y, d.B * d.n_planes), dim3(256), 0, stream, g);
+    const dim3 gather_grid(grid_x, grid_y, d.B * d.n_planes);
+    if (w.rows_per_chunk < 2 * kGatherRows) LVLM_LAUNCH(prof, (gather_kernel<1, false>), gather_grid, dim3(256), 0, stream, g);
+    else if (source_bytes <= kGatherCached) LVLM_LAUNCH(prof, (gather_kernel<2, false>), gather_grid, dim3(512), 0, stream, g);
+    else LVLM_LAUNCH(prof, (gather_kernel<2, true>), gather_grid, dim3(512), 0, stream, g);
     prof.end();
     if (r > 0 && any_weighted) {
         prof.begin("merge_finalize");

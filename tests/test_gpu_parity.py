@@ -351,6 +351,40 @@ def test_merge_compact_ragged_batch_and_tables(ctx):
     _merge_case(ctx, torch.bfloat16, 1, 3, 300, 4, 257, 120, w_mode=lv.MERGE_LINEAR_RAW, seed=4)  # odd row: 2-byte units
 
 
+@pytest.mark.parametrize("dtype,B,n_sys,n_img,n_txt,C,n_keep", [
+    (torch.bfloat16, 2, 2, 3067, 3, 64, 900),          # chunks of 16 rows, two batches: the first size with two teams
+    (torch.bfloat16, 2, 2, 3066, 3, 64, 900),          # ... and the last with one
+    (torch.float32, 3, 0, 2501, 0, 100, 1700),         # fp32, a last chunk of five rows
+    (torch.bfloat16, 2, 5, 3000, 7, 2056, 1),          # a second column block of one unit, everything merged
+    (torch.bfloat16, 2, 1, 3901, 0, 257, 3000),        # 2-byte units, chunks of 20 rows: the second team's batch is half full
+    (torch.bfloat16, 1, 3, 49500, 9, 16, 20000),       # chunks of 128 rows, two threads a row
+])
+def test_merge_compact_teams_of_a_chunk(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep):
+    """The gather at the edges of the rule that gives a chunk of rows to two teams of threads: copied rows bit-exact, the
+    merged row the sum over both teams' rows."""
+    _merge_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed=n_img)
+
+
+def test_merge_compact_planes_larger_than_the_memory_side_cache(ctx):
+    # more than 256 MiB of source rows are loaded past the caches; the reference runs on the GPU in 64 bits
+    B, n_img, C, n_keep = 2, 9000, 7680, 4000
+    g = torch.Generator(device=DEV).manual_seed(77)
+    hid = torch.randn(B, n_img, C, generator=g, device=DEV).to(torch.bfloat16)
+    pos = torch.arange(n_img, dtype=torch.int32, device=DEV).view(1, n_img, 1).repeat(B, 1, 1)
+    score = torch.rand(B, n_img, generator=g, device=DEV)
+    assert hid.numel() * 2 > 256 << 20
+    (out, opos), keep, merged = ctx.merge_compact([hid, pos], score, img_begin=0, n_img=n_img, n_keep=n_keep,
+                                                  rules=[lv.RULE_WEIGHTED, lv.RULE_TOP])
+    w = lv.merge_weights(lv.MERGE_LINEAR_RANK, n_img - n_keep + 1).double().to(DEV)
+    for b in range(B):
+        order = torch.argsort(score[b], descending=True, stable=True)
+        kept = order[:n_keep - 1].sort().values
+        assert torch.equal(keep[b].long(), kept) and torch.equal(merged[b].long(), order[n_keep - 1:])
+        assert torch.equal(out[b, :n_keep - 1], hid[b, kept]) and torch.equal(opos[b, :n_keep - 1], pos[b, kept])
+        ref = (w[:, None] * hid[b, order[n_keep - 1:]].double()).sum(0)
+        assert rel_err(out[b, n_keep - 1].cpu().double(), ref.cpu()) < TOL[torch.bfloat16]
+
+
 def test_merge_compact_ties_and_special_scores(ctx):
     n_img = 700
     _merge_case(ctx, torch.float32, 1, 2, n_img, 2, 64, 300, score=torch.full((1, n_img), 0.25), seed=5)
