@@ -89,7 +89,7 @@ __global__ __launch_bounds__(1024) void sim_index_kernel(SimArgs a) {
 }
 
 // ---- dot products dominant x others on the matrix cores, arg-max over the dominant axis ----
-// Workgroup tile: 128 dominant rows x 128 other rows, each wave 64 x 32 TC of it.  Rows are gathered by index; the
+// Workgroup tile: TM dominant rows x TN other rows, each wave 32 TR x 32 TC of it.  Rows are gathered by index; the
 // contraction runs over 128-byte slices of the rows, which go from memory straight into a ring of LDS buffers (the
 // direct loads need no staging registers and no LDS store instructions).  One wait and one barrier per slice: a
 // wave waits for its own share of slice k, the barrier makes that everybody's share and at the same time frees
@@ -100,11 +100,17 @@ __global__ __launch_bounds__(1024) void sim_index_kernel(SimArgs a) {
 // A direct load fills 1024 consecutive LDS bytes lane by lane, so rows cannot be padded apart; instead the
 // eight 16-byte units of row R lie in the order u ^ (R / 2 % 8), chosen by the address each lane reads from: the sixteen
 // lanes an LDS read serves at a time then hit sixteen different bank groups (no conflicts counted).
-// What bounds a workgroup is the time a slice takes to arrive, so there are two forms:
-//   up to 256 tiles (one per compute unit): a ring of four slices, eight waves, the loads of a slice spread over the
-//       products (a compute unit takes 16 cycles per direct load: all of a slice's at once hold the products up)
-//   more: a ring of two and four waves, so that two workgroups share a compute unit and cover each other's waits; the
-//       loads go out first
+// What bounds a workgroup is the time a slice takes to arrive, so there are three forms:
+//   up to 256 tiles of 128 x 128 (one per compute unit): a ring of four slices, eight waves, the loads of a slice spread
+//       over the products (a compute unit takes 16 cycles per direct load: all of a slice's at once hold the products up)
+//   more, but up to 256 tiles of 128 x 192 or 192 x 128: these, with a ring of three.  A unit then has one tile and a half to do
+//       instead of up to two, and takes in 320 rows for it instead of 512 (8 x 1263 x 529 of 4096 channels: 400 -> 240 tiles, 61 ->
+//       52 us, the whole call 133 -> 123; of 54 shapes of 260 to 400 tiles all gain, 3 % at 1024 channels to 13 % at 4096; from
+//       257 of the larger tiles on the second turn costs 20 to 30 %)
+//   more: 128 x 128, a ring of two and four waves, so that two workgroups share a compute unit and cover each other's waits;
+//       the loads go out first
+// (At 8 x 1263 x 529 of 4096 the loads alone take 38 us of the 52, the products alone 45, LDS reads and barriers alone 28; the
+// reads of a slice beside the products of the one before, and four waves of 64 x 96, gave nothing.)
 // (wider slices than 64 bytes: half a cache line each time fetched every line twice.  256 x 128 and 256 x 256 tiles, which
 // load less per product, leave the last turn of workgroups emptier and came out even or behind.)
 // Measured (staging through registers and LDS stores, with the 128- and 256-row tiles it had -> this): 300 x 276 tokens of
@@ -117,14 +123,14 @@ __global__ __launch_bounds__(1024) void sim_index_kernel(SimArgs a) {
 // sweep the contraction axis together: a row slice fetched into that XCD's L2 serves up to GM (dominant
 // rows) or GN (other rows) of them.  A run is an eighth of the tiles where that is what an XCD can hold at a time (64):
 // every XCD gets one stretch and fetches few rows that another one fetches too; else GN * GM.
-constexpr int kSimTile = 128, kSimGN = 8, kSimGM = 4;
+constexpr int kSimGN = 8, kSimGM = 4;
 
 __device__ __attribute__((aligned(16))) const uint32_t kSimZero[4] = {0, 0, 0, 0};     // what lies beyond the end of a row
 
-template <int DT, int NWM, int RING, bool RAGGED>
-__global__ __launch_bounds__(128 * NWM) void sim_gemm_kernel(SimArgs a) {
-    constexpr int NWN = 2, NW = NWN * NWM, NT = 64 * NW;
-    constexpr int TM = kSimTile, TN = kSimTile, TR = TM / NWN / 32, TC = TN / NWM / 32;
+template <int DT, int TM, int TN, int NWN, int NWM, int RING, bool RAGGED>
+__global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
+    constexpr int NW = NWN * NWM, NT = 64 * NW;
+    constexpr int TR = TM / NWN / 32, TC = TN / NWM / 32;
     constexpr int SB = 128;              // bytes of one slice of a row
     constexpr int UPS = SB / 16, RPL = 64 / UPS;     // 16-byte units of a row's slice, rows per direct load
     constexpr int SLOT = (TM + TN) * SB; // the dominant rows, then the others
@@ -161,8 +167,8 @@ __global__ __launch_bounds__(128 * NWM) void sim_gemm_kernel(SimArgs a) {
     // changes.  The offsets fit: the image rows of one batch row span less than 2 GiB (checked on the host).
     const char *img = p.src + (long long)b * p.src_stride_b + (long long)a.img_begin * p.row_bytes;
     auto place = [](int row) { return (row >> 1) & 7; };
-    static_assert(DPW % 2 == 0, "rows 8 x .. of a wave: bit 3 of a row's number is that of x");
-    auto unit_of = [&](int x) { return (lane % UPS) ^ place(RPL * x + lane / UPS); };
+    // (rows 8 (wave DPW + x) ..: the place depends on bit 3 of a row's number, so an even DPW leaves the wave out of it)
+    auto unit_of = [&](int x) { return (lane % UPS) ^ place(RPL * (DPW % 2 ? wave + x : x) + lane / UPS); };
     unsigned off[DPW];
 #pragma unroll
     for (int x = 0; x < DPW; ++x) {
@@ -572,20 +578,30 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     prof.end();
     prof.begin("sim_gemm");
     {
-        const long long tiles = (long long)d.B * ((d.n_keep + kSimTile - 1) / kSimTile) * ((r + kSimTile - 1) / kSimTile);
+        auto tiles_of = [&](int tm, int tn) { return (long long)d.B * ((d.n_keep + tm - 1) / tm) * ((r + tn - 1) / tn); };
+        int tm = 128, tn = 128;
+        if (tiles_of(128, 128) > 256) {
+            if (tiles_of(128, 192) <= 256) tn = 192;
+            else if (tiles_of(192, 128) <= 256) tm = 192;
+        }
+        const long long tiles = tiles_of(tm, tn);
         const long long per_xcd = (tiles + 7) / 8;
         a.run = (int)(per_xcd <= 64 ? per_xcd : kSimGN * kSimGM);
         const dim3 ggrid((unsigned)(((tiles + a.run - 1) / a.run + 7) / 8 * 8 * a.run));
         const bool bf = planes[0].dtype == LVLM_BF16;
         const bool ragged = (planes[0].row_elems * (bf ? 2 : 4)) % 128 != 0;
-#define LVLM_GEMM(DT, NWM, RING)                                                                                  \
-    if (ragged) LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, NWM, RING, true>), ggrid, dim3(128 * NWM), 0, stream, a);   \
-    else LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, NWM, RING, false>), ggrid, dim3(128 * NWM), 0, stream, a)
-        if (tiles <= 256) {
-            if (bf) { LVLM_GEMM(LVLM_BF16, 4, 4); } else { LVLM_GEMM(LVLM_F32, 4, 4); }
-        } else {
-            if (bf) { LVLM_GEMM(LVLM_BF16, 2, 2); } else { LVLM_GEMM(LVLM_F32, 2, 2); }
-        }
+#define LVLM_GEMM_OF(DT, RAGGED, TM, TN, NWN, NWM, RING) \
+    LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, TM, TN, NWN, NWM, RING, RAGGED>), ggrid, dim3(64 * NWN * NWM), 0, stream, a)
+#define LVLM_GEMM(...)                                                                                                      \
+    if (bf && ragged) LVLM_GEMM_OF(LVLM_BF16, true, __VA_ARGS__);                                                          \
+    else if (bf) LVLM_GEMM_OF(LVLM_BF16, false, __VA_ARGS__);                                                              \
+    else if (ragged) LVLM_GEMM_OF(LVLM_F32, true, __VA_ARGS__);                                                            \
+    else LVLM_GEMM_OF(LVLM_F32, false, __VA_ARGS__)
+        if (tn == 192) { LVLM_GEMM(128, 192, 4, 2, 3); }
+        else if (tm == 192) { LVLM_GEMM(192, 128, 2, 4, 3); }
+        else if (tiles <= 256) { LVLM_GEMM(128, 128, 2, 4, 4); }
+        else { LVLM_GEMM(128, 128, 2, 2, 2); }
+#undef LVLM_GEMM_OF
 #undef LVLM_GEMM
     }
     prof.end();

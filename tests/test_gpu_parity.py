@@ -1188,8 +1188,22 @@ def test_merge_similar_planes_shared_between_workgroups(ctx, dtype, B, n_img, n_
     (torch.float32, 1, 4400, 2200, 72),       # fp32, three slices, the last partial
     (torch.float32, 1, 4400, 2200, 96)])      # fp32, three whole slices
 def test_merge_similar_products_of_several_slices(ctx, dtype, B, n_img, n_keep, C):
-    """More tiles than compute units: two slots and two workgroups a unit, whose slots are refilled and read again here."""
+    """More square tiles than compute units: the ring's slots are refilled and read again here."""
     _similar_case(ctx, dtype, B, 1, n_img, 2, C, n_keep, 800 + C, clusters=0, extra=False)
+
+
+@pytest.mark.parametrize("dtype,B,n_img,n_keep,C", [
+    (torch.bfloat16, 1, 5000, 2000, 256),     # 384 square tiles, 256 of 128 x 192: the last count of the wide ones
+    (torch.bfloat16, 1, 4201, 2049, 328),     # 289 -> 204, one dominant row and 104 others in the last tiles, six slices, the last partial
+    (torch.float32, 8, 1730, 1200, 72),       # 400 -> 240 over eight sequences, fp32, three slices, the last partial
+    (torch.bfloat16, 1, 10560, 560, 192),     # 395 -> 265 wide ones, but 237 of 192 x 128; three slices: the ring is never refilled
+    (torch.float32, 1, 10560, 560, 136),      # ... fp32, five slices, the last partial
+    (torch.bfloat16, 1, 5081, 3000, 256),     # 408 -> 264 and 272: the square tiles with two slots
+    (torch.bfloat16, 1, 5081, 3000, 200),     # ... the fourth slice partial
+    (torch.float32, 1, 5081, 3000, 72)])      # ... fp32, three slices, the last partial
+def test_merge_similar_tile_shapes(ctx, dtype, B, n_img, n_keep, C):
+    """The edges of the rule that picks the tiles of the similarity product when square ones outnumber the compute units."""
+    _similar_case(ctx, dtype, B, 1, n_img, 2, C, n_keep, 700 + C, clusters=0, extra=False)
 
 
 @pytest.mark.parametrize("n_img,n_keep,clusters", [(200, 60, 5), (700, 2, 2), (40, 39, 0)])
