@@ -175,7 +175,7 @@ hipError_t attn_static_scratch(int device, char **ptr, size_t *bytes);
 // ---- device helpers ----
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// A load of something that passes through once and should not take up a cache.
+// Loads and stores of what passes through once and should not take up a cache.
 template <class T>
 __device__ __forceinline__ T load_once(const T *p) {
     if constexpr (sizeof(T) == 16) {
@@ -183,6 +183,15 @@ __device__ __forceinline__ T load_once(const T *p) {
         return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const u4 *>(p)));
     } else {
         return __builtin_nontemporal_load(p);
+    }
+}
+template <class T>
+__device__ __forceinline__ void store_once(T *p, T v) {
+    if constexpr (sizeof(T) == 16) {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        __builtin_nontemporal_store(__builtin_bit_cast(u4, v), reinterpret_cast<u4 *>(p));
+    } else {
+        __builtin_nontemporal_store(v, p);
     }
 }
 

@@ -595,16 +595,22 @@ __global__ __launch_bounds__(NT) void kv_select_kernel(KvArgs a) {
 
 constexpr int kFillInKernel = 64;  // most FILL moves per head that the selection kernel performs itself
 constexpr int kFillRows = 32;      // moves per batch of kv_fill_kernel (at most 4 row units per thread)
-constexpr int kFillWgs = 16384;    // workgroups the fill launch aims for
+constexpr int kFillWgs = 32768;    // workgroups the fill launch aims for
+constexpr long long kFillCached = 256ll << 20;     // bytes of rows that the memory-side cache can hold
 
 // LVLM_ORDER_FILL with many moves per head: entry list_b[i] (at or beyond the new length) goes to hole
 // list_a[i] (below it).  Sources and destinations are disjoint, so the moves are independent.
+// Bound by HBM, and by the chain lengths -> slots -> rows in front of it.  The rows are stored past the caches, and loaded past
+// them too (ONCE) where the call's heads span more than the 256 MB cache in front of the memory: 1536 heads of 1888 entries of
+// 256 bytes 157 -> 138 us (the stores alone: 148), 192 heads of 16512 the same; of 112 heads of 2115, which fit, the call would
+// take 33.6 instead of 29.2 us with such loads (start: 30.2).  32768 workgroups against 16384: 2 % where heads are many.
+template <bool ONCE>
 __global__ __launch_bounds__(256) void kv_fill_kernel(KvArgs a) {
     const int tid = threadIdx.x;
     const int hg = blockIdx.y;
     const int n_moves = a.meta[2 * hg + 1];
     const long long base = (long long)hg * a.Lmax;
-    const int units = a.row_bytes / 16;
+    const int ulog = 31 - __clz(a.row_bytes >> 4);        // units of a row: a power of two up to 32
     char *kc = a.k + base * a.row_bytes;
     char *vc = a.v + base * a.row_bytes;
     // The head's workgroups take batches of 32 moves in turn (how many moves a head has is known only on the
@@ -614,32 +620,46 @@ __global__ __launch_bounds__(256) void kv_fill_kernel(KvArgs a) {
     const int32_t *holes = a.list_a + base + i0;
     const int32_t *tails = a.list_b + base + i0;
     // rows have at most 32 units (fp32, 128 channels): 32 rows are at most 4 units per thread
-    const int n_units = cnt * units;
+    const int n_units = cnt << ulog;
     uint4 kv0, kv1, kv2, kv3, vv0, vv1, vv2, vv3;
     long long d0, d1, d2, d3;
 #define LVLM_FILL_LOAD(x)                                                            \
     {                                                                                \
         const int idx = min(256 * x + tid, n_units - 1);                             \
-        const int i = idx / units, u = idx - i * units;                              \
+        const int i = idx >> ulog, u = idx & ((1 << ulog) - 1);                      \
         const long long src = (long long)tails[i] * a.row_bytes + 16 * u;            \
         d##x = (long long)holes[i] * a.row_bytes + 16 * u;                           \
-        kv##x = *reinterpret_cast<const uint4 *>(kc + src);                          \
-        vv##x = *reinterpret_cast<const uint4 *>(vc + src);                          \
+        const uint4 *ks = reinterpret_cast<const uint4 *>(kc + src), *vs = reinterpret_cast<const uint4 *>(vc + src); \
+        kv##x = ONCE ? load_once(ks) : *ks;                                          \
+        vv##x = ONCE ? load_once(vs) : *vs;                                          \
     }
 #define LVLM_FILL_STORE(x)                                    \
     if (256 * x + tid < n_units) {                            \
-        *reinterpret_cast<uint4 *>(kc + d##x) = kv##x;        \
-        *reinterpret_cast<uint4 *>(vc + d##x) = vv##x;        \
+        store_once(reinterpret_cast<uint4 *>(kc + d##x), kv##x);        \
+        store_once(reinterpret_cast<uint4 *>(vc + d##x), vv##x);        \
     }
-    LVLM_FILL_LOAD(0) LVLM_FILL_LOAD(1) LVLM_FILL_LOAD(2) LVLM_FILL_LOAD(3)
+    // the small arrays ride along with the first wave
+    int dst = 0;
+    float sc = 0.f;
+    uint8_t kd = 0;
+    int32_t ps = 0;
+    if (tid < cnt) {
+        const long long src = base + tails[tid];
+        dst = holes[tid];
+        sc = a.score[src];
+        kd = a.kind[src];
+        ps = a.pos[src];
+    }
+    LVLM_FILL_LOAD(0)
+    if (n_units > 256) { LVLM_FILL_LOAD(1) }
+    if (n_units > 512) { LVLM_FILL_LOAD(2) LVLM_FILL_LOAD(3) }
     LVLM_FILL_STORE(0) LVLM_FILL_STORE(1) LVLM_FILL_STORE(2) LVLM_FILL_STORE(3)
 #undef LVLM_FILL_LOAD
 #undef LVLM_FILL_STORE
     if (tid < cnt) {
-        const int src = tails[tid], dst = holes[tid];
-        a.score[base + dst] = a.score[base + src];
-        a.kind[base + dst] = a.kind[base + src];
-        a.pos[base + dst] = a.pos[base + src];
+        a.score[base + dst] = sc;
+        a.kind[base + dst] = kd;
+        a.pos[base + dst] = ps;
     }
     }
 }
@@ -779,11 +799,13 @@ hipError_t launch_kv_compress(const Prof &prof, const lvlm_kv_desc &d, const KvW
         prof.end();
     } else if (a.fill_external) {
         prof.begin("kv_fill");
-        // about 16384 workgroups in all, at most one per batch of moves the longest head can have
+        // about 32768 workgroups in all, at most one per batch of moves the longest head can have
         const long long most = (max_moves + kFillRows - 1) / kFillRows;
         long long per_head = (kFillWgs + (long long)heads - 1) / (long long)heads;
         per_head = per_head < 1 ? 1 : (per_head > most ? most : per_head);
-        LVLM_LAUNCH(prof, kv_fill_kernel, dim3((unsigned)per_head, (unsigned)heads), dim3(256), 0, stream, a);
+        const dim3 fill_grid((unsigned)per_head, (unsigned)heads);
+        if (2ll * (long long)heads * bound * a.row_bytes > kFillCached) LVLM_LAUNCH(prof, kv_fill_kernel<true>, fill_grid, dim3(256), 0, stream, a);
+        else LVLM_LAUNCH(prof, kv_fill_kernel<false>, fill_grid, dim3(256), 0, stream, a);
         prof.end();
     }
     return hipGetLastError();

@@ -1097,6 +1097,27 @@ def test_degenerate_sizes(ctx):
     _kv_case(ctx, torch.bfloat16, 1, 2, 8, 128, [8, 1], 98, mode=lv.KV_BUDGET, budget=1, n_recent=0, order=lv.ORDER_FILL)
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 128)])
+def test_kv_compress_moves_of_caches_larger_than_the_memory_side_cache(ctx, dtype, d):
+    # The bulk moves of a call whose bounds span more than 256 MiB of rows are loaded past the caches: the result is bit for
+    # bit that of the same heads under a tight bound (checked against the oracle elsewhere).
+    Lmax, lens = 70000 * 256 // (d * (2 if dtype == torch.bfloat16 else 4)), [3000, 2999, 1, 0, 129, 2048, 1777, 2500]
+    n = max(lens)
+    src = [t.to(DEV) for t in _cache(dtype, 2, 4, n, d, lens, 640)]
+    for kw in (dict(mode=lv.KV_THRESHOLD, beta=0.9), dict(mode=lv.KV_BUDGET, budget=1100, n_recent=3)):
+        got = []
+        for L in (n, Lmax):
+            c = [torch.zeros(2, 4, L, *t.shape[3:], dtype=t.dtype, device=DEV) if t.dim() > 2 else t.clone() for t in src]
+            for x, t in zip(c, src):
+                if t.dim() > 2:
+                    x[:, :, :n] = t
+            assert (2 * c[0].numel() * c[0].element_size() > 256 << 20) == (L == Lmax)
+            ctx.kv_compress(*c, order=lv.ORDER_FILL, len_bound=L, **kw)
+            got.append([x[:, :, :n] if x.dim() > 2 else x for x in c])
+        for x, y in zip(*got):
+            assert torch.equal(x, y)
+
+
 # --------------------------------------------------------------------------- step 3b: similarity merge
 def _similar_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed, clusters=0, with_size=True, extra=True,
                   identical=False):
