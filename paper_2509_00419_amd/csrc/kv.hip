@@ -46,7 +46,6 @@ constexpr int kDigitBits = 9;     // radix digit width: three passes cover 27 di
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kSub = 2;           // copies of every histogram bin (lane % kSub picks one): scores of one head
                                   // may crowd into few digits, and LDS atomics on one address go one at a time
-constexpr int kChunkMax = 17;     // most chunks (one slot per thread each) numbered per round of the slot-order pass
 
 // Exact fixed-point mass of a candidate, from its order-preserving key alone: keys with the top bit set
 // are the non-negative scores (bit pattern = key without that bit); negative scores and NaN weigh 0.
@@ -60,6 +59,7 @@ __device__ __forceinline__ unsigned long long key_mass(uint32_t key) {
 static_assert(kBins == 512, "eight digits per lane");
 __device__ __forceinline__ uint32_t digit_row(uint32_t d) { return ((d & 7u) << 6) | (d >> 3); }
 
+template <int COUNTS>
 struct SelectShared {
     unsigned long long hist_m[2][kBins][kSub];   // two histograms: one is cleared while the other is in use;
     unsigned int hist_c[2][kBins][kSub];         // rows by digit_row()
@@ -70,14 +70,15 @@ struct SelectShared {
     unsigned long long w_mass[16];
     uint32_t w_min[16], w_max[16];
     int w_cnt[16];
-    int cnt[2][kChunkMax * 16 + 1];  // slot-order pass: per (chunk, wave) counts of two flags, then their
+    int cnt[2][COUNTS + 1];          // slot-order pass: per (chunk, wave) counts of two flags, then their
                                      // exclusive prefixes in (chunk, wave) order; last element: the total
 };
 
 // Wave 0, after a histogram pass: suffix sums over the digits give the mass (and count) above each
 // digit; the digit in which the quota `need` (> 0, at most the mass in the histogram) is met becomes the
 // next digit of the key.
-__device__ __forceinline__ void pick_digit(SelectShared &sh, int cur, unsigned long long need, bool count_only) {
+template <int COUNTS>
+__device__ __forceinline__ void pick_digit(SelectShared<COUNTS> &sh, int cur, unsigned long long need, bool count_only) {
     const int lane = threadIdx.x & 63;
     constexpr int PER = kBins / 64;     // lane owns PER consecutive digits
     unsigned long long loc_m = 0ull;
@@ -130,9 +131,9 @@ __device__ __forceinline__ void pick_digit(SelectShared &sh, int cur, unsigned l
 // a round has fewer than 2^16 slots), and the round totals.  Every wave files its ballots'
 // counts, waves 0 and 1 turn the two NCH x NT/64 tables into exclusive prefixes, every thread adds the lanes below it.
 // Two barriers; the table may be reused after one more barrier.
-template <int NCH, int NT>
-__device__ __forceinline__ void chunk_scan2(SelectShared &sh, uint32_t f0, uint32_t f1, uint32_t (&e)[NCH], int &t0,
-                                            int &t1) {
+template <int NCH, int NT, int COUNTS>
+__device__ __forceinline__ void chunk_scan2(SelectShared<COUNTS> &sh, uint32_t f0, uint32_t f1, uint32_t (&e)[NCH],
+                                            int &t0, int &t1) {
     static_assert(NCH * NT < 65536, "packed counts need 16 bits");
     constexpr int NW = NT / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -187,16 +188,17 @@ __device__ __forceinline__ void chunk_scan2(SelectShared &sh, uint32_t f0, uint3
 // NT threads per head.  KPT > 0: every thread keeps the keys of its KPT slots (slot = NT i + thread) in
 // registers, so the scores are read once, with all loads in flight together; heads longer than NT KPT are not accepted
 // by the launch.  KPT == 0: any length, scores re-read from memory in every pass.
-template <int KPT, int NT>
-__global__ __launch_bounds__(NT) void kv_select_kernel(KvArgs a) {
+// WPE: waves per SIMD the registers are held to.  A head is a chain of latencies (barriers, LDS atomics, one wave's digit
+// scan), so what counts with many heads is how many of them a compute unit holds: the histograms leave room for six.
+template <int KPT, int NT, int WPE>
+__global__ __launch_bounds__(NT, WPE) void kv_select_kernel(KvArgs a) {
     constexpr int NW = NT / 64;
-    __shared__ SelectShared sh;
     constexpr int NREG = KPT > 0 ? KPT : 1;
     // slots per thread in one round of the slot-order pass: register-resident keys go in one round, or in two
     // when there are many (the numbering state of a round is live across its barriers)
     constexpr int CH = KPT > 8 ? (KPT + 1) / 2 : KPT > 0 ? KPT : 16;
     constexpr int NROUND = KPT > 0 ? (KPT + CH - 1) / CH : 1;
-    static_assert(CH <= kChunkMax, "count table too small");
+    __shared__ SelectShared<CH * NW> sh;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int hg = blockIdx.x;
@@ -778,14 +780,24 @@ hipError_t launch_kv_compress(const Prof &prof, const lvlm_kv_desc &d, const KvW
     const int max_moves = d.mode == LVLM_KV_BUDGET ? (bound - d.budget < bound / 2 ? bound - d.budget : bound / 2) : bound / 2;
     a.fill_external = d.order == LVLM_ORDER_FILL && max_moves > kFillInKernel;
     prof.begin("kv_select");
-    // Much of the selection is one wave's chain of latencies, so with more heads than the chip holds workgroups of
-    // 1024 threads, short heads go to workgroups of 256 threads: more heads are in flight at once.
-    if (bound <= 2048 && heads > 512) LVLM_LAUNCH(prof, (kv_select_kernel<8, 256>), dim3((unsigned)heads), dim3(256), 0, stream, a);
-    else if (bound <= 2048) LVLM_LAUNCH(prof, (kv_select_kernel<2, 1024>), dim3((unsigned)heads), dim3(1024), 0, stream, a);
-    else if (bound <= 4096) LVLM_LAUNCH(prof, (kv_select_kernel<4, 1024>), dim3((unsigned)heads), dim3(1024), 0, stream, a);
-    else if (bound <= 8192) LVLM_LAUNCH(prof, (kv_select_kernel<8, 1024>), dim3((unsigned)heads), dim3(1024), 0, stream, a);
-    else if (bound <= 17408) LVLM_LAUNCH(prof, (kv_select_kernel<17, 1024>), dim3((unsigned)heads), dim3(1024), 0, stream, a);
-    else LVLM_LAUNCH(prof, (kv_select_kernel<0, 1024>), dim3((unsigned)heads), dim3(1024), 0, stream, a);
+    // Threads and keys per thread by length and number of heads (times of a threshold selection with its moves of 128-byte rows,
+    // other form -> this one).  Up to 2048 entries 512 threads as long as three heads to a compute unit are all of them (against
+    // 1024 threads, one to a unit: 256 heads of 1888 22.9 -> 21.7 us, 512 heads 38.0 -> 26.9), then 256 threads and six to a unit
+    // (against 512: 640 heads 33.9 -> 31.1, 1024 heads 45.4 -> 40.6 us; five to a unit: 1536 heads 27.5 -> 21.0 for the kernel
+    // alone).  Fewer keys per thread where they do (1536 heads of 1025: 59.5 -> 53.5; 1024 threads at 2500 entries: 512 heads
+    // 47.4 -> 38.1, 2048 heads 173 -> 105, at 4000 49.0 -> 38.7 and 195 -> 135).  Up to 8192 entries 1024 threads for one head per
+    // unit (256 heads 41.8 -> 38.9), 512 for more (320 heads 59.9 -> 51.1, 2048 heads 265 -> 214).
+#define LVLM_SELECT(KPT, NT, WPE) LVLM_LAUNCH(prof, (kv_select_kernel<KPT, NT, WPE>), dim3((unsigned)heads), dim3(NT), 0, stream, a)
+    if (bound <= 1280 && heads > 256) LVLM_SELECT(5, 256, 6);
+    else if (bound <= 2048 && heads > 768) LVLM_SELECT(8, 256, 6);
+    else if (bound <= 2048) LVLM_SELECT(4, 512, 6);
+    else if (bound <= 2560) LVLM_SELECT(5, 512, 6);
+    else if (bound <= 4096) LVLM_SELECT(8, 512, 6);
+    else if (bound <= 8192 && heads > 256) LVLM_SELECT(16, 512, 4);
+    else if (bound <= 8192) LVLM_SELECT(8, 1024, 4);
+    else if (bound <= 17408) LVLM_SELECT(17, 1024, 4);
+    else LVLM_SELECT(0, 1024, 4);
+#undef LVLM_SELECT
     prof.end();
     if (d.order == LVLM_ORDER_STABLE) {
         prof.begin("kv_move");

@@ -1097,6 +1097,38 @@ def test_degenerate_sizes(ctx):
     _kv_case(ctx, torch.bfloat16, 1, 2, 8, 128, [8, 1], 98, mode=lv.KV_BUDGET, budget=1, n_recent=0, order=lv.ORDER_FILL)
 
 
+@pytest.mark.parametrize("heads,bound", [
+    (257, 1280), (257, 70), (769, 1281), (769, 2048),    # 256 threads a head, five and eight keys each
+    (768, 2048), (300, 1281),                            # 512 threads, four keys: the most heads and the first length
+    (300, 2049), (300, 2560), (300, 2561), (300, 4096),  # five and eight keys
+    (257, 4097), (257, 8192)])                           # sixteen
+def test_kv_compress_forms_of_many_heads(ctx, heads, bound):
+    """The selection's forms for many heads, at the lengths where the rule changes: both modes and orders, ragged heads (whole,
+    empty, one entry, one over the budget), bit for bit what calls of at most 64 heads (whose forms the oracle checks) leave."""
+    g = torch.Generator(device=DEV).manual_seed(heads + bound)
+    d, dt = 64, torch.bfloat16
+    lens = torch.randint(0, bound + 1, (heads, 1), generator=g, device=DEV).to(torch.int32)
+    lens[:4, 0] = torch.tensor([bound, 0, 1, bound - 1], dtype=torch.int32)
+    lens[-1, 0] = bound
+    src = [torch.randn(heads, 1, bound, d, generator=g, device=DEV).to(dt) for _ in range(2)]
+    score = torch.rand(heads, 1, bound, generator=g, device=DEV) ** 4
+    score[::3] = (score[::3] * 16).floor() / 16                                            # ties
+    src += [score, torch.randint(0, 3, (heads, 1, bound), generator=g, device=DEV).to(torch.uint8),
+            torch.arange(bound, dtype=torch.int32, device=DEV).repeat(heads, 1, 1).contiguous(), lens]
+    for kw in (dict(mode=lv.KV_THRESHOLD, beta=0.9, order=lv.ORDER_FILL), dict(mode=lv.KV_THRESHOLD, beta=0.6, order=lv.ORDER_STABLE),
+               dict(mode=lv.KV_BUDGET, budget=bound - 1, n_recent=2, order=lv.ORDER_FILL),
+               dict(mode=lv.KV_BUDGET, budget=max(1, bound // 3), n_recent=0, order=lv.ORDER_STABLE)):
+        whole, parts = [t.clone() for t in src], [t.clone() for t in src]
+        n_whole = ctx.kv_compress(*whole, len_bound=bound, **kw)
+        n_parts = [ctx.kv_compress(*[t[i:i + 64] for t in parts], len_bound=bound, **kw) for i in range(0, heads, 64)]
+        assert torch.equal(n_whole, torch.cat(n_parts))
+        live = torch.arange(bound, device=DEV)[None, None] < whole[5][..., None]
+        for x, y in zip(whole, parts):
+            if x.dim() == 4:
+                x, y = x.view(torch.int16), y.view(torch.int16)
+            assert torch.equal(x[live], y[live]) if x.dim() > 2 else torch.equal(x, y)
+
+
 @pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 128)])
 def test_kv_compress_moves_of_caches_larger_than_the_memory_side_cache(ctx, dtype, d):
     # The bulk moves of a call whose bounds span more than 256 MiB of rows are loaded past the caches: the result is bit for
