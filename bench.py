@@ -457,14 +457,15 @@ def run_decode_compress(ctx, lv, w, states, reserve):
 # ----------------------------------------------------------------------------- algorithmic work per kernel
 def score_form(ctx, lv, w, N, n_img, batch, given_lse=False):
     """The launch form the library takes for `batch` sequences of N keys (lvlm_score_plan: 0 two passes, 1 / 2 one launch,
-    3 the shared-tile kernel with the keys in runs, one launch per sweep), and whether its kernel for few query rows (one
-    launch, one sweep) takes the place of form 0 or 1 (lvlm_score_few_rows)."""
+    3 the shared-tile kernel with the keys in runs, one launch per sweep), whether its kernel for few query rows (one
+    launch, one sweep) takes the place of form 0 or 1 (lvlm_score_few_rows), and whether the one with equal shares of the keys
+    (one launch per sweep, the row normalisers folded in the second) that of 0, 2 or 3 (lvlm_score_shares)."""
     from paper_2509_00419_amd import binding as bd
     d = bd.ScoreDesc(bd.BF16 if w.dtype == "bf16" else bd.F32, batch, N, w.n_text, w.n_sys + n_img, w.n_q_heads,
                      w.n_kv_heads, w.head_dim, w.n_sys, n_img, 1, w.head_dim ** -0.5,
                      w.n_text * w.n_q_heads * w.head_dim, w.n_q_heads * w.head_dim, w.head_dim,
                      N * w.n_kv_heads * w.head_dim, w.n_kv_heads * w.head_dim, w.head_dim, 0, 0)
-    return ctx.score_plan(d), ctx.score_few_rows(d, given_lse) > 0
+    return ctx.score_plan(d), ctx.score_few_rows(d, given_lse) > 0, ctx.score_shares(d, given_lse) > 0
 
 
 def moved_entries(pos_before, pos_after, len_after, torch):
@@ -493,13 +494,13 @@ def kernel_work(ctx, lv, w, layers, dec_lens, moved, merge="rank", per_layer=Fal
     for first, last in score_groups(layers, per_layer):
         n_img = layers[last]["n_img"]
         N, gb = w.n_sys + n_img + T, (last - first + 1) * B
-        form, few_rows = score_form(ctx, lv, w, N, n_img, gb, given_lse)
+        form, few_rows, shares = score_form(ctx, lv, w, N, n_img, gb, given_lse)
         if few_rows:                                                         # the column sums come from the same products
             add("score_single", "mfma", 2.0 * gb * T * (n_img if given_lse else N) * d * Hq)
-        elif form != 0:
-            launches = 2 if form == 3 and not given_lse else 1               # form 3: one launch per sweep
+        elif form != 0 or shares:
+            launches = 2 if (form == 3 or shares) and not given_lse else 1   # form 3, shares: one launch per sweep
             add("score_single", "mfma", 2.0 * gb * T * ((0 if given_lse else N) + n_img) * d * Hq, launches=launches)
-            if form == 3 and not given_lse:
+            if form == 3 and not shares and not given_lse:
                 add("score_lse", "hbm", 4.0 * gb * Hq * T)                   # the row normalisers folded in between
         else:
             if not given_lse:
@@ -814,7 +815,7 @@ def main_score_load(args, w, layers, ctx, lv, torch, dev):
             sm = torch.empty(B, n_img, dtype=torch.float32, device=dev)
             kw = dict(q_pos0=w.n_sys + n_img, img_begin=w.n_sys, n_img=n_img, score_head=sh, score_mean=sm)
             desc = ctx.score_desc(q, k, q_pos0=kw["q_pos0"], img_begin=kw["img_begin"], n_img=n_img)
-            form, few_rows = ctx.score_plan(desc), ctx.score_few_rows(desc) > 0
+            form, few_rows, shares = ctx.score_plan(desc), ctx.score_few_rows(desc) > 0, ctx.score_shares(desc) > 0
             ctx.score_tokens(q, k, **kw)
             torch.cuda.synchronize()
             ctx.profile(True)
@@ -827,11 +828,11 @@ def main_score_load(args, w, layers, ctx, lv, torch, dev):
             flops = 2.0 * B * Hq * T * d * (N if few_rows else N + n_img)
             wgs = B * Hkv * ((n_chunks + 3) // 4)
             rows.append({"n_img": n_img, "keys": N, "sequences": B,
-                         "form": "few query rows, one sweep" if few_rows else ["two passes", "one launch, a chunk per workgroup",
+                         "form": "few query rows, one sweep" if few_rows else "equal shares of the keys" if shares else ["two passes", "one launch, a chunk per workgroup",
                                                                                "one launch, shared tiles",
                                                                                "shared tiles, keys in runs"][form],
-                         "workgroups": wgs if form >= 2 else None,
-                         "workgroups_per_cu": round(wgs / 256, 2) if form >= 2 else None, "us": round(us, 1),
+                         "workgroups": wgs if form >= 2 and not shares else None,
+                         "workgroups_per_cu": round(wgs / 256, 2) if form >= 2 and not shares else None, "us": round(us, 1),
                          "TFLOPs": round(flops / us / 1e6, 1), "frac_of_peak": round(flops / us / 1e6 / peak, 4)})
             del q, k, sh, sm
     best = max(rows, key=lambda r: r["TFLOPs"])

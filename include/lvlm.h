@@ -174,13 +174,19 @@ LVLM_API lvlm_status lvlm_score_tokens(lvlm_ctx *ctx, void *stream, const lvlm_s
  * sums), 1 both sweeps in one launch with one query chunk per workgroup, 2 both sweeps in one launch with
  * four query chunks per workgroup sharing the key tiles, 3 the kernel of form 2 with the keys cut into runs
  * (one launch per sweep, the runs' normaliser partials folded in between: launches of few workgroups).
- * Forms 0 and 1 are what the shape takes unless lvlm_score_few_rows says otherwise. */
+ * Forms 0 and 1 are what the shape takes unless lvlm_score_few_rows says otherwise, forms 0, 2 and 3 unless
+ * lvlm_score_shares does. */
 LVLM_API lvlm_status lvlm_score_plan(const lvlm_ctx *ctx, const lvlm_score_desc *d, int32_t *form);
 
 /* Whether a shape of form 0 or 1 goes to the kernel for few query rows instead, which reads and multiplies every
  * key once in one launch and keeps the logits in registers: *chunks = its chunks of 16 query rows per KV head,
  * 0 = not taken.  lse_given: nonzero if the call passes row_lse. */
 LVLM_API lvlm_status lvlm_score_few_rows(const lvlm_ctx *ctx, const lvlm_score_desc *d, int lse_given, int32_t *chunks);
+
+/* Whether a shape of form 0, 2 or 3 goes to the kernel for much work instead, which deals the keys of all (batch, KV
+ * head) pairs out in equal shares (a launch per sweep, two query chunks per wave): *shares = the shares of the
+ * column-sum sweep, 0 = not taken.  lse_given as above (without a normaliser sweep). */
+LVLM_API lvlm_status lvlm_score_shares(const lvlm_ctx *ctx, const lvlm_score_desc *d, int lse_given, int32_t *shares);
 
 /* The same scores from attention probabilities the caller already holds -- a
  * plain attention that materialises its matrix (Sec. 3.2.2 names both sources:

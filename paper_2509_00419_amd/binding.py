@@ -119,6 +119,7 @@ def _load():
     lib.lvlm_score_tokens.argtypes = [vp, vp, C.POINTER(ScoreDesc), vp, vp, f32p, f32p, f32p]
     lib.lvlm_score_plan.argtypes = [vp, C.POINTER(ScoreDesc), C.POINTER(C.c_int32)]
     lib.lvlm_score_few_rows.argtypes = [vp, C.POINTER(ScoreDesc), C.c_int, C.POINTER(C.c_int32)]
+    lib.lvlm_score_shares.argtypes = lib.lvlm_score_few_rows.argtypes
     lib.lvlm_score_from_probs.argtypes = [vp, vp, C.POINTER(ProbsDesc), vp, f32p, f32p]
     lib.lvlm_prefill_attn.argtypes = [vp, vp, C.POINTER(PrefillDesc), vp, vp, vp, vp, f32p, f32p, f32p]
     lib.lvlm_merge_compact.argtypes = [vp, vp, C.POINTER(MergeDesc), f32p, f32p, C.POINTER(Plane), i32p, i32p]
@@ -131,7 +132,7 @@ def _load():
     lib.lvlm_profile.argtypes = [C.c_void_p, C.c_int]
     lib.lvlm_profile_read.argtypes = [C.c_void_p, C.POINTER(ProfileEntry), C.c_int, C.POINTER(C.c_int)]
     for name in ("lvlm_profile", "lvlm_profile_read", "lvlm_create", "lvlm_destroy", "lvlm_workspace_bytes", "lvlm_set_workspace", "lvlm_schedule",
-                 "lvlm_merge_weights", "lvlm_score_tokens", "lvlm_score_plan", "lvlm_score_few_rows", "lvlm_score_from_probs", "lvlm_prefill_attn", "lvlm_merge_compact",
+                 "lvlm_merge_weights", "lvlm_score_tokens", "lvlm_score_plan", "lvlm_score_few_rows", "lvlm_score_shares", "lvlm_score_from_probs", "lvlm_prefill_attn", "lvlm_merge_compact",
                  "lvlm_merge_similar",
                  "lvlm_kv_compress",
                  "lvlm_decode_attn", "lvlm_decode_attn_static", "lvlm_decode_plan", "lvlm_stream_probe"):
@@ -267,6 +268,13 @@ class Context(_ContextCalls):
         chunks = C.c_int32()
         self._check(lib.lvlm_score_few_rows(self._h, C.byref(desc), int(lse_given), C.byref(chunks)))
         return chunks.value
+
+    def score_shares(self, desc: ScoreDesc, lse_given: bool = False) -> int:
+        """lvlm_score_shares: shares the keys are dealt out in where the kernel for much work takes the place of form 0, 2 or 3
+        (a launch per sweep), else 0."""
+        shares = C.c_int32()
+        self._check(lib.lvlm_score_shares(self._h, C.byref(desc), int(lse_given), C.byref(shares)))
+        return shares.value
 
     # ---- step 6 ----
     def decode_plan(self, desc: AttnDesc):

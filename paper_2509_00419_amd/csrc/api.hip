@@ -382,6 +382,16 @@ lvlm_status lvlm_score_few_rows(const lvlm_ctx *ctx, const lvlm_score_desc *d, i
     return LVLM_OK;
 }
 
+lvlm_status lvlm_score_shares(const lvlm_ctx *ctx, const lvlm_score_desc *d, int lse_given, int32_t *shares) {
+    lvlm_ctx *c = const_cast<lvlm_ctx *>(ctx);
+    if (!ctx || !shares) return fail(c, LVLM_ERR_INVALID_ARG, "score_shares: null argument");
+    if (const char *why = check_score(d)) return fail(c, LVLM_ERR_INVALID_ARG, "score_shares: %s", why);
+    const ScoreWs w = score_ws(*d);
+    const ScoreShares &s = lse_given ? w.shares_given : w.shares;
+    *shares = s.waves ? s.runs2.shares : 0;
+    return LVLM_OK;
+}
+
 lvlm_status lvlm_score_tokens(lvlm_ctx *ctx, void *stream, const lvlm_score_desc *d, const void *q, const void *k,
                               const float *row_lse, float *score_head, float *score_mean) {
     if (!ctx) return LVLM_ERR_INVALID_ARG;

@@ -30,6 +30,25 @@ constexpr float kLog2e = 1.4426950408889634f;
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ---- workspace layouts (host arithmetic shared by the size query and the launch) ----
+// The keys of all (batch, KV head) pairs, one pair behind the other in steps, in consecutive shares: the first `longer` of
+// them of size + 1 steps, the others of `size`.  A share is part of one pair or reaches into the next ones.
+struct KeyRuns {
+    int steps;              // of a pair
+    int shares, size, longer;
+#if defined(__HIPCC__)
+    __device__ __forceinline__ int begin(int j) const { return j * size + (j < longer ? j : longer); }
+    __device__ __forceinline__ int share_of(int step) const {
+        const int cut = longer * (size + 1);
+        return step < cut ? step / (size + 1) : longer + (step - cut) / size;
+    }
+    __device__ __forceinline__ int first(int pair) const { return share_of(pair * steps); }       // share with the pair's first step
+    __device__ __forceinline__ int count(int pair) const { return share_of(pair * steps + steps - 1) - first(pair) + 1; }
+#endif
+};
+struct ScoreShares {
+    int waves;     // per workgroup, two query chunks each; 0: not that form
+    KeyRuns runs1, runs2;   // the normaliser sweep over all keys, the column sums over the image keys
+};
 struct ScoreWs {
     size_t part_m, part_l, lse2, colpart, total;
     int nkb;       // key blocks of the normaliser pass
@@ -38,6 +57,7 @@ struct ScoreWs {
     bool single;   // short sequence: both passes in one launch, one part of column sums per query chunk
     bool shared_tiles;   // ... with four query chunks per workgroup sharing the key tiles through LDS
     int key_segs;        // ... and the keys cut into this many runs, a launch per sweep (1 = one launch)
+    ScoreShares shares, shares_given;   // much work: the keys in equal shares, a launch per sweep; the same with the normalisers given
     int rows, rows_given;   // few query rows: chunks of 16 of them, one workgroup each, in one launch (0: not that form); the
                             // same with the normalisers given
 };

@@ -43,6 +43,7 @@ struct ScoreArgs {
     int rs;             // row splits: workgroups that share a key block and take different query chunks
     int cps;            // chunks per split
     int n_seg;          // shared-tile form: runs the keys are cut into (1 = both sweeps in one launch)
+    KeyRuns runs1, runs2;   // equal shares: how the keys of the two sweeps are dealt out
     unsigned t_magic;   // floor(2^32 / T) + 1: rho / T == umulhi(rho, t_magic) for rho, T < 65536
     float scale_log2;
     long long qsb, qst, qsh, ksb, ksn, ksh, shb, shh;
@@ -793,6 +794,370 @@ __global__ __launch_bounds__(256, (DT == LVLM_F32 && HD == 128) ? 2 : 4) void sc
     if (jb < je) sweep(jb, je, true, std::true_type{});
 }
 
+// ---- many query chunks over long sequences: the keys of all pairs in equal shares, a launch per sweep ----------
+// The two sweeps of score_chunks_kernel for bf16 calls of much work.  There the fragments that every wave reads from LDS for
+// one 32-row chunk, a barrier per 32 keys and turns of workgroups that do not come out even cost more than the products.  Here
+// a wave holds TWO chunks, so that a fragment feeds two products, a workgroup of NW waves owns 2 NW chunks of a (batch, KV head)
+// pair, and the launch has two waves per SIMD, each with an equal share of the keys: the pairs' keys lie behind each
+// other in steps of 64, and share j, whichever pairs it reaches into, goes to the workgroups of one XCD that own the pair's chunks
+// (they read the same keys at the same time).
+// Steps go from memory straight into a ring of LDS slots (direct loads, 16-byte units swizzled as in the few-rows kernel below;
+// the loads are assembly for the reason given there, their waits counted by hand; one barrier per step).  Only two steps are
+// requested before anything else, the rest of the ring when these have landed: all at once, every workgroup would wait for
+// everybody's whole ring.
+// Products and softmax of different chunks go side by side: the products of chunk 0 with the softmax of chunk 1 of the tile
+// before, those of chunk 1 with the softmax of chunk 0, cut into slots of one product and two logits (scaling, exponential
+// and sum a slot apart; the scheduling barriers keep the compiler from drawing them apart).
+// SECOND = false: rows = keys, columns = queries; each row's (max, sum) of the share.  SECOND = true: rows = queries, columns =
+// keys; the shares' normalisers are folded at the start of a pair (they are few), or the caller's taken, and a wave leaves the
+// column sums of its two chunks as one part.
+// What bounds it: vector issue beside the products at the clock the power allows (a probe of 8 products and 32 exponentials,
+// scalings and sums alone takes 180 ns per tile and SIMD, this loop 220; without its fetches, barriers and fragment reads 190).
+// Against score_chunks_kernel in runs and its fold: 12 sequences x 5219 keys x 48 heads 241 -> 221 us for the call with the
+// fold of half as many parts of column sums (900 TFLOP/s).
+constexpr int kShareStep = 64;               // keys per step
+template <int HD, bool SECOND, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void score_shares_kernel(ScoreArgs a) {
+    constexpr int ES = 2, ROWB = HD * ES, NV = HD / 16;
+    constexpr int RING = NW == 4 ? 4 : 2;   // slots: what two waves per SIMD leave room for
+    constexpr int STEP = kShareStep, SLOT = STEP * ROWB;
+    constexpr int UPR = ROWB / 16, RPL = 1024 / ROWB;      // 16-byte units per row, rows per direct load
+    constexpr int DPW = SLOT / 1024 / NW;   // direct loads per wave and step
+    constexpr int NOFF = DPW < 16 / RPL ? DPW : 16 / RPL;  // the swizzle repeats after 16 rows, and so do the offsets
+    __shared__ __attribute__((aligned(1024))) char k_lds[RING * SLOT];
+    __shared__ float lse_s[2 * NW][32];
+    __shared__ int pos_s[2 * NW][32];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hf = lane >> 5, l32 = lane & 31;
+    const int GT = a.G * a.T;
+    const int n_chunks = (GT + 31) >> 5;
+    const int wpp = (n_chunks + 2 * NW - 1) / (2 * NW);   // workgroups per pair
+    const int xcd = blockIdx.x & 7, seq = (int)(blockIdx.x >> 3);
+    const int c0 = (seq % wpp) * 2 * NW + 2 * wave;       // this wave's first chunk
+    const bool live = c0 < n_chunks;                      // a wave without a chunk only helps to move the keys
+    const KeyRuns &runs = SECOND ? a.runs2 : a.runs1;
+    const int per_xcd = (runs.shares + 7) >> 3, share = xcd * per_xcd + seq / wpp;
+    if (seq / wpp >= per_xcd || share >= runs.shares) return;
+    int at = runs.begin(share);
+    const int at_end = runs.begin(share + 1);
+    const long long rows = (long long)a.B * a.Hq * a.T;
+    auto div_t = [&](int rho) -> int { return a.T == 1 ? rho : (int)__umulhi((unsigned)rho, a.t_magic); };
+
+    // load x of this wave fills rows RPL (DPW wave + x) .. of a slot, lane -> row lane / UPR, place lane % UPR
+    const unsigned ksb = (unsigned)(a.ksn * ES);          // (the host checks that a step's rows span less than 2 GiB)
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)k_lds + 1024u * (DPW * wave);
+    auto place = [](int row) { return ROWB == 128 ? (row >> 1) & 7 : row & 15; };
+    const int frow = RPL * DPW * wave + lane / UPR;       // this lane's row in load 0
+    unsigned off[NOFF];
+#pragma unroll
+    for (int x = 0; x < NOFF; ++x) off[x] = (frow + RPL * x) * ksb + 16 * ((lane % UPR) ^ place(frow + RPL * x));
+    // contraction step i of lane half hf takes bytes [32 i + 16 hf, +16) of a row
+    unsigned uo[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) uo[i] = l32 * ROWB + 16 * ((2 * i + hf) ^ place(l32));
+    auto frag = [&](int slot, int s, int i) {             // word i of this lane's row of tile s of a slot
+        return *reinterpret_cast<const uint4 *>(&k_lds[slot * SLOT + s * (32 * ROWB) + uo[i]]);
+    };
+    // All steps fetched have landed everywhere -- but the RING - 2 youngest if that many are under way -- and everybody's reads
+    // of the step before are back.
+    auto landed = [](bool full) {
+        if (full) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(DPW * (RING - 2)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    const int key_lo = a.img_begin, key_hi = a.img_begin + a.n_img;
+
+    for (int pair = at / runs.steps;; ++pair) {           // the pairs of this share
+        const int b = pair / a.Hkv, g = pair % a.Hkv;
+        const long long rowbase = ((long long)b * a.Hq + (long long)g * a.G) * a.T;
+        const int s0 = at - pair * runs.steps, n_steps = min(runs.steps - s0, at_end - at);
+        at += n_steps;
+        const int jb = (SECOND ? key_lo : 0) + STEP * s0, je = min(SECOND ? key_hi : a.N, jb + STEP * n_steps);
+        const char *kbase = a.k + ((long long)b * a.ksb + (long long)g * a.ksh) * ES;
+        auto fetch = [&](int t) {                         // step t: rows clamped to the share's last one
+            const int j0 = jb + STEP * t;
+            const unsigned dst = lds0 + (unsigned)(t % RING * SLOT);
+            const char *base = kbase + (long long)j0 * a.ksn * ES;
+#pragma unroll
+            for (int x = 0; x < DPW; ++x) {
+                const int row = frow + RPL * x;
+                const char *src = base;                   // uniform
+                unsigned o = off[x % NOFF];
+                if (j0 + STEP <= je) src += (long long)(x / NOFF * NOFF * RPL) * a.ksn * ES;
+                else o = (unsigned)min(row, je - 1 - j0) * ksb + 16 * ((lane % UPR) ^ place(row));
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(o), "s"(src), "s"(dst + 1024u * x)
+                             : "memory", "m0");
+            }
+        };
+        auto begin = [&] {
+            fetch(0);
+            if (n_steps > 1) fetch(1);
+        };
+        begin();
+
+        // this lane's query rows (padding rows repeat the last row and get an infinite LSE)
+        int rho[2], pos[2];
+        HalfRow<LVLM_BF16, HD> qa[2];
+        int pos_min = INT_MAX;      // earliest position of the wave's rows (uniform): tiles at or before it need no mask
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int c = c0 + x;
+            rho[x] = c * 32 + l32;
+            const int rc = min(rho[x], GT - 1);
+            const int hl = div_t(rc), qi = rc - hl * a.T;
+            pos[x] = a.causal ? a.q_pos0 + qi : INT_MAX;
+            const char *src = a.q + ((long long)b * a.qsb + (long long)qi * a.qst + (long long)(g * a.G + hl) * a.qsh) * ES + 16 * hf;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) qa[x].v[i] = *reinterpret_cast<const uint4 *>(src + 32 * i);
+            if (hf == 0) pos_s[2 * wave + x][l32] = pos[x];
+            const int r_first = min(c * 32, GT - 1), r_last = min(c * 32 + 31, GT - 1);
+            const int hc0 = div_t(r_first), hc1 = div_t(r_last);
+            if (a.causal) pos_min = min(pos_min, a.q_pos0 + ((hc0 != hc1) ? 0 : r_first - hc0 * a.T));
+        }
+        float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};     // sweep 1: the rows' (max, sum)
+        float lse_r[2][16];                               // sweep 2: the normalisers of this lane's 16 accumulator rows
+        if constexpr (SECOND) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const long long row = rowbase + min(rho[x], GT - 1);
+                float lse;
+                if (a.row_lse) {
+                    lse = a.row_lse[row] * kLog2e;
+                } else {
+                    // what the shares of sweep 1 left, every second one per lane half, sixteen at a time
+                    const int n_part = a.runs1.count(pair);
+                    float mx = -INFINITY, lx = 0.f;
+                    for (int i0 = hf; i0 < n_part; i0 += 16) {
+                        float mi[8], li[8];
+#pragma unroll
+                        for (int y = 0; y < 8; ++y) {
+                            const long long from = min(i0 + 2 * y, n_part - 1) * rows + row;
+                            mi[y] = a.part_m[from], li[y] = a.part_l[from];
+                        }
+                        float mn = mx;
+#pragma unroll
+                        for (int y = 0; y < 8; ++y) {
+                            if (i0 + 2 * y >= n_part) mi[y] = -INFINITY, li[y] = 0.f;
+                            mn = fmaxf(mn, mi[y]);
+                        }
+                        const float ms = (mn == -INFINITY) ? 0.f : mn;
+                        lx *= exp2f(mx - ms);
+#pragma unroll
+                        for (int y = 0; y < 8; ++y) lx += li[y] * exp2f(mi[y] - ms);      // exp2(-inf) = 0 covers empty shares
+                        mx = mn;
+                    }
+                    const float mo = other_half(mx), lo = other_half(lx);
+                    const float mn = fmaxf(mx, mo), ms = (mn == -INFINITY) ? 0.f : mn;
+                    lx = lx * exp2f(mx - ms) + lo * exp2f(mo - ms);
+                    lse = lx > 0.f ? mn + log2f(lx) : INFINITY;      // no visible key: contributes nothing
+                }
+                if (hf == 0) lse_s[2 * wave + x][l32] = rho[x] < GT ? lse : INFINITY;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) lse_r[x][r] = lse_s[2 * wave + x][acc_row(r, hf)];
+        }
+        float *out = a.colpart + (((long long)(min(c0, n_chunks - 1) / 2) * a.B + b) * a.Hkv + g) * a.n_img;
+
+        // One tile with every check: sweep 1 follows the running maximum, sweep 2 stores lane by lane.  `stands`: the rows'
+        // references were set by a whole tile, so that later tiles take neither a maximum nor a rescale (FAST sweeps only).
+        auto careful = [&](int j0, bool stands, const HalfRow<LVLM_BF16, HD> &kf) {
+            float col = 0.f;
+            const bool whole = j0 + 32 <= je && j0 + 31 <= pos_min;
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                f32x16 acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+                if constexpr (SECOND) {
+                    mma_tile<LVLM_BF16, HD>(acc, qa[x], kf);
+                    float part = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float p = __builtin_amdgcn_exp2f(fmaf(acc[r], a.scale_log2, -lse_r[x][r]));
+                        part += whole || j0 + l32 <= pos_s[2 * wave + x][acc_row(r, hf)] ? p : 0.f;
+                    }
+                    col += part;
+                } else {
+                    mma_tile<LVLM_BF16, HD>(acc, kf, qa[x]);
+                    float tmax = -INFINITY;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int j = j0 + acc_row(r, hf);
+                        acc[r] = whole || (j <= pos[x] && j < je) ? acc[r] * a.scale_log2 : -INFINITY;
+                        tmax = fmaxf(tmax, acc[r]);
+                    }
+                    const float mn = stands ? m[x] : fmaxf(m[x], tmax), ms = (mn == -INFINITY) ? 0.f : mn;
+                    float sum = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(acc[r] - ms);      // exp2(-inf) = 0
+                    l[x] = (stands ? l[x] : l[x] * __builtin_amdgcn_exp2f(m[x] - ms)) + sum;
+                    m[x] = mn;
+                }
+            }
+            if constexpr (SECOND) {
+                col += other_half(col);
+                if (hf == 0 && j0 + l32 < je) out[j0 + l32 - key_lo] = col;
+            }
+        };
+        // Steps [0, n_fast), whose keys all rows of the wave see.  Sweep 1: the first tile's maximum is every row's reference; a
+        // logit far above it shows as an overflowing sum, checked after the sweep.
+        auto fast = [&](int n_fast) {
+            uint4 kf[NV];
+            f32x16 acc[2], zero;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+            float part[2][2];       // column sums: [tile of the step][chunk]
+            auto mfma = [&](const uint4 &kw, const uint4 &qw, const f32x16 &c) {
+                const bf16x8 kv = __builtin_bit_cast(bf16x8, kw), qv = __builtin_bit_cast(bf16x8, qw);
+                return SECOND ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv, kv, c, 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f32_32x32x16_bf16(kv, qv, c, 0, 0, 0);
+            };
+            constexpr int LPS = 16 / NV;                  // logits per slot
+            float e_arg[16], e_p[16], sum0, sum1;
+            auto arg = [&](int x, int r) { return fmaf(acc[x][r], a.scale_log2, SECOND ? -lse_r[x][r] : -m[x]); };
+            auto vec_begin = [&](int x) {
+                sum0 = sum1 = 0.f;
+#pragma unroll
+                for (int e = 0; e < LPS; ++e) e_arg[e] = arg(x, e);
+            };
+            auto vec_slot = [&](int x, int i) {
+#pragma unroll
+                for (int e = LPS * i; e < LPS * (i + 1); ++e) {
+                    if (i + 1 < NV) e_arg[LPS + e] = arg(x, LPS + e);
+                    e_p[e] = __builtin_amdgcn_exp2f(e_arg[e]);
+                }
+                if (i > 0) {
+#pragma unroll
+                    for (int e = LPS * (i - 1); e < LPS * i; e += 2) sum0 += e_p[e], sum1 += e_p[e + 1];
+                }
+            };
+            auto vec_end = [&](int x, int tile) {
+#pragma unroll
+                for (int e = 16 - LPS; e < 16; e += 2) sum0 += e_p[e], sum1 += e_p[e + 1];
+                if (SECOND) part[tile][x] = sum0 + sum1;
+                else l[x] += sum0 + sum1;
+            };
+            auto softmax = [&](int x, int tile) {
+                vec_begin(x);
+#pragma unroll
+                for (int i = 0; i < NV; ++i) vec_slot(x, i);
+                vec_end(x, tile);
+            };
+            // products of chunk x beside the softmax of the other chunk (of tile `tile` of its step); behind the last use of a
+            // fragment (`next`) the read of tile ns of slot nslot
+            auto phase = [&](int x, int tile, bool next, int nslot, int ns) {
+                vec_begin(x ^ 1);
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    acc[x] = mfma(kf[i], qa[x].v[i], i == 0 ? zero : acc[x]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (next) kf[i] = frag(nslot, ns, i);
+                    vec_slot(x ^ 1, i);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                vec_end(x ^ 1, tile);
+            };
+            auto put = [&](int t) {                       // the column sums of step t: lanes 0-31 its first tile, 32-63 its second
+                if constexpr (SECOND) {
+                    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+                    const u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(part[0][0] + part[0][1]),
+                                                                  __float_as_uint(part[1][0] + part[1][1]), false, false);
+                    out[jb + STEP * t - key_lo + lane] = __uint_as_float(r.x) + __uint_as_float(r.y);
+                }
+            };
+#pragma unroll
+            for (int i = 0; i < NV; ++i) kf[i] = frag(0, 0, i);
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+#pragma unroll
+                for (int x = 0; x < 2; ++x) acc[x] = mfma(kf[i], qa[x].v[i], i == 0 ? zero : acc[x]);
+            if constexpr (!SECOND) {
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    float tmax = acc[x][0];
+#pragma unroll
+                    for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, acc[x][r]);
+                    m[x] = tmax * a.scale_log2;           // scale >= 0 (checked on the host)
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NV; ++i) kf[i] = frag(0, 1, i);
+            softmax(0, 0);
+            // step t from the products of its second tile on, and the first tile of the next one
+            auto step = [&](int t, auto slot_tag) {
+                constexpr int next_slot = (decltype(slot_tag)::value + 1) % RING;
+                phase(0, 0, false, 0, 0);
+                if (t + 1 < n_steps) landed(t + RING - 1 < n_steps);      // step t + 1 is complete, step t's slot free
+                if (t + RING < n_steps) fetch(t + RING);
+                phase(1, 1, true, next_slot, 0);          // (past the last step: fragments that nothing uses)
+                if (t + 1 < n_fast) {
+                    phase(0, 1, false, 0, 0);
+                    put(t);
+                    phase(1, 0, true, next_slot, 1);
+                } else {
+                    softmax(1, 1);
+                    put(t);
+                }
+            };
+            for (int t = 0; t < n_fast; t += RING) {
+                step(t, std::integral_constant<int, 0>{});
+                if (t + 1 < n_fast) step(t + 1, std::integral_constant<int, 1>{});
+                if constexpr (RING > 2) {
+                    if (t + 2 < n_fast) step(t + 2, std::integral_constant<int, 2>{});
+                    if (t + 3 < n_fast) step(t + 3, std::integral_constant<int, 3>{});
+                }
+            }
+        };
+        // One sweep, begun: every wave passes n_steps barriers, whatever its n_fast.
+        auto sweep = [&](bool safe) {
+            landed(false);
+#pragma unroll
+            for (int t = 2; t < RING; ++t)
+                if (t < n_steps) fetch(t);
+            const int seen = (pos_min == INT_MAX ? je : min(je, pos_min + 1)) - jb;      // keys all rows of the wave see
+            const int n_fast = live && !safe && seen >= STEP ? seen / STEP : 0;
+            if (n_fast > 0) fast(n_fast);
+            for (int t = n_fast; t < n_steps; ++t) {
+                for (int s = 0; s < 2 && live; ++s) {
+                    const int j0 = jb + STEP * t + 32 * s;
+                    if (j0 >= je) continue;
+                    HalfRow<LVLM_BF16, HD> kf;
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) kf.v[i] = frag(t % RING, s, i);
+                    careful(j0, n_fast > 0, kf);
+                }
+                if (t + 1 < n_steps) landed(t + RING - 1 < n_steps);
+                if (t + RING < n_steps) fetch(t + RING);
+            }
+        };
+        sweep(false);
+        if constexpr (!SECOND) {
+            if (__syncthreads_or(!(l[0] < 1.0e30f) || !(l[1] < 1.0e30f))) {      // some sum ran away (or is not a number)
+                m[0] = m[1] = -INFINITY, l[0] = l[1] = 0.f;
+                begin();
+                sweep(true);
+            }
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const float mo = other_half(m[x]), lo = other_half(l[x]);
+                const float mn = fmaxf(m[x], mo), ms = (mn == -INFINITY) ? 0.f : mn;
+                l[x] = l[x] * __builtin_amdgcn_exp2f(m[x] - ms) + lo * __builtin_amdgcn_exp2f(mo - ms);
+                if (hf == 0 && rho[x] < GT) {             // this share's part of the rows' normalisers
+                    const long long to = (long long)(share - runs.first(pair)) * rows + rowbase + rho[x];
+                    a.part_m[to] = mn;
+                    a.part_l[to] = l[x];
+                }
+            }
+        }
+        if (at >= at_end) return;
+        __syncthreads();                                  // nobody reads the slots, positions or normalisers any more
+    }
+}
+
 // ---- few query rows: the logits of a chunk over ALL keys in registers, one sweep -------------------------
 // A workgroup of eight waves owns 16 query rows of one (batch, KV head) pair.  Wave w takes the 16-key tiles w, w + 8,
 // ... (NTW of them at most) and keeps every logit -- 4 registers per tile -- so the keys are read and multiplied once
@@ -1234,9 +1599,33 @@ __global__ __launch_bounds__(256) void probs_colsum_vec_kernel(ProbsArgs a, int 
     }
 }
 
+template <int HD, int NW>
+void launch_shares(const Prof &prof, const ScoreArgs &a, bool need_lse) {
+    const int wpp = ((a.G * a.T + 31) / 32 + 2 * NW - 1) / (2 * NW);
+    auto grid = [&](const KeyRuns &r) { return dim3((r.shares + 7) / 8 * 8 * wpp); };
+    if (need_lse) {
+        prof.begin("score_single");
+        LVLM_LAUNCH(prof, (score_shares_kernel<HD, false, NW>), grid(a.runs1), dim3(64 * NW), 0, prof.stream, a);
+        prof.end();
+    }
+    prof.begin("score_single");
+    LVLM_LAUNCH(prof, (score_shares_kernel<HD, true, NW>), grid(a.runs2), dim3(64 * NW), 0, prof.stream, a);
+    prof.end();
+    launch_finalize(prof, a);
+}
+
 template <int DT, int HD, int KPW>
-void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool single, bool shared_tiles, int rows) {
+void launch_passes(const Prof &prof, const ScoreArgs &a, bool need_lse, bool single, bool shared_tiles, int rows, int share_waves) {
     hipStream_t stream = prof.stream;
+    if constexpr (DT == LVLM_BF16) {
+        if (share_waves) {
+            ScoreArgs r = a;
+            r.rs = ((a.G * a.T + 31) / 32 + 1) / 2;       // parts: one per wave
+            if (share_waves == 4) launch_shares<HD, 4>(prof, r, need_lse);
+            else launch_shares<HD, 2>(prof, r, need_lse);
+            return;
+        }
+    }
     constexpr int BN = 4 * KPW * 32;
     constexpr bool can_rows = !(DT == LVLM_F32 && HD == 128);
     if (rows && can_rows) {
@@ -1393,6 +1782,37 @@ static int few_rows(const lvlm_score_desc &d, const ScoreWs &w, int n_chunks, bo
     return d.N <= 2050 || heads >= 8 || wgs >= 64 ? n16 : 0;
 }
 
+// Equal shares of the keys (score_shares_kernel): for bf16 calls of much work, whose two launches and start-up (some 25 us;
+// 11 with the normalisers given) are then worth it.  Work: products of 32 rows and 32 keys, in 1024 SIMDs' turns.  Of 90 random shapes
+// timed both ways (3 to 32 chunks a KV head, 4 or 8 heads of 64 and 128 channels) those beyond the lines gain 10 % on average and
+// lose 0 % at most (15 % and 0 with the normalisers given); between 250 and 320 turns they are 1 % behind, at 100 twenty (88 us
+// 1.0, 55 us 1.2 times).  Under 3072 keys many pairs to a share, each with a start-up of its own, cost what the rest gives (52
+// sequences x 2939 keys 652 -> 683 us, 86 x 443 86 -> 106).  The span has to be visible to every row: the masked path is slow.
+static ScoreShares score_shares(const lvlm_score_desc &d, int n_chunks, bool given) {
+    ScoreShares s{};
+    const long long pairs = (long long)d.B * d.Hkv;
+    const long long tiles = (given ? 0 : (d.N + 31) / 32) + (d.n_img + 31) / 32;
+    if (d.dtype != LVLM_BF16 || n_chunks < 3 || n_chunks > 32 || d.n_img < (given ? 2048 : 3072) || d.k_stride_n * 2 >= (1ll << 25) ||
+        (d.causal && d.q_pos0 + 1 < d.img_begin + d.n_img) || pairs * n_chunks * tiles < 1024ll * (given ? 130 : 320) ||
+        pairs * ((d.N + kShareStep - 1) / kShareStep) >= (1ll << 30))
+        return s;
+    // workgroups of eight chunks, which read the keys half as often, unless ones of four leave fewer places empty
+    s.waves = (n_chunks + 7) / 8 * 8 == (n_chunks + 3) / 4 * 4 ? 4 : 2;
+    const int wpp = (n_chunks + 2 * s.waves - 1) / (2 * s.waves);
+    auto deal = [&](int keys) {
+        KeyRuns r{};
+        r.steps = (keys + kShareStep - 1) / kShareStep;
+        const int total = (int)pairs * r.steps;
+        r.shares = std::min(2048 / s.waves / wpp / 8 * 8, (total + 3) / 4);      // two waves per SIMD, four steps at least
+        r.size = total / r.shares;
+        r.longer = total % r.shares;
+        return r;
+    };
+    s.runs1 = deal(d.N);
+    s.runs2 = deal(d.n_img);
+    return s;
+}
+
 ScoreWs score_ws(const lvlm_score_desc &d) {
     ScoreWs w{};
     // Wide key blocks (2 tiles per wave) once they still give every CU two workgroups.
@@ -1455,13 +1875,17 @@ ScoreWs score_ws(const lvlm_score_desc &d) {
     }
     w.rows = few_rows(d, w, n_chunks, false);
     w.rows_given = few_rows(d, w, n_chunks, true);
+    w.shares = score_shares(d, n_chunks, false);
+    w.shares_given = score_shares(d, n_chunks, true);
     const size_t rows = (size_t)d.B * d.Hq * d.T;
     w.part_m = 0;
-    const size_t n_part = (size_t)w.nkb * 4 > (size_t)w.key_segs ? (size_t)w.nkb * 4 : (size_t)w.key_segs;
+    const int share_parts = w.shares.waves || w.shares_given.waves ? (n_chunks + 1) / 2 : 0;      // of column sums
+    const size_t n_share_part = w.shares.waves ? (size_t)((w.shares.runs1.steps - 1) / w.shares.runs1.size + 2) : 0;
+    const size_t n_part = std::max((size_t)w.nkb * 4, std::max((size_t)w.key_segs, n_share_part));
     w.part_l = align_up(w.part_m + rows * n_part * sizeof(float), 256);
     w.lse2 = align_up(w.part_l + rows * n_part * sizeof(float), 256);
     w.colpart = align_up(w.lse2 + rows * sizeof(float), 256);
-    w.total = align_up(w.colpart + (size_t)std::max(w.rs, std::max(w.rows, w.rows_given)) * d.B * d.Hkv * d.n_img * sizeof(float), 256);
+    w.total = align_up(w.colpart + (size_t)std::max(std::max(w.rs, share_parts), std::max(w.rows, w.rows_given)) * d.B * d.Hkv * d.n_img * sizeof(float), 256);
     return w;
 }
 
@@ -1492,16 +1916,20 @@ hipError_t launch_score(const Prof &prof, const lvlm_score_desc &d, const ScoreW
     const bool need_lse = row_lse == nullptr;
     const bool wide = w.block_keys == 256;
     const int rows = need_lse ? w.rows : w.rows_given;
+    const ScoreShares &sh = need_lse ? w.shares : w.shares_given;
+    const int share_waves = sh.waves;
+    a.runs1 = sh.runs1;
+    a.runs2 = sh.runs2;
     if (d.dtype == LVLM_BF16 && d.hd == 128) {
-        if (wide) launch_passes<LVLM_BF16, 128, 2>(prof, a, need_lse, w.single, w.shared_tiles, rows);
-        else launch_passes<LVLM_BF16, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);
+        if (wide) launch_passes<LVLM_BF16, 128, 2>(prof, a, need_lse, w.single, w.shared_tiles, rows, share_waves);
+        else launch_passes<LVLM_BF16, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows, share_waves);
     } else if (d.dtype == LVLM_BF16 && d.hd == 64) {
-        if (wide) launch_passes<LVLM_BF16, 64, 2>(prof, a, need_lse, w.single, w.shared_tiles, rows);
-        else launch_passes<LVLM_BF16, 64, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);
+        if (wide) launch_passes<LVLM_BF16, 64, 2>(prof, a, need_lse, w.single, w.shared_tiles, rows, share_waves);
+        else launch_passes<LVLM_BF16, 64, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows, share_waves);
     } else if (d.dtype == LVLM_F32 && d.hd == 128) {
-        launch_passes<LVLM_F32, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);
+        launch_passes<LVLM_F32, 128, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows, share_waves);
     } else {
-        launch_passes<LVLM_F32, 64, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows);
+        launch_passes<LVLM_F32, 64, 1>(prof, a, need_lse, w.single, w.shared_tiles, rows, share_waves);
     }
     return hipGetLastError();
 }

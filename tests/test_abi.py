@@ -139,6 +139,32 @@ def test_score_few_rows_rule():
         chunks(1, 100, 4, 6, 4)
 
 
+def test_score_shares_rule():
+    """lvlm_score_shares is the library's own choice of the kernel with equal shares of the keys, at the edges of the rule:
+    work, length, chunks, type, stride, mask, normalisers."""
+    ctx = _ctx()
+
+    def shares(B, N, T, Hq, Hkv, given=False, hd=128, dtype=bd.BF16, stride=None, q_pos0=None, n_img=None, causal=1):
+        d = bd.ScoreDesc(dtype, B, N, T, N - T if q_pos0 is None else q_pos0, Hq, Hkv, hd, 0, n_img or N - T, causal, 0.088,
+                         T * Hq * hd, Hq * hd, hd, N * Hkv * hd, stride or Hkv * hd, hd)
+        return ctx.score_shares(d, given)
+
+    assert shares(12, 5219, 128, 48, 8) == 168                                         # 24 chunks: workgroups of eight, three a pair
+    assert shares(8, 4604, 100, 48, 8) == 200                                          # 19 chunks: of four, five a pair
+    assert shares(8, 5153, 128, 32, 8) == 256 and shares(8, 5152, 128, 32, 8) == 0     # 64 pairs x 16 chunks x 320 tiles, and 318
+    assert shares(8, 4257, 128, 32, 8, given=True) == 256 and shares(8, 4256, 128, 32, 8, given=True) == 0      # x 130, and 129
+    assert shares(96, 3200, 128, 48, 8) == 168 and shares(96, 3199, 128, 48, 8) == 0   # 3072 image keys
+    assert shares(96, 2176, 128, 48, 8, given=True) == 168 and shares(96, 2175, 128, 48, 8, given=True) == 0
+    assert shares(48, 9000, 31, 16, 8) == 0 and shares(48, 9000, 33, 16, 8) > 0        # two and three chunks
+    assert shares(12, 5219, 128, 64, 8) > 0 and shares(12, 5219, 129, 64, 8) == 0      # 32 chunks, and one more
+    assert shares(12, 5219, 128, 48, 8, dtype=bd.F32) == 0
+    assert shares(12, 5219, 128, 48, 8, stride=(1 << 24) - 8) > 0 and shares(12, 5219, 128, 48, 8, stride=1 << 24) == 0
+    assert shares(12, 5219, 128, 48, 8, q_pos0=5090, n_img=5091) > 0 and shares(12, 5219, 128, 48, 8, q_pos0=5089, n_img=5091) == 0
+    assert shares(12, 5219, 128, 48, 8, q_pos0=5089, n_img=5091, causal=0) > 0
+    with pytest.raises(lv.LvlmError):
+        shares(1, 100, 4, 6, 4)
+
+
 def test_score_plan_reports_the_launch_form():
     """lvlm_score_plan is the library's own launch decision (bench.py asks it instead of restating the rule)."""
     ctx = _ctx()

@@ -109,6 +109,59 @@ def test_score_tokens_keys_in_runs(ctx, B, T, Hq, Hkv, n_sys, n_img):
     assert rel_err(sh2.cpu(), osh) < 1e-5 and rel_err(sm2.cpu(), osm) < 1e-5
 
 
+def _score_ref64(q, k, *, q_pos0, img_begin, n_img, causal=True):
+    """The scores in 64 bits on the GPU, head by head (and the rows' normalisers): for shapes the CPU oracle is slow on."""
+    B, T, Hq, d = q.shape
+    N, Hkv = k.shape[1], k.shape[2]
+    sh = torch.zeros(B, Hkv, n_img, dtype=torch.float64, device=DEV)
+    lse = torch.empty(B, Hq, T, device=DEV)
+    hidden = torch.arange(N, device=DEV)[None, :] > q_pos0 + torch.arange(T, device=DEV)[:, None]
+    for b in range(B):
+        for h in range(Hq):
+            s = q[b, :, h].double() @ k[b, :, h // (Hq // Hkv)].double().t() / math.sqrt(d)
+            if causal:
+                s = s.masked_fill(hidden, float("-inf"))
+            lse[b, h] = torch.logsumexp(s, -1).float()
+            sh[b, h // (Hq // Hkv)] += torch.softmax(s, -1)[:, img_begin:img_begin + n_img].sum(0) / (Hq // Hkv)
+    return sh, sh.mean(1), lse
+
+
+@pytest.mark.parametrize("B,T,Hq,Hkv,d,n_sys,n_img,causal", [
+    (4, 128, 48, 8, 128, 0, 6800, True),       # 24 chunks: three workgroups of eight, shares of whole and of two pairs
+    (8, 100, 48, 8, 128, 3, 4501, True),       # 19 chunks: workgroups of four, an empty chunk, a last tile of one key
+    (20, 100, 28, 4, 128, 96, 3100, True),     # G = 7, a long prefix before the span
+    (27, 60, 32, 4, 64, 5, 3333, True),        # 64 channels
+    (34, 11, 32, 4, 64, 0, 13000, False),      # three chunks, the last of 24 rows; no mask
+    (1, 128, 48, 8, 128, 0, 28000, True),      # one sequence: 21 shares and more to a pair
+])
+def test_score_tokens_keys_in_equal_shares(ctx, B, T, Hq, Hkv, d, n_sys, n_img, causal):
+    """Calls of much work deal the keys out in equal shares: the scores of a reference in 64 bits, with the library's own
+    normalisers and with the caller's, and with a logit far above its share's first tile (the sweep that takes that tile's
+    maximum as reference must notice)."""
+    N = n_sys + n_img + T
+    g = torch.Generator(device=DEV).manual_seed(B + n_img)
+    q = torch.randn(B, T, Hq, d, generator=g, device=DEV).to(torch.bfloat16)
+    k = torch.randn(B, N, Hkv, d, generator=g, device=DEV).to(torch.bfloat16)
+    kw = dict(q_pos0=n_sys + n_img, img_begin=n_sys, n_img=n_img, causal=causal)
+    assert ctx.score_shares(ctx.score_desc(q, k, **kw)) > 0 and ctx.score_shares(ctx.score_desc(q, k, **kw), True) > 0
+    for far in (False, True):
+        if far:
+            k[B - 1, n_sys + (7 * n_img) // 8, Hkv - 1] = (40.0 * q[B - 1, T // 2, Hq - 1].float()).to(torch.bfloat16)
+        rsh, rsm, lse = _score_ref64(q, k, **kw)
+        for given in (None, lse):
+            sh, sm = ctx.score_tokens(q, k, row_lse=given, **kw)
+            assert rel_err(sh.cpu(), rsh.cpu()) < 1e-5 and rel_err(sm.cpu(), rsm.cpu()) < 1e-5, (far, given is not None)
+
+
+def test_score_equal_shares_stay_in_their_workspace(ctx):
+    def score(c, reserve):
+        q, k = _rand((8, 100, 48, 128), torch.bfloat16, 192).to(DEV), _rand((8, 4604, 8, 128), torch.bfloat16, 193).to(DEV)
+        kw = dict(q_pos0=4504, img_begin=3, n_img=4501)
+        assert c.score_shares(c.score_desc(q, k, **kw)) > 0
+        c.score_tokens(q, k, reserve=reserve, **kw)
+    _guarded(score)
+
+
 @pytest.mark.parametrize("dtype,B,T,Hq,Hkv,d,n_sys,n_img,causal,scale", [
     (torch.bfloat16, 1, 1, 1, 1, 128, 0, 1, True, None),            # one row, two keys
     (torch.bfloat16, 1, 3, 5, 1, 128, 2, 107, True, None),          # 15 rows, 112 keys: the last wave has no tile
