@@ -22,6 +22,8 @@
 //                    one partial sum.
 //   finalize_kernel  adds the partial sums in chunk order, rounds once and
 //                    writes P_new behind P_unmerged.
+#include <limits.h>
+
 #include "common.h"
 #include "planes.h"
 
@@ -297,73 +299,56 @@ struct IndexArgs {
     int n, n_keep;
 };
 
-// One workgroup per 4096 tokens of a sequence (thread t holds tokens 4t..4t+3 of its chunk).  The workgroup
-// first counts the kept tokens in front of its chunk -- a pass over the ranks before it, all loads in flight
-// together -- so the chunks need nothing from each other; one block-wide scan then gives every kept token its
-// row in P_unmerged.  Then keep_idx (ascending), merged_idx (by rank) and the per-token destination are written.
-constexpr int kIndexChunk = 4096;
+// One workgroup per 1024 tokens of a sequence, one per thread.  The workgroup first counts the kept tokens in front of its
+// chunk -- a pass over the ranks before it, four of a thread's loads in flight together -- so the chunks need nothing from each
+// other; ballots and one exchange through LDS then give every kept token its row in P_unmerged.  Then keep_idx (ascending),
+// merged_idx (by rank) and the per-token destination are written.  Bound by its chain of latencies: with 4096 tokens to a
+// workgroup and scans by lane exchanges 7.1 us at 16384 tokens against 4.7, 7.0 against 3.9 at 8000, 3.4 against 2.7 at 2048.
+constexpr int kIndexChunk = 1024;
 __global__ __launch_bounds__(1024) void index_kernel(IndexArgs a) {
-    __shared__ int wave_tot[16], wave_before[16];
+    __shared__ __attribute__((aligned(16))) int wave_kept[16], wave_before[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.y;
-    const int s0 = blockIdx.x * kIndexChunk;
+    const int s0 = blockIdx.x * kIndexChunk, j = s0 + tid;
     const int n_unmerged = a.n_keep - 1;
     const int32_t *rank = a.rank + (long long)b * a.n;
-    int32_t *dst_of = a.dst_of + (long long)b * a.n;
-    float *wgt = a.wgt + (long long)b * a.n;
     const int m = a.n - n_unmerged;
 
-    // this chunk's ranks
-    int rk[4];
-    const int j0 = s0 + 4 * tid;
-    if (j0 + 3 < a.n && (a.n & 3) == 0) {
-        const int4 v = *reinterpret_cast<const int4 *>(rank + j0);
-        rk[0] = v.x; rk[1] = v.y; rk[2] = v.z; rk[3] = v.w;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) rk[e] = j0 + e < a.n ? rank[j0 + e] : 0x7fffffff;
-    }
-    // kept tokens before the chunk (s0 is a multiple of 4096: whole 16-byte words when the rows are aligned)
-    int before = 0;
+    const int rk = j < a.n ? rank[j] : INT_MAX;
+    // kept tokens before the chunk (s0 is a multiple of 1024: whole 16-byte words when the rows are aligned)
+    uint32_t before = 0;
     if ((a.n & 3) == 0) {
+#pragma unroll 4
         for (int i = 4 * tid; i < s0; i += 4 * 1024) {
             const int4 v = *reinterpret_cast<const int4 *>(rank + i);
             before += (v.x < n_unmerged) + (v.y < n_unmerged) + (v.z < n_unmerged) + (v.w < n_unmerged);
         }
     } else {
+#pragma unroll 4
         for (int i = tid; i < s0; i += 1024) before += rank[i] < n_unmerged;
     }
-    int cnt = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) cnt += rk[e] < n_unmerged;
-    int incl = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-        before += __shfl_xor(before, o);
+    const bool kept = rk < n_unmerged;
+    const unsigned long long bal = __ballot(kept);
+    before = wave_reduce_u32(before, [](uint32_t x, uint32_t y) { return x + y; });
+    if (lane == 0) {
+        wave_kept[wave] = __popcll(bal);
+        wave_before[wave] = (int)before;
     }
-    if (lane == 63) wave_tot[wave] = incl;
-    if (lane == 0) wave_before[wave] = before;
     __syncthreads();
-    int p = incl - cnt;
+    int p = __popcll(bal & ((1ull << lane) - 1ull));
 #pragma unroll
-    for (int w = 0; w < 16; ++w) p += wave_before[w] + (w < wave ? wave_tot[w] : 0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int j = j0 + e;
-        if (j >= a.n) continue;
-        if (rk[e] < n_unmerged) {
-            dst_of[j] = p;
-            wgt[j] = 0.f;
-            if (a.keep_idx) a.keep_idx[(long long)b * n_unmerged + p] = j;
-            ++p;
-        } else {
-            const int k = rk[e] - n_unmerged;
-            dst_of[j] = k == 0 ? -1 : -2;
-            wgt[j] = a.w ? a.w[k] : (float)(m - k) * a.lin_scale;
-            if (a.merged_idx) a.merged_idx[(long long)b * m + k] = j;
-        }
+    for (int w = 0; w < 16; ++w) p += wave_before[w] + (w < wave ? wave_kept[w] : 0);
+    if (j >= a.n) return;
+    const long long at = (long long)b * a.n + j;
+    if (kept) {
+        a.dst_of[at] = p;
+        a.wgt[at] = 0.f;
+        if (a.keep_idx) a.keep_idx[(long long)b * n_unmerged + p] = j;
+    } else {
+        const int k = rk - n_unmerged;
+        a.dst_of[at] = k == 0 ? -1 : -2;
+        a.wgt[at] = a.w ? a.w[k] : (float)(m - k) * a.lin_scale;
+        if (a.merged_idx) a.merged_idx[(long long)b * m + k] = j;
     }
 }
 
@@ -505,18 +490,22 @@ __global__ __launch_bounds__(256 * TEAMS) void gather_kernel(GatherArgs a) {
     }
 }
 
-// P_new[c] = sum of the chunks' partial sums, rounded once.  A workgroup owns 16 columns; its 16 thread
+// P_new[c] = sum of the chunks' partial sums, rounded once.  A workgroup owns S columns; its S thread
 // rows each add a contiguous share of the chunks (independent loads, unrolled), then the shares are
 // added in order -- a fixed summation tree, so the result is reproducible.
-__global__ __launch_bounds__(256) void finalize_kernel(GatherArgs a) {
-    __shared__ float share[16][17];
+// S = 32 shortens the chain where the chunks are many and the workgroups few (413 chunks of 6144 columns 6.5 -> 4.7 us, 360 of 2 x
+// 3584 5.2 -> 4.6); with fewer chunks the larger workgroups cost what it gives (266 of 3584 3.9 -> 4.4), with more than a turn of
+// them they cost more (16 x 5120 columns 6.5 -> 11.2).
+template <int S>
+__global__ __launch_bounds__(S * S) void finalize_kernel(GatherArgs a) {
+    __shared__ float share[S][S + 1];
     const int pi = blockIdx.y / a.B, b = blockIdx.y % a.B;
     const PlaneDev &p = a.plane[pi];
     if (p.rule != LVLM_RULE_WEIGHTED) return;
-    const int col = threadIdx.x & 15, grp = threadIdx.x >> 4;
-    const int c = blockIdx.x * 16 + col;
-    if ((int)blockIdx.x * 16 >= p.row_elems) return;
-    const int per = (p.n_sub + 15) / 16;
+    const int col = threadIdx.x % S, grp = threadIdx.x / S;
+    const int c = blockIdx.x * S + col;
+    if ((int)blockIdx.x * S >= p.row_elems) return;
+    const int per = (p.n_sub + S - 1) / S;
     const int i_lo = grp * per, i_hi = min(p.n_sub, i_lo + per);
     float s = 0.f;
     if (c < p.row_elems) {
@@ -529,7 +518,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(GatherArgs a) {
     if (grp == 0 && c < p.row_elems) {
         float t = 0.f;
 #pragma unroll
-        for (int g2 = 0; g2 < 16; ++g2) t += share[g2][col];
+        for (int g2 = 0; g2 < S; ++g2) t += share[g2][col];
         char *dst = p.dst + (long long)b * p.dst_stride_b + (long long)(a.img_begin + a.n_keep - 1) * p.row_bytes;
         if (p.dtype == LVLM_BF16)
             reinterpret_cast<uint16_t *>(dst)[c] = f32_to_bf16(t);
@@ -666,8 +655,11 @@ hipError_t launch_merge(const Prof &prof, const lvlm_merge_desc &d, const MergeW
     prof.end();
     if (r > 0 && any_weighted) {
         prof.begin("merge_finalize");
-        LVLM_LAUNCH(prof, finalize_kernel, dim3((w.max_row_elems + 15) / 16, d.B * d.n_planes), dim3(256), 0,
-                           stream, g);
+        const dim3 wide((w.max_row_elems + 31) / 32, d.B * d.n_planes);
+        if (w.n_chunk >= 320 && (long long)wide.x * wide.y <= 512)
+            LVLM_LAUNCH(prof, finalize_kernel<32>, wide, dim3(1024), 0, stream, g);
+        else
+            LVLM_LAUNCH(prof, finalize_kernel<16>, dim3((w.max_row_elems + 15) / 16, d.B * d.n_planes), dim3(256), 0, stream, g);
         prof.end();
     }
     return hipGetLastError();

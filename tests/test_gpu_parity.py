@@ -418,6 +418,15 @@ def test_merge_compact_teams_of_a_chunk(ctx, dtype, B, n_sys, n_img, n_txt, C, n
     _merge_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed=n_img)
 
 
+@pytest.mark.parametrize("dtype,B,n_img,C,n_keep", [
+    (torch.bfloat16, 1, 1023, 64, 500), (torch.float32, 2, 1025, 40, 1024),       # index chunks of 1024: one short, one over
+    (torch.bfloat16, 2, 4100, 64, 2), (torch.float32, 3, 2047, 64, 1),            # nearly nothing, nothing kept
+    (torch.bfloat16, 1, 2560, 8200, 1200), (torch.bfloat16, 1, 2552, 8200, 1200), # 320 and 319 chunks of rows: the fold's two widths
+    (torch.float32, 1, 2565, 8195, 900)])                                         # ... a last group of three columns
+def test_merge_compact_index_chunks_and_fold_widths(ctx, dtype, B, n_img, C, n_keep):
+    _merge_case(ctx, dtype, B, 0, n_img, 0, C, n_keep, seed=n_img, extra_planes=False)
+
+
 def test_merge_compact_planes_larger_than_the_memory_side_cache(ctx):
     # more than 256 MiB of source rows are loaded past the caches; the reference runs on the GPU in 64 bits
     B, n_img, C, n_keep = 2, 9000, 7680, 4000
