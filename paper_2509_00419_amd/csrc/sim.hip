@@ -41,50 +41,37 @@ struct SimArgs {
 };
 
 // ---- dominant positions and the list of the other tokens, both in ascending index ----
-// One workgroup per 4096 tokens of a sequence (thread t holds four of them); it counts the dominant tokens in front of
-// its chunk itself, all loads in flight together, so the chunks need nothing from each other.
-constexpr int kSimChunk = 4096;
+// One workgroup per 1024 tokens of a sequence, one per thread; it counts the dominant tokens in front of
+// its chunk itself, four of a thread's loads in flight together, so the chunks need nothing from each other.
+constexpr int kSimChunk = 1024;
 __global__ __launch_bounds__(1024) void sim_index_kernel(SimArgs a) {
-    __shared__ int wave_tot[16], wave_before[16];
+    __shared__ __attribute__((aligned(16))) int wave_dom[16], wave_before[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int b = blockIdx.y, s0 = blockIdx.x * kSimChunk, j0 = s0 + 4 * tid;
+    const int b = blockIdx.y, s0 = blockIdx.x * kSimChunk, j = s0 + tid;
     const int32_t *rank = a.rank + (long long)b * a.n;
-    bool dom[4];
-    int cnt = 0, before = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        dom[e] = j0 + e < a.n && rank[min(j0 + e, a.n - 1)] < a.n_keep;
-        cnt += dom[e];
-    }
+    const bool dom = j < a.n && rank[min(j, a.n - 1)] < a.n_keep;
+    uint32_t before = 0;
 #pragma unroll 4
     for (int i = tid; i < s0; i += 1024) before += rank[i] < a.n_keep;
-    int incl = cnt;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-        before += __shfl_xor(before, o);
+    const unsigned long long bal = __ballot(dom);
+    before = wave_reduce_u32(before, [](uint32_t x, uint32_t y) { return x + y; });
+    if (lane == 0) {
+        wave_dom[wave] = __popcll(bal);
+        wave_before[wave] = (int)before;
     }
-    if (lane == 63) wave_tot[wave] = incl;
-    if (lane == 0) wave_before[wave] = before;
     __syncthreads();
-    int p = incl - cnt;
+    int p = __popcll(bal & ((1ull << lane) - 1ull));
 #pragma unroll
-    for (int w = 0; w < 16; ++w) p += wave_before[w] + (w < wave ? wave_tot[w] : 0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int j = j0 + e;
-        if (j >= a.n) continue;
-        if (dom[e]) {
-            a.dom_of[(long long)b * a.n + j] = p;
-            a.keep_idx[(long long)b * a.n_keep + p] = j;
-            ++p;
-        } else {
-            const int q = j - p;              // tokens before j that are not dominant
-            a.dom_of[(long long)b * a.n + j] = -(q + 1);
-            a.rest_idx[(long long)b * a.r + q] = j;
-            a.best[(long long)b * a.r + q] = 0ull;
-        }
+    for (int w = 0; w < 16; ++w) p += wave_before[w] + (w < wave ? wave_dom[w] : 0);
+    if (j >= a.n) return;
+    if (dom) {
+        a.dom_of[(long long)b * a.n + j] = p;
+        a.keep_idx[(long long)b * a.n_keep + p] = j;
+    } else {
+        const int q = j - p;                  // tokens before j that are not dominant
+        a.dom_of[(long long)b * a.n + j] = -(q + 1);
+        a.rest_idx[(long long)b * a.r + q] = j;
+        a.best[(long long)b * a.r + q] = 0ull;
     }
 }
 
