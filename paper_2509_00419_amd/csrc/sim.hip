@@ -87,8 +87,12 @@ __global__ __launch_bounds__(1024) void sim_index_kernel(SimArgs a) {
 // A direct load fills 1024 consecutive LDS bytes lane by lane, so rows cannot be padded apart; instead the
 // eight 16-byte units of row R lie in the order u ^ (R / 2 % 8), chosen by the address each lane reads from: the sixteen
 // lanes an LDS read serves at a time then hit sixteen different bank groups (no conflicts counted).
-// What bounds a workgroup is the time a slice takes to arrive, so there are three forms:
-//   up to 256 tiles of 128 x 128 (one per compute unit): a ring of four slices, eight waves, the loads of a slice spread
+// What bounds a workgroup is the time a slice takes to arrive, so there are four forms:
+//   up to 288 tiles of 64 x 64: these, on four waves with a ring of four.  A workgroup takes in half the rows of a larger tile, and
+//       more of them do (276 x 300 tokens of 3584 channels 9 -> 25 tiles, the whole call 43.3 -> 32.5 us; 4 x 270 x 630 of 6144 60 -> 200
+//       tiles, 73 -> 56; of 43 shapes up to 288 tiles all gain, 4 to 36 %; 441 tiles are even, 768 lose 14 %; slices of 256 and 512
+//       bytes and a ring of eight give nothing)
+//   more, but up to 256 tiles of 128 x 128 (one per compute unit): a ring of four slices, eight waves, the loads of a slice spread
 //       over the products (a compute unit takes 16 cycles per direct load: all of a slice's at once hold the products up)
 //   more, but up to 256 tiles of 128 x 192 or 192 x 128: these, with a ring of three.  A unit then has one tile and a half to do
 //       instead of up to two, and takes in 320 rows for it instead of 512 (8 x 1263 x 529 of 4096 channels: 400 -> 240 tiles, 61 ->
@@ -567,7 +571,8 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     {
         auto tiles_of = [&](int tm, int tn) { return (long long)d.B * ((d.n_keep + tm - 1) / tm) * ((r + tn - 1) / tn); };
         int tm = 128, tn = 128;
-        if (tiles_of(128, 128) > 256) {
+        if (tiles_of(64, 64) <= 288) tm = tn = 64;
+        else if (tiles_of(128, 128) > 256) {
             if (tiles_of(128, 192) <= 256) tn = 192;
             else if (tiles_of(192, 128) <= 256) tm = 192;
         }
@@ -584,7 +589,8 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     else if (bf) LVLM_GEMM_OF(LVLM_BF16, false, __VA_ARGS__);                                                              \
     else if (ragged) LVLM_GEMM_OF(LVLM_F32, true, __VA_ARGS__);                                                            \
     else LVLM_GEMM_OF(LVLM_F32, false, __VA_ARGS__)
-        if (tn == 192) { LVLM_GEMM(128, 192, 4, 2, 3); }
+        if (tm == 64) { LVLM_GEMM(64, 64, 2, 2, 4); }
+        else if (tn == 192) { LVLM_GEMM(128, 192, 4, 2, 3); }
         else if (tm == 192) { LVLM_GEMM(192, 128, 2, 4, 3); }
         else if (tiles <= 256) { LVLM_GEMM(128, 128, 2, 4, 4); }
         else { LVLM_GEMM(128, 128, 2, 2, 2); }

@@ -1308,6 +1308,9 @@ def test_merge_similar_products_of_several_slices(ctx, dtype, B, n_img, n_keep, 
 
 
 @pytest.mark.parametrize("dtype,B,n_img,n_keep,C", [
+    (torch.bfloat16, 1, 2176, 1152, 328),     # 288 tiles of 64 x 64: the last count of the small ones, six slices, the last partial
+    (torch.bfloat16, 1, 2175, 1087, 256),     # 289 of them: 81 of 128 x 128, one row short in either direction
+    (torch.float32, 3, 430, 129, 72),         # 3 x 3 x 5 small tiles, a dominant row and 45 others in the last ones, fp32
     (torch.bfloat16, 1, 5000, 2000, 256),     # 384 square tiles, 256 of 128 x 192: the last count of the wide ones
     (torch.bfloat16, 1, 4201, 2049, 328),     # 289 -> 204, one dominant row and 104 others in the last tiles, six slices, the last partial
     (torch.float32, 8, 1730, 1200, 72),       # 400 -> 240 over eight sequences, fp32, three slices, the last partial
