@@ -1509,9 +1509,9 @@ void launch_finalize(const Prof &prof, const ScoreArgs &a) {
 }
 
 // ---- scores from probabilities the caller already holds ---------------------------------------------
-// Workgroup (column block, row group c): thread j sums probs[b][g*G + hl][i][img_begin + j] over the 32
-// rows rho = hl*T + i of group c (neighbouring threads read neighbouring columns), all 32 loads in flight;
-// the per-group sums go through the same finalize kernel as the column sums of the passes.
+// Workgroup (column block, row group c): thread (sub, cj) sums the 16 / ES columns of word cj of
+// probs[b][g*G + hl][i][img_begin ..] over rows 8 sub .. of the group's 32 rows rho = hl*T + i, all of its loads in flight; the four
+// row subsets are folded through LDS, the groups' sums go through the same finalize kernel as the column sums of the passes.
 struct ProbsArgs {
     const char *p;
     float *colpart;
@@ -1520,37 +1520,13 @@ struct ProbsArgs {
     long long psb, psh, pst;
 };
 
-template <int DT>
+// Bound by HBM.  Rows of odd lengths start anywhere: a word is then loaded from an address aligned to an element only (the memory
+// pipeline takes it whole, a wave touches nine lines for eight), and the last word of a row, where it is partial, element by element.
+// Against one element per thread and load: 4 x 28 x 150 rows of 9000 of 9150 columns 178 -> 69 us for the call (4.4 TB/s), 4 x 48 x 130
+// of 15000 of 15194 416 -> 160.
+// ONCE: loads past the caches, for a matrix that outgrows the 256 MB cache in front of the memory.
+template <int DT, bool ALIGNED, bool ONCE>
 __global__ __launch_bounds__(256) void probs_colsum_kernel(ProbsArgs a, int n_col_blocks) {
-    constexpr int ES = esize<DT>();
-    const int cb = blockIdx.x % n_col_blocks, c = blockIdx.x / n_col_blocks;
-    const int g = blockIdx.y, b = blockIdx.z;
-    const int j = cb * 256 + threadIdx.x;
-    if (j >= a.n_img) return;
-    const int GT = a.G * a.T;
-    const int r0 = c * 32, r1 = min(GT, r0 + 32);
-    const char *base = a.p + ((long long)b * a.psb + (long long)g * a.G * a.psh + a.img_begin + j) * ES;
-    auto at = [&](int rho) -> float {
-        const int hl = a.T == 1 ? rho : (int)__umulhi((unsigned)rho, a.t_magic), i = rho - hl * a.T;
-        const char *q = base + ((long long)hl * a.psh + (long long)i * a.pst) * ES;
-        if constexpr (DT == LVLM_BF16) return bf16_to_f32(*reinterpret_cast<const uint16_t *>(q));
-        else return *reinterpret_cast<const float *>(q);
-    };
-    // all 32 loads of the group are issued before the first is used
-    float v[32];
-#pragma unroll
-    for (int u = 0; u < 32; ++u) v[u] = r0 + u < r1 ? at(r0 + u) : 0.f;
-    float sum = 0.f;
-#pragma unroll
-    for (int u = 0; u < 32; ++u) sum += v[u];
-    a.colpart[(((long long)c * a.B + b) * a.Hkv + g) * a.n_img + j] = sum;
-}
-
-// The same with 16-byte loads, for probabilities whose rows and image span start on 16-byte boundaries and
-// whose image span is a whole number of 16-byte words: thread (sub, cj) sums 8 rows (group c, rows 8 sub ..)
-// of the 16 / ES columns of word cj; the four row subsets are folded through LDS.
-template <int DT>
-__global__ __launch_bounds__(256) void probs_colsum_vec_kernel(ProbsArgs a, int n_col_blocks) {
     constexpr int ES = esize<DT>();
     constexpr int CPT = 16 / ES;              // columns per thread
     constexpr int WC = 64 * CPT;              // columns per workgroup
@@ -1567,11 +1543,33 @@ __global__ __launch_bounds__(256) void probs_colsum_vec_kernel(ProbsArgs a, int 
     if (j0 < a.n_img) {
         const char *base = a.p + ((long long)b * a.psb + (long long)g * a.G * a.psh + a.img_begin + j0) * ES;
         uint4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        auto row_at = [&](int u) {
             const int rho = min(r0 + u, GT - 1);
             const int hl = a.T == 1 ? rho : (int)__umulhi((unsigned)rho, a.t_magic), i = rho - hl * a.T;
-            v[u] = *reinterpret_cast<const uint4 *>(base + ((long long)hl * a.psh + (long long)i * a.pst) * ES);
+            return base + ((long long)hl * a.psh + (long long)i * a.pst) * ES;
+        };
+        if (ALIGNED || j0 + CPT <= a.n_img) {
+            typedef unsigned word16 __attribute__((ext_vector_type(4)));
+            typedef unsigned word2 __attribute__((ext_vector_type(4), aligned(2)));
+            using word = std::conditional_t<ALIGNED, word16, word2>;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const word *at = reinterpret_cast<const word *>(row_at(u));
+                v[u] = __builtin_bit_cast(uint4, ONCE ? __builtin_nontemporal_load(at) : *at);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const char *at = row_at(u);
+                uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int e = 0; e < CPT - 1; ++e) {
+                    if (j0 + e >= a.n_img) continue;
+                    if constexpr (DT == LVLM_BF16) w[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(at)[e] << (16 * (e & 1));
+                    else w[e] = reinterpret_cast<const uint32_t *>(at)[e];
+                }
+                v[u] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
@@ -1714,24 +1712,24 @@ hipError_t launch_score_probs(const Prof &prof, const lvlm_probs_desc &d, const 
     pa.t_magic = (unsigned)(0x100000000ull / (unsigned long long)d.T) + 1u;
     pa.psb = d.p_stride_b; pa.psh = d.p_stride_h; pa.pst = d.p_stride_t;
     const int es = d.dtype == LVLM_BF16 ? 2 : 4, cpt = 16 / es;
-    const bool vec = (d.p_stride_b * es) % 16 == 0 && (d.p_stride_h * es) % 16 == 0 && (d.p_stride_t * es) % 16 == 0 &&
-                     (d.img_begin * es) % 16 == 0 && d.n_img % cpt == 0;      // the base pointer is 16-byte aligned
+    const bool aligned = (d.p_stride_b * es) % 16 == 0 && (d.p_stride_h * es) % 16 == 0 && (d.p_stride_t * es) % 16 == 0 &&
+                         (d.img_begin * es) % 16 == 0 && d.n_img % cpt == 0;      // the base pointer is 16-byte aligned
+    // (2 x 48 x 128 rows of 16384 columns, 403 MB: 85 -> 79 us with loads past the caches)
+    const bool once = (long long)d.B * d.Hq * d.T * d.n_img * es > (320ll << 20);
+    const int ncb = (d.n_img + 64 * cpt - 1) / (64 * cpt);
+    const dim3 grid(ncb * w.rs, d.Hkv, d.B);
     prof.begin("score_probs");
-    if (vec) {
-        const int ncb = (d.n_img + 64 * cpt - 1) / (64 * cpt);
-        const dim3 grid(ncb * w.rs, d.Hkv, d.B);
-        if (d.dtype == LVLM_BF16)
-            LVLM_LAUNCH(prof, probs_colsum_vec_kernel<LVLM_BF16>, grid, dim3(256), 0, prof.stream, pa, ncb);
-        else
-            LVLM_LAUNCH(prof, probs_colsum_vec_kernel<LVLM_F32>, grid, dim3(256), 0, prof.stream, pa, ncb);
-    } else {
-        const int ncb = (d.n_img + 255) / 256;
-        const dim3 grid(ncb * w.rs, d.Hkv, d.B);
-        if (d.dtype == LVLM_BF16)
-            LVLM_LAUNCH(prof, probs_colsum_kernel<LVLM_BF16>, grid, dim3(256), 0, prof.stream, pa, ncb);
-        else
-            LVLM_LAUNCH(prof, probs_colsum_kernel<LVLM_F32>, grid, dim3(256), 0, prof.stream, pa, ncb);
-    }
+#define LVLM_PROBS(DT, ALIGNED, ONCE) \
+    LVLM_LAUNCH(prof, (probs_colsum_kernel<DT, ALIGNED, ONCE>), grid, dim3(256), 0, prof.stream, pa, ncb)
+#define LVLM_PROBS_OF(DT)                              \
+    if (aligned && once) LVLM_PROBS(DT, true, true);   \
+    else if (aligned) LVLM_PROBS(DT, true, false);     \
+    else if (once) LVLM_PROBS(DT, false, true);        \
+    else LVLM_PROBS(DT, false, false)
+    if (d.dtype == LVLM_BF16) { LVLM_PROBS_OF(LVLM_BF16); }
+    else { LVLM_PROBS_OF(LVLM_F32); }
+#undef LVLM_PROBS_OF
+#undef LVLM_PROBS
     prof.end();
     ScoreArgs a{};
     a.colpart = pa.colpart;

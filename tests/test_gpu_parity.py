@@ -322,6 +322,23 @@ def test_score_from_probs(ctx, dtype):
     assert rel_err(a_h.cpu(), b_h.cpu()) < 1e-5 and rel_err(a_m.cpu(), b_m.cpu()) < 1e-5
 
 
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,T,N,img0,n_img", [
+    *[(torch.bfloat16, 2, 6, 2, 11, 640 + x, x, 512 + 8 - x) for x in range(8)],       # every misalignment, every partial last word
+    (torch.bfloat16, 1, 4, 4, 1, 9, 2, 7), (torch.bfloat16, 1, 4, 1, 9, 8, 0, 1),      # less than a word
+    (torch.bfloat16, 2, 4, 2, 33, 1031, 4, 1027), (torch.float32, 2, 4, 2, 33, 515, 0, 515),
+    (torch.float32, 1, 2, 1, 40, 262, 3, 256), (torch.float32, 1, 2, 2, 3, 5, 1, 3),
+    (torch.bfloat16, 3, 28, 4, 150, 13001, 0, 13001)])                                 # 328 MB of them: past the caches
+def test_score_from_probs_of_rows_that_start_anywhere(ctx, dtype, B, Hq, Hkv, T, N, img0, n_img):
+    """Whole words from addresses aligned to an element, and partial last words, against sums in 64 bits."""
+    g = torch.Generator(device=DEV).manual_seed(N)
+    p = torch.rand(B, Hq, T, N, generator=g, device=DEV).to(dtype)
+    p[..., :img0] = float("nan")                         # columns outside the span count for nothing
+    p[..., img0 + n_img:] = float("nan")
+    sh, sm = ctx.score_from_probs(p, n_kv_heads=Hkv, img_begin=img0, n_img=n_img)
+    ref = torch.stack([p[b, :, :, img0:img0 + n_img].double().sum(1).view(Hkv, Hq // Hkv, n_img).mean(1) for b in range(B)])
+    assert rel_err(sh.cpu(), ref.cpu()) < 1e-5 and rel_err(sm.cpu(), ref.mean(1).cpu()) < 1e-5
+
+
 def test_score_batched_form_with_logits_far_above_the_first_tile(ctx):
     # 32 sequences x 8 KV heads, three query chunks each: the one-launch form whose workgroups share the key tiles.
     # Its first sweep keeps the first tile's reference; keys whose logits lie far above everything before them
