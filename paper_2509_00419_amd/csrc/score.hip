@@ -1877,13 +1877,18 @@ ScoreWs score_ws(const lvlm_score_desc &d) {
     w.shares_given = score_shares(d, n_chunks, true);
     const size_t rows = (size_t)d.B * d.Hq * d.T;
     w.part_m = 0;
-    const int share_parts = w.shares.waves || w.shares_given.waves ? (n_chunks + 1) / 2 : 0;      // of column sums
-    const size_t n_share_part = w.shares.waves ? (size_t)((w.shares.runs1.steps - 1) / w.shares.runs1.size + 2) : 0;
-    const size_t n_part = std::max((size_t)w.nkb * 4, std::max((size_t)w.key_segs, n_share_part));
+    const size_t n_part = std::max((size_t)w.nkb * 4, (size_t)w.key_segs), n_col = (size_t)std::max(w.rs, std::max(w.rows, w.rows_given));
+    // Equal shares have to do with the scratch of the forms they replace, so that a workspace which held a call still does: a few
+    // shapes of some 100000 keys, whose query chunks the two passes split over fewer workgroups than the shares leave parts, are not
+    // worth up to 1.44 times the bytes.
+    const size_t share_parts = (size_t)(n_chunks + 1) / 2;      // of column sums
+    if (share_parts > n_col || (w.shares.waves && (size_t)((w.shares.runs1.steps - 1) / w.shares.runs1.size + 2) > n_part))
+        w.shares = ScoreShares{};
+    if (share_parts > n_col) w.shares_given = ScoreShares{};
     w.part_l = align_up(w.part_m + rows * n_part * sizeof(float), 256);
     w.lse2 = align_up(w.part_l + rows * n_part * sizeof(float), 256);
     w.colpart = align_up(w.lse2 + rows * sizeof(float), 256);
-    w.total = align_up(w.colpart + (size_t)std::max(std::max(w.rs, share_parts), std::max(w.rows, w.rows_given)) * d.B * d.Hkv * d.n_img * sizeof(float), 256);
+    w.total = align_up(w.colpart + n_col * d.B * d.Hkv * d.n_img * sizeof(float), 256);
     return w;
 }
 
