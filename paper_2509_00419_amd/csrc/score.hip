@@ -1791,7 +1791,7 @@ static ScoreShares score_shares(const lvlm_score_desc &d, int n_chunks, bool giv
     const long long pairs = (long long)d.B * d.Hkv;
     const long long tiles = (given ? 0 : (d.N + 31) / 32) + (d.n_img + 31) / 32;
     if (d.dtype != LVLM_BF16 || n_chunks < 3 || n_chunks > 32 || d.n_img < (given ? 2048 : 3072) || d.k_stride_n * 2 >= (1ll << 25) ||
-        (d.causal && d.q_pos0 + 1 < d.img_begin + d.n_img) || pairs * n_chunks * tiles < 1024ll * (given ? 130 : 320) ||
+        (d.causal && d.q_pos0 < d.img_begin + d.n_img - 1) || pairs * n_chunks * tiles < 1024ll * (given ? 130 : 320) ||
         pairs * ((d.N + kShareStep - 1) / kShareStep) >= (1ll << 30))
         return s;
     // workgroups of eight chunks, which read the keys half as often, unless ones of four leave fewer places empty

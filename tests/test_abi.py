@@ -161,6 +161,7 @@ def test_score_shares_rule():
     assert shares(12, 5219, 128, 48, 8, stride=(1 << 24) - 8) > 0 and shares(12, 5219, 128, 48, 8, stride=1 << 24) == 0
     assert shares(12, 5219, 128, 48, 8, q_pos0=5090, n_img=5091) > 0 and shares(12, 5219, 128, 48, 8, q_pos0=5089, n_img=5091) == 0
     assert shares(12, 5219, 128, 48, 8, q_pos0=5089, n_img=5091, causal=0) > 0
+    assert shares(12, 5219, 128, 48, 8, q_pos0=2 ** 31 - 1) > 0                         # (the trap build: nothing overflows)
     assert shares(1, 125836, 33, 40, 4) == 0               # six parts of column sums, where the two passes' scratch holds one
     with pytest.raises(lv.LvlmError):
         shares(1, 100, 4, 6, 4)
