@@ -144,7 +144,8 @@ LVLM_API lvlm_status lvlm_merge_weights(lvlm_merge_mode mode, int m, float *w_ho
 typedef struct {
     int32_t dtype;     /* LVLM_BF16 or LVLM_F32: element type of q and k          */
     int32_t B, N, T;   /* batch, keys per sequence, query rows                    */
-    int32_t q_pos0;    /* absolute position of query row 0                        */
+    int32_t q_pos0;    /* absolute position of query row 0 (>= 0; from N on all the
+                          same: every row sees every key)                          */
     int32_t Hq, Hkv;   /* query heads, KV heads (Hq % Hkv == 0)                   */
     int32_t hd;        /* head dimension: 64 or 128                               */
     int32_t img_begin; /* first image key                                         */

@@ -49,6 +49,14 @@ struct ScoreShares {
     int waves;     // per workgroup, two query chunks each; 0: not that form
     KeyRuns runs1, runs2;   // the normaliser sweep over all keys, the column sums over the image keys
 };
+// Position of query row 0 as the kernels take it.  A row at or behind the last key sees every key, so all positions beyond the
+// keys are one, and a row's number (below 2^16) added to this one cannot overflow.
+inline int first_row_position(const lvlm_score_desc &d) { return d.q_pos0 < d.N ? d.q_pos0 : d.N; }
+// Whole steps of the keys [jb, je), from jb on, that a row at position `pos` sees: inside the range whatever the position is.
+__host__ __device__ inline int steps_seen(int jb, int je, int pos, int step) {
+    const int last = pos < je - 1 ? pos : je - 1;
+    return last >= jb + step - 1 ? (last - jb + 1) / step : 0;
+}
 struct ScoreWs {
     size_t part_m, part_l, lse2, colpart, total;
     int nkb;       // key blocks of the normaliser pass

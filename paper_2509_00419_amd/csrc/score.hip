@@ -1118,8 +1118,7 @@ __global__ __launch_bounds__(64 * NW, 2) void score_shares_kernel(ScoreArgs a) {
 #pragma unroll
             for (int t = 2; t < RING; ++t)
                 if (t < n_steps) fetch(t);
-            const int seen = (pos_min == INT_MAX ? je : min(je, pos_min + 1)) - jb;      // keys all rows of the wave see
-            const int n_fast = live && !safe && seen >= STEP ? seen / STEP : 0;
+            const int n_fast = live && !safe ? steps_seen(jb, je, pos_min, STEP) : 0;      // steps that all rows of the wave see
             if (n_fast > 0) fast(n_fast);
             for (int t = n_fast; t < n_steps; ++t) {
                 for (int s = 0; s < 2 && live; ++s) {
@@ -1908,7 +1907,7 @@ hipError_t launch_score(const Prof &prof, const lvlm_score_desc &d, const ScoreW
     a.t_magic = (unsigned)(0x100000000ull / (unsigned long long)d.T) + 1u;
     a.score_head = score_head;
     a.score_mean = score_mean;
-    a.B = d.B; a.N = d.N; a.T = d.T; a.q_pos0 = d.q_pos0; a.Hq = d.Hq; a.Hkv = d.Hkv; a.G = d.Hq / d.Hkv;
+    a.B = d.B; a.N = d.N; a.T = d.T; a.q_pos0 = first_row_position(d); a.Hq = d.Hq; a.Hkv = d.Hkv; a.G = d.Hq / d.Hkv;
     a.img_begin = d.img_begin; a.n_img = d.n_img; a.causal = d.causal; a.nkb = w.nkb;
     a.scale_log2 = d.scale * kLog2e;
     a.qsb = d.q_stride_b; a.qst = d.q_stride_t; a.qsh = d.q_stride_h;

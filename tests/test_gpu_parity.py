@@ -153,6 +153,28 @@ def test_score_tokens_keys_in_equal_shares(ctx, B, T, Hq, Hkv, d, n_sys, n_img, 
             assert rel_err(sh.cpu(), rsh.cpu()) < 1e-5 and rel_err(sm.cpu(), rsm.cpu()) < 1e-5, (far, given is not None)
 
 
+@pytest.mark.parametrize("dtype,B,T,Hq,Hkv,d,n_img,form", [
+    (torch.bfloat16, 2, 9, 6, 2, 128, 5000, "two passes"), (torch.float32, 2, 5, 4, 2, 128, 700, "two passes"),
+    (torch.float32, 1, 40, 4, 4, 128, 200, "one launch"), (torch.bfloat16, 32, 20, 32, 8, 128, 600, "shared tiles"),
+    (torch.bfloat16, 4, 128, 48, 8, 128, 2072, "runs"), (torch.bfloat16, 1, 64, 28, 4, 128, 717, "few rows"),
+    (torch.bfloat16, 8, 100, 48, 8, 128, 4504, "equal shares")])
+def test_score_positions_behind_the_last_key_are_all_the_same(ctx, dtype, B, T, Hq, Hkv, d, n_img, form):
+    """Rows at the largest positions a call may name see every key, as without a mask: bit for bit, in every form."""
+    N = n_img + T
+    g = torch.Generator(device=DEV).manual_seed(n_img)
+    q = torch.randn(B, T, Hq, d, generator=g, device=DEV).to(dtype)
+    k = torch.randn(B, N, Hkv, d, generator=g, device=DEV).to(dtype)
+    kw = dict(img_begin=0, n_img=n_img)
+    desc = ctx.score_desc(q, k, q_pos0=N, causal=False, **kw)
+    taken = ("equal shares" if ctx.score_shares(desc) else "few rows" if ctx.score_few_rows(desc) else
+             ["two passes", "one launch", "shared tiles", "runs"][ctx.score_plan(desc)])
+    assert taken == form
+    want = ctx.score_tokens(q, k, q_pos0=N, causal=False, **kw)
+    for q_pos0 in (N - 1, N, 2 ** 31 - T, 2 ** 31 - T + 1, 2 ** 31 - 1):
+        got = ctx.score_tokens(q, k, q_pos0=q_pos0, causal=True, **kw)
+        assert all(torch.equal(x, y) for x, y in zip(got, want)), q_pos0
+
+
 def test_score_equal_shares_stay_in_their_workspace(ctx):
     def score(c, reserve):
         q, k = _rand((8, 100, 48, 128), torch.bfloat16, 192).to(DEV), _rand((8, 4604, 8, 128), torch.bfloat16, 193).to(DEV)
