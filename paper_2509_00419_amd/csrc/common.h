@@ -101,6 +101,17 @@ struct KvWs {
     size_t src, total;
 };
 KvWs kv_ws(const lvlm_kv_desc &d);
+constexpr int kFillRows = 32;      // moves per batch of kv_fill_kernel
+constexpr int kFillWgs = 32768;    // workgroups its launch aims for
+// Workgroups of kv_fill_kernel per head: some kFillWgs in all (2 % over 16384 where heads are many), at most one per batch of
+// moves the longest head can have, and an odd number of them.  A head's first workgroups find its moves and the others nothing, and
+// workgroups go to the 8 XCDs and the 4 shader engines of each in turn: by an even number per head, the ones with work are the
+// same few engines' in every head (32 per head -> 33, caches just read: 800 heads of 2000 entries of 256 bytes at a third kept by mass
+// 98 -> 64 us, with a budget of 200 83 -> 35, 500 heads 64 -> 40).
+inline int kv_fill_workgroups(long long heads, int max_moves) {
+    const long long most = (max_moves + kFillRows - 1) / kFillRows, share = (kFillWgs + heads - 1) / heads;
+    return (int)(share < most ? share : most) | 1;
+}
 
 struct AttnWs {
     size_t part_ml, part_o, logits, cur_len, total;

@@ -596,8 +596,6 @@ __global__ __launch_bounds__(NT, WPE) void kv_select_kernel(KvArgs a) {
 }
 
 constexpr int kFillInKernel = 64;  // most FILL moves per head that the selection kernel performs itself
-constexpr int kFillRows = 32;      // moves per batch of kv_fill_kernel (at most 4 row units per thread)
-constexpr int kFillWgs = 32768;    // workgroups the fill launch aims for
 constexpr long long kFillCached = 256ll << 20;     // bytes of rows that the memory-side cache can hold
 
 // LVLM_ORDER_FILL with many moves per head: entry list_b[i] (at or beyond the new length) goes to hole
@@ -605,7 +603,7 @@ constexpr long long kFillCached = 256ll << 20;     // bytes of rows that the mem
 // Bound by HBM, and by the chain lengths -> slots -> rows in front of it.  The rows are stored past the caches, and loaded past
 // them too (ONCE) where the call's heads span more than the 256 MB cache in front of the memory: 1536 heads of 1888 entries of
 // 256 bytes 157 -> 138 us (the stores alone: 148), 192 heads of 16512 the same; of 112 heads of 2115, which fit, the call would
-// take 33.6 instead of 29.2 us with such loads (start: 30.2).  32768 workgroups against 16384: 2 % where heads are many.
+// take 33.6 instead of 29.2 us with such loads (start: 30.2).  Workgroups: kv_fill_workgroups.
 template <bool ONCE>
 __global__ __launch_bounds__(256) void kv_fill_kernel(KvArgs a) {
     const int tid = threadIdx.x;
@@ -811,11 +809,7 @@ hipError_t launch_kv_compress(const Prof &prof, const lvlm_kv_desc &d, const KvW
         prof.end();
     } else if (a.fill_external) {
         prof.begin("kv_fill");
-        // about 32768 workgroups in all, at most one per batch of moves the longest head can have
-        const long long most = (max_moves + kFillRows - 1) / kFillRows;
-        long long per_head = (kFillWgs + (long long)heads - 1) / (long long)heads;
-        per_head = per_head < 1 ? 1 : (per_head > most ? most : per_head);
-        const dim3 fill_grid((unsigned)per_head, (unsigned)heads);
+        const dim3 fill_grid((unsigned)kv_fill_workgroups((long long)heads, max_moves), (unsigned)heads);
         if (2ll * (long long)heads * bound * a.row_bytes > kFillCached) LVLM_LAUNCH(prof, kv_fill_kernel<true>, fill_grid, dim3(256), 0, stream, a);
         else LVLM_LAUNCH(prof, kv_fill_kernel<false>, fill_grid, dim3(256), 0, stream, a);
         prof.end();

@@ -1,0 +1,43 @@
+"""Rules of the cache compression's launches: the library's own host arithmetic, compiled on its own (no GPU needed)."""
+import importlib.util
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _run(tmp_path, body):
+    """Compiles `body` (the statements of main) against the library's header, host side only, and runs it."""
+    spec = importlib.util.spec_from_file_location("lvlm_build", os.path.join(ROOT, "paper_2509_00419_amd", "build.py"))
+    build = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(build)
+    src, exe = str(tmp_path / "rules.hip"), str(tmp_path / "rules")
+    with open(src, "w") as f:
+        f.write('#include "common.h"\n#include <algorithm>\nusing namespace lvlm;\nint main() {\n' + body + "\n    return 0;\n}\n")
+    subprocess.run([build.HIPCC, "--offload-host-only", "--offload-arch=gfx950", "-std=c++17", "-O1", "-I" + build.CSRC, "-Xarch_host",
+                    "-fsanitize=undefined", "-Xarch_host", "-fsanitize-trap=undefined", src, "-o", exe], check=True)
+    assert subprocess.run([exe]).returncode == 0
+
+
+def test_fill_workgroups_with_work_are_spread_over_the_chip(tmp_path):
+    """Workgroups go round 8 XCDs of 4 shader engines in launch order, and a head's first ones have its moves: whatever the
+    heads and bounds, every engine gets its share of those."""
+    _run(tmp_path, r"""
+    for (long long heads : {256, 400, 500, 640, 800, 1000, 1024, 1536, 2048, 4096})
+        for (int max_moves : {65, 250, 512, 1000, 1024, 2048, 8192}) {
+            const int wgs = kv_fill_workgroups(heads, max_moves), most = (max_moves + kFillRows - 1) / kFillRows;
+            if (wgs < 1 || wgs > most + 1 || wgs * heads < std::min<long long>(kFillWgs, heads * most)) return 1;
+            for (int eighths = 1; eighths <= 4; ++eighths) {               // batches a head really has
+                const int batches = std::max(1, most * eighths / 8);
+                long long load[32] = {}, total = 0, top = 0;
+                for (long long h = 0; h < heads; ++h)
+                    for (int x = 0; x < wgs && x < batches; ++x) {
+                        const long long at = h * wgs + x, n = (batches - x + wgs - 1) / wgs;
+                        load[at % 8 * 4 + at / 8 % 4] += n;
+                        total += n;
+                    }
+                for (long long l : load) top = std::max(top, l);
+                if (32 * top > total + total / 4 + 64 * most) return 2;
+            }
+        }
+    if (kv_fill_workgroups(1, 1 << 30) != (kFillWgs | 1)) return 3;""")
