@@ -113,6 +113,15 @@ inline int kv_fill_workgroups(long long heads, int max_moves) {
     return (int)(share < most ? share : most) | 1;
 }
 
+// Whether kv_fill_kernel loads the rows of a head of `entries` entries past the caches: where all heads, taken as long as this one,
+// hold more rows than the 256 MB cache in front of the memory, so that those written or read last push the others out.  The
+// lengths count, not what the caller reserves.  Moves loaded through the caches -> past them, us: 1536 heads of 1888 entries of
+// 256 bytes 182 -> 133 where the caches have just been written, 131 -> 121 just read, 183 -> 132 long before; 500 heads of 2000
+// (488 MB) 52 -> 50, 42 -> 41, 76 -> 52; 112 heads of 2115 (115 MB), 16512 reserved, 11 -> 14, 10 -> 11, 21 -> 16.
+__host__ __device__ inline bool fill_past_caches(long long heads, long long entries, int row_bytes) {
+    return 2 * heads * entries * row_bytes > (256ll << 20);
+}
+
 struct AttnWs {
     size_t part_ml, part_o, logits, cur_len, total;
     int n_split, split_len, lcap, tail_entry;

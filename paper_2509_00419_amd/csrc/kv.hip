@@ -564,7 +564,7 @@ __global__ __launch_bounds__(NT, WPE) void kv_select_kernel(KvArgs a) {
     const int n_moves = base_hole;           // = base_tail: as many holes as tail survivors
     if (a.fill_external) {
         if (tid == 0) {
-            a.meta[2 * hg] = n_new;
+            a.meta[2 * hg] = L;
             a.meta[2 * hg + 1] = n_moves;
             a.len[hg] = n_new;
             if (a.n_evicted) a.n_evicted[hg] = n_evict;
@@ -596,19 +596,14 @@ __global__ __launch_bounds__(NT, WPE) void kv_select_kernel(KvArgs a) {
 }
 
 constexpr int kFillInKernel = 64;  // most FILL moves per head that the selection kernel performs itself
-constexpr long long kFillCached = 256ll << 20;     // bytes of rows that the memory-side cache can hold
 
 // LVLM_ORDER_FILL with many moves per head: entry list_b[i] (at or beyond the new length) goes to hole
 // list_a[i] (below it).  Sources and destinations are disjoint, so the moves are independent.
-// Bound by HBM, and by the chain lengths -> slots -> rows in front of it.  The rows are stored past the caches, and loaded past
-// them too (ONCE) where the call's heads span more than the 256 MB cache in front of the memory: 1536 heads of 1888 entries of
-// 256 bytes 157 -> 138 us (the stores alone: 148), 192 heads of 16512 the same; of 112 heads of 2115, which fit, the call would
-// take 33.6 instead of 29.2 us with such loads (start: 30.2).  Workgroups: kv_fill_workgroups.
+// Bound by HBM, and by the chain lengths -> slots -> rows in front of it.  The rows are stored past the caches.  ONCE: they are
+// loaded past them too (fill_past_caches).  Workgroups: kv_fill_workgroups.
 template <bool ONCE>
-__global__ __launch_bounds__(256) void kv_fill_kernel(KvArgs a) {
+__device__ __forceinline__ void fill_moves(const KvArgs &a, int hg, int n_moves) {
     const int tid = threadIdx.x;
-    const int hg = blockIdx.y;
-    const int n_moves = a.meta[2 * hg + 1];
     const long long base = (long long)hg * a.Lmax;
     const int ulog = 31 - __clz(a.row_bytes >> 4);        // units of a row: a power of two up to 32
     char *kc = a.k + base * a.row_bytes;
@@ -662,6 +657,13 @@ __global__ __launch_bounds__(256) void kv_fill_kernel(KvArgs a) {
         a.pos[base + dst] = ps;
     }
     }
+}
+
+__global__ __launch_bounds__(256) void kv_fill_kernel(KvArgs a) {
+    const int hg = blockIdx.y;
+    const int2 head = reinterpret_cast<const int2 *>(a.meta)[hg];     // its entries before the call, its moves
+    if (fill_past_caches(gridDim.y, head.x, a.row_bytes)) fill_moves<true>(a, hg, head.y);
+    else fill_moves<false>(a, hg, head.y);
 }
 
 constexpr int kMoveUpt = 8;       // 16-byte units per thread per step (two such sets are in flight)
@@ -809,9 +811,7 @@ hipError_t launch_kv_compress(const Prof &prof, const lvlm_kv_desc &d, const KvW
         prof.end();
     } else if (a.fill_external) {
         prof.begin("kv_fill");
-        const dim3 fill_grid((unsigned)kv_fill_workgroups((long long)heads, max_moves), (unsigned)heads);
-        if (2ll * (long long)heads * bound * a.row_bytes > kFillCached) LVLM_LAUNCH(prof, kv_fill_kernel<true>, fill_grid, dim3(256), 0, stream, a);
-        else LVLM_LAUNCH(prof, kv_fill_kernel<false>, fill_grid, dim3(256), 0, stream, a);
+        LVLM_LAUNCH(prof, kv_fill_kernel, dim3((unsigned)kv_fill_workgroups((long long)heads, max_moves), (unsigned)heads), dim3(256), 0, stream, a);
         prof.end();
     }
     return hipGetLastError();

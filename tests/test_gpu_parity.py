@@ -1232,8 +1232,8 @@ def test_kv_compress_forms_of_many_heads(ctx, heads, bound):
 
 @pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 128)])
 def test_kv_compress_moves_of_caches_larger_than_the_memory_side_cache(ctx, dtype, d):
-    # The bulk moves of a call whose bounds span more than 256 MiB of rows are loaded past the caches: the result is bit for
-    # bit that of the same heads under a tight bound (checked against the oracle elsewhere).
+    # Heads that hold little of caches whose bounds span more than 256 MiB of rows: the result is bit for bit that of the same
+    # heads under a tight bound (checked against the oracle elsewhere).
     Lmax, lens = 70000 * 256 // (d * (2 if dtype == torch.bfloat16 else 4)), [3000, 2999, 1, 0, 129, 2048, 1777, 2500]
     n = max(lens)
     src = [t.to(DEV) for t in _cache(dtype, 2, 4, n, d, lens, 640)]
@@ -1248,6 +1248,29 @@ def test_kv_compress_moves_of_caches_larger_than_the_memory_side_cache(ctx, dtyp
             ctx.kv_compress(*c, order=lv.ORDER_FILL, len_bound=L, **kw)
             got.append([x[:, :, :n] if x.dim() > 2 else x for x in c])
         for x, y in zip(*got):
+            assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 128)])
+def test_kv_compress_moves_loaded_past_the_caches(ctx, dtype, d):
+    # The rows of heads that are long for their call (as many heads of that length hold more than 256 MiB) are loaded past the
+    # caches, those of the short heads beside them are not: bit for bit what calls of four heads leave, which never do.
+    row = d * (2 if dtype == torch.bfloat16 else 4)
+    L = 70016 * 256 // row
+    lens = torch.tensor([L, L - 1, 1, 0, 129, L - 777, 3000, L // 2], dtype=torch.int32, device=DEV).view(8, 1)
+    assert 2 * 8 * (L - 777) * row > 256 << 20 > 2 * 4 * L * row
+    g = torch.Generator(device=DEV).manual_seed(641)
+    src = [torch.randn(8, 1, L, d, generator=g, device=DEV).to(dtype) for _ in range(2)]
+    src += [torch.rand(8, 1, L, generator=g, device=DEV) ** 4, torch.randint(0, 3, (8, 1, L), generator=g, device=DEV).to(torch.uint8),
+            torch.arange(L, dtype=torch.int32, device=DEV).repeat(8, 1, 1).contiguous(), lens]
+    for kw in (dict(mode=lv.KV_THRESHOLD, beta=0.9), dict(mode=lv.KV_BUDGET, budget=L // 3, n_recent=3)):
+        whole, parts = [t.clone() for t in src], [t.clone() for t in src]
+        ctx.kv_compress(*whole, order=lv.ORDER_FILL, len_bound=L, **kw)
+        for i in range(0, 8, 4):
+            ctx.kv_compress(*[t[i:i + 4] for t in parts], order=lv.ORDER_FILL, len_bound=L, **kw)
+        for x, y in zip(whole, parts):
+            if x.dim() == 4:
+                x, y = x.view(torch.uint8), y.view(torch.uint8)
             assert torch.equal(x, y)
 
 

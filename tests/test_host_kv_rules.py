@@ -41,3 +41,11 @@ def test_fill_workgroups_with_work_are_spread_over_the_chip(tmp_path):
             }
         }
     if (kv_fill_workgroups(1, 1 << 30) != (kFillWgs | 1)) return 3;""")
+
+
+def test_rows_go_past_the_caches_by_what_the_heads_hold(tmp_path):
+    """The rule's line at 256 MiB of live rows, and no overflow at the largest calls."""
+    _run(tmp_path, r"""
+    if (fill_past_caches(112, 2115, 256) || !fill_past_caches(1536, 1888, 256)) return 1;
+    if (fill_past_caches(256, 2048, 256) || !fill_past_caches(256, 2049, 256) || !fill_past_caches(1, (256ll << 20) / 1024 + 1, 512)) return 2;
+    if (fill_past_caches(65535, 0, 512) || !fill_past_caches(1ll << 20, 1 << 30, 512)) return 3;""")
