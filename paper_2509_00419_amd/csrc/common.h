@@ -101,6 +101,26 @@ struct KvWs {
     size_t src, total;
 };
 KvWs kv_ws(const lvlm_kv_desc &d);
+// Keys per thread (0: any number, from memory), threads and waves per SIMD of kv_select_kernel, by length and number of heads
+// (times of the kernel alone, us, other form -> this one).
+//   One head to a compute unit: 1024 threads beyond 1024 entries (512 threads: 64 heads of 2048 13.4 -> 12.9, 256 heads of 1500
+//   13.4 -> 13.0, 64 heads of 4096 18.3 -> 15.8), but 512 threads to 1024 (256 heads of 500 13.0 -> 12.5) and, with five keys
+//   instead of four, to 2560 (256 heads of 2300 14.6 -> 14.5).
+//   More: as many heads on a unit as may be.  256 threads to 1280 entries (512 threads: 1000 heads of 1280 25.3 -> 18.1); to 2048
+//   entries 512 threads while three heads to a unit are all of them (256 threads: 640 heads of 2048 19.9 -> 18.4), then 256
+//   (1000 heads of 2048 27.6 -> 23.4); 512 threads to 8192 (1024 threads: 300 heads of 2560 26.2 -> 17.2, 768 heads of 4096
+//   42.2 -> 27.3; whole calls: 320 heads of 8192 59.9 -> 51.1, 2048 heads 265 -> 214).
+struct SelectForm { int keys, threads, waves; };
+inline SelectForm kv_select_form(int bound, long long heads) {
+    const bool one = heads <= 256;      // a compute unit's
+    if (bound <= 1024) return one ? SelectForm{4, 512, 6} : SelectForm{5, 256, 6};
+    if (bound <= 1280 && !one) return {5, 256, 6};
+    if (bound <= 2048) return one ? SelectForm{2, 1024, 4} : heads <= 768 ? SelectForm{4, 512, 6} : SelectForm{8, 256, 6};
+    if (bound <= 2560) return {5, 512, 6};
+    if (bound <= 4096) return one ? SelectForm{4, 1024, 4} : SelectForm{8, 512, 6};
+    if (bound <= 8192) return one ? SelectForm{8, 1024, 4} : SelectForm{16, 512, 4};
+    return bound <= 17408 ? SelectForm{17, 1024, 4} : SelectForm{0, 1024, 4};
+}
 constexpr int kFillRows = 32;      // moves per batch of kv_fill_kernel
 constexpr int kFillWgs = 32768;    // workgroups its launch aims for
 // Workgroups of kv_fill_kernel per head: some kFillWgs in all (2 % over 16384 where heads are many), no more than the batches of
@@ -122,6 +142,8 @@ inline int kv_fill_workgroups(long long heads, int mode, int bound, int budget) 
 // lengths count, not what the caller reserves.  Moves loaded through the caches -> past them, us: 1536 heads of 1888 entries of
 // 256 bytes 182 -> 133 where the caches have just been written, 131 -> 121 just read, 183 -> 132 long before; 500 heads of 2000
 // (488 MB) 52 -> 50, 42 -> 41, 76 -> 52; 112 heads of 2115 (115 MB), 16512 reserved, 11 -> 14, 10 -> 11, 21 -> 16.
+// (The same call again at once, its moved rows all cached, has the faster loads through the caches up to 512 MB -- 200 heads of
+// 3000 19 against 29 -- but slots are not compressed again before they are written.)
 __host__ __device__ inline bool fill_past_caches(long long heads, long long entries, int row_bytes) {
     return 2 * heads * entries * row_bytes > (256ll << 20);
 }

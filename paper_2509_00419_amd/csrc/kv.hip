@@ -780,23 +780,21 @@ hipError_t launch_kv_compress(const Prof &prof, const lvlm_kv_desc &d, const KvW
     const int max_moves = d.mode == LVLM_KV_BUDGET ? (bound - d.budget < bound / 2 ? bound - d.budget : bound / 2) : bound / 2;
     a.fill_external = d.order == LVLM_ORDER_FILL && max_moves > kFillInKernel;
     prof.begin("kv_select");
-    // Threads and keys per thread by length and number of heads (times of a threshold selection with its moves of 128-byte rows,
-    // other form -> this one).  Up to 2048 entries 512 threads as long as three heads to a compute unit are all of them (against
-    // 1024 threads, one to a unit: 256 heads of 1888 22.9 -> 21.7 us, 512 heads 38.0 -> 26.9), then 256 threads and six to a unit
-    // (against 512: 640 heads 33.9 -> 31.1, 1024 heads 45.4 -> 40.6 us; five to a unit: 1536 heads 27.5 -> 21.0 for the kernel
-    // alone).  Fewer keys per thread where they do (1536 heads of 1025: 59.5 -> 53.5; 1024 threads at 2500 entries: 512 heads
-    // 47.4 -> 38.1, 2048 heads 173 -> 105, at 4000 49.0 -> 38.7 and 195 -> 135).  Up to 8192 entries 1024 threads for one head per
-    // unit (256 heads 41.8 -> 38.9), 512 for more (320 heads 59.9 -> 51.1, 2048 heads 265 -> 214).
-#define LVLM_SELECT(KPT, NT, WPE) LVLM_LAUNCH(prof, (kv_select_kernel<KPT, NT, WPE>), dim3((unsigned)heads), dim3(NT), 0, stream, a)
-    if (bound <= 1280 && heads > 256) LVLM_SELECT(5, 256, 6);
-    else if (bound <= 2048 && heads > 768) LVLM_SELECT(8, 256, 6);
-    else if (bound <= 2048) LVLM_SELECT(4, 512, 6);
-    else if (bound <= 2560) LVLM_SELECT(5, 512, 6);
-    else if (bound <= 4096) LVLM_SELECT(8, 512, 6);
-    else if (bound <= 8192 && heads > 256) LVLM_SELECT(16, 512, 4);
-    else if (bound <= 8192) LVLM_SELECT(8, 1024, 4);
-    else if (bound <= 17408) LVLM_SELECT(17, 1024, 4);
-    else LVLM_SELECT(0, 1024, 4);
+    const SelectForm form = kv_select_form(bound, (long long)heads);
+#define LVLM_SELECT(KPT, NT, WPE)                             \
+    if (form.keys == KPT && form.threads == NT && form.waves == WPE) \
+    LVLM_LAUNCH(prof, (kv_select_kernel<KPT, NT, WPE>), dim3((unsigned)heads), dim3(NT), 0, stream, a)
+    LVLM_SELECT(5, 256, 6);
+    LVLM_SELECT(8, 256, 6);
+    LVLM_SELECT(4, 512, 6);
+    LVLM_SELECT(5, 512, 6);
+    LVLM_SELECT(8, 512, 6);
+    LVLM_SELECT(16, 512, 4);
+    LVLM_SELECT(2, 1024, 4);
+    LVLM_SELECT(4, 1024, 4);
+    LVLM_SELECT(8, 1024, 4);
+    LVLM_SELECT(17, 1024, 4);
+    LVLM_SELECT(0, 1024, 4);
 #undef LVLM_SELECT
     prof.end();
     if (d.order == LVLM_ORDER_STABLE) {

@@ -59,3 +59,17 @@ def test_rows_go_past_the_caches_by_what_the_heads_hold(tmp_path):
     if (fill_past_caches(112, 2115, 256) || !fill_past_caches(1536, 1888, 256)) return 1;
     if (fill_past_caches(256, 2048, 256) || !fill_past_caches(256, 2049, 256) || !fill_past_caches(1, (256ll << 20) / 1024 + 1, 512)) return 2;
     if (fill_past_caches(65535, 0, 512) || !fill_past_caches(1ll << 20, 1 << 30, 512)) return 3;""")
+
+
+def test_select_form_of_few_heads(tmp_path):
+    """Where every head has a compute unit of its own, long heads take 1024 threads; every form holds the heads it is taken for."""
+    _run(tmp_path, r"""
+    for (long long heads : {1, 8, 64, 256, 257, 300, 512, 513, 768, 769, 1280, 1281, 1536, 1537, 5000, 1 << 20})
+        for (int bound : {1, 70, 1024, 1025, 1280, 1281, 2048, 2049, 2560, 2561, 4096, 4097, 8192, 8193, 17408, 17409, 1 << 30}) {
+            const SelectForm f = kv_select_form(bound, heads);
+            if (f.keys ? f.keys * f.threads < bound : bound <= 17408) return 1;
+            if (f.waves * 4 * 64 < f.threads) return 2;
+            const bool wide = (bound > 1024 && bound <= 2048) || bound > 2560;
+            if (heads <= 256 && wide && f.threads != 1024) return 3;
+            if (heads > 256 && bound <= 8192 && f.threads == 1024) return 4;
+        }""")
