@@ -108,16 +108,20 @@ KvWs kv_ws(const lvlm_kv_desc &d);
 //   instead of four, to 2560 (256 heads of 2300 14.6 -> 14.5).
 //   More: as many heads on a unit as may be.  256 threads to 1280 entries (512 threads: 1000 heads of 1280 25.3 -> 18.1); to 2048
 //   entries 512 threads while three heads to a unit are all of them (256 threads: 640 heads of 2048 19.9 -> 18.4), then 256
-//   (1000 heads of 2048 27.6 -> 23.4); 512 threads to 8192 (1024 threads: 300 heads of 2560 26.2 -> 17.2, 768 heads of 4096
+//   (1000 heads of 2048 27.6 -> 22.1); 512 threads to 8192 (1024 threads: 300 heads of 2560 26.2 -> 17.2, 768 heads of 4096
 //   42.2 -> 27.3; whole calls: 320 heads of 8192 59.9 -> 51.1, 2048 heads 265 -> 214).
+//   Eight keys per thread do not fit the registers of six waves per SIMD (four go to scratch memory): that form only where it
+//   saves a turn of the chip (1536 heads of 2048 by 256 threads 33.7 -> 28.2, 640 heads of 4096 by 512 33.4 -> 26.6), the other
+//   where it does not (1000 heads 23.4 -> 22.1, 2048 heads of 1600 36.9 -> 35.8; 512 heads of 4096 22.8 -> 21.6).
 struct SelectForm { int keys, threads, waves; };
 inline SelectForm kv_select_form(int bound, long long heads) {
     const bool one = heads <= 256;      // a compute unit's
+    auto turns = [&](int per_unit) { return (heads + 256 * per_unit - 1) / (256 * per_unit); };
     if (bound <= 1024) return one ? SelectForm{4, 512, 6} : SelectForm{5, 256, 6};
     if (bound <= 1280 && !one) return {5, 256, 6};
-    if (bound <= 2048) return one ? SelectForm{2, 1024, 4} : heads <= 768 ? SelectForm{4, 512, 6} : SelectForm{8, 256, 6};
+    if (bound <= 2048) return one ? SelectForm{2, 1024, 4} : heads <= 768 ? SelectForm{4, 512, 6} : SelectForm{8, 256, turns(6) < turns(5) ? 6 : 5};
     if (bound <= 2560) return {5, 512, 6};
-    if (bound <= 4096) return one ? SelectForm{4, 1024, 4} : SelectForm{8, 512, 6};
+    if (bound <= 4096) return one ? SelectForm{4, 1024, 4} : SelectForm{8, 512, turns(3) < turns(2) ? 6 : 4};
     if (bound <= 8192) return one ? SelectForm{8, 1024, 4} : SelectForm{16, 512, 4};
     return bound <= 17408 ? SelectForm{17, 1024, 4} : SelectForm{0, 1024, 4};
 }

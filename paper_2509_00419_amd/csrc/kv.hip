@@ -785,9 +785,11 @@ hipError_t launch_kv_compress(const Prof &prof, const lvlm_kv_desc &d, const KvW
     if (form.keys == KPT && form.threads == NT && form.waves == WPE) \
     LVLM_LAUNCH(prof, (kv_select_kernel<KPT, NT, WPE>), dim3((unsigned)heads), dim3(NT), 0, stream, a)
     LVLM_SELECT(5, 256, 6);
+    LVLM_SELECT(8, 256, 5);
     LVLM_SELECT(8, 256, 6);
     LVLM_SELECT(4, 512, 6);
     LVLM_SELECT(5, 512, 6);
+    LVLM_SELECT(8, 512, 4);
     LVLM_SELECT(8, 512, 6);
     LVLM_SELECT(16, 512, 4);
     LVLM_SELECT(2, 1024, 4);

@@ -73,3 +73,19 @@ def test_select_form_of_few_heads(tmp_path):
             if (heads <= 256 && wide && f.threads != 1024) return 3;
             if (heads > 256 && bound <= 8192 && f.threads == 1024) return 4;
         }""")
+
+
+def test_select_form_spills_only_where_it_saves_a_turn(tmp_path):
+    """Eight keys per thread at six waves per SIMD put registers into scratch memory: taken only where the heads then need fewer
+    turns of the chip (five heads of 256 threads, or two of 512, fit a compute unit without)."""
+    _run(tmp_path, r"""
+    for (long long heads = 257; heads < 9000; ++heads)
+        for (int bound : {1500, 2048, 3000, 4096}) {
+            const SelectForm f = kv_select_form(bound, heads);
+            if (f.keys != 8) continue;
+            const long long without = 256 * (f.threads == 256 ? 5 : 2), with = 256 * (f.threads == 256 ? 6 : 3);
+            const bool saves = (heads + with - 1) / with < (heads + without - 1) / without;
+            if ((f.waves == 6) != saves) return 1;
+        }
+    if (kv_select_form(2048, 1536).waves != 6 || kv_select_form(2048, 1000).waves != 5) return 2;
+    if (kv_select_form(4096, 640).waves != 6 || kv_select_form(4096, 512).waves != 4) return 3;""")
