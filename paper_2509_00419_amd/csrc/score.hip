@@ -1520,7 +1520,9 @@ struct ProbsArgs {
 };
 
 // Bound by HBM.  Rows of odd lengths start anywhere: a word is then loaded from an address aligned to an element only (the memory
-// pipeline takes it whole, a wave touches nine lines for eight), and the last word of a row, where it is partial, element by element.
+// pipeline takes it whole, a wave touches nine lines for eight), and the last word of a row ends with the row (element by element, where
+// it would be partial, its loads went one after the other: 11 x 4 x 10 rows of 349 columns 5.8 -> 8.9 us).  Waves without a row of a
+// last, partial group load nothing (the last row again and again: 14 x 32 rows of 37 columns 5.5 -> 6.5).
 // Against one element per thread and load: 4 x 28 x 150 rows of 9000 of 9150 columns 178 -> 69 us for the call (4.4 TB/s), 4 x 48 x 130
 // of 15000 of 15194 416 -> 160.
 // ONCE: loads past the caches, for a matrix that outgrows the 256 MB cache in front of the memory.
@@ -1539,15 +1541,17 @@ __global__ __launch_bounds__(256) void probs_colsum_kernel(ProbsArgs a, int n_co
     float acc[CPT];
 #pragma unroll
     for (int e = 0; e < CPT; ++e) acc[e] = 0.f;
-    if (j0 < a.n_img) {
-        const char *base = a.p + ((long long)b * a.psb + (long long)g * a.G * a.psh + a.img_begin + j0) * ES;
+    // a row's last word, where it would be partial, begins `early` columns early
+    const int early = ALIGNED || j0 >= a.n_img || a.n_img < CPT ? 0 : max(0, j0 + CPT - a.n_img);
+    if (j0 < a.n_img && r0 < r1) {
+        const char *base = a.p + ((long long)b * a.psb + (long long)g * a.G * a.psh + a.img_begin + j0 - early) * ES;
         uint4 v[8];
         auto row_at = [&](int u) {
             const int rho = min(r0 + u, GT - 1);
             const int hl = a.T == 1 ? rho : (int)__umulhi((unsigned)rho, a.t_magic), i = rho - hl * a.T;
             return base + ((long long)hl * a.psh + (long long)i * a.pst) * ES;
         };
-        if (ALIGNED || j0 + CPT <= a.n_img) {
+        if (ALIGNED || a.n_img >= CPT) {
             typedef unsigned word16 __attribute__((ext_vector_type(4)));
             typedef unsigned word2 __attribute__((ext_vector_type(4), aligned(2)));
             using word = std::conditional_t<ALIGNED, word16, word2>;
@@ -1556,16 +1560,16 @@ __global__ __launch_bounds__(256) void probs_colsum_kernel(ProbsArgs a, int n_co
                 const word *at = reinterpret_cast<const word *>(row_at(u));
                 v[u] = __builtin_bit_cast(uint4, ONCE ? __builtin_nontemporal_load(at) : *at);
             }
-        } else {
+        } else {                              // fewer columns than a word has (what the others repeat is not used)
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const char *at = row_at(u);
                 uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
                 for (int e = 0; e < CPT - 1; ++e) {
-                    if (j0 + e >= a.n_img) continue;
-                    if constexpr (DT == LVLM_BF16) w[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(at)[e] << (16 * (e & 1));
-                    else w[e] = reinterpret_cast<const uint32_t *>(at)[e];
+                    const int x = min(e, a.n_img - 1);
+                    if constexpr (DT == LVLM_BF16) w[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t *>(at)[x] << (16 * (e & 1));
+                    else w[e] = reinterpret_cast<const uint32_t *>(at)[x];
                 }
                 v[u] = make_uint4(w[0], w[1], w[2], w[3]);
             }
@@ -1586,7 +1590,8 @@ __global__ __launch_bounds__(256) void probs_colsum_kernel(ProbsArgs a, int n_co
         }
     }
 #pragma unroll
-    for (int e = 0; e < CPT; ++e) part[sub][cj * CPT + e] = acc[e];
+    for (int e = 0; e < CPT; ++e)
+        if (ALIGNED || e >= early) part[sub][cj * CPT + e - early] = acc[e];
     __syncthreads();
     for (int x = threadIdx.x; x < WC; x += 256) {
         const int j = cb * WC + x;

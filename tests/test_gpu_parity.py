@@ -349,6 +349,8 @@ def test_score_from_probs(ctx, dtype):
     (torch.bfloat16, 1, 4, 4, 1, 9, 2, 7), (torch.bfloat16, 1, 4, 1, 9, 8, 0, 1),      # less than a word
     (torch.bfloat16, 2, 4, 2, 33, 1031, 4, 1027), (torch.float32, 2, 4, 2, 33, 515, 0, 515),
     (torch.float32, 1, 2, 1, 40, 262, 3, 256), (torch.float32, 1, 2, 2, 3, 5, 1, 3),
+    (torch.bfloat16, 1, 4, 4, 1, 600, 1, 515), (torch.float32, 2, 4, 2, 2, 300, 3, 257),   # the partial word begins a block of columns
+    (torch.bfloat16, 1, 2, 2, 9, 9, 0, 8), (torch.float32, 1, 2, 1, 17, 6, 1, 5),          # one whole word; one and a column
     (torch.bfloat16, 3, 28, 4, 150, 13001, 0, 13001)])                                 # 328 MB of them: past the caches
 def test_score_from_probs_of_rows_that_start_anywhere(ctx, dtype, B, Hq, Hkv, T, N, img0, n_img):
     """Whole words from addresses aligned to an element, and partial last words, against sums in 64 bits."""
