@@ -1785,11 +1785,16 @@ static int few_rows(const lvlm_score_desc &d, const ScoreWs &w, int n_chunks, bo
 }
 
 // Equal shares of the keys (score_shares_kernel): for bf16 calls of much work, whose two launches and start-up (some 25 us;
-// 11 with the normalisers given) are then worth it.  Work: products of 32 rows and 32 keys, in 1024 SIMDs' turns.  Of 90 random shapes
-// timed both ways (3 to 32 chunks a KV head, 4 or 8 heads of 64 and 128 channels) those beyond the lines gain 10 % on average and
-// lose 0 % at most (15 % and 0 with the normalisers given); between 250 and 320 turns they are 1 % behind, at 100 twenty (88 us
-// 1.0, 55 us 1.2 times).  Under 3072 keys many pairs to a share, each with a start-up of its own, cost what the rest gives (52
-// sequences x 2939 keys 652 -> 683 us, 86 x 443 86 -> 106).  The span has to be visible to every row: the masked path is slow.
+// 11 with the normalisers given) are then worth it.  Work: products of 32 rows and 32 keys, in 1024 SIMDs' turns; between 250 and
+// 320 turns the other forms are 1 % ahead, at 100 twenty (88 us 1.0, 55 us 1.2 times).  Under 3072 keys many pairs to a share, each
+// with a start-up of its own, cost what the rest gives (52 sequences x 2939 keys 652 -> 683 us, 86 x 443 86 -> 106).  The span has
+// to be visible to every row: the masked path is slow.
+// Beyond these lines, of 238 random shapes timed both ways (2 to 472 pairs of 3 to 32 chunks of 64 and 128 channels) those taken
+// are 5 % faster on average with a normaliser sweep -- 9 % by workgroups of eight chunks, none slower; 4 % by workgroups of four,
+// whose ring of two slots hides less, from 22 % faster to 7 % slower, nine of 112 by more than 2 % -- and 11 % with the normalisers
+// given (4 % slower at worst).  Not taken, with a normaliser sweep: pairs of five or seven workgroups of four chunks with more
+// than one chunk's place empty (17, 18, 25, 26 chunks), of which 72 were 1 % slower on average and up to 12 % (10 sequences x 4193
+// keys x 64 heads of 64 channels, 17 chunks, 101 -> 114 us; 16 x 6719 x 64 of 128, 26 chunks, 458 -> 493).
 static ScoreShares score_shares(const lvlm_score_desc &d, int n_chunks, bool given) {
     ScoreShares s{};
     const long long pairs = (long long)d.B * d.Hkv;
@@ -1801,11 +1806,12 @@ static ScoreShares score_shares(const lvlm_score_desc &d, int n_chunks, bool giv
     // workgroups of eight chunks, which read the keys half as often, unless ones of four leave fewer places empty
     s.waves = (n_chunks + 7) / 8 * 8 == (n_chunks + 3) / 4 * 4 ? 4 : 2;
     const int wpp = (n_chunks + 2 * s.waves - 1) / (2 * s.waves);
+    if (!given && wpp > 4 && 2 * s.waves * wpp - n_chunks > 1) return ScoreShares{};
     auto deal = [&](int keys) {
         KeyRuns r{};
         r.steps = (keys + kShareStep - 1) / kShareStep;
         const int total = (int)pairs * r.steps;
-        r.shares = std::min(2048 / s.waves / wpp / 8 * 8, (total + 3) / 4);      // two waves per SIMD, four steps at least
+        r.shares = std::min(2048 / s.waves / wpp / 8 * 8, (total + 3) / 4);      // two waves per SIMD, none of under three steps
         r.size = total / r.shares;
         r.longer = total % r.shares;
         return r;

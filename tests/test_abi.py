@@ -157,6 +157,10 @@ def test_score_shares_rule():
     assert shares(96, 2176, 128, 48, 8, given=True) == 168 and shares(96, 2175, 128, 48, 8, given=True) == 0
     assert shares(48, 9000, 31, 16, 8) == 0 and shares(48, 9000, 33, 16, 8) > 0        # two and three chunks
     assert shares(12, 5219, 128, 64, 8) > 0 and shares(12, 5219, 129, 64, 8) == 0      # 32 chunks, and one more
+    for chunks, taken in ((16, 1), (17, 0), (18, 0), (19, 1), (20, 1), (21, 1), (24, 1), (25, 0), (26, 0), (27, 1), (28, 1)):
+        # 17, 18, 25, 26: five or seven workgroups of four chunks a pair, with more than one place empty
+        assert (shares(12, 6000, 4 * chunks, 64, 8) > 0) == taken and shares(12, 6000, 4 * chunks, 64, 8, given=True) > 0
+    assert shares(1, 200000, 128, 16, 2, n_img=3136) == 25                             # 98 steps in 25 shares: of four, and three
     assert shares(12, 5219, 128, 48, 8, dtype=bd.F32) == 0
     assert shares(12, 5219, 128, 48, 8, stride=(1 << 24) - 8) > 0 and shares(12, 5219, 128, 48, 8, stride=1 << 24) == 0
     assert shares(12, 5219, 128, 48, 8, q_pos0=5090, n_img=5091) > 0 and shares(12, 5219, 128, 48, 8, q_pos0=5089, n_img=5091) == 0
