@@ -175,6 +175,56 @@ def test_score_positions_behind_the_last_key_are_all_the_same(ctx, dtype, B, T, 
         assert all(torch.equal(x, y) for x, y in zip(got, want)), q_pos0
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,d,n_sys,n_img", [
+    (4, 128, 48, 8, 128, 0, 6800),             # workgroups of eight chunks
+    (8, 100, 48, 8, 128, 5, 4501),             # of four, a last tile of one key
+    (27, 60, 32, 4, 64, 5, 3333)])             # 64 channels
+def test_score_equal_shares_of_caches_and_into_them(ctx, B, T, Hq, Hkv, d, n_sys, n_img):
+    """Head-major caches with room behind the keys, and the per-head scores into the caches' own array: the bits of the same
+    call on compact arrays, and nothing written beside the span."""
+    N = n_sys + n_img + T
+    g = torch.Generator(device=DEV).manual_seed(N)
+    q = torch.randn(B, T, Hq, d, generator=g, device=DEV).to(torch.bfloat16)
+    cache = torch.full((B, Hkv, N + 72, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    cache[:, :, :N] = torch.randn(B, Hkv, N, d, generator=g, device=DEV).to(torch.bfloat16)
+    scores = torch.full((B, Hkv, N + 72), -7.0, device=DEV)
+    k, into = cache[:, :, :N].permute(0, 2, 1, 3), scores[:, :, 4:4 + n_img]
+    kw = dict(q_pos0=n_sys + n_img, img_begin=n_sys, n_img=n_img)
+    assert ctx.score_shares(ctx.score_desc(q, k, score_head=into, **kw)) > 0
+    sh, sm = ctx.score_tokens(q, k, score_head=into, **kw)
+    want_h, want_m = ctx.score_tokens(q, k.contiguous(), **kw)
+    assert sh.data_ptr() == into.data_ptr() and torch.equal(into, want_h) and torch.equal(sm, want_m)
+    assert (scores[:, :, :4] == -7.0).all() and (scores[:, :, 4 + n_img:] == -7.0).all()
+    rsh, _, _ = _score_ref64(q, k, **kw)
+    assert rel_err(into.cpu(), rsh.cpu()) < 1e-5
+
+
+@pytest.mark.parametrize("what", ["nan key", "inf key", "nan query", "inf query"])
+def test_score_equal_shares_with_values_that_are_not_finite(ctx, what):
+    """A NaN or an infinity in one key or query of one KV head: what the forms of smaller calls (one sequence at a time) make of
+    it there, and every other head's scores as without it."""
+    B, T, Hq, Hkv, d, n_img = 8, 100, 48, 8, 128, 4504
+    N, bad = n_img + T, float("nan") if what.startswith("nan") else float("inf")
+    g = torch.Generator(device=DEV).manual_seed(5)
+    q = torch.randn(B, T, Hq, d, generator=g, device=DEV).to(torch.bfloat16)
+    k = torch.randn(B, N, Hkv, d, generator=g, device=DEV).to(torch.bfloat16)
+    kw = dict(q_pos0=n_img, img_begin=0, n_img=n_img)
+    assert ctx.score_shares(ctx.score_desc(q, k, **kw)) > 0 and ctx.score_shares(ctx.score_desc(q[:1], k[:1], **kw)) == 0
+    clean = ctx.score_tokens(q, k, **kw)[0]
+    if what.endswith("key"):
+        k[3, 3000, 2, 17] = bad
+    else:
+        q[3, 41, 2 * 6 + 1, 17] = bad
+    got = ctx.score_tokens(q, k, **kw)[0]
+    for b in range(B):
+        one = ctx.score_tokens(q[b:b + 1], k[b:b + 1], **kw)[0][0]
+        for h in range(Hkv):
+            if (b, h) != (3, 2):
+                assert torch.equal(got[b, h], clean[b, h])
+            assert torch.equal(torch.isnan(got[b, h]), torch.isnan(one[h])), (b, h)
+            assert rel_err(got[b, h].nan_to_num(0.0).cpu(), one[h].nan_to_num(0.0).cpu()) < 1e-5
+
+
 def test_score_equal_shares_stay_in_their_workspace(ctx):
     def score(c, reserve):
         q, k = _rand((8, 100, 48, 128), torch.bfloat16, 192).to(DEV), _rand((8, 4604, 8, 128), torch.bfloat16, 193).to(DEV)
@@ -642,8 +692,12 @@ def test_kv_compress_bulk_config5_head(ctx):
 
 @pytest.mark.parametrize("order", [lv.ORDER_STABLE, lv.ORDER_FILL])
 def test_kv_compress_every_length_class(ctx, order):
-    # the selection kernel keeps keys in registers up to 2048 / 4096 / 8192 / 17408 slots per head and
-    # re-reads them beyond that: one ragged case per class, both rules
+    # the selection kernel keeps keys in registers up to 2048 / 2560 / 4096 / 8192 / 17408 slots per head and
+    # re-reads them beyond that: a ragged case per class, both rules, and the edges of the class in the middle
+    for Lmax, lens in ((2049, [2049, 2048]), (2560, [2560, 2111]), (2561, [2561, 2560]), (4096, [4096, 3333])):
+        _kv_case(ctx, torch.bfloat16, 1, 2, Lmax, 64, lens, 41 + Lmax, mode=lv.KV_BUDGET, budget=Lmax // 3, n_recent=1,
+                 order=order)
+        _kv_case(ctx, torch.bfloat16, 1, 2, Lmax, 64, lens, 40 + Lmax, mode=lv.KV_THRESHOLD, beta=0.7, order=order, dyadic=True)
     for Lmax, lens in ((3000, [2999, 2500]), (6000, [5999, 4097]), (12000, [11111, 8193]), (20000, [19990, 17409])):
         _kv_case(ctx, torch.bfloat16, 1, 2, Lmax, 64, lens, 42 + Lmax, mode=lv.KV_BUDGET, budget=Lmax // 2, n_recent=2,
                  order=order)
@@ -655,13 +709,13 @@ def test_kv_compress_every_length_class(ctx, order):
 
 
 @pytest.mark.parametrize("order", [lv.ORDER_STABLE, lv.ORDER_FILL])
-def test_kv_compress_many_short_heads(ctx, order):
-    # more than 512 short heads take workgroups of 256 threads with eight keys per thread: ragged lengths,
-    # both rules, ties included
-    B, H, Lmax = 36, 16, 1100
+@pytest.mark.parametrize("B,H,Lmax", [(36, 16, 1100), (49, 16, 1300)])
+def test_kv_compress_many_short_heads(ctx, B, H, Lmax, order):
+    # more than 256 heads of up to 1280 entries take workgroups of 256 threads with five keys per thread, more than 768 of up to
+    # 2048 with eight: ragged lengths, both rules, ties included
     g = torch.Generator().manual_seed(77)
     lens = torch.randint(0, Lmax + 1, (B * H,), generator=g).tolist()
-    lens[:6] = [1100, 1099, 1, 0, 257, 1025]
+    lens[:6] = [Lmax, Lmax - 1, 1, 0, 257, 1025]
     _kv_case(ctx, torch.bfloat16, B, H, Lmax, 64, lens, 78, mode=lv.KV_THRESHOLD, beta=0.9, order=order)
     _kv_case(ctx, torch.bfloat16, B, H, Lmax, 64, lens, 79, mode=lv.KV_BUDGET, budget=400, n_recent=3, order=order,
              dyadic=True)
@@ -1203,7 +1257,9 @@ def test_degenerate_sizes(ctx):
 @pytest.mark.parametrize("heads,bound", [
     (257, 1280), (257, 70), (769, 1281), (769, 2048),    # 256 threads a head, five and eight keys each
     (768, 2048), (300, 1281),                            # 512 threads, four keys: the most heads and the first length
-    (300, 2049), (300, 2560), (300, 2561), (300, 4096),  # five and eight keys
+    (1281, 2048),                                        # 256 threads, eight keys, six heads to a compute unit
+    (300, 2049), (300, 2560),                            # 512 threads, five keys (the form of few heads as well)
+    (300, 2561), (300, 4096), (513, 2561),               # eight, two heads to a compute unit and three
     (257, 4097), (257, 8192)])                           # sixteen
 def test_kv_compress_forms_of_many_heads(ctx, heads, bound):
     """The selection's forms for many heads, at the lengths where the rule changes: both modes and orders, ragged heads (whole,
