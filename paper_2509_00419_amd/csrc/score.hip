@@ -816,6 +816,9 @@ __global__ __launch_bounds__(256, (DT == LVLM_F32 && HD == 128) ? 2 : 4) void sc
 // Against score_chunks_kernel in runs and its fold: 12 sequences x 5219 keys x 48 heads 241 -> 221 us for the call with the
 // fold of half as many parts of column sums (900 TFLOP/s).
 constexpr int kShareStep = 64;               // keys per step
+// Normaliser of the rows that fill up the last chunk, or a wave's second one: their probabilities are zero, and where the row they
+// repeat has an infinite logit they are infinite as its own is (an infinite normaliser would make a NaN of it).
+constexpr float kNoRowLse = 3.0e38f;
 template <int HD, bool SECOND, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void score_shares_kernel(ScoreArgs a) {
     constexpr int ES = 2, ROWB = HD * ES, NV = HD / 16;
@@ -896,7 +899,7 @@ __global__ __launch_bounds__(64 * NW, 2) void score_shares_kernel(ScoreArgs a) {
         };
         begin();
 
-        // this lane's query rows (padding rows repeat the last row and get an infinite LSE)
+        // this lane's query rows (padding rows repeat the last row, with kNoRowLse)
         int rho[2], pos[2];
         HalfRow<LVLM_BF16, HD> qa[2];
         int pos_min = INT_MAX;      // earliest position of the wave's rows (uniform): tiles at or before it need no mask
@@ -952,7 +955,7 @@ __global__ __launch_bounds__(64 * NW, 2) void score_shares_kernel(ScoreArgs a) {
                     lx = lx * exp2f(mx - ms) + lo * exp2f(mo - ms);
                     lse = lx > 0.f ? mn + log2f(lx) : INFINITY;      // no visible key: contributes nothing
                 }
-                if (hf == 0) lse_s[2 * wave + x][l32] = rho[x] < GT ? lse : INFINITY;
+                if (hf == 0) lse_s[2 * wave + x][l32] = rho[x] < GT ? lse : kNoRowLse;
             }
             __syncthreads();
 #pragma unroll

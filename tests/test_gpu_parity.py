@@ -225,6 +225,26 @@ def test_score_equal_shares_with_values_that_are_not_finite(ctx, what):
             assert rel_err(got[b, h].nan_to_num(0.0).cpu(), one[h].nan_to_num(0.0).cpu()) < 1e-5
 
 
+def test_score_equal_shares_with_an_infinite_key_under_given_normalisers(ctx):
+    """15 chunks of query rows, so that a wave's second one is empty: a column of infinite probabilities is infinite, as it is one
+    sequence at a time, and not a NaN of the rows that fill up the empty chunk."""
+    B, T, Hq, Hkv, d, n_img = 27, 60, 32, 4, 64, 3333
+    g = torch.Generator(device=DEV).manual_seed(5)
+    q = torch.randn(B, T, Hq, d, generator=g, device=DEV).to(torch.bfloat16)
+    k = torch.randn(B, n_img + T, Hkv, d, generator=g, device=DEV).to(torch.bfloat16)
+    lse = torch.full((B, Hq, T), 9.0, device=DEV)
+    kw = dict(q_pos0=n_img, img_begin=0, n_img=n_img)
+    assert ctx.score_shares(ctx.score_desc(q, k, **kw), True) > 0 and ctx.score_shares(ctx.score_desc(q[:1], k[:1], **kw), True) == 0
+    for last in (1.0, -1.0):                             # the last row's logit: +inf and -inf
+        q[3, T - 1, 2 * 8 + 7, 17] = last
+        k[3, 3000, 2, 17] = float("inf")
+        got = ctx.score_tokens(q, k, row_lse=lse, **kw)[0]
+        one = ctx.score_tokens(q[3:4], k[3:4], row_lse=lse[3:4], **kw)[0][0]
+        assert got[3, 2, 3000] == float("inf") and one[2, 3000] == float("inf")
+        got[3, 2, 3000] = one[2, 3000] = 0.0
+        assert torch.isfinite(got).all() and rel_err(got[3].cpu(), one.cpu()) < 1e-5
+
+
 def test_score_equal_shares_stay_in_their_workspace(ctx):
     def score(c, reserve):
         q, k = _rand((8, 100, 48, 128), torch.bfloat16, 192).to(DEV), _rand((8, 4604, 8, 128), torch.bfloat16, 193).to(DEV)
