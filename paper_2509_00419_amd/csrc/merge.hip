@@ -460,10 +460,14 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
 }
 
 // What bounds it: HBM.  A thread keeps the eight loads of a batch in flight and then waits for them, so the chip is kept
-// busy by the workgroups resident beside each other; a second team of 256 threads on the same chunk doubles them at the
-// same number of partial sums (half as many rows per chunk instead: 20 MB more of them to write and read).  One team -> two:
-// 16384 -> 5091 rows of 12 KB 53 -> 46 us (267 MB, 5.8 TB/s; the whole call 90.4 -> 83), 8 x 3000 -> 1000 rows of 12 KB in
-// three planes 119 -> 112, 2 x 10000 -> 5000 rows of 7 KB 79 -> 70; chunks too short for two batches keep one team (2048 ->
+// busy by the workgroups resident beside each other.  A chunk's batches go to two teams of 256 threads where it has two or more.  That
+// puts no more loads in flight (84 registers: two such workgroups, 16 waves, on a compute unit against five of one team, 20), but a
+// chunk is done in half the time and two fifths as many are under way: one team with chunks of half the rows gains as much here
+// (16384 -> 5091 rows of 12 KB: 53.6 us, two teams 49.0, half the rows 47.4) and pays for twice the partial sums in the fold.
+// One team -> two, whole calls: 16384 -> 5091 rows of 12 KB 90.4 -> 83 us, 8 x 3000 -> 1000 rows of 12 KB in three planes 119 ->
+// 112, 2 x 10000 -> 5000 rows of 7 KB 79 -> 70; of 120 shapes beyond the line 7 % faster on average (with the index lists and the
+// fold), nine slower by more than 1 %: chunks of 16 rows of planes of several widths (at worst 5 x 769 -> 76 rows of 14 KB and 2 KB
+// 29.3 -> 32.0) and rows of 512 bytes (4 x 10000 -> 3100, 63.2 -> 66.7).  Chunks too short for two batches keep one team (2048 ->
 // 1000 rows of 7 KB 22.9 -> 26.4 us with two).
 // ONCE: loads past the caches, for planes that outgrow the 256 MB cache in front of the memory: they would only push each
 // other out of it (305 MB: the call 112 -> 100 us; 353 MB: 150 -> 129); smaller ones may still lie there since they were

@@ -805,16 +805,19 @@ __global__ __launch_bounds__(256, (DT == LVLM_F32 && HD == 128) ? 2 : 4) void sc
 // the loads are assembly for the reason given there, their waits counted by hand; one barrier per step).  Only two steps are
 // requested before anything else, the rest of the ring when these have landed: all at once, every workgroup would wait for
 // everybody's whole ring.
-// Products and softmax of different chunks go side by side: the products of chunk 0 with the softmax of chunk 1 of the tile
-// before, those of chunk 1 with the softmax of chunk 0, cut into slots of one product and two logits (scaling, exponential
-// and sum a slot apart; the scheduling barriers keep the compiler from drawing them apart).
+// Products and softmax of different chunks are meant to go side by side: the products of chunk 0 with the softmax of chunk 1 of the
+// tile before, those of chunk 1 with the softmax of chunk 0, cut into slots of one product and two logits (scaling, exponential and
+// sum a slot apart), with scheduling barriers between the slots.  Those hold inside a basic block only, and a step has branches
+// (around its wait and its fetch): as compiled, one of a step's four softmaxes (column sums), or two (normalisers), are moved behind
+// the branches and run alone, after products that nothing runs beside.
 // SECOND = false: rows = keys, columns = queries; each row's (max, sum) of the share.  SECOND = true: rows = queries, columns =
 // keys; the shares' normalisers are folded at the start of a pair (they are few), or the caller's taken, and a wave leaves the
 // column sums of its two chunks as one part.
-// What bounds it: vector issue beside the products at the clock the power allows (a probe of 8 products and 32 exponentials,
-// scalings and sums alone takes 180 ns per tile and SIMD, this loop 220; without its fetches, barriers and fragment reads 190).
-// Against score_chunks_kernel in runs and its fold: 12 sequences x 5219 keys x 48 heads 241 -> 221 us for the call with the
-// fold of half as many parts of column sums (900 TFLOP/s).
+// A tile takes 220 ns per SIMD; without its fetches, barriers and fragment reads (and so without the branches) 190; a probe of 8
+// products and 32 exponentials, scalings and sums alone 180, which is vector issue beside the products at the clock the power
+// allows.  Against score_chunks_kernel in runs and its fold: 12 sequences x 5219 keys x 48 heads 244 -> 224 us for the call, with
+// the fold of half as many parts of column sums (818 TFLOP/s over the two sweeps, 124 and 114 us under the profiler; the kernel it
+// replaces 822 over 119 and 118, its fold between the sweeps and twice the parts not counted).
 constexpr int kShareStep = 64;               // keys per step
 // Normaliser of the rows that fill up the last chunk, or a wave's second one: their probabilities are zero, and where the row they
 // repeat has an infinite logit they are infinite as its own is (an infinite normaliser would make a NaN of it).
@@ -1528,7 +1531,9 @@ struct ProbsArgs {
 // last, partial group load nothing (the last row again and again: 14 x 32 rows of 37 columns 5.5 -> 6.5).
 // Against one element per thread and load: 4 x 28 x 150 rows of 9000 of 9150 columns 178 -> 69 us for the call (4.4 TB/s), 4 x 48 x 130
 // of 15000 of 15194 416 -> 160.
-// ONCE: loads past the caches, for a matrix that outgrows the 256 MB cache in front of the memory.
+// ONCE: loads past the caches, for a matrix that clearly outgrows the 256 MB cache in front of the memory.  Kernel, repeated at once
+// and on a matrix just written: 240 MB 39 -> 46 and 39 -> 39 us, 264 MB 46 -> 51 and 48 -> 44, 288 MB 58 -> 55 and 78 -> 48 (rows of
+// odd lengths 53 -> 61 and 71 -> 70), 336 MB 70 -> 63 and 101 -> 56.
 template <int DT, bool ALIGNED, bool ONCE>
 __global__ __launch_bounds__(256) void probs_colsum_kernel(ProbsArgs a, int n_col_blocks) {
     constexpr int ES = esize<DT>();
@@ -1721,7 +1726,7 @@ hipError_t launch_score_probs(const Prof &prof, const lvlm_probs_desc &d, const 
     const int es = d.dtype == LVLM_BF16 ? 2 : 4, cpt = 16 / es;
     const bool aligned = (d.p_stride_b * es) % 16 == 0 && (d.p_stride_h * es) % 16 == 0 && (d.p_stride_t * es) % 16 == 0 &&
                          (d.img_begin * es) % 16 == 0 && d.n_img % cpt == 0;      // the base pointer is 16-byte aligned
-    // (2 x 48 x 128 rows of 16384 columns, 403 MB: 85 -> 79 us with loads past the caches)
+    // (the line lies where both kinds of rows gain: probs_colsum_kernel)
     const bool once = (long long)d.B * d.Hq * d.T * d.n_img * es > (320ll << 20);
     const int ncb = (d.n_img + 64 * cpt - 1) / (64 * cpt);
     const dim3 grid(ncb * w.rs, d.Hkv, d.B);
