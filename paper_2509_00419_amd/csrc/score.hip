@@ -815,9 +815,9 @@ __global__ __launch_bounds__(256, (DT == LVLM_F32 && HD == 128) ? 2 : 4) void sc
 // column sums of its two chunks as one part.
 // A tile takes 220 ns per SIMD; without its fetches, barriers and fragment reads (and so without the branches) 190; a probe of 8
 // products and 32 exponentials, scalings and sums alone 180, which is vector issue beside the products at the clock the power
-// allows.  Against score_chunks_kernel in runs and its fold: 12 sequences x 5219 keys x 48 heads 244 -> 224 us for the call, with
-// the fold of half as many parts of column sums (818 TFLOP/s over the two sweeps, 124 and 114 us under the profiler; the kernel it
-// replaces 822 over 119 and 118, its fold between the sweeps and twice the parts not counted).
+// allows.  Against score_chunks_kernel in runs and its folds: 12 sequences x 5219 keys x 48 heads 249 -> 225 us for the call; under
+// the profiler, on one machine, 135 and 133 us for the sweeps and 5 and 11 for the folds -> 131, 123 and 8 (725 -> 768 TFLOP/s over
+// the sweeps; 818 on a machine that held a higher clock).
 constexpr int kShareStep = 64;               // keys per step
 // Normaliser of the rows that fill up the last chunk, or a wave's second one: their probabilities are zero, and where the row they
 // repeat has an infinite logit they are infinite as its own is (an infinite normaliser would make a NaN of it).
