@@ -126,20 +126,21 @@ inline SelectForm kv_select_form(int bound, long long heads) {
     return bound <= 17408 ? SelectForm{17, 1024, 4} : SelectForm{0, 1024, 4};
 }
 constexpr int kFillRows = 32;      // moves per batch of kv_fill_kernel
-constexpr int kFillWgs = 32768;    // workgroups its launch aims for
-// Workgroups of kv_fill_kernel per head: some kFillWgs in all (2 % over 16384 where heads are many), no more than the batches of
-// moves that a head at the bound is likely to have, and an odd number of them.
-// Likely: with a share f of the entries kept, evicted ones anywhere, f (1 - f) of them move (a head with more gives its workgroups
-// more batches in turn); workgroups that find nothing cost as much to start as the others (112 heads of 2115 entries, 16512
-// reserved: 259 per head, one for every batch there could be, 12.9 us, 147 10.5, 131 9.2).
+// Workgroups of kv_fill_kernel per head: one for every batch of moves the longest head can have, while that is at most 16384 in all
+// -- or 32768 where a head has no more than 33 -- and an odd number of them.
+// Heads can be shorter than their bound, and workgroups that find nothing cost as much to start as the others: 112 heads of 2115
+// entries, 16512 reserved, 259 per head 12.9 us, 147 10.5.  Fewer than the batches there are cost the heads that evict their first
+// entries and move half of what they keep: 8 heads of 4000, a half kept, 33 instead of 63 per head 10.6 against 7.3 us, 800 heads of
+// 2000, 17 instead of 33, 156 against 144; 1536 heads of 1888, 11 instead of 23, 136 against 130 at a third kept by mass.
 // Odd: a head's first workgroups find its moves and the others nothing, and
 // workgroups go to the 8 XCDs and the 4 shader engines of each in turn: by an even number per head, the ones with work are the
 // same few engines' in every head (32 per head -> 33, caches just read: 800 heads of 2000 entries of 256 bytes at a third kept by mass
 // 98 -> 64 us, with a budget of 200 83 -> 35, 500 heads 64 -> 40).
-inline int kv_fill_workgroups(long long heads, int mode, int bound, int budget) {
-    const long long moves = mode == LVLM_KV_BUDGET ? (long long)budget * (bound - budget) / bound : bound / 4;
-    const long long likely = moves / kFillRows + 2, share = (kFillWgs + heads - 1) / heads;
-    return (int)(share < likely ? share : likely) | 1;
+inline int kv_fill_workgroups(long long heads, int max_moves) {
+    const long long batches = (max_moves + kFillRows - 1) / kFillRows;
+    const long long sixteen = (16384 + heads - 1) / heads, more = (32768 + heads - 1) / heads;
+    const long long most = sixteen > 33 ? sixteen : (more < 33 ? more : 33);
+    return (int)(batches < most ? batches : most) | 1;
 }
 // Whether kv_fill_kernel loads the rows of a head of `entries` entries past the caches: where all heads, taken as long as this one,
 // hold more rows than the 256 MB cache in front of the memory, so that those written or read last push the others out.  The

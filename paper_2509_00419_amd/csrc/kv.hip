@@ -811,7 +811,7 @@ hipError_t launch_kv_compress(const Prof &prof, const lvlm_kv_desc &d, const KvW
         prof.end();
     } else if (a.fill_external) {
         prof.begin("kv_fill");
-        const dim3 grid((unsigned)kv_fill_workgroups((long long)heads, d.mode, bound, d.budget), (unsigned)heads);
+        const dim3 grid((unsigned)kv_fill_workgroups((long long)heads, max_moves), (unsigned)heads);
         LVLM_LAUNCH(prof, kv_fill_kernel, grid, dim3(256), 0, stream, a);
         prof.end();
     }

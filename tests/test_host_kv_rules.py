@@ -21,36 +21,33 @@ def _run(tmp_path, body):
 
 def test_fill_workgroups_with_work_are_spread_over_the_chip(tmp_path):
     """Workgroups go round 8 XCDs of 4 shader engines in launch order, and a head's first ones have its moves: whatever the
-    heads, bounds and budgets, every engine gets its share of those."""
+    heads and bounds, every engine gets its share of those."""
     _run(tmp_path, r"""
     for (long long heads : {256, 400, 500, 640, 800, 1000, 1024, 1536, 2048, 4096})
-        for (int bound : {130, 500, 1024, 2000, 2048, 4096, 16512})
-            for (int budget : {0, bound / 10, bound / 2, bound * 9 / 10}) {        // 0: by threshold
-                const int wgs = kv_fill_workgroups(heads, budget ? LVLM_KV_BUDGET : LVLM_KV_THRESHOLD, bound, budget);
-                const int most = (std::min(budget ? bound - budget : bound, bound / 2) + kFillRows - 1) / kFillRows;
-                for (int eighths = 1; eighths <= 8; ++eighths) {           // batches a head really has
-                    const int batches = std::max(1, most * eighths / 8);
-                    long long load[32] = {}, total = 0, top = 0;
-                    for (long long h = 0; h < heads; ++h)
-                        for (int x = 0; x < wgs && x < batches; ++x) {
-                            const long long at = h * wgs + x, n = (batches - x + wgs - 1) / wgs;
-                            load[at % 8 * 4 + at / 8 % 4] += n;
-                            total += n;
-                        }
-                    for (long long l : load) top = std::max(top, l);
-                    if (32 * top > total + total / 4 + 64 * most) return 1;
-                }
-            }""")
+        for (int max_moves : {65, 250, 512, 1000, 1024, 2048, 8256}) {
+            const int wgs = kv_fill_workgroups(heads, max_moves), most = (max_moves + kFillRows - 1) / kFillRows;
+            for (int eighths = 1; eighths <= 8; ++eighths) {               // batches a head really has
+                const int batches = std::max(1, most * eighths / 8);
+                long long load[32] = {}, total = 0, top = 0;
+                for (long long h = 0; h < heads; ++h)
+                    for (int x = 0; x < wgs && x < batches; ++x) {
+                        const long long at = h * wgs + x, n = (batches - x + wgs - 1) / wgs;
+                        load[at % 8 * 4 + at / 8 % 4] += n;
+                        total += n;
+                    }
+                for (long long l : load) top = std::max(top, l);
+                if (32 * top > total + total / 4 + 64 * most) return 1;
+            }
+        }""")
 
 
-def test_fill_workgroups_are_no_more_than_likely_have_moves(tmp_path):
-    """Reserved caches and budgets close to a bound start no workgroups for batches that hardly any head has."""
+def test_fill_workgroups_by_heads_and_batches(tmp_path):
+    """One workgroup for every batch there can be while those are not too many; reserved caches start no more than 16384."""
     _run(tmp_path, r"""
-    if (kv_fill_workgroups(112, LVLM_KV_THRESHOLD, 16512, 0) > 147) return 1;                  // 16384 in all, as many as ever
-    if (kv_fill_workgroups(800, LVLM_KV_BUDGET, 2000, 1900) > 7 || kv_fill_workgroups(8, LVLM_KV_BUDGET, 200, 100) > 3) return 2;
-    if (kv_fill_workgroups(64, LVLM_KV_BUDGET, 4000, 2000) < 32 || kv_fill_workgroups(1536, LVLM_KV_THRESHOLD, 1888, 0) < 15) return 3;
-    if (kv_fill_workgroups(1, LVLM_KV_BUDGET, 2147483647, 1 << 30) != (kFillWgs | 1)) return 4;
-    if (kv_fill_workgroups(1 << 20, LVLM_KV_THRESHOLD, 200, 0) != 1) return 5;""")
+    if (kv_fill_workgroups(112, 16512 / 2) != 147) return 1;                                   // 258 batches a head
+    if (kv_fill_workgroups(8, 2000) != 63 || kv_fill_workgroups(64, 1000) != 33 || kv_fill_workgroups(800, 1000) != 33) return 2;
+    if (kv_fill_workgroups(1536, 944) != 23 || kv_fill_workgroups(64, 8256) != 257 || kv_fill_workgroups(800, 100) != 5) return 3;
+    if (kv_fill_workgroups(1, 1 << 30) != 16385 || kv_fill_workgroups(1 << 20, 100) != 1 || kv_fill_workgroups(1, 65) != 3) return 4;""")
 
 
 def test_rows_go_past_the_caches_by_what_the_heads_hold(tmp_path):
