@@ -18,7 +18,6 @@ struct PrefillArgs {
     char *out;
     float *row_lse;     // [B][Hq][N]
     float *lse_t;       // [B][Hq][T] or null: the last T rows again
-    int *redo;          // [grid]: workgroups the FAST kernel gave up, for the SAFE kernel
     int B, N, Hq, Hkv, G, causal, T;
     int nqb;            // query blocks per head
     int heads_per_xcd;  // ceil(B * Hq / 8)
@@ -27,7 +26,7 @@ struct PrefillArgs {
 };
 
 constexpr float kLazy = 8.f;    // SAFE sweep: log2 of how far the row maximum may run ahead of the reference before a rescale
-constexpr float kRisk = 64.f;   // FAST sweep: ... before the workgroup falls back to the SAFE sweep
+constexpr float kRisk = 64.f;   // FAST sweep: ... before the workgroup takes the SAFE sweep
 
 // max of a value and the one held by the lane 32 places away (the other half-wave): one lane-swap instruction
 // instead of a trip through the LDS permute unit.  The swap exchanges lanes 32..63 of its first operand with
@@ -54,14 +53,14 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // keys inside V^T's rows are stored in the order the accumulator registers hold them.  Both blocks of a wave
 // use each K and V^T fragment read from LDS.
 //
-// There are two kernels.  The FAST one fixes each row's reference maximum at the first tile (every row sees
+// There are two sweeps.  The FAST one fixes each row's reference maximum at the first tile (every row sees
 // key 0 there) and never rescales: probabilities are exp2 of the distance to that reference, possibly far
 // above 1, which fp32 sums and bf16 operands carry at unchanged relative precision.
-// Should a logit rise more than 2^kRisk above its row's reference, the wave writes nothing and the workgroup
-// marks itself in `redo`; the SAFE
-// kernel, launched right after, does the marked workgroups again with the textbook online
-// softmax, whose reference follows the running maximum (lazily, in steps of 2^kLazy) and rescales sums and
-// accumulators when it moves.
+// Should a logit rise more than 2^kRisk above its row's reference, the wave writes nothing and the workgroup does its
+// block again in the SAFE sweep, the textbook online softmax, whose reference follows the running maximum (lazily, in
+// steps of 2^kLazy) and rescales sums and accumulators when it moves.  Both are in one kernel, one behind the other in the
+// same LDS: as a second kernel that looked through the marks of the first the SAFE sweep cost every call a launch (4 x 95 tokens,
+// 40 heads 18.6 -> 16.5 us, 542 tokens 32.2 -> 30.1).
 
 // Workgroup number -> (batch, head, query block); false: padding.  Numbers with the same remainder modulo 8 run on one
 // XCD.  The B * Hq heads, in memory order (heads of one KV head next to each other), are dealt to the 8 XCDs in
@@ -133,6 +132,9 @@ __device__ __forceinline__ void prefill_write(const PrefillArgs &a, const Prefil
     }
 }
 
+template <int HD, bool SAFE>
+__device__ __forceinline__ bool prefill_plain_block(const PrefillArgs &a, const PrefillBlock &w, char *k_mem, char *v_mem);
+
 // The FAST kernel.  The matrix pipe and the vector ALUs of a SIMD work side by side when a wave has independent
 // instructions for both (measured: 16 products with 4 fused multiply-adds or 2 exponentials behind each take the time
 // of the products alone), and one tile's products and softmax, which depend on each other, are about equally long.
@@ -167,10 +169,7 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform: conditions on it are scalar branches
     const int hf = lane >> 5, l32 = lane & 31;
     PrefillBlock w;
-    if (!prefill_block(a, blockIdx.x, w)) {           // padding: nothing for the SAFE kernel either
-        if (threadIdx.x == 0) a.redo[blockIdx.x] = 0;
-        return;
-    }
+    if (!prefill_block(a, blockIdx.x, w)) return;     // padding
     const int wrow0 = w.q0 + 64 * wave;               // this wave's first row
     const int kmax = a.causal ? min(a.N, w.q0 + 128) : a.N;
     const int n_tiles = (kmax + 31) >> 5;
@@ -374,14 +373,14 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
             for (int x = 0; x < 2; ++x) oacc[x][i >> 1] = mfma(f, quad(pa[x], i & 1), oacc[x][i >> 1]);
         }
     }
-    // A wave that saw the risk writes nothing, and the mark makes the SAFE kernel do the whole workgroup again.
+    // A wave that sees the risk writes nothing, and the whole workgroup does its block again.
     const bool risky = risky_sums(l_run[0], l_run[1]);
     if (lane == 0) bail_s[wave] = risky;
-    __syncthreads();
-    if (tid == 0) a.redo[blockIdx.x] = bail_s[0] | bail_s[1];
-    if (risky) return;
+    if (!risky)
 #pragma unroll
-    for (int x = 0; x < 2; ++x) prefill_write<NCB>(a, w, wrow0 + 32 * x + l32, hf, m_run[x], l_run[x], oacc[x]);
+        for (int x = 0; x < 2; ++x) prefill_write<NCB>(a, w, wrow0 + 32 * x + l32, hf, m_run[x], l_run[x], oacc[x]);
+    __syncthreads();
+    if (bail_s[0] | bail_s[1]) prefill_plain_block<HD, true>(a, w, &k_lds[0][0], &v_lds[0][0]);
 }
 
 // One tile after the other, products and softmax in turn: the SAFE sweep (a rescale touches everything in flight, so
@@ -389,7 +388,7 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
 // products per logit to hide the softmax behind and two waves per SIMD -- 230 registers here, 300 there -- do
 // better (2 x 4000 tokens, 32 heads: 185 us here, 221 us pipelined).  Returns whether a FAST sweep has to be done again.
 template <int HD, bool SAFE>
-__device__ __forceinline__ bool prefill_plain_block(const PrefillArgs &a, const PrefillBlock &w) {
+__device__ __forceinline__ bool prefill_plain_block(const PrefillArgs &a, const PrefillBlock &w, char *k_mem, char *v_mem) {
     constexpr int ROWB = HD * 2;
     constexpr int KP = ROWB + 16;           // K tile pitch: odd multiple of 16 bytes
     constexpr int VP = kVtPitch;
@@ -398,8 +397,8 @@ __device__ __forceinline__ bool prefill_plain_block(const PrefillArgs &a, const 
     constexpr int UPR = ROWB / 16;          // 16-byte units per row
     constexpr int KUPT = 32 * UPR / 128;    // K units per thread and tile
     constexpr int KTPR = UPR / KUPT;        // threads per K row
-    __shared__ __attribute__((aligned(16))) char k_lds[2][32 * KP];
-    __shared__ __attribute__((aligned(16))) char v_lds[2][HD * VP];
+    char(*k_lds)[32 * KP] = reinterpret_cast<char(*)[32 * KP]>(k_mem);
+    char(*v_lds)[HD * VP] = reinterpret_cast<char(*)[HD * VP]>(v_mem);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform: conditions on it are scalar branches
@@ -625,36 +624,24 @@ __device__ __forceinline__ bool prefill_plain_block(const PrefillArgs &a, const 
 }
 
 __global__ __launch_bounds__(128, 1) void prefill_attn_d64_kernel(PrefillArgs a) {
+    __shared__ __attribute__((aligned(16))) char k_lds[2][32 * (64 * 2 + 16)];
+    __shared__ __attribute__((aligned(16))) char v_lds[2][64 * kVtPitch];
     __shared__ int bail_s[2];
     PrefillBlock w;
-    if (!prefill_block(a, blockIdx.x, w)) {           // padding: nothing for the SAFE kernel either
-        if (threadIdx.x == 0) a.redo[blockIdx.x] = 0;
-        return;
-    }
-    const bool again = prefill_plain_block<64, false>(a, w);
+    if (!prefill_block(a, blockIdx.x, w)) return;     // padding
+    const bool again = prefill_plain_block<64, false>(a, w, &k_lds[0][0], &v_lds[0][0]);
     if ((threadIdx.x & 63) == 0) bail_s[threadIdx.x >> 6] = again;
     __syncthreads();
-    if (threadIdx.x == 0) a.redo[blockIdx.x] = bail_s[0] | bail_s[1];
+    if (bail_s[0] | bail_s[1]) prefill_plain_block<64, true>(a, w, &k_lds[0][0], &v_lds[0][0]);
 }
 
-// The SAFE kernel: the marked workgroups of a FAST one (or all of them, redo null).  Up to 1024 of them a workgroup looks
-// at its one mark: looking through several, all lanes loading, made short calls 0.4 to 0.6 us longer (4 heads x 33 tokens, 64 channels,
-// 8.6 -> 9.2 us).  Beyond that 512 workgroups, two to a compute unit, look through the marks 64 at a time.
+// The SAFE sweep alone: rows too far apart for the FAST kernels' 32-bit offsets.
 template <int HD>
-__global__ __launch_bounds__(128, 1) void prefill_attn_safe_kernel(PrefillArgs a, int total) {
-    if (total <= (int)gridDim.x && a.redo && a.redo[blockIdx.x] == 0) return;
-    const int lane = threadIdx.x & 63;
-    for (long long id0 = blockIdx.x; id0 < total; id0 += 64ll * gridDim.x) {
-        const long long mine = id0 + (long long)lane * gridDim.x;
-        unsigned long long todo = __ballot(mine < total && (!a.redo || a.redo[mine] != 0));
-        while (todo) {
-            const int k = __ffsll((unsigned long long)todo) - 1;
-            todo &= todo - 1;
-            PrefillBlock w;
-            if (prefill_block(a, (int)(id0 + (long long)k * gridDim.x), w)) prefill_plain_block<HD, true>(a, w);
-            __syncthreads();
-        }
-    }
+__global__ __launch_bounds__(128, 1) void prefill_attn_safe_kernel(PrefillArgs a) {
+    __shared__ __attribute__((aligned(16))) char k_lds[2][32 * (HD * 2 + 16)];
+    __shared__ __attribute__((aligned(16))) char v_lds[2][HD * kVtPitch];
+    PrefillBlock w;
+    if (prefill_block(a, blockIdx.x, w)) prefill_plain_block<HD, true>(a, w, &k_lds[0][0], &v_lds[0][0]);
 }
 
 // component c of a 16-byte word
@@ -1013,10 +1000,8 @@ bool f32_shares_tiles(const lvlm_prefill_desc &d) {
 PrefillWs prefill_ws(const lvlm_prefill_desc &d) {
     PrefillWs w{};
     w.lse_t = 0;
-    w.redo = align_up((size_t)d.B * d.Hq * (d.T > 0 ? d.T : 0) * sizeof(float), 256);
-    const size_t grid = (size_t)((d.B * d.Hq + 7) / 8) * 8 * ((d.N + 127) / 128);
-    w.score = align_up(w.redo + grid * sizeof(int), 256);
-    w.total = w.score;
+    w.score = align_up((size_t)d.B * d.Hq * (d.T > 0 ? d.T : 0) * sizeof(float), 256);
+    w.total = w.score > 256 ? w.score : 256;        // (never none, so that every call asks for a workspace alike)
     if (d.T > 0) w.total += align_up(score_ws(prefill_score_desc(d)).total, 256);
     return w;
 }
@@ -1041,7 +1026,6 @@ hipError_t launch_prefill_attn(const Prof &prof, const lvlm_prefill_desc &d, con
     a.out = static_cast<char *>(out);
     a.row_lse = row_lse;
     a.lse_t = d.T > 0 ? reinterpret_cast<float *>(ws + w.lse_t) : nullptr;
-    a.redo = reinterpret_cast<int *>(ws + w.redo);
     a.B = d.B; a.N = d.N; a.Hq = d.Hq; a.Hkv = d.Hkv; a.G = d.Hq / d.Hkv; a.causal = d.causal; a.T = d.T;
     a.nqb = (d.N + 127) / 128;
     a.heads_per_xcd = (d.B * d.Hq + 7) / 8;
@@ -1053,16 +1037,15 @@ hipError_t launch_prefill_attn(const Prof &prof, const lvlm_prefill_desc &d, con
     prof.begin("prefill_attn");
     if (d.dtype == LVLM_BF16) {
         const long long grid = (long long)a.heads_per_xcd * 8 * a.nqb;
-        // the FAST kernel addresses a tile's rows by 32-bit offsets; row strides beyond that leave all of it to the other
+        // the FAST kernels address a tile's rows by 32-bit offsets
         const bool fast = d.k_stride_n * es < (1ll << 26) && d.v_stride_n * es < (1ll << 26);
-        if (!fast) a.redo = nullptr;
-        const dim3 safe_grid((unsigned)(grid <= 1024 ? grid : 512));
+        const dim3 g((unsigned)grid);
         if (d.hd == 128) {
-            if (fast) LVLM_LAUNCH(prof, prefill_attn_bf16_kernel, dim3((unsigned)grid), dim3(128), 0, stream, a);
-            LVLM_LAUNCH(prof, prefill_attn_safe_kernel<128>, safe_grid, dim3(128), 0, stream, a, (int)grid);
+            if (fast) LVLM_LAUNCH(prof, prefill_attn_bf16_kernel, g, dim3(128), 0, stream, a);
+            else LVLM_LAUNCH(prof, prefill_attn_safe_kernel<128>, g, dim3(128), 0, stream, a);
         } else {
-            if (fast) LVLM_LAUNCH(prof, prefill_attn_d64_kernel, dim3((unsigned)grid), dim3(128), 0, stream, a);
-            LVLM_LAUNCH(prof, prefill_attn_safe_kernel<64>, safe_grid, dim3(128), 0, stream, a, (int)grid);
+            if (fast) LVLM_LAUNCH(prof, prefill_attn_d64_kernel, g, dim3(128), 0, stream, a);
+            else LVLM_LAUNCH(prof, prefill_attn_safe_kernel<64>, g, dim3(128), 0, stream, a);
         }
     } else if (f32_shares_tiles(d)) {
         const dim3 grid((unsigned)a.nqb, (unsigned)d.Hq, (unsigned)d.B);
