@@ -311,6 +311,29 @@ def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal):
     assert np.abs(lse[pick].cpu().numpy() - o_lse).max() < 1e-5 * max(1.0, np.abs(o_lse).max())
 
 
+@pytest.mark.parametrize("N", [1, 3, 31, 33, 63, 65, 97, 127, 130, 161])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("far", [False, True])
+def test_prefill_attn_writes_its_rows_and_nothing_else(ctx, N, d, far):
+    """Rows leave the bf16 kernels several to a store: block and store edges, into rows of a wider and longer array whose other
+    elements stay as they were; `far`: every block is done again with the running reference."""
+    B, Hq, Hkv = 2, 5, 1
+    g = torch.Generator().manual_seed(N + d)
+    q, k, v = (torch.randn(B, N, h, d, generator=g) for h in (Hq, Hkv, Hkv))
+    if far:
+        q, k = 0.05 * q, 0.05 * k
+        q[..., 0] = k[..., 0] = (60.0 * d ** 0.5) ** 0.5
+        k[:, :32, :, 0] *= -1.0
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    wide = torch.full((B, N + 5, Hq + 2, d + 8), -7.0, dtype=torch.bfloat16, device=DEV)
+    out = wide[:, 2:2 + N, 1:1 + Hq, :d]
+    ctx.prefill_attn(q.to(DEV), k.to(DEV), v.to(DEV), out=out)
+    o_out, _ = O.prefill_attn(f64(q), f64(k), f64(v), dtype="bf16")
+    assert rel_err(out.float().cpu(), o_out) < 2e-2
+    out.fill_(-7.0)
+    assert bool((wide == -7.0).all())
+
+
 def test_prefill_attn_rejects_bad_arguments(ctx):
     fused, split = _qkv(1, 64, 4, 2, 64, torch.bfloat16, 1)
     qd, kd, vd = split(fused.to(DEV))
