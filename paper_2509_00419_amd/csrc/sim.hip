@@ -3,7 +3,8 @@
 // other token joins the dominant token it is most similar to (cosine of the rows of plane 0) and each
 // dominant token becomes the size-weighted mean of its cluster.
 //
-//   rank_kernel (merge.hip)  ranks by score -> dominant = rank < n_keep; in the same launch 1 / |row| of every image token
+//   rank_kernel (merge.hip)  ranks by score -> dominant = rank < n_keep; in the same launch 1 / |row| of every image token, where
+//                            the product does not do that
 //   sim_index_kernel         positions of dominant tokens, list of the others (both ascending)
 //   sim_gemm_kernel          the one dense contraction of the path: (dominant x others) dot products on
 //                            the matrix cores, with the arg-max over the dominant axis taken in the epilogue (nothing
@@ -30,7 +31,7 @@ struct SimArgs {
     int32_t *dom_of;        // [B, n]  p >= 0: dominant position; -(q+1): q-th other token
     int32_t *keep_idx;      // [B, n_keep]
     int32_t *rest_idx;      // [B, r]
-    float *inv_norm;        // [B, n]
+    float *inv_norm;        // [B, n], or null: the product takes the norms itself
     unsigned long long *best;   // [B, r]  (key of the cosine, ~dominant position)
     int32_t *assign;        // [B, n]
     int32_t *order;         // [B, n]   other tokens by (assignment, index), then the dominant ones
@@ -116,9 +117,25 @@ __global__ __launch_bounds__(1024) void sim_index_kernel(SimArgs a) {
 // every XCD gets one stretch and fetches few rows that another one fetches too; else GN * GM.
 constexpr int kSimGN = 8, kSimGM = 4;
 
+// Adds the squares of a unit's elements to s, one after the other.
+template <int DT>
+__device__ __forceinline__ void squares(const uint4 &u, float &s) {
+    const uint32_t d[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if constexpr (DT == LVLM_BF16) {
+            const float lo = __uint_as_float(d[i] << 16), hi = __uint_as_float(d[i] & 0xffff0000u);
+            s = fmaf(lo, lo, s);
+            s = fmaf(hi, hi, s);
+        } else {
+            s = fmaf(__uint_as_float(d[i]), __uint_as_float(d[i]), s);
+        }
+    }
+}
+
 __device__ __attribute__((aligned(16))) const uint32_t kSimZero[4] = {0, 0, 0, 0};     // what lies beyond the end of a row
 
-template <int DT, int TM, int TN, int NWN, int NWM, int RING, bool RAGGED>
+template <int DT, int TM, int TN, int NWN, int NWM, int RING, bool NORMS, bool RAGGED>
 __global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
     constexpr int NW = NWN * NWM, NT = 64 * NW;
     constexpr int TR = TM / NWN / 32, TC = TN / NWM / 32;
@@ -167,7 +184,8 @@ __global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
         const int row = R < TM ? keep[min(nb * TM + R, a.n_keep - 1)] : rest[min(mb * TN + R - TM, a.r - 1)];
         off[x] = (unsigned)row * (unsigned)p.row_bytes + 16 * unit_of(x);
     }
-    for (int i = tid; i < TM; i += NT) invn[i] = a.inv_norm[(long long)b * a.n + keep[min(nb * TM + i, a.n_keep - 1)]];
+    if constexpr (!NORMS)
+        for (int i = tid; i < TM; i += NT) invn[i] = a.inv_norm[(long long)b * a.n + keep[min(nb * TM + i, a.n_keep - 1)]];
     const int nk = (p.row_bytes + SB - 1) / SB;      // the last slice may be partial: zero-filled
     const unsigned ring0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char *)ring + 1024 * DPW * wave;
     // direct loads [lo, hi) of slice k (the last slice again past the end) into slot k % RING
@@ -202,46 +220,84 @@ __global__ __launch_bounds__(64 * NWN * NWM) void sim_gemm_kernel(SimArgs a) {
     for (int k = 0; k < RING - 1; ++k) fetch(k, 0, DPW);
     // contraction step i of lane half hf takes unit NS hf + i of a row's slice
     constexpr int NS = UPS / 2;
+    // NORMS: squares of the dominant rows, NU units of a slice to a thread, always of the same rows, and a sum for every slice of eight:
+    // the sums that a wave with a row to itself would have in its 64 lanes (norm_rows), so that both ways give the same bits
+    constexpr int NU = TM * UPS / NT, PH = NORMS ? 8 : 1;
+    static_assert(NU >= 1 && NU <= NS && NU * NT == TM * UPS, "at most one unit per contraction step");
+    float sq[PH][NU];
+#pragma unroll
+    for (int ph = 0; ph < PH; ++ph)
+#pragma unroll
+        for (int x = 0; x < NU; ++x) sq[ph][x] = 0.f;
     int uo[NS];
 #pragma unroll
     for (int i = 0; i < NS; ++i) uo[i] = l32 * SB + 16 * ((NS * hf + i) ^ place(l32));
     const char *const ar = ring + wn * (TR * 32 * SB), *const br = ring + TM * SB + wm * (TC * 32 * SB);
-    for (int k = 0; k < nk; ++k) {
-        // all but the RING - 2 youngest slices' loads of this wave have landed: slice k is complete when everybody is here;
-        // and this wave's reads of slice k - 1 are back, whose slot is written next
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(DPW * (RING - 2)) : "memory");
-        if constexpr (RING == 2) fetch(k + RING - 1, 0, DPW);
-        const int at = (k % RING) * SLOT;
-        uint4 fa[NS][TR], fb[NS][TC];
+    for (int k0 = 0; k0 < nk; k0 += PH) {
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
+        for (int ph = 0; ph < PH; ++ph) {
+            const int k = k0 + ph;
+            if (PH > 1 && k >= nk) break;
+            // all but the RING - 2 youngest slices' loads of this wave have landed: slice k is complete when everybody is here;
+            // and this wave's reads of slice k - 1 are back, whose slot is written next
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(DPW * (RING - 2)) : "memory");
+            if constexpr (RING == 2) fetch(k + RING - 1, 0, DPW);
+            const int at = (k % RING) * SLOT;
+            uint4 fa[NS][TR], fb[NS][TC];
 #pragma unroll
-            for (int t2 = 0; t2 < TR; ++t2) fa[i][t2] = *reinterpret_cast<const uint4 *>(ar + at + uo[i] + t2 * 32 * SB);
+            for (int i = 0; i < NS; ++i) {
 #pragma unroll
-            for (int t2 = 0; t2 < TC; ++t2) fb[i][t2] = *reinterpret_cast<const uint4 *>(br + at + uo[i] + t2 * 32 * SB);
-        }
-        if constexpr (RING > 2) __builtin_amdgcn_sched_barrier(0);
+                for (int t2 = 0; t2 < TR; ++t2) fa[i][t2] = *reinterpret_cast<const uint4 *>(ar + at + uo[i] + t2 * 32 * SB);
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
+                for (int t2 = 0; t2 < TC; ++t2) fb[i][t2] = *reinterpret_cast<const uint4 *>(br + at + uo[i] + t2 * 32 * SB);
+            }
+            uint4 own[NU];
+            if constexpr (NORMS) {
 #pragma unroll
-            for (int nd = 0; nd < TR; ++nd)
+                for (int x = 0; x < NU; ++x) own[x] = *reinterpret_cast<const uint4 *>(ring + at + 16 * (tid + NT * x));
+            }
+            if constexpr (RING > 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int nr = 0; nr < TC; ++nr) {
-                    if constexpr (DT == LVLM_BF16) {
-                        mfma_one<DT>(acc[nd][nr], fa[i][nd], fb[i][nr], 0);      // rows = dominant, cols = others
-                    } else {
+            for (int i = 0; i < NS; ++i) {
 #pragma unroll
-                        for (int cpt = 0; cpt < 4; ++cpt) mfma_one<DT>(acc[nd][nr], fa[i][nd], fb[i][nr], cpt);
+                for (int nd = 0; nd < TR; ++nd)
+#pragma unroll
+                    for (int nr = 0; nr < TC; ++nr) {
+                        if constexpr (DT == LVLM_BF16) {
+                            mfma_one<DT>(acc[nd][nr], fa[i][nd], fb[i][nr], 0);      // rows = dominant, cols = others
+                        } else {
+#pragma unroll
+                            for (int cpt = 0; cpt < 4; ++cpt) mfma_one<DT>(acc[nd][nr], fa[i][nd], fb[i][nr], cpt);
+                        }
                     }
+                // (behind the products: they do not wait for the units, which arrive last)
+                if constexpr (NORMS)
+                    if (i >= NS - NU) squares<DT>(own[i - (NS - NU)], sq[ph][i - (NS - NU)]);
+                if constexpr (RING > 2) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    fetch(k + RING - 1, DPW * i / NS, DPW * (i + 1) / NS);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-            if constexpr (RING > 2) {
-                __builtin_amdgcn_sched_barrier(0);
-                fetch(k + RING - 1, DPW * i / NS, DPW * (i + 1) / NS);
-                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // no load may land after the workgroup has left its LDS
+    if constexpr (NORMS) {
+        // wave_sum's order: the eight units of a slice (they lie permuted by an exclusive or, which this tree does not see), then the slices
+#pragma unroll
+        for (int x = 0; x < NU; ++x) {
+            float t[8];
+#pragma unroll
+            for (int ph = 0; ph < 8; ++ph) {
+                t[ph] = sq[ph][x];
+                t[ph] += dpp_quad1(t[ph]);
+                t[ph] += dpp_quad2(t[ph]);
+                t[ph] += dpp_half_mirror(t[ph]);
+            }
+            const float s = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+            if (tid % UPS == 0) invn[(tid + NT * x) / UPS] = s > 0.f ? 1.0f / sqrtf(s) : 1.0f;
+        }
+    }
     __syncthreads();
 
     // arg-max over the dominant rows: lane-local over its TR x 16 registers, then the other lane half, then
@@ -534,7 +590,6 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     a.dom_of = reinterpret_cast<int32_t *>(ws + w.dom_of);
     a.keep_idx = keep_idx ? keep_idx : reinterpret_cast<int32_t *>(ws + w.keep_idx);
     a.rest_idx = reinterpret_cast<int32_t *>(ws + w.rest_idx);
-    a.inv_norm = reinterpret_cast<float *>(ws + w.inv_norm);
     a.best = reinterpret_cast<unsigned long long *>(ws + w.best);
     a.assign = assign ? assign : reinterpret_cast<int32_t *>(ws + w.assign);
     a.order = reinterpret_cast<int32_t *>(ws + w.order);
@@ -556,44 +611,61 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
         return hipGetLastError();
     }
 
+    auto tiles_of = [&](int tm, int tn) { return (long long)d.B * ((d.n_keep + tm - 1) / tm) * ((r + tn - 1) / tn); };
+    int tm = 128, tn = 128;
+    if (tiles_of(64, 64) <= 288) tm = tn = 64;
+    else if (tiles_of(128, 128) > 256) {
+        if (tiles_of(128, 192) <= 256) tn = 192;
+        else if (tiles_of(192, 128) <= 256) tm = 192;
+    }
+    const long long tiles = tiles_of(tm, tn);
+    // Who takes the norms; either way gives the same bits.  In the product they cost every tile its dominant rows' squares again, and LDS
+    // reads, which are what bounds a slice; beside the ranking, on workgroups of 16 rows, they cost the launch a pass over all rows,
+    // little of it while all its workgroups are on the chip at once.  Beside the ranking -> in the product, whole calls, us (bf16 unless said):
+    //   64 x 64 tiles: in it when the launch would have more than 256 workgroups, one to a compute unit (16 x 256 rows of 12 KB 62.8 ->
+    //       57.9, 9 x 460 64.5 -> 59.8, 13 x 936 of 1 KB in fp32 55.6 -> 50.1; with fewer 2 x 1300 of 7 KB 42.6 -> 43.6, 4 x 576 even)
+    //   128 x 128, a ring of four: when it would have more than 512 (7 x 1733 of 7 KB 93.4 -> 89.0; with fewer 1 x 2600 of 12 KB 76.1 ->
+    //       84.5, 3 x 1300 80.5 -> 84)
+    //   128 x 192: always (8 x 1792 of 8 KB 123.2 -> 118.5, 1 x 4500 of 12 KB 113.7 -> 109.7); 192 x 128: never (their squares' sums and
+    //       the products' do not fit the registers: 1 x 10560 of 12 KB 171 -> 187), nor a ring of two, whose workgroups would no longer
+    //       share a compute unit (9 x 2034 of 10 KB 188 -> 249)
+    const long long beside_wgs = (long long)d.B * ((d.n_img + 63) / 64 + (d.n_img + 15) / 16);
+    const bool beside = tm == 64 ? beside_wgs <= 256 : tn == 192 ? false : tm == 192 || tiles > 256 || beside_wgs <= 512;
     NormJob norm{};
-    norm.src = a.plane[0].src + (long long)d.img_begin * a.plane[0].row_bytes;
-    norm.stride_b = a.plane[0].src_stride_b;
-    norm.inv_norm = a.inv_norm;
-    norm.row_bytes = a.plane[0].row_bytes; norm.dtype = planes[0].dtype; norm.n = d.n_img;
+    if (beside) {
+        a.inv_norm = reinterpret_cast<float *>(ws + w.inv_norm);
+        norm.src = a.plane[0].src + (long long)d.img_begin * a.plane[0].row_bytes;
+        norm.stride_b = a.plane[0].src_stride_b;
+        norm.inv_norm = a.inv_norm;
+        norm.row_bytes = a.plane[0].row_bytes; norm.dtype = planes[0].dtype; norm.n = d.n_img;
+    }
     prof.begin("sim_rank");
-    launch_rank(prof, score_mean, a.rank, d.n_img, d.B, ws + w.sorted, &norm);
+    launch_rank(prof, score_mean, a.rank, d.n_img, d.B, ws + w.sorted, beside ? &norm : nullptr);
     prof.end();
     prof.begin("sim_index");
     LVLM_LAUNCH(prof, sim_index_kernel, dim3((d.n_img + kSimChunk - 1) / kSimChunk, d.B), dim3(1024), 0, stream, a);
     prof.end();
     prof.begin("sim_gemm");
     {
-        auto tiles_of = [&](int tm, int tn) { return (long long)d.B * ((d.n_keep + tm - 1) / tm) * ((r + tn - 1) / tn); };
-        int tm = 128, tn = 128;
-        if (tiles_of(64, 64) <= 288) tm = tn = 64;
-        else if (tiles_of(128, 128) > 256) {
-            if (tiles_of(128, 192) <= 256) tn = 192;
-            else if (tiles_of(192, 128) <= 256) tm = 192;
-        }
-        const long long tiles = tiles_of(tm, tn);
         const long long per_xcd = (tiles + 7) / 8;
         a.run = (int)(per_xcd <= 64 ? per_xcd : kSimGN * kSimGM);
         const dim3 ggrid((unsigned)(((tiles + a.run - 1) / a.run + 7) / 8 * 8 * a.run));
         const bool bf = planes[0].dtype == LVLM_BF16;
         const bool ragged = (planes[0].row_elems * (bf ? 2 : 4)) % 128 != 0;
-#define LVLM_GEMM_OF(DT, RAGGED, TM, TN, NWN, NWM, RING) \
-    LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, TM, TN, NWN, NWM, RING, RAGGED>), ggrid, dim3(64 * NWN * NWM), 0, stream, a)
+#define LVLM_GEMM_OF(DT, RAGGED, NORMS, TM, TN, NWN, NWM, RING) \
+    LVLM_LAUNCH(prof, (sim_gemm_kernel<DT, TM, TN, NWN, NWM, RING, NORMS, RAGGED>), ggrid, dim3(64 * NWN * NWM), 0, stream, a)
 #define LVLM_GEMM(...)                                                                                                      \
     if (bf && ragged) LVLM_GEMM_OF(LVLM_BF16, true, __VA_ARGS__);                                                          \
     else if (bf) LVLM_GEMM_OF(LVLM_BF16, false, __VA_ARGS__);                                                              \
     else if (ragged) LVLM_GEMM_OF(LVLM_F32, true, __VA_ARGS__);                                                            \
     else LVLM_GEMM_OF(LVLM_F32, false, __VA_ARGS__)
-        if (tm == 64) { LVLM_GEMM(64, 64, 2, 2, 4); }
-        else if (tn == 192) { LVLM_GEMM(128, 192, 4, 2, 3); }
-        else if (tm == 192) { LVLM_GEMM(192, 128, 2, 4, 3); }
-        else if (tiles <= 256) { LVLM_GEMM(128, 128, 2, 4, 4); }
-        else { LVLM_GEMM(128, 128, 2, 2, 2); }
+        if (tm == 64 && beside) { LVLM_GEMM(false, 64, 64, 2, 2, 4); }
+        else if (tm == 64) { LVLM_GEMM(true, 64, 64, 2, 2, 4); }
+        else if (tn == 192) { LVLM_GEMM(true, 128, 192, 4, 2, 3); }
+        else if (tm == 192) { LVLM_GEMM(false, 192, 128, 2, 4, 3); }
+        else if (tiles <= 256 && beside) { LVLM_GEMM(false, 128, 128, 2, 4, 4); }
+        else if (tiles <= 256) { LVLM_GEMM(true, 128, 128, 2, 4, 4); }
+        else { LVLM_GEMM(false, 128, 128, 2, 2, 2); }
 #undef LVLM_GEMM_OF
 #undef LVLM_GEMM
     }

@@ -1464,6 +1464,30 @@ def test_merge_similar_tile_shapes(ctx, dtype, B, n_img, n_keep, C):
     _similar_case(ctx, dtype, B, 1, n_img, 2, C, n_keep, 700 + C, clusters=0, extra=False)
 
 
+@pytest.mark.parametrize("dtype,B,n_img,n_keep,C", [
+    (torch.bfloat16, 2, 1300, 400, 200),      # 64 x 64 tiles, norms beside the ranking: 206 workgroups
+    (torch.bfloat16, 11, 300, 150, 200),      # ... in the product: 264
+    (torch.float32, 16, 300, 129, 72),
+    (torch.bfloat16, 1, 2175, 1087, 200),     # 128 x 128, four slots, beside
+    (torch.bfloat16, 7, 1733, 1573, 328),     # ... in the product
+    (torch.float32, 7, 1733, 1573, 72),
+    (torch.bfloat16, 8, 1730, 1200, 328),     # 128 x 192
+    (torch.float32, 8, 1730, 1200, 840),      # ... fp32, 27 slices: every one of the eight sums is come back to
+    (torch.float32, 1, 10560, 560, 136),      # 192 x 128, beside
+    (torch.bfloat16, 3, 3000, 1500, 328)])    # 128 x 128, two slots, beside
+def test_merge_similar_norms(ctx, dtype, B, n_img, n_keep, C):
+    """Rows times powers of two have the same cosines to the last bit (products, sums and norms scale exactly), so every token
+    joins the same dominant one; rows of zeros, whose norm counts as one, stay what they are."""
+    g = torch.Generator().manual_seed(C + n_img)
+    hid = torch.randn(B, n_img + 3, C, generator=g).to(dtype)
+    hid[:, 5:n_img:97] = 0
+    scaled = (hid.float() * torch.exp2(torch.randint(-9, 10, (B, n_img + 3, 1), generator=g).float())).to(dtype)
+    score = torch.rand(B, n_img, generator=g).to(DEV)
+    joined = [ctx.merge_similar([h.to(DEV)], score, img_begin=1, n_img=n_img, n_keep=n_keep, rules=[lv.RULE_TOP])[2]
+              for h in (hid, scaled)]
+    assert torch.equal(joined[0], joined[1])
+
+
 @pytest.mark.parametrize("n_img,n_keep,clusters", [(200, 60, 5), (700, 2, 2), (40, 39, 0)])
 def test_merge_similar_sizes_of_planes_that_are_only_kept(ctx, n_img, n_keep, clusters):
     """Cluster sizes are an output of their own: planes whose rows are all kept (no weighted plane) change nothing about
