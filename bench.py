@@ -523,8 +523,8 @@ def kernel_work(ctx, lv, w, layers, dec_lens, moved, merge="rank", per_layer=Fal
                 add("sim_merge", "hbm", B * (n_img + en["merge_to"] + 2.0 * outside) * rowb)
             else:
                 add("merge_rank", "hbm", 8.0 * B * en["n_img"])             # scores in, ranks out
-                add("merge_index", "hbm", 8.0 * B * en["n_img"])            # ranks in, index lists out
-                add("merge_gather", "hbm", B * (N + N - r) * (w.hidden * e + 3 * 4))
+                # ranks in, index lists out, and the rows
+                add("merge_gather", "hbm", B * (8.0 * en["n_img"] + (N + N - r) * (w.hidden * e + 3 * 4)))
                 add("merge_finalize", "hbm", B * w.hidden * e)              # the merged row
         elif en["merge_to"] is not None:                                    # a 100 % stage copies the planes
             add("sim_copy" if merge == "similar" else "merge_gather", "hbm", B * 2 * N * (w.hidden * e + 3 * 4))

@@ -84,7 +84,7 @@ PrefillWs prefill_ws(const lvlm_prefill_desc &d);
 lvlm_score_desc prefill_score_desc(const lvlm_prefill_desc &d);   // the score call the last T rows amount to
 
 struct MergeWs {
-    size_t rank_part, dst_of, wgt, partial, sorted, total;
+    size_t rank_part, kept, partial, sorted, total;
     int n_split;   // always 1: the rank kernel leaves complete ranks
     int n_chunk;   // source-row chunks of the gather kernel (partial sums per chunk)
     int rows_per_chunk;
@@ -199,6 +199,7 @@ struct Prof {
 // ---- launches (defined in the .hip files; all asynchronous on `stream`) ----
 // scratch: rank_scratch_bytes(n, B) bytes for the sorted blocks of long sequences, or null (counting at any length)
 size_t rank_scratch_bytes(int n, int B);
+// kept: [B, ceil(n / 64)], how many of every 64 tokens have a rank below n_kept (null: not counted)
 // norm: 1 / |row| of these rows on the side, in the same launch (null: none)
 struct NormJob {
     const char *src;        // row 0 of sequence 0; rows of row_bytes (a multiple of 16)
@@ -206,7 +207,8 @@ struct NormJob {
     float *inv_norm;        // [B, n]
     int row_bytes, dtype, n;
 };
-void launch_rank(const Prof &prof, const float *score, int32_t *rank, int n, int B, void *scratch, const NormJob *norm = nullptr);
+void launch_rank(const Prof &prof, const float *score, int32_t *rank, int n, int B, void *scratch, const NormJob *norm = nullptr,
+                 int32_t *kept = nullptr, int n_kept = 0);
 // Which dominant token every other token joined, and what the similarity merge makes of it: the tokens ordered by
 // (owner, index), the dominant ones behind.
 struct OwnerJob {

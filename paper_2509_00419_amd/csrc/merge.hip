@@ -8,14 +8,11 @@
 //                    over the 16 waves.  Nothing iterative or data dependent.
 //                    Long sequences: rank_block_kernel + rank_search_kernel
 //                    (blocks of 1024 tokens sorted by counting, then one
-//                    binary search per token and block).
-//   index_kernel     one workgroup per 4096 tokens: counts the kept tokens in
-//                    front of its chunk, prefix-scans its own "kept" flags
-//                    in index order and emits
-//                    keep_idx (ascending), merged_idx (rank order) and, per
-//                    source token, where it goes (row of P_unmerged or its
-//                    rank inside P_merged).
-//   gather_kernel    one streaming pass over every source row of every plane:
+//                    binary search per token and block).  Counts the kept
+//                    tokens of every 64 on the way.
+//   gather_kernel    works out where its rows' tokens go (and emits keep_idx,
+//                    ascending, and merged_idx, in rank order); then
+//                    one streaming pass over every source row of every plane:
 //                    a kept row is copied to its new place with 128-bit loads
 //                    and stores, a merged row is multiplied by its rank weight
 //                    and accumulated in fp32 registers; each row chunk leaves
@@ -32,6 +29,11 @@ namespace {
 
 constexpr int kGatherRows = 8;     // rows per batch (all of a batch's loads are in flight together)
 constexpr int kGatherWgs = 1536;   // workgroups the gather launch aims for (six per compute unit)
+// Chunks of rows to a workgroup of the gather: as many as its threads hold, of no more tokens than its table does.
+__host__ __device__ inline int gather_chunks(const PlaneDev &p, int rows_per_chunk) {
+    const int most = 1024 / rows_per_chunk, fit = 256 >> p.tpr_log2;
+    return fit < most ? fit : most;
+}
 constexpr long long kGatherCached = 256ll << 20;       // bytes of source rows that the memory-side cache can hold
 
 
@@ -47,6 +49,8 @@ struct RankArgs {
     KEY key;
     int32_t *rank;                  // [B, n]
     unsigned long long *sorted;     // [B, n_blocks, 1024]  (long sequences)
+    int32_t *kept;                  // [B, ceil(n / 64)]  tokens of every 64 with rank < n_kept, or null
+    int n_kept;
     int n, n_blocks;
     int rank_wgs;                   // workgroups of the launch that rank; the rest take rows of `norm`
     NormJob norm;
@@ -110,6 +114,16 @@ __device__ __forceinline__ void norm_rows(const NormJob &w, int wg, int b) {
     if (lane == 0) w.inv_norm[(long long)b * w.n + j] = s > 0.f ? 1.0f / sqrtf(s) : 1.0f;
 }
 
+// One wave's 64 tokens, j = 64 m + lane (lanes past the last token are not here): their ranks, and how many of them are kept.
+template <class KEY>
+__device__ __forceinline__ void put_rank(const RankArgs<KEY> &a, int b, int j, int rank) {
+    a.rank[(long long)b * a.n + j] = rank;
+    if (a.kept) {
+        const unsigned long long bal = __ballot(rank < a.n_kept);
+        if ((j & 63) == 0) a.kept[(long long)b * ((a.n + 63) / 64) + j / 64] = __popcll(bal);
+    }
+}
+
 // rank[j] = #{i : key_i > key_j, or key_i == key_j and i < j}.  A workgroup ranks 64 tokens: every wave
 // holds the same 64 tokens (one per lane) and counts over its own sixteenth of the staged keys, read
 // from LDS as broadcast 128-bit words; the sixteen counts are added through LDS.
@@ -168,7 +182,7 @@ __global__ __launch_bounds__(1024) void rank_kernel(RankArgs<KEY> a) {
 #pragma unroll
         for (int w = 0; w < 16; ++w) tot += cnt_lds[w][lane];
         if constexpr (KEY::kOrder) a.key.put(b, a.n, j, tot);
-        else a.rank[(long long)b * a.n + j] = tot;
+        else put_rank(a, b, j, tot);
     }
 }
 
@@ -180,11 +194,11 @@ __global__ __launch_bounds__(1024) void rank_kernel(RankArgs<KEY> a) {
 //                       token, spread over all workgroups): a token's word goes to its place in the block's
 //                       descending order; places past the last token of a partly filled block hold 0 (below every word)
 //   rank_search_kernel  a token's rank = over all sorted blocks, the number of words above its own, each found by
-//                       a binary search (11 probes) in LDS; a workgroup stages eight blocks and searches them for
-//                       256 tokens, the groups of eight add their counts into the rank
+//                       a binary search (11 probes) in LDS; a workgroup stages sixteen blocks at a time, and each of its
+//                       waves searches one of them for the same 64 tokens
 constexpr int kSortBlock = 1024;
 constexpr int kSortMinTokens = 4096;
-constexpr int kSortStage = 8;        // sorted blocks held in LDS at a time (64 KB)
+constexpr int kSortStage = 16;       // sorted blocks held in LDS at a time (128 KB)
 
 __device__ __forceinline__ unsigned long long order_word(uint32_t key, int idx) {
     return ((unsigned long long)key << 32) | (unsigned long long)(0xffffffffu - (uint32_t)idx);
@@ -228,155 +242,123 @@ __global__ __launch_bounds__(1024) void rank_block_kernel(RankArgs<KEY> a) {
 #pragma unroll
         for (int w = 0; w < 16; ++w) place += cnt_lds[w][lane];
         // tokens past the end fill the places past the last token (the real ones take 0 .. count-1 between them)
-        if (j < a.n) {
-            out[place] = mine;
-            a.rank[(long long)b * a.n + j] = 0;          // the searches add to it
-        } else {
-            out[j - r0] = 0ull;
-        }
+        if (j < a.n) out[place] = mine;
+        else out[j - r0] = 0ull;
     }
 }
 
+// A workgroup's time is what it stages (128 KB, a compute unit's L2 bandwidth) and eleven dependent LDS probes.  16384 tokens are one
+// workgroup for every compute unit.  (Eight blocks and 256 tokens to a workgroup, the groups of eight adding up in the
+// rank by atomics, and a third launch to lay out the order by owner: the whole similarity merge of 11908 tokens 315 -> 310 us.)
 template <class KEY>
-__global__ __launch_bounds__(256) void rank_search_kernel(RankArgs<KEY> a) {
+__global__ __launch_bounds__(1024) void rank_search_kernel(RankArgs<KEY> a) {
     __shared__ __attribute__((aligned(16))) unsigned long long words[kSortStage * kSortBlock];
-    const int tid = threadIdx.x;
-    const int b = blockIdx.y;
-    const int j = blockIdx.x * 256 + tid;
-    const unsigned long long mine = j < a.n ? order_word(a.key.at(b, a.n, j), j) : ~0ull;
-    const uint4 *src = reinterpret_cast<const uint4 *>(a.sorted + (long long)b * a.n_blocks * kSortBlock);
-    int rank = 0;
-    {
-        // one group of eight sorted blocks per workgroup (blockIdx.z): the groups' counts meet in rank[j], which
-        // rank_block_kernel has set to 0, by an atomic add -- a CU streams too slowly to stage them all in turn
-        const int g0 = blockIdx.z * kSortStage;
-        const int nb = min(kSortStage, a.n_blocks - g0);
-        const int units = nb * (kSortBlock / 2);                       // 16-byte units to stage
-        constexpr int kUnits = kSortStage * (kSortBlock / 2), kPer = kUnits / 256;
-        uint4 v[kPer];                                                 // all of a thread's loads in flight together
-#pragma unroll
-        for (int x = 0; x < kPer; ++x) v[x] = src[(long long)g0 * (kSortBlock / 2) + min(256 * x + tid, units - 1)];
-#pragma unroll
-        for (int x = 0; x < kPer; ++x)                                 // blocks past the last one: words of 0
-            reinterpret_cast<uint4 *>(words)[256 * x + tid] = 256 * x + tid < units ? v[x] : make_uint4(0, 0, 0, 0);
-        __syncthreads();
-        // words above `mine` in each staged block: the blocks descend, so that is the first place whose word is
-        // not above it.  Branch-free bisections, the eight blocks' side by side: their probes are independent.
-        int pos[kSortStage];
-#pragma unroll
-        for (int bb = 0; bb < kSortStage; ++bb) pos[bb] = 0;
-#pragma unroll
-        for (int step = kSortBlock / 2; step >= 1; step >>= 1) {
-#pragma unroll
-            for (int bb = 0; bb < kSortStage; ++bb) pos[bb] += words[bb * kSortBlock + pos[bb] + step - 1] > mine ? step : 0;
-        }
-#pragma unroll
-        for (int bb = 0; bb < kSortStage; ++bb) rank += pos[bb] + (words[bb * kSortBlock + pos[bb]] > mine ? 1 : 0);   // place 1023 itself
-    }
-    if (j < a.n) {
-        if (gridDim.z > 1) atomicAdd(&a.rank[(long long)b * a.n + j], rank);
-        else if constexpr (KEY::kOrder) a.key.put(b, a.n, j, rank);
-        else a.rank[(long long)b * a.n + j] = rank;
-    }
-}
-
-// the order from ranks that several workgroups added up
-__global__ __launch_bounds__(256) void rank_order_kernel(RankArgs<ByOwner> a) {
-    const int j = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
-    if (j < a.n) a.key.put(b, a.n, j, a.rank[(long long)b * a.n + j]);
-}
-
-
-struct IndexArgs {
-    const int32_t *rank;
-    int32_t *dst_of;       // [B, n]: >= 0 row inside the new image span; -1: most important merged token;
-                           //         -2: any other merged token
-    float *wgt;            // [B, n]: merge weight of the token (0 for kept tokens)
-    int32_t *keep_idx;     // [B, n_keep-1] or null
-    int32_t *merged_idx;   // [B, r+1] or null
-    const float *w;        // rank -> weight table, or null for the linear table
-    float lin_scale;       // 1 / (m (m+1) / 2)
-    int n, n_keep;
-};
-
-// One workgroup per 1024 tokens of a sequence, one per thread.  The workgroup first counts the kept tokens in front of its
-// chunk -- a pass over the ranks before it, four of a thread's loads in flight together -- so the chunks need nothing from each
-// other; ballots and one exchange through LDS then give every kept token its row in P_unmerged.  Then keep_idx (ascending),
-// merged_idx (by rank) and the per-token destination are written.  Bound by its chain of latencies: with 4096 tokens to a
-// workgroup and scans by lane exchanges 7.1 us at 16384 tokens against 4.7, 7.0 against 3.9 at 8000, 3.4 against 2.7 at 2048.
-constexpr int kIndexChunk = 1024;
-__global__ __launch_bounds__(1024) void index_kernel(IndexArgs a) {
-    __shared__ __attribute__((aligned(16))) int wave_kept[16], wave_before[16];
+    __shared__ int above[kSortStage][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.y;
-    const int s0 = blockIdx.x * kIndexChunk, j = s0 + tid;
-    const int n_unmerged = a.n_keep - 1;
-    const int32_t *rank = a.rank + (long long)b * a.n;
-    const int m = a.n - n_unmerged;
-
-    const int rk = j < a.n ? rank[j] : INT_MAX;
-    // kept tokens before the chunk (s0 is a multiple of 1024: whole 16-byte words when the rows are aligned)
-    uint32_t before = 0;
-    if ((a.n & 3) == 0) {
-#pragma unroll 4
-        for (int i = 4 * tid; i < s0; i += 4 * 1024) {
-            const int4 v = *reinterpret_cast<const int4 *>(rank + i);
-            before += (v.x < n_unmerged) + (v.y < n_unmerged) + (v.z < n_unmerged) + (v.w < n_unmerged);
-        }
-    } else {
-#pragma unroll 4
-        for (int i = tid; i < s0; i += 1024) before += rank[i] < n_unmerged;
-    }
-    const bool kept = rk < n_unmerged;
-    const unsigned long long bal = __ballot(kept);
-    before = wave_reduce_u32(before, [](uint32_t x, uint32_t y) { return x + y; });
-    if (lane == 0) {
-        wave_kept[wave] = __popcll(bal);
-        wave_before[wave] = (int)before;
-    }
-    __syncthreads();
-    int p = __popcll(bal & ((1ull << lane) - 1ull));
+    const int j = blockIdx.x * 64 + lane;
+    const unsigned long long mine = j < a.n ? order_word(a.key.at(b, a.n, j), j) : ~0ull;
+    const uint4 *src = reinterpret_cast<const uint4 *>(a.sorted + (long long)b * a.n_blocks * kSortBlock);
+    int cnt = 0;
+    for (int g0 = 0; g0 < a.n_blocks; g0 += kSortStage) {
+        const int nb = min(kSortStage, a.n_blocks - g0);
+        const int units = nb * (kSortBlock / 2);                       // 16-byte units to stage
+        constexpr int kPer = kSortStage * (kSortBlock / 2) / 1024;
+        if (g0) __syncthreads();                                       // the blocks before have been searched
 #pragma unroll
-    for (int w = 0; w < 16; ++w) p += wave_before[w] + (w < wave ? wave_kept[w] : 0);
-    if (j >= a.n) return;
-    const long long at = (long long)b * a.n + j;
-    if (kept) {
-        a.dst_of[at] = p;
-        a.wgt[at] = 0.f;
-        if (a.keep_idx) a.keep_idx[(long long)b * n_unmerged + p] = j;
-    } else {
-        const int k = rk - n_unmerged;
-        a.dst_of[at] = k == 0 ? -1 : -2;
-        a.wgt[at] = a.w ? a.w[k] : (float)(m - k) * a.lin_scale;
-        if (a.merged_idx) a.merged_idx[(long long)b * m + k] = j;
+        for (int x = 0; x < kPer; ++x)                                 // (places past the last block are not read)
+            reinterpret_cast<uint4 *>(words)[1024 * x + tid] = src[(long long)g0 * (kSortBlock / 2) + min(1024 * x + tid, units - 1)];
+        __syncthreads();
+        if (wave < nb) {
+            // words above `mine` in the wave's block: the block descends, so that is the first place whose word is not above it
+            const unsigned long long *const blk = words + wave * kSortBlock;
+            int pos = 0;
+#pragma unroll
+            for (int step = kSortBlock / 2; step >= 1; step >>= 1) pos += blk[pos + step - 1] > mine ? step : 0;
+            cnt += pos + (blk[pos] > mine ? 1 : 0);                    // place 1023 itself
+        }
+    }
+    above[wave][lane] = cnt;
+    __syncthreads();
+    if (wave == 0 && j < a.n) {
+        int rank = 0;
+#pragma unroll
+        for (int w = 0; w < kSortStage; ++w) rank += above[w][lane];
+        if constexpr (KEY::kOrder) a.key.put(b, a.n, j, rank);
+        else put_rank(a, b, j, rank);
     }
 }
+
 
 // ---- gather -----------------------------------------------------------------
 
 struct GatherArgs {
     PlaneDev plane[LVLM_MAX_PLANES];
-    const int32_t *dst_of;   // null: identity (nothing removed)
-    const float *wgt;        // per-token merge weight
+    const int32_t *rank;     // [B, n_img], null: identity (nothing removed)
+    const int32_t *kept;     // [B, ceil(n_img / 64)]  how many of every 64 tokens are kept
+    int32_t *keep_idx;       // [B, n_keep-1] or null
+    int32_t *merged_idx;     // [B, r+1] or null
+    const float *w;          // rank -> weight table, or null for the linear table
+    float lin_scale;         // 1 / (m (m+1) / 2)
     float *partial;          // [B][n_planes][n_sub_max][max_row_elems]
     int B, N, img_begin, n_img, n_keep, n_planes;
     int rows_per_sub, n_sub_max, max_row_elems;
 };
 
+// Where the image tokens of a workgroup's rows go, and with what weight they are merged.
+constexpr int kGatherTable = 1024;
+struct GatherTable {
+    int code[kGatherTable];      // >= 0: row inside the new image span; -1: most important merged token; -2: any other merged token
+    float wgt[kGatherTable];     // merge weight (0 for kept tokens)
+};
+
+// Tokens [lo, hi) of a sequence, 64 of them (aligned) to a wave at a time: kept tokens stay in index order, so a token's row is the
+// number of kept ones before it -- those of the 64s in front, which the ranking has counted, and those of its own.  It is a
+// chain of one load and a reduction, beside the workgroup's first rows on their way; as a launch of its own, with destination and weight
+// of every token through memory, it took 2.3 to 4.8 us of a
+// call (whole calls, the search of long sequences above included: 16384 -> 5091 rows of 12 KB 78.0 -> 69.0 us, 4626 -> 2313 of 10 KB
+// 31.0 -> 26.9, 7 x 465 -> 144 of 8 KB and twice 2 KB 25.6 -> 23.4, 514 -> 359 of 10 KB 15.6 -> 15.1).  `list`: the index lists are written too.
+__device__ __forceinline__ void gather_table(const GatherArgs &a, int b, int lo, int hi, bool list, GatherTable &t) {
+    const int lane = threadIdx.x & 63, n_unmerged = a.n_keep - 1, m = a.n_img - n_unmerged;
+    const int32_t *rank = a.rank + (long long)b * a.n_img, *kept = a.kept + (long long)b * ((a.n_img + 63) / 64);
+    for (int blk = lo / 64 + (threadIdx.x >> 6); 64 * blk < hi; blk += blockDim.x >> 6) {
+        const int j = 64 * blk + lane;
+        const int rk = j < a.n_img ? rank[j] : INT_MAX;
+        uint32_t before = 0;
+#pragma unroll 4
+        for (int i = lane; i < blk; i += 64) before += kept[i];
+        before = wave_reduce_u32(before, [](uint32_t x, uint32_t y) { return x + y; });
+        const unsigned long long bal = __ballot(rk < n_unmerged);
+        if (j < lo || j >= hi) continue;
+        if (rk < n_unmerged) {
+            const int p = (int)before + __popcll(bal & ((1ull << lane) - 1ull));
+            t.code[j - lo] = p;
+            t.wgt[j - lo] = 0.f;
+            if (list && a.keep_idx) a.keep_idx[(long long)b * n_unmerged + p] = j;
+        } else {
+            const int k = rk - n_unmerged;
+            t.code[j - lo] = k == 0 ? -1 : -2;
+            t.wgt[j - lo] = a.w ? a.w[k] : (float)(m - k) * a.lin_scale;
+            if (list && a.merged_idx) a.merged_idx[(long long)b * m + k] = j;
+        }
+    }
+}
+
 // One thread group walks `rows_per_sub` consecutive source rows of one plane, one unit column per thread.
-// The loop is free of data-dependent branches before its stores: row data, destination code and weight
-// of a batch of RB rows are loaded unconditionally (indices clamped into range), so the loads of many
-// rows are in flight at once; then kept rows are stored and every row is multiplied by its weight (zero
-// unless it is merged) and accumulated.
+// The loop is free of data-dependent branches before its stores: the rows of a batch are loaded unconditionally (indices
+// clamped into range), so the loads of many rows are in flight at once; then kept rows are stored and merged ones are
+// multiplied by their weights and accumulated.
 template <int DT, int UB, int TEAMS, bool ONCE>
-__device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev &p, int pi, int b, float (*other)[256]) {
+__device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev &p, int pi, int b, float (*other)[256],
+                                             GatherTable &table) {
     using U = typename Unit<UB>::type;
     constexpr int RB = kGatherRows;
     const int tid = threadIdx.x;
     const int tpr = 1 << p.tpr_log2;
-    const int chunks = 256 >> p.tpr_log2;                 // of rows, per workgroup
+    const int chunks = gather_chunks(p, a.rows_per_sub);  // of rows, per workgroup
     const int team = tid >> 8;                            // a chunk's batches of rows go to the teams in turn
-    const int sub = blockIdx.x * chunks + ((tid & 255) >> p.tpr_log2);
+    const int group = (tid & 255) >> p.tpr_log2;
+    const int sub = blockIdx.x * chunks + group;
     const int row_units = p.row_bytes / UB;
     if ((int)blockIdx.x * chunks >= p.n_sub || (int)blockIdx.y >= p.col_blocks) return;      // uniform
     const int unit_raw = blockIdx.y * 256 + (tid & (tpr - 1));
@@ -385,9 +367,9 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
     const int r = a.n_img - a.n_keep;
     const char *src = p.src + (long long)b * p.src_stride_b + (long long)unit * UB;
     char *dst = p.dst + (long long)b * p.dst_stride_b + (long long)unit * UB;
-    const int n_lo = sub * a.rows_per_sub;
+    const int n_lo = group < chunks ? min(a.N, sub * a.rows_per_sub) : a.N;
     const int n_hi = min(a.N, n_lo + a.rows_per_sub);     // (a chunk past the last one has no rows)
-    if (a.dst_of == nullptr) {
+    if (a.rank == nullptr) {
         // nothing is removed (kernel-uniform case): plain row copy
         if (active) {
 #pragma unroll 4
@@ -397,45 +379,49 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
         }
         return;
     }
-    const int32_t *dst_of = a.dst_of + (long long)b * a.n_img;
-    const float *wgt = a.wgt + (long long)b * a.n_img;
     const bool weighted = p.rule == LVLM_RULE_WEIGHTED;             // uniform per plane
     const int new_row = a.img_begin + a.n_keep - 1;
+
+    U val[RB];
+    auto load = [&](int n0) {
+#pragma unroll
+        for (int x = 0; x < RB; ++x) {
+            const U *at = reinterpret_cast<const U *>(src + (long long)min(n0 + x, n_hi - 1) * p.row_bytes);
+            val[x] = ONCE ? load_once(at) : *at;
+        }
+    };
+    int n0 = n_lo + team * RB;
+    load(n0);
+    // image tokens of the workgroup's rows, no more than chunks * rows_per_sub <= kGatherTable of them
+    const int row0 = blockIdx.x * chunks * a.rows_per_sub;
+    const int lo = max(row0 - a.img_begin, 0);
+    gather_table(a, b, lo, min(row0 + chunks * a.rows_per_sub - a.img_begin, a.n_img), pi == 0 && blockIdx.y == 0, table);
+    __syncthreads();
 
     Acc<DT, UB> acc;
 #pragma unroll
     for (int i = 0; i < Acc<DT, UB>::NE; ++i) acc.v[i] = 0.f;
 
-    for (int n0 = n_lo + team * RB; n0 < n_hi; n0 += TEAMS * RB) {
-        // all loads of the batch first (clamped row / token indices keep every address valid) ...
-        U val[RB];
-        int code[RB];
-        float wk[RB];
-#pragma unroll
-        for (int x = 0; x < RB; ++x) {
-            const int n = min(n0 + x, n_hi - 1);
-            const int j = min(max(n - a.img_begin, 0), a.n_img - 1);
-            const U *at = reinterpret_cast<const U *>(src + (long long)n * p.row_bytes);
-            val[x] = ONCE ? load_once(at) : *at;
-            code[x] = dst_of[j];
-            wk[x] = wgt[j];
-        }
-        // ... then the stores and the weighted accumulation
+    while (n0 < n_hi) {
 #pragma unroll
         for (int x = 0; x < RB; ++x) {
             const int n = n0 + x;
             const bool valid = active && n < n_hi;
             const bool in_img = n >= a.img_begin && n < a.img_begin + a.n_img;
+            const int at = min(max(n - a.img_begin - lo, 0), kGatherTable - 1);
+            const int code = table.code[at];
             int dest = n < a.img_begin ? n : n - r;                  // rows outside the image span
-            if (in_img) dest = code[x] >= 0 ? a.img_begin + code[x] : (code[x] == -1 && !weighted ? new_row : -1);
+            if (in_img) dest = code >= 0 ? a.img_begin + code : (code == -1 && !weighted ? new_row : -1);
             if (valid && dest >= 0) *reinterpret_cast<U *>(dst + (long long)dest * p.row_bytes) = val[x];
             // Only the rows of P_merged enter the sum (a kept or text row must not, whatever it holds: 0 * inf
             // would poison the merged token).  A row is shared by whole waves for all but the narrowest planes,
             // so the test is uniform there.
             if constexpr (DT != LVLM_I32) {
-                if (weighted && valid && in_img && code[x] < 0) accumulate<DT, UB>(acc, val[x], wk[x]);
+                if (weighted && valid && in_img && code < 0) accumulate<DT, UB>(acc, val[x], table.wgt[at]);
             }
         }
+        n0 += TEAMS * RB;
+        if (n0 < n_hi) load(n0);
     }
     if constexpr (DT != LVLM_I32) {
         if (!weighted) return;                                       // uniform
@@ -450,7 +436,7 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
 #pragma unroll
             for (int i = 0; i < NE; ++i) acc.v[i] += other[i][tid];
         }
-        if (active && sub < p.n_sub) {
+        if (active && group < chunks && sub < p.n_sub) {
             float *out = a.partial + (((long long)b * a.n_planes + pi) * a.n_sub_max + sub) * a.max_row_elems +
                          (long long)unit * NE;
 #pragma unroll
@@ -475,6 +461,7 @@ __device__ __forceinline__ void gather_plane(const GatherArgs &a, const PlaneDev
 template <int TEAMS, bool ONCE>
 __global__ __launch_bounds__(256 * TEAMS) void gather_kernel(GatherArgs a) {
     __shared__ float other[TEAMS > 1 ? 8 : 1][256];       // the second team's sums
+    __shared__ GatherTable table;
     const int pi = blockIdx.z / a.B, b = blockIdx.z % a.B;
     // (selected by comparison: indexing the argument array with a run-time value would copy it to scratch)
     PlaneDev p = a.plane[0];
@@ -482,15 +469,15 @@ __global__ __launch_bounds__(256 * TEAMS) void gather_kernel(GatherArgs a) {
     for (int i = 1; i < LVLM_MAX_PLANES; ++i)
         if (pi == i) p = a.plane[i];
     if (p.dtype == LVLM_BF16) {
-        if (p.unit_bytes == 16) gather_plane<LVLM_BF16, 16, TEAMS, ONCE>(a, p, pi, b, other);
-        else if (p.unit_bytes == 4) gather_plane<LVLM_BF16, 4, TEAMS, ONCE>(a, p, pi, b, other);
-        else gather_plane<LVLM_BF16, 2, TEAMS, ONCE>(a, p, pi, b, other);
+        if (p.unit_bytes == 16) gather_plane<LVLM_BF16, 16, TEAMS, ONCE>(a, p, pi, b, other, table);
+        else if (p.unit_bytes == 4) gather_plane<LVLM_BF16, 4, TEAMS, ONCE>(a, p, pi, b, other, table);
+        else gather_plane<LVLM_BF16, 2, TEAMS, ONCE>(a, p, pi, b, other, table);
     } else if (p.dtype == LVLM_F32) {
-        if (p.unit_bytes == 16) gather_plane<LVLM_F32, 16, TEAMS, ONCE>(a, p, pi, b, other);
-        else gather_plane<LVLM_F32, 4, TEAMS, ONCE>(a, p, pi, b, other);
+        if (p.unit_bytes == 16) gather_plane<LVLM_F32, 16, TEAMS, ONCE>(a, p, pi, b, other, table);
+        else gather_plane<LVLM_F32, 4, TEAMS, ONCE>(a, p, pi, b, other, table);
     } else {
-        if (p.unit_bytes == 16) gather_plane<LVLM_I32, 16, TEAMS, ONCE>(a, p, pi, b, other);
-        else gather_plane<LVLM_I32, 4, TEAMS, ONCE>(a, p, pi, b, other);
+        if (p.unit_bytes == 16) gather_plane<LVLM_I32, 16, TEAMS, ONCE>(a, p, pi, b, other, table);
+        else gather_plane<LVLM_I32, 4, TEAMS, ONCE>(a, p, pi, b, other, table);
     }
 }
 
@@ -540,12 +527,15 @@ size_t rank_scratch_bytes(int n, int B) {
 
 namespace {
 template <class KEY>
-void launch_rank_by(const Prof &prof, const KEY &key, int32_t *rank, int n, int B, void *scratch, const NormJob *norm) {
+void launch_rank_by(const Prof &prof, const KEY &key, int32_t *rank, int n, int B, void *scratch, const NormJob *norm,
+                    int32_t *kept = nullptr, int n_kept = 0) {
     hipStream_t stream = prof.stream;
     RankArgs<KEY> a{};
     a.key = key;
     a.rank = rank;
     a.n = n;
+    a.kept = kept;
+    a.n_kept = n_kept;
     int norm_wgs = 0;
     if (norm) {
         a.norm = *norm;
@@ -555,12 +545,8 @@ void launch_rank_by(const Prof &prof, const KEY &key, int32_t *rank, int n, int 
         a.sorted = static_cast<unsigned long long *>(scratch);
         a.n_blocks = (n + kSortBlock - 1) / kSortBlock;
         a.rank_wgs = a.n_blocks * (kSortBlock / 64);
-        const int z = (a.n_blocks + kSortStage - 1) / kSortStage;
         LVLM_LAUNCH(prof, rank_block_kernel<KEY>, dim3(a.rank_wgs + norm_wgs, B), dim3(1024), 0, stream, a);
-        LVLM_LAUNCH(prof, rank_search_kernel<KEY>, dim3((n + 255) / 256, B, z), dim3(256), 0, stream, a);
-        if constexpr (KEY::kOrder) {
-            if (z > 1) LVLM_LAUNCH(prof, rank_order_kernel, dim3((n + 255) / 256, B), dim3(256), 0, stream, a);
-        }
+        LVLM_LAUNCH(prof, rank_search_kernel<KEY>, dim3((n + 63) / 64, B), dim3(1024), 0, stream, a);
         return;
     }
     a.rank_wgs = (n + kRankBlock - 1) / kRankBlock;
@@ -568,8 +554,9 @@ void launch_rank_by(const Prof &prof, const KEY &key, int32_t *rank, int n, int 
 }
 }  // namespace
 
-void launch_rank(const Prof &prof, const float *score, int32_t *rank, int n, int B, void *scratch, const NormJob *norm) {
-    launch_rank_by(prof, ByScore{score}, rank, n, B, scratch, norm);
+void launch_rank(const Prof &prof, const float *score, int32_t *rank, int n, int B, void *scratch, const NormJob *norm,
+                 int32_t *kept, int n_kept) {
+    launch_rank_by(prof, ByScore{score}, rank, n, B, scratch, norm, kept, n_kept);
 }
 
 void launch_owner_order(const Prof &prof, const OwnerJob &owners, int32_t *rank, int n, int B, void *scratch) {
@@ -594,9 +581,8 @@ MergeWs merge_ws(const lvlm_merge_desc &d, const lvlm_plane *planes) {
     w.n_chunk = (d.N + w.rows_per_chunk - 1) / w.rows_per_chunk;
     w.max_row_elems = max_elems;
     w.rank_part = 0;
-    w.dst_of = align_up(w.rank_part + (size_t)d.B * w.n_split * d.n_img * sizeof(int32_t), 256);
-    w.wgt = align_up(w.dst_of + (size_t)d.B * d.n_img * sizeof(int32_t), 256);
-    w.partial = align_up(w.wgt + (size_t)d.B * d.n_img * sizeof(float), 256);
+    w.kept = align_up(w.rank_part + (size_t)d.B * w.n_split * d.n_img * sizeof(int32_t), 256);
+    w.partial = align_up(w.kept + (size_t)d.B * ((d.n_img + 63) / 64) * sizeof(int32_t), 256);
     w.sorted = align_up(w.partial + (size_t)d.B * d.n_planes * w.n_chunk * max_elems * sizeof(float), 256);
     w.total = align_up(w.sorted + rank_scratch_bytes(d.n_img, d.B), 256);
     return w;
@@ -615,8 +601,13 @@ hipError_t launch_merge(const Prof &prof, const lvlm_merge_desc &d, const MergeW
     g.max_row_elems = w.max_row_elems;
     g.partial = reinterpret_cast<float *>(ws + w.partial);
     const double m = (double)r + 1.0;
-    g.dst_of = r > 0 ? reinterpret_cast<const int32_t *>(ws + w.dst_of) : nullptr;
-    g.wgt = reinterpret_cast<const float *>(ws + w.wgt);
+    int32_t *rank = reinterpret_cast<int32_t *>(ws + w.rank_part), *kept = reinterpret_cast<int32_t *>(ws + w.kept);
+    g.rank = r > 0 ? rank : nullptr;
+    g.kept = kept;
+    g.keep_idx = keep_idx;
+    g.merged_idx = merged_idx;
+    g.w = wtab;
+    g.lin_scale = (float)(1.0 / (m * (m + 1.0) / 2.0));
 
     int grid_x = 1, grid_y = 1;
     bool any_weighted = false;
@@ -625,7 +616,7 @@ hipError_t launch_merge(const Prof &prof, const lvlm_merge_desc &d, const MergeW
         PlaneDev &p = g.plane[i];
         p = make_plane_dev(planes[i]);
         p.n_sub = w.n_chunk;
-        const int groups = 256 >> p.tpr_log2;
+        const int groups = gather_chunks(p, w.rows_per_chunk);
         const int gx = (p.n_sub + groups - 1) / groups;
         if (gx > grid_x) grid_x = gx;
         if (p.col_blocks > grid_y) grid_y = p.col_blocks;
@@ -634,21 +625,8 @@ hipError_t launch_merge(const Prof &prof, const lvlm_merge_desc &d, const MergeW
     }
 
     if (r > 0) {
-        int32_t *rank = reinterpret_cast<int32_t *>(ws + w.rank_part);
         prof.begin("merge_rank");
-        launch_rank(prof, score_mean, rank, d.n_img, d.B, ws + w.sorted);
-        prof.end();
-        IndexArgs ia{};
-        ia.rank = rank;
-        ia.dst_of = reinterpret_cast<int32_t *>(ws + w.dst_of);
-        ia.wgt = reinterpret_cast<float *>(ws + w.wgt);
-        ia.w = wtab;
-        ia.lin_scale = (float)(1.0 / (m * (m + 1.0) / 2.0));
-        ia.keep_idx = keep_idx;
-        ia.merged_idx = merged_idx;
-        ia.n = d.n_img; ia.n_keep = d.n_keep;
-        prof.begin("merge_index");
-        LVLM_LAUNCH(prof, index_kernel, dim3((d.n_img + kIndexChunk - 1) / kIndexChunk, d.B), dim3(1024), 0, stream, ia);
+        launch_rank(prof, score_mean, rank, d.n_img, d.B, ws + w.sorted, nullptr, kept, d.n_keep - 1);
         prof.end();
     }
     prof.begin("merge_gather");

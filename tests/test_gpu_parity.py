@@ -538,6 +538,22 @@ def test_merge_compact_index_chunks_and_fold_widths(ctx, dtype, B, n_img, C, n_k
     _merge_case(ctx, dtype, B, 0, n_img, 0, C, n_keep, seed=n_img, extra_planes=False)
 
 
+@pytest.mark.parametrize("dtype,B,n_sys,n_img,n_txt,C,n_keep", [
+    (torch.bfloat16, 1, 0, 2, 0, 8, 1),             # one 64, nearly empty
+    (torch.float32, 2, 9, 63, 1, 8, 20),
+    (torch.bfloat16, 2, 7, 64, 70, 8, 63),          # exactly one 64; more rows behind the image than one workgroup's
+    (torch.bfloat16, 3, 130, 65, 3, 24, 2),         # a second 64 of one token, whole workgroups in front of the image
+    (torch.float32, 1, 1, 1025, 5, 64, 500),        # tables of a narrow plane: 128 chunks of eight rows
+    (torch.bfloat16, 5, 33, 4095, 31, 8, 2000),     # the last length ranked by counting
+    (torch.bfloat16, 1, 3, 16384, 2, 8, 9000),      # sixteen sorted blocks: one round of the searches
+    (torch.float32, 2, 0, 16385, 0, 8, 1),          # a token more: two rounds
+    (torch.bfloat16, 1, 5, 33001, 40, 8, 20000),    # three rounds
+    (torch.bfloat16, 2, 3, 30000, 1, 8, 29999)])    # chunks of 128 rows, eight to a table
+def test_merge_compact_where_rows_go(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep):
+    """Kept tokens are counted in 64s by the ranking and placed by the workgroups that move their rows."""
+    _merge_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed=n_img)
+
+
 def test_merge_compact_planes_larger_than_the_memory_side_cache(ctx):
     # more than 256 MiB of source rows are loaded past the caches; the reference runs on the GPU in 64 bits
     B, n_img, C, n_keep = 2, 9000, 7680, 4000
