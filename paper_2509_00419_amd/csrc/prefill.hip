@@ -21,6 +21,8 @@ struct PrefillArgs {
     int B, N, Hq, Hkv, G, causal, T;
     int nqb;            // query blocks per head
     int heads_per_xcd;  // ceil(B * Hq / 8)
+    int parts_log2;     // balanced_block: parts of a head (log2), parts per XCD
+    int xcd_parts;
     float scale, scale_log2;
     long long qsb, qsn, qsh, ksb, ksn, ksh, vsb, vsn, vsh, osb, osn, osh;   // bytes
 };
@@ -679,7 +681,29 @@ __device__ __forceinline__ float word(const uint4 &v, int c) {
 // Measured (4 heads, 64 channels; a wave per 32 rows walking all tiles, K and V shared through LDS -> this kernel):
 // 640 tokens 57.1 -> 10.9 us, 2048 171 -> 50, 4200 347 -> 135 us (67 TFLOP/s), 16 sequences of 4200 1486 -> 1425 us
 // (101 TFLOP/s of the 155 a large fp32 matrix product reaches).
-template <int HD, int QB>
+// Workgroup number -> (head, batch, block), for blocks that are on the chip beside each other: causal ones are as long as their
+// last row, so what a compute unit is handed adds up to its time.  Heads are cut into parts (every P-th block) until the eight XCDs --
+// workgroups with the same remainder -- get equally many, neighbours in memory order; an XCD takes its parts' blocks longest first in
+// turns of its 32 compute units, every other turn backwards: the unit with the longest block of one turn has the shortest of the next.
+// Head by head instead, the first units had the longest block of every head (4 heads of 64 channels, 1503 tokens 42.1 -> 32.1 us, 2203
+// 60.6 -> 43.5, 4103 138 -> 109; 16 x 4 heads, 1103 tokens 151 -> 137, 3603 1160 -> 1125).  Up to 256 blocks, one to a unit, take the plain
+// grid: nothing to level, and the divisions here are 0.4 us before the first load (154 tokens 13.7 -> 14.2).
+struct BalancedBlock {
+    int b, h, qb;
+};
+__device__ __forceinline__ bool balanced_block(const PrefillArgs &a, int n_blocks, BalancedBlock &w) {
+    const int P = 1 << a.parts_log2, xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+    const int total = a.xcd_parts * ((n_blocks + P - 1) >> a.parts_log2);
+    const int turn = seq & ~31, last = min(turn + 31, total - 1);
+    const int rank = (seq & 32) ? turn + last - seq : seq;
+    const int level = rank / a.xcd_parts, part = xcd * a.xcd_parts + rank - level * a.xcd_parts, head = part >> a.parts_log2;
+    w.qb = n_blocks - 1 - ((level << a.parts_log2) + (part & (P - 1)));
+    w.b = head / a.Hq;
+    w.h = head - w.b * a.Hq;
+    return w.qb >= 0;
+}
+
+template <int HD, int QB, bool BALANCED>
 __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a) {
     constexpr int NW = HD / 16;             // 16-byte words of a row per lane
     constexpr int CPL = HD / 16;            // channels per lane
@@ -691,9 +715,11 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
-    const int qb = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;      // longest blocks first
-    const int g = h / a.G;
-    const int q0 = qb * 16 * QB;
+    BalancedBlock blk{(int)blockIdx.z, (int)blockIdx.y, (int)(gridDim.x - 1 - blockIdx.x)};      // longest blocks first
+    if constexpr (BALANCED)
+        if (!balanced_block(a, (a.N + 16 * QB - 1) / (16 * QB), blk)) return;
+    const int h = blk.h, b = blk.b, g = h / a.G;
+    const int q0 = blk.qb * 16 * QB;
     const int kmax = a.causal ? min(a.N, q0 + 16 * QB) : a.N;
     const int n_tiles = (kmax + 31) >> 5;
 
@@ -1071,13 +1097,22 @@ hipError_t launch_prefill_attn(const Prof &prof, const lvlm_prefill_desc &d, con
         // 16000 workgroups on and slower by up to 1.7 times below 4000
         const long long n16 = (d.N + 15) / 16;
         const bool two = n16 * d.Hq * d.B >= 16384;
-        const dim3 grid((unsigned)(two ? (n16 + 1) / 2 : n16), (unsigned)d.Hq, (unsigned)d.B);
-        if (d.hd == 128) {
-            if (two) LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<128, 2>), grid, dim3(256), 0, stream, a);
-            else LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<128, 1>), grid, dim3(256), 0, stream, a);
+        const long long blocks = two ? (n16 + 1) / 2 : n16, heads = (long long)d.B * d.Hq;
+        if (blocks * heads <= 256) {
+            const dim3 grid((unsigned)blocks, (unsigned)d.Hq, (unsigned)d.B);
+            if (d.hd == 128) LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<128, 1, false>), grid, dim3(256), 0, stream, a);
+            else LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<64, 1, false>), grid, dim3(256), 0, stream, a);
         } else {
-            if (two) LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<64, 2>), grid, dim3(256), 0, stream, a);
-            else LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<64, 1>), grid, dim3(256), 0, stream, a);
+            while (a.parts_log2 < 3 && (heads << a.parts_log2) % 8) ++a.parts_log2;
+            a.xcd_parts = (int)((heads << a.parts_log2) / 8);
+            const dim3 grid((unsigned)(8 * a.xcd_parts * (((blocks - 1) >> a.parts_log2) + 1)));
+            if (d.hd == 128) {
+                if (two) LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<128, 2, true>), grid, dim3(256), 0, stream, a);
+                else LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<128, 1, true>), grid, dim3(256), 0, stream, a);
+            } else {
+                if (two) LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<64, 2, true>), grid, dim3(256), 0, stream, a);
+                else LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<64, 1, true>), grid, dim3(256), 0, stream, a);
+            }
         }
     }
     prof.end();

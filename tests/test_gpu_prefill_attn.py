@@ -311,6 +311,25 @@ def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal):
     assert np.abs(lse[pick].cpu().numpy() - o_lse).max() < 1e-5 * max(1.0, np.abs(o_lse).max())
 
 
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
+    (1, 1024, 4, 4, 64, True),          # 256 blocks: the plain grid
+    (1, 1025, 4, 2, 64, True),          # 260: halves of heads, two turns and one block of an XCD's 32 compute units
+    (1, 4097, 1, 1, 64, True),          # eighths of one head, 33 levels of which the last is one part's
+    (1, 1377, 3, 1, 128, True),         # three eighths to an XCD, a turn and one block
+    (3, 1300, 2, 1, 64, True),          # quarters
+    (5, 700, 5, 1, 64, True),           # 25 heads of 44 blocks
+    (2, 660, 8, 2, 128, False)])        # whole heads, no mask
+def test_prefill_attn_fp32_blocks_dealt_to_compute_units(ctx, B, N, Hq, Hkv, d, causal):
+    """Every block of every head is done once, however heads are cut for the XCDs and turns end."""
+    fused, split = _qkv(B, N, Hq, Hkv, d, torch.float32, 900 + N, 2.0)
+    out = torch.full((B, N, Hq, d), float("nan"), device=DEV)
+    out, lse, _, _ = ctx.prefill_attn(*split(fused.to(DEV)), causal=causal, out=out)
+    q, k, v = split(fused)
+    o_out, o_lse = O.prefill_attn(f64(q), f64(k), f64(v), causal=causal, dtype="f32")
+    assert rel_err(out.cpu(), o_out) < 1e-5
+    assert np.abs(lse.cpu().numpy() - o_lse).max() < 1e-5 * max(1.0, np.abs(o_lse).max())
+
+
 @pytest.mark.parametrize("N", [1, 3, 31, 33, 63, 65, 97, 127, 130, 161])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("far", [False, True])
