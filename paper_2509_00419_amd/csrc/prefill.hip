@@ -872,7 +872,7 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a)
 // are rescaled when it moves).  For O^T += V^T P^T the contraction of one instruction is two keys, one per
 // half-wave: exactly the two keys the two halves hold in the same accumulator register, so register r of the
 // probabilities is the second operand as it stands and the first is V[that key][channel] read from the tile.
-template <int HD>
+template <int HD, bool BALANCED>
 __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(PrefillArgs a) {
     constexpr int ROWB = HD * 4;
     constexpr int KP = ROWB + 16;           // tile pitch: odd multiple of 16 bytes
@@ -887,9 +887,11 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(Prefill
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hf = lane >> 5, l32 = lane & 31;
-    const int qb = gridDim.x - 1 - blockIdx.x, h = blockIdx.y, b = blockIdx.z;      // longest blocks first
-    const int g = h / a.G;
-    const int q0 = qb * 128, blk0 = q0 + 32 * wave;
+    BalancedBlock blk{(int)blockIdx.z, (int)blockIdx.y, (int)(gridDim.x - 1 - blockIdx.x)};      // longest blocks first
+    if constexpr (BALANCED)
+        if (!balanced_block(a, a.nqb, blk)) return;
+    const int h = blk.h, b = blk.b, g = h / a.G;
+    const int q0 = blk.qb * 128, blk0 = q0 + 32 * wave;
     const int row = blk0 + l32;
     const int kmax = a.causal ? min(a.N, q0 + 128) : a.N;
     const int n_tiles = (kmax + 31) >> 5;
@@ -1011,16 +1013,23 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(Prefill
 
 // Whether the fp32 kernel that shares its tiles is the faster one, from 680 shapes timed both ways (1 to 960 heads, 20 to
 // 4288 tokens).  It works in turns of 256 workgroups of 128 rows, each as long as its longest block: it needs turns that are
-// nearly full, and under a causal mask few blocks, or the longest ones are waited for (the other kernel's 16-row blocks
-// level that out).  Heads of 64 channels: where the four waves of the other kernel have equally many tiles (all but, of few
+// nearly full.  Heads of 64 channels: where the four waves of the other kernel have equally many tiles (all but, of few
 // blocks), it reads less per product -- 256 heads x 384 tokens 95 -> 64 us, 512 heads x 128 tokens 45 -> 28 us, but 128 heads x 800 causal 144 -> 167 us.  Of 128
 // channels the other kernel is bound by reading K and V, and loses from three quarters of a turn on while the work is
 // small: 256 heads x 128 tokens 57 -> 31 us, 512 heads x 256 290 -> 189 us, 384 of 94 tokens 57 -> 43 us.
+// Causal blocks dealt out by balanced_block, beyond one turn, gain with their number (other kernel, dealt out too -> this one; before, with
+// a head's blocks one after the other, four to a head came to the same compute units in every turn): 128 heads x 500 tokens
+// 75.5 -> 66.7 us (91 before), 256 x 500 151 -> 109 (162), of 128 channels 448 x 512 591 -> 436 (625).  One turn of several blocks
+// has nothing to level with and waits for the longest: 64 heads x 512 tokens 59.5 -> 45.4 us with the other kernel, 84 x 380 48.2 -> 39.7, of 128
+// channels 56 x 500 110 -> 98, but 84 x 384 96.5 -> 89.4 with this one.  More than five blocks to a head: from 640 of them on (128 channels: 1024):
+// 64 heads x 1400 tokens 193 -> 182 us, 64 x 3600 1070 -> 974, 128 x 700 119 -> 108, of 128 channels 112 x 1500 814 -> 724;
+// below, 40 x 1700 174 -> 184, 16 x 4100 351 -> 371, of 128 channels 112 x 900 359 -> 369.
 bool f32_shares_tiles(const lvlm_prefill_desc &d) {
     const long long heads = (long long)d.B * d.Hq, nqb = (d.N + 127) / 128, wgs = heads * nqb;
     const int tiles = (d.N + 31) / 32, n16 = (d.N + 15) / 16;
     if (tiles < 2 && d.hd == 64) return false;
-    if (d.causal && nqb > 5) return false;
+    if (d.causal && nqb > 5) return wgs > (d.hd == 64 ? 640 : 1024);
+    if (d.causal && wgs <= 256 && nqb > (d.hd == 64 ? 1 : 3)) return false;
     const double fill = (double)wgs / (double)((wgs + 255) / 256 * 256);
     // tiles a wave of the other kernel takes in turn, over its blocks of 16 rows; tiles a workgroup of this one takes
     long long in_turn = 0, shared = 0;
@@ -1087,33 +1096,31 @@ hipError_t launch_prefill_attn(const Prof &prof, const lvlm_prefill_desc &d, con
             if (fast) LVLM_LAUNCH(prof, prefill_attn_d64_kernel, g, dim3(128), 0, stream, a);
             else LVLM_LAUNCH(prof, prefill_attn_safe_kernel<64>, g, dim3(128), 0, stream, a);
         }
-    } else if (f32_shares_tiles(d)) {
-        const dim3 grid((unsigned)a.nqb, (unsigned)d.Hq, (unsigned)d.B);
-        if (d.hd == 128) LVLM_LAUNCH(prof, prefill_attn_f32_shared_kernel<128>, grid, dim3(256), 0, stream, a);
-        else LVLM_LAUNCH(prof, prefill_attn_f32_shared_kernel<64>, grid, dim3(256), 0, stream, a);
     } else {
-        // one block of 16 rows per workgroup; two (each K and V operand feeds two products, 64 bytes of L2 traffic per
+        const bool shared = f32_shares_tiles(d);
+        // Not shared: one block of 16 rows per workgroup; two (each K and V operand feeds two products, 64 bytes of L2 traffic per
         // product instead of 128) once that still leaves many rounds of the chip: it is 3-4 % faster from about
         // 16000 workgroups on and slower by up to 1.7 times below 4000
-        const long long n16 = (d.N + 15) / 16;
-        const bool two = n16 * d.Hq * d.B >= 16384;
-        const long long blocks = two ? (n16 + 1) / 2 : n16, heads = (long long)d.B * d.Hq;
-        if (blocks * heads <= 256) {
-            const dim3 grid((unsigned)blocks, (unsigned)d.Hq, (unsigned)d.B);
-            if (d.hd == 128) LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<128, 1, false>), grid, dim3(256), 0, stream, a);
-            else LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<64, 1, false>), grid, dim3(256), 0, stream, a);
-        } else {
+        const long long n16 = (d.N + 15) / 16, heads = (long long)d.B * d.Hq;
+        const bool two = !shared && n16 * heads >= 16384;
+        const long long blocks = shared ? a.nqb : two ? (n16 + 1) / 2 : n16;
+        const bool balanced = d.causal && blocks > 1 && blocks * heads > 256;     // (else nothing to level)
+        dim3 grid((unsigned)blocks, (unsigned)d.Hq, (unsigned)d.B);
+        if (balanced) {
             while (a.parts_log2 < 3 && (heads << a.parts_log2) % 8) ++a.parts_log2;
             a.xcd_parts = (int)((heads << a.parts_log2) / 8);
-            const dim3 grid((unsigned)(8 * a.xcd_parts * (((blocks - 1) >> a.parts_log2) + 1)));
-            if (d.hd == 128) {
-                if (two) LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<128, 2, true>), grid, dim3(256), 0, stream, a);
-                else LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<128, 1, true>), grid, dim3(256), 0, stream, a);
-            } else {
-                if (two) LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<64, 2, true>), grid, dim3(256), 0, stream, a);
-                else LVLM_LAUNCH(prof, (prefill_attn_f32_kernel<64, 1, true>), grid, dim3(256), 0, stream, a);
-            }
+            grid = dim3((unsigned)(8 * a.xcd_parts * (((blocks - 1) >> a.parts_log2) + 1)));
         }
+#define LVLM_F32(KERNEL, ...)                                                                                              \
+    if (d.hd == 128) LVLM_LAUNCH(prof, (KERNEL<128, __VA_ARGS__>), grid, dim3(256), 0, stream, a);                         \
+    else LVLM_LAUNCH(prof, (KERNEL<64, __VA_ARGS__>), grid, dim3(256), 0, stream, a)
+        if (shared && balanced) { LVLM_F32(prefill_attn_f32_shared_kernel, true); }
+        else if (shared) { LVLM_F32(prefill_attn_f32_shared_kernel, false); }
+        else if (two && balanced) { LVLM_F32(prefill_attn_f32_kernel, 2, true); }
+        else if (two) { LVLM_F32(prefill_attn_f32_kernel, 2, false); }
+        else if (balanced) { LVLM_F32(prefill_attn_f32_kernel, 1, true); }
+        else { LVLM_F32(prefill_attn_f32_kernel, 1, false); }
+#undef LVLM_F32
     }
     prof.end();
     hipError_t e = hipGetLastError();
