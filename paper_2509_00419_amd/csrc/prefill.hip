@@ -1021,14 +1021,14 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(Prefill
 // a head's blocks one after the other, four to a head came to the same compute units in every turn): 128 heads x 500 tokens
 // 75.5 -> 66.7 us (91 before), 256 x 500 151 -> 109 (162), of 128 channels 448 x 512 591 -> 436 (625).  One turn of several blocks
 // has nothing to level with and waits for the longest: 64 heads x 512 tokens 59.5 -> 45.4 us with the other kernel, 84 x 380 48.2 -> 39.7, of 128
-// channels 56 x 500 110 -> 98, but 84 x 384 96.5 -> 89.4 with this one.  More than five blocks to a head: from 640 of them on (128 channels: 1024):
-// 64 heads x 1400 tokens 193 -> 182 us, 64 x 3600 1070 -> 974, 128 x 700 119 -> 108, of 128 channels 112 x 1500 814 -> 724;
-// below, 40 x 1700 174 -> 184, 16 x 4100 351 -> 371, of 128 channels 112 x 900 359 -> 369.
+// channels 56 x 500 110 -> 98, but 84 x 384 96.5 -> 89.4 with this one.  More than five blocks to a head stay with the other kernel: from 640 blocks on this one
+// is faster (64 heads x 1400 tokens 193 -> 182 us, 64 x 3600 1070 -> 974; 40 x 1700 174 -> 184), but a row's sums are one chain here and four there:
+// against 64 bits 9.0e-7 instead of 7.0e-7 (2-norm) at 3600 tokens.
 bool f32_shares_tiles(const lvlm_prefill_desc &d) {
     const long long heads = (long long)d.B * d.Hq, nqb = (d.N + 127) / 128, wgs = heads * nqb;
     const int tiles = (d.N + 31) / 32, n16 = (d.N + 15) / 16;
     if (tiles < 2 && d.hd == 64) return false;
-    if (d.causal && nqb > 5) return wgs > (d.hd == 64 ? 640 : 1024);
+    if (d.causal && nqb > 5) return false;
     if (d.causal && wgs <= 256 && nqb > (d.hd == 64 ? 1 : 3)) return false;
     const double fill = (double)wgs / (double)((wgs + 255) / 256 * 256);
     // tiles a wave of the other kernel takes in turn, over its blocks of 16 rows; tiles a workgroup of this one takes

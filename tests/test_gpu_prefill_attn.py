@@ -296,7 +296,7 @@ def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causa
     (32, 250, 4, 4, 64, False), (32, 250, 4, 4, 64, True), (16, 510, 4, 4, 64, True), (8, 610, 26, 2, 64, True),  # up to five blocks
     (64, 1, 4, 4, 128, True), (64, 31, 4, 4, 128, False), (50, 33, 4, 2, 128, True), (32, 129, 4, 1, 128, True),  # 200 of 256 places
     (16, 500, 4, 4, 128, False), (8, 640, 7, 1, 128, True),
-    (100, 643, 4, 2, 128, True)])                  # six blocks, nine turns
+    (100, 643, 4, 2, 128, True)])                  # six blocks: sixteen-row blocks again, two per workgroup
 def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal):
     """fp32 launches of whole turns of the chip: the kernel whose four waves share their tiles, at the edges of its rule, of
     its 128-row blocks and of its 32-key tiles.  Sampled sequences against the oracle, every row written."""
@@ -321,7 +321,7 @@ def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal):
     (2, 660, 8, 2, 128, False),         # whole heads, no mask
     (64, 129, 5, 1, 64, True),          # shared tiles: two blocks to each of 320 heads
     (9, 500, 28, 4, 128, True),         # ... four, 252 heads in halves
-    (27, 700, 4, 2, 64, True),          # ... six, the first number beyond 640
+    (27, 700, 4, 2, 64, True),          # six: blocks of 16 rows, whole turns
     (16, 512, 4, 4, 64, True)])         # one turn of four blocks: not shared
 def test_prefill_attn_fp32_blocks_dealt_to_compute_units(ctx, B, N, Hq, Hkv, d, causal):
     """Every block of every head is done once, however heads are cut for the XCDs and turns end."""
