@@ -197,6 +197,24 @@ struct Prof {
     } while (0)
 
 // ---- launches (defined in the .hip files; all asynchronous on `stream`) ----
+// How the sorted blocks of long sequences are searched: `groups` times 64 tokens to a workgroup, `parts` workgroups to a token.
+// One group while every workgroup has a compute unit of its own, then two, then four: each halves what is staged in all (ranking
+// alone, one group -> the form taken, us: 5 x 4800 tokens 11.9 -> 9.4, 8 x 8192 21.6 -> 15.7, 32 x 4096 34.9 -> 20.7; the other way
+// round four groups -> one at 1 x 12000 13.6 -> 9.8, -> two at 2 x 16384 16.0 -> 12.1).  Beyond 32 blocks the few workgroups, each with
+// five rounds or more, leave the last turn of the chip uneven: every round goes to a workgroup of its own, which adds its counts to the
+// rank, and a further launch finishes it (rounds in turn -> shared: 1 x 33000 24.4 -> 22.5, 1 x 100000 87 -> 71, 1 x 400000 1000 -> 849;
+// below, 2 x 24000 20.1 -> 22.7).
+struct SearchForm {
+    int groups, parts;
+};
+inline SearchForm rank_search_form(int n, int B) {
+    const long long alone = (long long)B * ((n + 63) / 64), pairs = (long long)B * ((n + 127) / 128);
+    const int blocks = (n + 1023) / 1024;
+    SearchForm f;
+    f.groups = alone <= 256 ? 1 : pairs <= 256 ? 2 : 4;
+    f.parts = blocks > 32 ? (blocks + 7) / 8 : 1;
+    return f;
+}
 // scratch: rank_scratch_bytes(n, B) bytes for the sorted blocks of long sequences, or null (counting at any length)
 size_t rank_scratch_bytes(int n, int B);
 // kept: [B, ceil(n / 64)], how many of every 64 tokens have a rank below n_kept (null: not counted)

@@ -52,6 +52,7 @@ struct RankArgs {
     int32_t *kept;                  // [B, ceil(n / 64)]  tokens of every 64 with rank < n_kept, or null
     int n_kept;
     int n, n_blocks;
+    int parts;                      // workgroups that share a token's searches
     int rank_wgs;                   // workgroups of the launch that rank; the rest take rows of `norm`
     NormJob norm;
 };
@@ -114,13 +115,17 @@ __device__ __forceinline__ void norm_rows(const NormJob &w, int wg, int b) {
     if (lane == 0) w.inv_norm[(long long)b * w.n + j] = s > 0.f ? 1.0f / sqrtf(s) : 1.0f;
 }
 
-// One wave's 64 tokens, j = 64 m + lane (lanes past the last token are not here): their ranks, and how many of them are kept.
+// The ranks of one wave's 64 tokens, j = 64 m + lane (lanes past the last token are not here), and how many of them are kept.
 template <class KEY>
-__device__ __forceinline__ void put_rank(const RankArgs<KEY> &a, int b, int j, int rank) {
-    a.rank[(long long)b * a.n + j] = rank;
-    if (a.kept) {
-        const unsigned long long bal = __ballot(rank < a.n_kept);
-        if ((j & 63) == 0) a.kept[(long long)b * ((a.n + 63) / 64) + j / 64] = __popcll(bal);
+__device__ __forceinline__ void done(const RankArgs<KEY> &a, int b, int j, int rank) {
+    if constexpr (KEY::kOrder) {
+        a.key.put(b, a.n, j, rank);
+    } else {
+        a.rank[(long long)b * a.n + j] = rank;
+        if (a.kept) {
+            const unsigned long long bal = __ballot(rank < a.n_kept);
+            if ((j & 63) == 0) a.kept[(long long)b * ((a.n + 63) / 64) + j / 64] = __popcll(bal);
+        }
     }
 }
 
@@ -181,8 +186,7 @@ __global__ __launch_bounds__(1024) void rank_kernel(RankArgs<KEY> a) {
         int tot = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) tot += cnt_lds[w][lane];
-        if constexpr (KEY::kOrder) a.key.put(b, a.n, j, tot);
-        else put_rank(a, b, j, tot);
+        done(a, b, j, tot);
     }
 }
 
@@ -194,11 +198,11 @@ __global__ __launch_bounds__(1024) void rank_kernel(RankArgs<KEY> a) {
 //                       token, spread over all workgroups): a token's word goes to its place in the block's
 //                       descending order; places past the last token of a partly filled block hold 0 (below every word)
 //   rank_search_kernel  a token's rank = over all sorted blocks, the number of words above its own, each found by
-//                       a binary search (11 probes) in LDS; a workgroup stages sixteen blocks at a time, and each of its
-//                       waves searches one of them for the same 64 tokens
+//                       a binary search (11 probes) in LDS; a workgroup stages eight or sixteen blocks at a time, and its
+//                       waves search them for 64 to 256 tokens
+//   rank_finish_kernel  (the longest sequences) what is made of a rank that several workgroups have added up
 constexpr int kSortBlock = 1024;
 constexpr int kSortMinTokens = 4096;
-constexpr int kSortStage = 16;       // sorted blocks held in LDS at a time (128 KB)
 
 __device__ __forceinline__ unsigned long long order_word(uint32_t key, int idx) {
     return ((unsigned long long)key << 32) | (unsigned long long)(0xffffffffu - (uint32_t)idx);
@@ -242,51 +246,69 @@ __global__ __launch_bounds__(1024) void rank_block_kernel(RankArgs<KEY> a) {
 #pragma unroll
         for (int w = 0; w < 16; ++w) place += cnt_lds[w][lane];
         // tokens past the end fill the places past the last token (the real ones take 0 .. count-1 between them)
-        if (j < a.n) out[place] = mine;
-        else out[j - r0] = 0ull;
+        if (j < a.n) {
+            out[place] = mine;
+            if (a.parts > 1) a.rank[(long long)b * a.n + j] = 0;      // the searches add to it
+        } else {
+            out[j - r0] = 0ull;
+        }
     }
 }
 
-// A workgroup's time is what it stages (128 KB, a compute unit's L2 bandwidth) and eleven dependent LDS probes.  16384 tokens are one
-// workgroup for every compute unit.  (Eight blocks and 256 tokens to a workgroup, the groups of eight adding up in the
-// rank by atomics, and a third launch to lay out the order by owner: the whole similarity merge of 11908 tokens 315 -> 310 us.)
-template <class KEY>
-__global__ __launch_bounds__(1024) void rank_search_kernel(RankArgs<KEY> a) {
-    __shared__ __attribute__((aligned(16))) unsigned long long words[kSortStage * kSortBlock];
-    __shared__ int above[kSortStage][64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// A workgroup searches S staged blocks (S x 8 KB) for TG times 64 tokens, and goes on to the next S or, with `parts`, leaves them to
+// another workgroup.  Its time is what it stages, at a compute unit's L2 bandwidth, and eleven dependent LDS probes for every round;
+// S = 8 leaves room for a second workgroup whose searches cover the staging (rank_search_form has the rule).
+template <class KEY, int TG, int S>
+__global__ __launch_bounds__(1024, S > 8 ? 4 : 8) void rank_search_kernel(RankArgs<KEY> a) {
+    constexpr int WPG = 16 / TG, CH = S / WPG;             // waves per 64 tokens; blocks a wave searches side by side
+    static_assert(CH >= 1 && CH * WPG == S, "every wave has blocks to search");
+    __shared__ __attribute__((aligned(16))) unsigned long long words[S * kSortBlock];
+    __shared__ int above[16][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), first = wave / TG;
     const int b = blockIdx.y;
-    const int j = blockIdx.x * 64 + lane;
+    const int j = (blockIdx.x * TG + wave % TG) * 64 + lane;
     const unsigned long long mine = j < a.n ? order_word(a.key.at(b, a.n, j), j) : ~0ull;
     const uint4 *src = reinterpret_cast<const uint4 *>(a.sorted + (long long)b * a.n_blocks * kSortBlock);
     int cnt = 0;
-    for (int g0 = 0; g0 < a.n_blocks; g0 += kSortStage) {
-        const int nb = min(kSortStage, a.n_blocks - g0);
+    for (int g0 = S * blockIdx.z; g0 < a.n_blocks; g0 += S * a.parts) {
+        const int nb = min(S, a.n_blocks - g0);
         const int units = nb * (kSortBlock / 2);                       // 16-byte units to stage
-        constexpr int kPer = kSortStage * (kSortBlock / 2) / 1024;
-        if (g0) __syncthreads();                                       // the blocks before have been searched
+        if (g0 >= S * a.parts) __syncthreads();                        // the blocks before have been searched
 #pragma unroll
-        for (int x = 0; x < kPer; ++x)                                 // (places past the last block are not read)
+        for (int x = 0; x < S * (kSortBlock / 2) / 1024; ++x)          // (places past the last block do not count)
             reinterpret_cast<uint4 *>(words)[1024 * x + tid] = src[(long long)g0 * (kSortBlock / 2) + min(1024 * x + tid, units - 1)];
         __syncthreads();
-        if (wave < nb) {
-            // words above `mine` in the wave's block: the block descends, so that is the first place whose word is not above it
-            const unsigned long long *const blk = words + wave * kSortBlock;
-            int pos = 0;
+        if (first < nb) {
+            // words above `mine` in each of the wave's blocks: they descend, so that is the first place whose word is not above it
+            const unsigned long long *const blk = words + first * kSortBlock;
+            int pos[CH];
 #pragma unroll
-            for (int step = kSortBlock / 2; step >= 1; step >>= 1) pos += blk[pos + step - 1] > mine ? step : 0;
-            cnt += pos + (blk[pos] > mine ? 1 : 0);                    // place 1023 itself
+            for (int x = 0; x < CH; ++x) pos[x] = 0;
+#pragma unroll
+            for (int step = kSortBlock / 2; step >= 1; step >>= 1)
+#pragma unroll
+                for (int x = 0; x < CH; ++x) pos[x] += blk[x * WPG * kSortBlock + pos[x] + step - 1] > mine ? step : 0;
+#pragma unroll
+            for (int x = 0; x < CH; ++x)
+                if (first + x * WPG < nb) cnt += pos[x] + (blk[x * WPG * kSortBlock + pos[x]] > mine ? 1 : 0);      // place 1023 itself
         }
     }
     above[wave][lane] = cnt;
     __syncthreads();
-    if (wave == 0 && j < a.n) {
+    if (wave < TG && j < a.n) {
         int rank = 0;
 #pragma unroll
-        for (int w = 0; w < kSortStage; ++w) rank += above[w][lane];
-        if constexpr (KEY::kOrder) a.key.put(b, a.n, j, rank);
-        else put_rank(a, b, j, rank);
+        for (int w = 0; w < WPG; ++w) rank += above[w * TG + wave][lane];
+        if (a.parts > 1) atomicAdd(&a.rank[(long long)b * a.n + j], rank);
+        else done(a, b, j, rank);
     }
+}
+
+template <class KEY>
+__global__ __launch_bounds__(256) void rank_finish_kernel(RankArgs<KEY> a) {
+    const int j = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+    if (j < a.n) done(a, b, j, a.rank[(long long)b * a.n + j]);
 }
 
 
@@ -545,8 +567,16 @@ void launch_rank_by(const Prof &prof, const KEY &key, int32_t *rank, int n, int 
         a.sorted = static_cast<unsigned long long *>(scratch);
         a.n_blocks = (n + kSortBlock - 1) / kSortBlock;
         a.rank_wgs = a.n_blocks * (kSortBlock / 64);
+        const SearchForm f = rank_search_form(n, B);
+        a.parts = f.parts;
         LVLM_LAUNCH(prof, rank_block_kernel<KEY>, dim3(a.rank_wgs + norm_wgs, B), dim3(1024), 0, stream, a);
-        LVLM_LAUNCH(prof, rank_search_kernel<KEY>, dim3((n + 63) / 64, B), dim3(1024), 0, stream, a);
+#define LVLM_SEARCH(TG, S) \
+    LVLM_LAUNCH(prof, (rank_search_kernel<KEY, TG, S>), dim3((n + 64 * TG - 1) / (64 * TG), B, a.parts), dim3(1024), 0, stream, a)
+        if (f.groups == 1) LVLM_SEARCH(1, 16);
+        else if (f.groups == 2) LVLM_SEARCH(2, 8);
+        else LVLM_SEARCH(4, 8);
+#undef LVLM_SEARCH
+        if (a.parts > 1) LVLM_LAUNCH(prof, rank_finish_kernel<KEY>, dim3((n + 255) / 256, B), dim3(256), 0, stream, a);
         return;
     }
     a.rank_wgs = (n + kRankBlock - 1) / kRankBlock;

@@ -546,12 +546,23 @@ def test_merge_compact_index_chunks_and_fold_widths(ctx, dtype, B, n_img, C, n_k
     (torch.float32, 1, 1, 1025, 5, 64, 500),        # tables of a narrow plane: 128 chunks of eight rows
     (torch.bfloat16, 5, 33, 4095, 31, 8, 2000),     # the last length ranked by counting
     (torch.bfloat16, 1, 3, 16384, 2, 8, 9000),      # sixteen sorted blocks: one round of the searches
-    (torch.float32, 2, 0, 16385, 0, 8, 1),          # a token more: two rounds
-    (torch.bfloat16, 1, 5, 33001, 40, 8, 20000),    # three rounds
+    (torch.float32, 2, 0, 16385, 0, 8, 1),          # three rounds
+    (torch.bfloat16, 1, 5, 33001, 40, 8, 20000),    # 33 blocks: five workgroups to a token
     (torch.bfloat16, 2, 3, 30000, 1, 8, 29999)])    # chunks of 128 rows, eight to a table
 def test_merge_compact_where_rows_go(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep):
     """Kept tokens are counted in 64s by the ranking and placed by the workgroups that move their rows."""
     _merge_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed=n_img)
+
+
+@pytest.mark.parametrize("B,n_img", [
+    (2, 8192), (3, 5441), (5, 4097),      # one 64 to a workgroup and 256 of them; two, one workgroup over 256; five blocks, a token in the last
+    (2, 16384), (1, 32768),               # two to a workgroup, 256 workgroups, two rounds and four
+    (9, 4200), (3, 12001), (1, 32700),    # four; a second round of four blocks; two again
+    (1, 32769), (2, 40961)])              # rounds shared out: five workgroups to a token, six, the last one's block of one token
+def test_rank_searches_of_batches_and_long_sequences(ctx, B, n_img):
+    """The forms of the search through sorted blocks, at the edges of their rule, for either key it ranks by."""
+    _merge_case(ctx, torch.float32, B, 1, n_img, 2, 8, n_img // 3, seed=n_img, extra_planes=False)
+    _similar_case(ctx, torch.bfloat16, B, 1, n_img, 2, 40, 33, n_img, clusters=20, extra=False)
 
 
 def test_merge_compact_planes_larger_than_the_memory_side_cache(ctx):
@@ -1524,7 +1535,7 @@ def test_merge_similar_sizes_of_planes_that_are_only_kept(ctx, n_img, n_keep, cl
 @pytest.mark.parametrize("n_img,n_keep,clusters,with_size", [
     (66, 65, 0, True), (66, 1, 0, False), (65, 64, 3, True), (130, 64, 2, False),   # owner search: one other token, 65, 66
     (4096, 3000, 3, False), (4097, 1, 0, True), (4400, 80, 2, True),                # chunk and block edges, hundreds per cluster
-    (8192, 8000, 0, False), (8300, 3900, 40, True)])                                # one and two groups of sorted blocks
+    (8192, 8000, 0, False), (8300, 3900, 40, True)])                                # eight and nine sorted blocks
 def test_merge_similar_cluster_bounds_and_long_rankings(ctx, n_img, n_keep, clusters, with_size):
     _similar_case(ctx, torch.float32 if n_img < 200 else torch.bfloat16, 1, 3, n_img, 4, 40, n_keep, 600 + n_img,
                   clusters=clusters, with_size=with_size)
