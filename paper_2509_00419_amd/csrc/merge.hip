@@ -29,9 +29,15 @@ namespace {
 
 constexpr int kGatherRows = 8;     // rows per batch (all of a batch's loads are in flight together)
 constexpr int kGatherWgs = 1536;   // workgroups the gather launch aims for (six per compute unit)
+constexpr int kGatherChunkRows = 128;   // rows of a chunk at most
+// Image tokens whose destinations a workgroup of the gather holds in LDS.  (4096 keep all threads of the narrowest planes in long chunks busy,
+// but are longer in the making than the rows are in coming: 2 x 16384 -> 5000 rows of 2 KB, twice, 51.2 -> 56.5 us, 8 x 9000 -> 3000
+// rows of 7 KB and twice 64 bytes 162.9 -> 168.4.)
+constexpr int kGatherTable = 1024;
+static_assert(kGatherRows <= kGatherChunkRows && kGatherChunkRows <= kGatherTable, "a workgroup takes at least one chunk");
 // Chunks of rows to a workgroup of the gather: as many as its threads hold, of no more tokens than its table does.
 __host__ __device__ inline int gather_chunks(const PlaneDev &p, int rows_per_chunk) {
-    const int most = 1024 / rows_per_chunk, fit = 256 >> p.tpr_log2;
+    const int most = kGatherTable / rows_per_chunk, fit = 256 >> p.tpr_log2;
     return fit < most ? fit : most;
 }
 constexpr long long kGatherCached = 256ll << 20;       // bytes of source rows that the memory-side cache can hold
@@ -328,7 +334,6 @@ struct GatherArgs {
 };
 
 // Where the image tokens of a workgroup's rows go, and with what weight they are merged.
-constexpr int kGatherTable = 1024;
 struct GatherTable {
     int code[kGatherTable];      // >= 0: row inside the new image span; -1: most important merged token; -2: any other merged token
     float wgt[kGatherTable];     // merge weight (0 for kept tokens)
@@ -607,7 +612,7 @@ MergeWs merge_ws(const lvlm_merge_desc &d, const lvlm_plane *planes) {
     // overlap comes from its neighbours); longer chunks would mean fewer partial sums to write and re-read
     long long rows = (long long)d.N * d.B * (units ? units : 1) / kGatherWgs;
     rows = rows / 4 * 4;
-    w.rows_per_chunk = (int)(rows < 8 ? 8 : (rows > 128 ? 128 : rows));
+    w.rows_per_chunk = (int)(rows < kGatherRows ? kGatherRows : (rows > kGatherChunkRows ? kGatherChunkRows : rows));
     w.n_chunk = (d.N + w.rows_per_chunk - 1) / w.rows_per_chunk;
     w.max_row_elems = max_elems;
     w.rank_part = 0;
