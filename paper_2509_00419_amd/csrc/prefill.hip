@@ -6,6 +6,7 @@
 // also left densely packed for the column-sum pass of the score kernels, which then needs no normaliser
 // pass of its own.
 #include "mma.h"
+#include "prefill_rules.h"
 
 #include <climits>
 #include <type_traits>
@@ -21,8 +22,7 @@ struct PrefillArgs {
     int B, N, Hq, Hkv, G, causal, T;
     int nqb;            // query blocks per head
     int heads_per_xcd;  // ceil(B * Hq / 8)
-    int parts_log2;     // balanced_block: parts of a head (log2), parts per XCD
-    int xcd_parts;
+    BlockDeal deal;
     float scale, scale_log2;
     long long qsb, qsn, qsh, ksb, ksn, ksh, vsb, vsn, vsh, osb, osn, osh;   // bytes
 };
@@ -681,29 +681,18 @@ __device__ __forceinline__ float word(const uint4 &v, int c) {
 // Measured (4 heads, 64 channels; a wave per 32 rows walking all tiles, K and V shared through LDS -> this kernel):
 // 640 tokens 57.1 -> 10.9 us, 2048 171 -> 50, 4200 347 -> 135 us (67 TFLOP/s), 16 sequences of 4200 1486 -> 1425 us
 // (101 TFLOP/s of the 155 a large fp32 matrix product reaches).
-// Workgroup number -> (head, batch, block), for blocks that are on the chip beside each other: causal ones are as long as their
-// last row, so what a compute unit is handed adds up to its time.  Heads are cut into parts (every P-th block) until the eight XCDs --
-// workgroups with the same remainder -- get equally many, neighbours in memory order; an XCD takes its parts' blocks longest first in
-// turns of its 32 compute units, every other turn backwards: the unit with the longest block of one turn has the shortest of the next.
-// Head by head instead, the first units had the longest block of every head (4 heads of 64 channels, 1503 tokens 42.1 -> 32.1 us, 2203
-// 60.6 -> 43.5, 4103 138 -> 109; 16 x 4 heads, 1103 tokens 151 -> 137, 3603 1160 -> 1125).  Up to 256 blocks, one to a unit, take the plain
-// grid: nothing to level, and the divisions here are 0.4 us before the first load (154 tokens 13.7 -> 14.2).
-struct BalancedBlock {
+struct F32Block {
     int b, h, qb;
 };
-__device__ __forceinline__ bool balanced_block(const PrefillArgs &a, int n_blocks, BalancedBlock &w) {
-    const int P = 1 << a.parts_log2, xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
-    const int total = a.xcd_parts * ((n_blocks + P - 1) >> a.parts_log2);
-    const int turn = seq & ~31, last = min(turn + 31, total - 1);
-    const int rank = (seq & 32) ? turn + last - seq : seq;
-    const int level = rank / a.xcd_parts, part = xcd * a.xcd_parts + rank - level * a.xcd_parts, head = part >> a.parts_log2;
-    w.qb = n_blocks - 1 - ((level << a.parts_log2) + (part & (P - 1)));
+__device__ __forceinline__ bool dealt_to(const PrefillArgs &a, int n_blocks, F32Block &w) {
+    int head;
+    const bool any = dealt_block(a.deal, n_blocks, blockIdx.x, head, w.qb);
     w.b = head / a.Hq;
     w.h = head - w.b * a.Hq;
-    return w.qb >= 0;
+    return any;
 }
 
-template <int HD, int QB, bool BALANCED>
+template <int HD, int QB, bool DEALT>
 __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a) {
     constexpr int NW = HD / 16;             // 16-byte words of a row per lane
     constexpr int CPL = HD / 16;            // channels per lane
@@ -715,9 +704,9 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
-    BalancedBlock blk{(int)blockIdx.z, (int)blockIdx.y, (int)(gridDim.x - 1 - blockIdx.x)};      // longest blocks first
-    if constexpr (BALANCED)
-        if (!balanced_block(a, (a.N + 16 * QB - 1) / (16 * QB), blk)) return;
+    F32Block blk{(int)blockIdx.z, (int)blockIdx.y, (int)(gridDim.x - 1 - blockIdx.x)};      // longest blocks first
+    if constexpr (DEALT)
+        if (!dealt_to(a, (a.N + 16 * QB - 1) / (16 * QB), blk)) return;
     const int h = blk.h, b = blk.b, g = h / a.G;
     const int q0 = blk.qb * 16 * QB;
     const int kmax = a.causal ? min(a.N, q0 + 16 * QB) : a.N;
@@ -872,7 +861,7 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a)
 // are rescaled when it moves).  For O^T += V^T P^T the contraction of one instruction is two keys, one per
 // half-wave: exactly the two keys the two halves hold in the same accumulator register, so register r of the
 // probabilities is the second operand as it stands and the first is V[that key][channel] read from the tile.
-template <int HD, bool BALANCED>
+template <int HD, bool DEALT>
 __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(PrefillArgs a) {
     constexpr int ROWB = HD * 4;
     constexpr int KP = ROWB + 16;           // tile pitch: odd multiple of 16 bytes
@@ -887,9 +876,9 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(Prefill
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hf = lane >> 5, l32 = lane & 31;
-    BalancedBlock blk{(int)blockIdx.z, (int)blockIdx.y, (int)(gridDim.x - 1 - blockIdx.x)};      // longest blocks first
-    if constexpr (BALANCED)
-        if (!balanced_block(a, a.nqb, blk)) return;
+    F32Block blk{(int)blockIdx.z, (int)blockIdx.y, (int)(gridDim.x - 1 - blockIdx.x)};      // longest blocks first
+    if constexpr (DEALT)
+        if (!dealt_to(a, a.nqb, blk)) return;
     const int h = blk.h, b = blk.b, g = h / a.G;
     const int q0 = blk.qb * 128, blk0 = q0 + 32 * wave;
     const int row = blk0 + l32;
@@ -1011,39 +1000,6 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(Prefill
     }
 }
 
-// Whether the fp32 kernel that shares its tiles is the faster one, from 680 shapes timed both ways (1 to 960 heads, 20 to
-// 4288 tokens).  It works in turns of 256 workgroups of 128 rows, each as long as its longest block: it needs turns that are
-// nearly full.  Heads of 64 channels: where the four waves of the other kernel have equally many tiles (all but, of few
-// blocks), it reads less per product -- 256 heads x 384 tokens 95 -> 64 us, 512 heads x 128 tokens 45 -> 28 us, but 128 heads x 800 causal 144 -> 167 us.  Of 128
-// channels the other kernel is bound by reading K and V, and loses from three quarters of a turn on while the work is
-// small: 256 heads x 128 tokens 57 -> 31 us, 512 heads x 256 290 -> 189 us, 384 of 94 tokens 57 -> 43 us.
-// Causal blocks dealt out by balanced_block, beyond one turn, gain with their number (other kernel, dealt out too -> this one; before, with
-// a head's blocks one after the other, four to a head came to the same compute units in every turn): 128 heads x 500 tokens
-// 75.5 -> 66.7 us (91 before), 256 x 500 151 -> 109 (162), of 128 channels 448 x 512 591 -> 436 (625).  One turn of several blocks
-// has nothing to level with and waits for the longest: 64 heads x 512 tokens 59.5 -> 45.4 us with the other kernel, 84 x 380 48.2 -> 39.7, of 128
-// channels 56 x 500 110 -> 98, but 84 x 384 96.5 -> 89.4 with this one.  More than five blocks to a head stay with the other kernel: from 640 blocks on this one
-// is faster (64 heads x 1400 tokens 193 -> 182 us, 64 x 3600 1070 -> 974; 40 x 1700 174 -> 184), but a row's sums are one chain here and four there:
-// against 64 bits 9.0e-7 instead of 7.0e-7 (2-norm) at 3600 tokens.
-bool f32_shares_tiles(const lvlm_prefill_desc &d) {
-    const long long heads = (long long)d.B * d.Hq, nqb = (d.N + 127) / 128, wgs = heads * nqb;
-    const int tiles = (d.N + 31) / 32, n16 = (d.N + 15) / 16;
-    if (tiles < 2 && d.hd == 64) return false;
-    if (d.causal && nqb > 5) return false;
-    if (d.causal && wgs <= 256 && nqb > (d.hd == 64 ? 1 : 3)) return false;
-    const double fill = (double)wgs / (double)((wgs + 255) / 256 * 256);
-    // tiles a wave of the other kernel takes in turn, over its blocks of 16 rows; tiles a workgroup of this one takes
-    long long in_turn = 0, shared = 0;
-    if (d.causal) {
-        for (int x = 0; x < n16; ++x) in_turn += ((x < n16 - 1 ? 16 * x + 16 : d.N) + 127) / 128;
-        for (int x = 0; x < nqb; ++x) shared += (x < nqb - 1 ? 4 * (x + 1) : tiles);
-    } else {
-        in_turn = (long long)n16 * ((tiles + 3) / 4);
-        shared = nqb * tiles;
-    }
-    if (d.hd == 64) return fill > 0.9 && (double)(4 * in_turn) > (nqb <= 3 ? 6.7 : 7.8) * (double)shared;
-    return fill > 0.9 || (fill > (d.causal ? 0.78 : 0.71) && heads * in_turn <= 36 * 256);
-}
-
 }  // namespace
 
 PrefillWs prefill_ws(const lvlm_prefill_desc &d) {
@@ -1097,28 +1053,17 @@ hipError_t launch_prefill_attn(const Prof &prof, const lvlm_prefill_desc &d, con
             else LVLM_LAUNCH(prof, prefill_attn_safe_kernel<64>, g, dim3(128), 0, stream, a);
         }
     } else {
-        const bool shared = f32_shares_tiles(d);
-        // Not shared: one block of 16 rows per workgroup; two (each K and V operand feeds two products, 64 bytes of L2 traffic per
-        // product instead of 128) once that still leaves many rounds of the chip: it is 3-4 % faster from about
-        // 16000 workgroups on and slower by up to 1.7 times below 4000
-        const long long n16 = (d.N + 15) / 16, heads = (long long)d.B * d.Hq;
-        const bool two = !shared && n16 * heads >= 16384;
-        const long long blocks = shared ? a.nqb : two ? (n16 + 1) / 2 : n16;
-        const bool balanced = d.causal && blocks > 1 && blocks * heads > 256;     // (else nothing to level)
-        dim3 grid((unsigned)blocks, (unsigned)d.Hq, (unsigned)d.B);
-        if (balanced) {
-            while (a.parts_log2 < 3 && (heads << a.parts_log2) % 8) ++a.parts_log2;
-            a.xcd_parts = (int)((heads << a.parts_log2) / 8);
-            grid = dim3((unsigned)(8 * a.xcd_parts * (((blocks - 1) >> a.parts_log2) + 1)));
-        }
+        const F32Form f = prefill_f32_form(d);
+        a.deal = f.deal;
+        const dim3 grid = f.dealt ? dim3(f.dealt) : dim3((unsigned)f.blocks, (unsigned)d.Hq, (unsigned)d.B);
 #define LVLM_F32(KERNEL, ...)                                                                                              \
     if (d.hd == 128) LVLM_LAUNCH(prof, (KERNEL<128, __VA_ARGS__>), grid, dim3(256), 0, stream, a);                         \
     else LVLM_LAUNCH(prof, (KERNEL<64, __VA_ARGS__>), grid, dim3(256), 0, stream, a)
-        if (shared && balanced) { LVLM_F32(prefill_attn_f32_shared_kernel, true); }
-        else if (shared) { LVLM_F32(prefill_attn_f32_shared_kernel, false); }
-        else if (two && balanced) { LVLM_F32(prefill_attn_f32_kernel, 2, true); }
-        else if (two) { LVLM_F32(prefill_attn_f32_kernel, 2, false); }
-        else if (balanced) { LVLM_F32(prefill_attn_f32_kernel, 1, true); }
+        if (f.shared && f.dealt) { LVLM_F32(prefill_attn_f32_shared_kernel, true); }
+        else if (f.shared) { LVLM_F32(prefill_attn_f32_shared_kernel, false); }
+        else if (f.two && f.dealt) { LVLM_F32(prefill_attn_f32_kernel, 2, true); }
+        else if (f.two) { LVLM_F32(prefill_attn_f32_kernel, 2, false); }
+        else if (f.dealt) { LVLM_F32(prefill_attn_f32_kernel, 1, true); }
         else { LVLM_F32(prefill_attn_f32_kernel, 1, false); }
 #undef LVLM_F32
     }

@@ -1,0 +1,97 @@
+// Host rules of the fp32 prefill attention, and the arithmetic that host and kernels share.
+#pragma once
+
+#include "common.h"
+
+namespace lvlm {
+
+// ---- causal blocks dealt out to the compute units ----
+// Workgroup number -> (head, block), for blocks that are on the chip beside each other: causal ones are as long as their
+// last row, so what a compute unit is handed adds up to its time.  Heads are cut into parts (every P-th block) until the eight XCDs --
+// workgroups with the same remainder -- get equally many, neighbours in memory order; an XCD takes its parts' blocks longest first in
+// turns of its 32 compute units, every other turn backwards: the unit with the longest block of one turn has the shortest of the next.
+// Head by head instead, the first units had the longest block of every head (4 heads of 64 channels, 1503 tokens 42.1 -> 32.1 us, 2203
+// 60.6 -> 43.5, 4103 138 -> 109; 16 x 4 heads, 1103 tokens 151 -> 137, 3603 1160 -> 1125).  Up to 256 blocks, one to a unit, take the plain
+// grid: nothing to level, and the divisions here are 0.4 us before the first load (154 tokens 13.7 -> 14.2).
+// The one grid dimension holds less than 2^32 threads: what does not fit it takes the plain grid too, whose three do.
+struct BlockDeal {
+    int parts_log2, xcd_parts;      // parts of a head (log2), parts per XCD
+};
+// Returns the workgroups, or 0 for the plain grid.
+inline unsigned deal_blocks(const lvlm_prefill_desc &d, long long blocks, BlockDeal &deal) {
+    const long long heads = (long long)d.B * d.Hq;
+    deal = BlockDeal{};
+    if (!d.causal || blocks <= 1 || blocks * heads <= 256) return 0;          // nothing to level
+    while (deal.parts_log2 < 3 && (heads << deal.parts_log2) % 8) ++deal.parts_log2;
+    deal.xcd_parts = (int)((heads << deal.parts_log2) / 8);
+    const long long grid = 8ll * deal.xcd_parts * (((blocks - 1) >> deal.parts_log2) + 1);
+    return grid * 256 < 1ll << 32 ? (unsigned)grid : 0;
+}
+// false: no block for this workgroup (its part of the head has one block less than others)
+__host__ __device__ __forceinline__ bool dealt_block(const BlockDeal &deal, int n_blocks, unsigned wg, int &head, int &qb) {
+    const int P = 1 << deal.parts_log2, xcd = wg & 7, seq = wg >> 3;
+    const int total = deal.xcd_parts * ((n_blocks + P - 1) >> deal.parts_log2);
+    const int turn = seq & ~31, last = min(turn + 31, total - 1);
+    const int rank = (seq & 32) ? turn + last - seq : seq;
+    const int level = rank / deal.xcd_parts, part = xcd * deal.xcd_parts + rank - level * deal.xcd_parts;
+    head = part >> deal.parts_log2;
+    qb = n_blocks - 1 - ((level << deal.parts_log2) + (part & (P - 1)));
+    return qb >= 0;
+}
+
+// ---- the kernel that shares its tiles ----
+// Whether the fp32 kernel that shares its tiles is the faster one, from 680 shapes timed both ways (1 to 960 heads, 20 to
+// 4288 tokens).  It works in turns of 256 workgroups of 128 rows, each as long as its longest block: it needs turns that are
+// nearly full.  Heads of 64 channels: where the four waves of the other kernel have equally many tiles (all but, of few
+// blocks), it reads less per product -- 256 heads x 384 tokens 95 -> 64 us, 512 heads x 128 tokens 45 -> 28 us, but 128 heads x 800 causal 144 -> 167 us.  Of 128
+// channels the other kernel is bound by reading K and V, and loses from three quarters of a turn on while the work is
+// small: 256 heads x 128 tokens 57 -> 31 us, 512 heads x 256 290 -> 189 us, 384 of 94 tokens 57 -> 43 us.
+// Causal blocks dealt out, beyond one turn, gain with their number (other kernel, dealt out too -> this one; before, with
+// a head's blocks one after the other, four to a head came to the same compute units in every turn): 128 heads x 500 tokens
+// 75.5 -> 66.7 us (91 before), 256 x 500 151 -> 109 (162), of 128 channels 448 x 512 591 -> 436 (625).  One turn of several blocks
+// has nothing to level with and waits for the longest: 64 heads x 512 tokens 59.5 -> 45.4 us with the other kernel, 84 x 380 48.2 -> 39.7, of 128
+// channels 56 x 500 110 -> 98, but 84 x 384 96.5 -> 89.4 with this one.  More than five blocks to a head stay with the other kernel: from 640 blocks on this one
+// is faster (64 heads x 1400 tokens 193 -> 182 us, 64 x 3600 1070 -> 974; 40 x 1700 174 -> 184), but a row's sums are one chain here and four there:
+// against 64 bits 9.0e-7 instead of 7.0e-7 (2-norm) at 3600 tokens.
+inline bool f32_shares_tiles(const lvlm_prefill_desc &d) {
+    const long long heads = (long long)d.B * d.Hq, nqb = (d.N + 127) / 128, wgs = heads * nqb;
+    const int tiles = (d.N + 31) / 32, n16 = (d.N + 15) / 16;
+    if (tiles < 2 && d.hd == 64) return false;
+    if (d.causal && nqb > 5) return false;
+    if (d.causal && wgs <= 256 && nqb > (d.hd == 64 ? 1 : 3)) return false;
+    const double fill = (double)wgs / (double)((wgs + 255) / 256 * 256);
+    // tiles a wave of the other kernel takes in turn, over its blocks of 16 rows; tiles a workgroup of this one takes
+    long long in_turn = 0, shared = 0;
+    if (d.causal) {
+        for (int x = 0; x < n16; ++x) in_turn += ((x < n16 - 1 ? 16 * x + 16 : d.N) + 127) / 128;
+        for (int x = 0; x < nqb; ++x) shared += (x < nqb - 1 ? 4 * (x + 1) : tiles);
+    } else {
+        in_turn = (long long)n16 * ((tiles + 3) / 4);
+        shared = nqb * tiles;
+    }
+    if (d.hd == 64) return fill > 0.9 && (double)(4 * in_turn) > (nqb <= 3 ? 6.7 : 7.8) * (double)shared;
+    return fill > 0.9 || (fill > (d.causal ? 0.78 : 0.71) && heads * in_turn <= 36 * 256);
+}
+
+// ---- the kernel a call takes ----
+struct F32Form {
+    bool shared;          // tiles shared by four waves of 32 rows, else blocks of 16 rows
+    bool two;             // ... two of them per workgroup
+    long long blocks;     // workgroups per head
+    unsigned dealt;       // workgroups in all if the blocks are dealt out, else 0
+    BlockDeal deal;
+};
+inline F32Form prefill_f32_form(const lvlm_prefill_desc &d) {
+    F32Form f{};
+    f.shared = f32_shares_tiles(d);
+    // Not shared: one block of 16 rows per workgroup; two (each K and V operand feeds two products, 64 bytes of L2 traffic per
+    // product instead of 128) once that still leaves many rounds of the chip: it is 3-4 % faster from about
+    // 16000 workgroups on and slower by up to 1.7 times below 4000
+    const long long n16 = (d.N + 15) / 16;
+    f.two = !f.shared && n16 * d.B * d.Hq >= 16384;
+    f.blocks = f.shared ? (d.N + 127) / 128 : f.two ? (n16 + 1) / 2 : n16;
+    f.dealt = deal_blocks(d, f.blocks, f.deal);
+    return f;
+}
+
+}  // namespace lvlm

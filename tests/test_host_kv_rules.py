@@ -6,17 +6,19 @@ import subprocess
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def _run(tmp_path, body):
-    """Compiles `body` (the statements of main) against the library's header, host side only, and runs it."""
+def _run(tmp_path, body, header="common.h"):
+    """Compiles `body` (the statements of main) against one of the library's headers, host side only, and runs it."""
     spec = importlib.util.spec_from_file_location("lvlm_build", os.path.join(ROOT, "paper_2509_00419_amd", "build.py"))
     build = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(build)
     src, exe = str(tmp_path / "rules.hip"), str(tmp_path / "rules")
     with open(src, "w") as f:
-        f.write('#include "common.h"\n#include <algorithm>\nusing namespace lvlm;\nint main() {\n' + body + "\n    return 0;\n}\n")
+        f.write(f'#include "{header}"\n#include <algorithm>\n#include <vector>\nusing namespace lvlm;\nint main() {{\n' + body +
+                "\n    return 0;\n}\n")
     subprocess.run([build.HIPCC, "--offload-host-only", "--offload-arch=gfx950", "-std=c++17", "-O1", "-I" + build.CSRC, "-Xarch_host",
                     "-fsanitize=undefined", "-Xarch_host", "-fsanitize-trap=undefined", src, "-o", exe], check=True)
-    assert subprocess.run([exe]).returncode == 0
+    code = subprocess.run([exe]).returncode
+    assert code == 0, code
 
 
 def test_fill_workgroups_with_work_are_spread_over_the_chip(tmp_path):
