@@ -441,9 +441,7 @@ __global__ __launch_bounds__(256) void attn_partial_f32_wide_kernel(AttnArgs a) 
             for (int r = 0; r < 16; ++r) oacc[nb][r] *= alpha;
 
         // the V tile is private to this wave: order the LDS traffic, no workgroup barrier
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync();
 
         // O^T += V^T P^T on the matrix cores.  The contraction index is free, so it is numbered the way
         // the probabilities already sit in this lane's registers: step s <-> entry acc_row(s, hf).  V is read transposed from LDS.
@@ -456,9 +454,7 @@ __global__ __launch_bounds__(256) void attn_partial_f32_wide_kernel(AttnArgs a) 
                 oacc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(va, p[s2], oacc[nb], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync();
         if (more) cur = nxt;
     }
 

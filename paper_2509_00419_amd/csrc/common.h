@@ -374,6 +374,13 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v)
 #undef LVLM_MIN_STEP
     return v;
 }
+// Orders the wave's LDS accesses before and after it, for values that lanes of one wave hand each other there: no workgroup barrier,
+// and no instruction (a wave's LDS operations run in order), but the compiler moves none of them across.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 // Any associative, commutative OP over the wave's 32-bit or 64-bit values, in every lane, by the same moves.
 template <class OP>
 __device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t v, OP op) {

@@ -121,6 +121,7 @@ __device__ __forceinline__ void prefill_write(const PrefillArgs &a, const Prefil
     const int hf = lane >> 5, l32 = lane & 31;
     const float l_tot = l_run + other_half(l_run);
     const float inv = 1.f / l_tot;
+    wave_sync();                            // the wave's block before has been read (said behind the reads, it sends their rows through scratch)
 #pragma unroll
     for (int cb = 0; cb < HD / 32; ++cb)
 #pragma unroll
@@ -130,6 +131,7 @@ __device__ __forceinline__ void prefill_write(const PrefillArgs &a, const Prefil
             u.y = pack_bf16(oacc[cb][4 * r4 + 2] * inv, oacc[cb][4 * r4 + 3] * inv);
             *reinterpret_cast<uint2 *>(io + l32 * P + 64 * cb + 16 * r4 + 8 * hf) = u;
         }
+    wave_sync();                            // the rows are read by other lanes than wrote them
     const int row = row0 + l32;
     if (hf == 0 && row < a.N) {
         const float lse = m_run * a.scale + __logf(l_tot);
