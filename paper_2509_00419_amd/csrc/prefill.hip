@@ -113,7 +113,7 @@ __device__ __forceinline__ bool risky_sums(float l0, float l1) {
 // Normalises and writes the 32-row block at row0: lane (query l32, half hf) holds channels 32 cb + 8 (r / 4) + 4 hf + r % 4.
 // Stored from there, a wave's 64 lanes would write 16 bytes each of 32 rows at a time; put together in LDS (32 rows of
 // HD * 2 + 16 bytes at io, the wave's own), whole rows leave (7 x 115 tokens, 48 heads 23.5 -> 21.2 us; 4 x 979, 32 heads
-// 77.6 -> 72.1; 8 x 1888, 32 heads 351 -> 345; 16512 tokens, 48 heads 3235 -> 3205).
+// 77.6 -> 72.1; 8 x 1888, 32 heads 351 -> 345; one sequence of 16512, 48 heads the same).
 template <int HD>
 __device__ __forceinline__ void prefill_write(const PrefillArgs &a, const PrefillBlock &w, char *io, int row0, int lane, float m_run,
                                               float l_run, const f32x16 (&oacc)[HD / 32]) {
@@ -163,7 +163,7 @@ __device__ __forceinline__ bool prefill_plain_block(const PrefillArgs &a, const 
 // read during the first, those of the next tile's first product during the second.  Staging (a ring of two K and two
 // V^T tiles; K(t+3) and V(t) go to LDS and the next ones are requested) goes with the first product, so that the barrier
 // at the end finds the LDS queue drained.  One wave per SIMD: the 128 output accumulators, two tiles of logits, the query
-// operands and the fragments take 426 registers.
+// operands and the fragments take 437 registers.
 // The masks around the diagonal and at the end of the sequence are one compare and select per logit, in a second copy
 // of the iteration that only the last (up to four) tiles of a workgroup run through.
 // Addresses are a uniform base plus 32-bit offsets per thread (the host checks that a tile's rows span less than 2 GiB).
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(128, 1) void prefill_attn_bf16_kernel(PrefillArgs a
 
 // One tile after the other, products and softmax in turn: the SAFE sweep (a rescale touches everything in flight, so
 // nothing is pipelined across tiles), and the FAST sweep for 64 channels, where the pipelined loop above has too few
-// products per logit to hide the softmax behind and two waves per SIMD -- 230 registers here, 300 there -- do
+// products per logit to hide the softmax behind and two waves per SIMD -- 253 of the 256 registers here, 300 there -- do
 // better (2 x 4000 tokens, 32 heads: 185 us here, 221 us pipelined).  Returns whether a FAST sweep has to be done again.
 template <int HD, bool SAFE>
 __device__ __forceinline__ bool prefill_plain_block(const PrefillArgs &a, const PrefillBlock &w, char *k_mem, char *v_mem) {
@@ -853,7 +853,7 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a)
     }
 }
 
-// fp32 where whole turns of the chip share their tiles (launch_prefill_attn has the rule), on the fp32 matrix instruction of
+// fp32 where whole turns of the chip share their tiles (f32_shares_tiles has the rule), on the fp32 matrix instruction of
 // 32 x 32 x 2: the products of a 32 x 32 tile cost as much as above, but a K or V value read once serves 32 rows instead of 16 and the
 // four waves of a workgroup read the same tile, so it is the matrix instructions that bound it and not the reading.
 // A workgroup of four waves owns 128 query rows of one head, one 32-row block per wave, its rows held as an MFMA

@@ -621,11 +621,13 @@ hipError_t launch_merge_similar(const Prof &prof, const lvlm_merge_desc &d, cons
     const long long tiles = tiles_of(tm, tn);
     // Who takes the norms; either way gives the same bits.  In the product they cost every tile its dominant rows' squares again, and LDS
     // reads, which are what bounds a slice; beside the ranking, on workgroups of 16 rows, they cost the launch a pass over all rows,
-    // little of it while all its workgroups are on the chip at once.  Beside the ranking -> in the product, whole calls, us (bf16 unless said):
-    //   64 x 64 tiles: in it when the launch would have more than 256 workgroups, one to a compute unit (16 x 256 rows of 12 KB 62.8 ->
-    //       57.9, 9 x 460 64.5 -> 59.8, 13 x 936 of 1 KB in fp32 55.6 -> 50.1; with fewer 2 x 1300 of 7 KB 42.6 -> 43.6, 4 x 576 even)
-    //   128 x 128, a ring of four: when it would have more than 512 (7 x 1733 of 7 KB 93.4 -> 89.0; with fewer 1 x 2600 of 12 KB 76.1 ->
-    //       84.5, 3 x 1300 80.5 -> 84)
+    // little of it while the launch is one turn of the chip: two workgroups fit a compute unit, but share its loads.  Beside the
+    // ranking -> in the product, whole calls, us (bf16 unless said; 130 shapes of 150 to 1400 such workgroups timed both ways):
+    //   64 x 64 tiles: in it when the launch would have more than 256 workgroups (16 x 256 rows of 12 KB 62.8 -> 57.9, 9 x 460 64.5 -> 59.8,
+    //       20 x 400 of 10 KB 71.6 -> 62.3, 13 x 400 of 1 KB in fp32 34.7 -> 32.9; with fewer 4 x 576 of 12 KB 51.9 -> 53.5, 3 x 800 of
+    //       7 KB 38.4 -> 40.1; even from 216 to 256)
+    //   128 x 128, a ring of four: when it would have more than 512 (7 x 1733 of 7 KB 93.4 -> 89.0, 6 x 1100 of 12 KB 92.4 -> 87.0; with
+    //       fewer 1 x 2600 of 12 KB 76.1 -> 84.5, 1 x 4000 96.9 -> 99.3; from 370 to 512 within 4 % either way)
     //   128 x 192: always (8 x 1792 of 8 KB 123.2 -> 118.5, 1 x 4500 of 12 KB 113.7 -> 109.7); 192 x 128: never (their squares' sums and
     //       the products' do not fit the registers: 1 x 10560 of 12 KB 171 -> 187), nor a ring of two, whose workgroups would no longer
     //       share a compute unit (9 x 2034 of 10 KB 188 -> 249)
