@@ -1380,9 +1380,18 @@ def test_kv_compress_moves_loaded_past_the_caches(ctx, dtype, d):
 
 
 # --------------------------------------------------------------------------- step 3b: similarity merge
+def _uneven_rows(hid, g, dtype):
+    """Rows of very different norms, each with most of its energy in one 128-byte slice of its own: a norm that misses a slice,
+    or takes one twice, changes which dominant token is nearest."""
+    per = 128 // (2 if dtype == torch.bfloat16 else 4)
+    B, n, C = hid.shape
+    loud = torch.randint(0, (C + per - 1) // per, (B, n, 1), generator=g) == torch.arange(C) // per
+    return hid * torch.where(loud, 6.0, 1.0) * torch.exp2(torch.randint(-5, 6, (B, n, 1), generator=g).float())
+
+
 def _similar_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed, clusters=0, with_size=True, extra=True,
-                  identical=False):
-    """extra: two more planes, or the widths of more weighted planes.
+                  identical=False, uneven=False):
+    """extra: two more planes, or the widths of more weighted planes; uneven: see _uneven_rows.
     GPU dominant set must equal the oracle's; each GPU assignment must be an arg-max of the oracle's
     fp64 cosines up to 1e-5 (exactly the oracle's choice wherever its margin is larger than that); merged
     values are checked against the oracle's merge under the GPU's assignment."""
@@ -1396,6 +1405,8 @@ def _similar_case(ctx, dtype, B, n_sys, n_img, n_txt, C, n_keep, seed, clusters=
             0.1 * torch.randn(B, n_img, C, generator=g)
     if identical:
         hid[:, n_sys:n_sys + n_img] = hid[:, n_sys:n_sys + 1]
+    if uneven:
+        hid = _uneven_rows(hid, g, dtype)
     hid = hid.to(dtype)
     score = torch.rand(B, n_img, generator=g)
     size = torch.randint(1, 4, (B, n_img), generator=g).float() if with_size else None
@@ -1499,7 +1510,7 @@ def test_merge_similar_tile_shapes(ctx, dtype, B, n_img, n_keep, C):
     (torch.bfloat16, 7, 1733, 1573, 328),     # ... in the product
     (torch.float32, 7, 1733, 1573, 72),
     (torch.bfloat16, 8, 1730, 1200, 328),     # 128 x 192
-    (torch.float32, 8, 1730, 1200, 840),      # ... fp32, 27 slices: every one of the eight sums is come back to
+    (torch.float32, 8, 1730, 1200, 840),      # ... fp32, 27 slices
     (torch.float32, 1, 10560, 560, 136),      # 192 x 128, beside
     (torch.bfloat16, 3, 3000, 1500, 328)])    # 128 x 128, two slots, beside
 def test_merge_similar_norms(ctx, dtype, B, n_img, n_keep, C):
@@ -1513,6 +1524,37 @@ def test_merge_similar_norms(ctx, dtype, B, n_img, n_keep, C):
     joined = [ctx.merge_similar([h.to(DEV)], score, img_begin=1, n_img=n_img, n_keep=n_keep, rules=[lv.RULE_TOP])[2]
               for h in (hid, scaled)]
     assert torch.equal(joined[0], joined[1])
+
+
+# batches that take the norms in the product, a sequence of which alone has them beside the ranking: more than eight slices of 128 bytes
+# (a thread comes back to its eight sums), the last one partial or whole
+NORMS_IN_PRODUCT = [
+    (torch.bfloat16, 11, 300, 150, 600), (torch.bfloat16, 11, 300, 150, 1088),            # 64 x 64 tiles; ten slices, seventeen
+    (torch.float32, 16, 300, 129, 296),
+    (torch.bfloat16, 7, 1733, 1573, 600), (torch.float32, 7, 1733, 1573, 544),            # 128 x 128, four slots
+    (torch.bfloat16, 8, 1730, 1200, 1096), (torch.float32, 8, 1730, 1200, 296)]           # 128 x 192
+
+
+@pytest.mark.parametrize("dtype,B,n_img,n_keep,C", NORMS_IN_PRODUCT)
+def test_merge_similar_norms_in_the_product(ctx, dtype, B, n_img, n_keep, C):
+    _similar_case(ctx, dtype, B, 1, n_img, 2, C, n_keep, 300 + C, extra=False, uneven=True)
+
+
+@pytest.mark.parametrize("dtype,B,n_img,n_keep,C", NORMS_IN_PRODUCT)
+def test_merge_similar_norms_have_the_same_bits_either_way(ctx, dtype, B, n_img, n_keep, C):
+    """Dominant rows in families that differ in the last bit of a few elements: cosines within a family are equal but for the last
+    bits of products and norms, which decide who is joined.  A sequence joins the same alone (its norms taken beside the ranking) as
+    in its batch."""
+    g = torch.Generator().manual_seed(C + n_img)
+    hid = torch.randn(B, 12, C, generator=g)[:, torch.randint(0, 12, (n_img,), generator=g)]
+    nudge = torch.rand(B, n_img, C, generator=g) < 4.0 / C
+    hid = torch.where(nudge, hid * (1.0 + (2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -20)), hid)
+    hid = (hid * torch.exp2(torch.randint(-5, 6, (B, n_img, 1), generator=g).float())).to(dtype).to(DEV)
+    score = torch.rand(B, n_img, generator=g).to(DEV)
+    kw = dict(img_begin=0, n_img=n_img, n_keep=n_keep, rules=[lv.RULE_TOP])
+    joined = ctx.merge_similar([hid], score, **kw)[2]
+    for b in range(B):
+        assert torch.equal(ctx.merge_similar([hid[b:b + 1]], score[b:b + 1], **kw)[2][0], joined[b])
 
 
 @pytest.mark.parametrize("n_img,n_keep,clusters", [(200, 60, 5), (700, 2, 2), (40, 39, 0)])

@@ -174,7 +174,7 @@ def test_prefill_attn_logits_far_above_the_first_tile(ctx):
 def test_prefill_attn_far_logits_in_the_middle_of_a_long_row(ctx):
     """One sequence of nine query blocks with few heads; logits that jump far above everything before them in the
     middle of the rows (natural-log distance 120 and more), so that only the workgroups whose rows reach those keys
-    take the fallback kernel, the others the plain one, in the same launch."""
+    do them again with the running reference, the others do not, in the same launch."""
     B, N, Hq, Hkv, d = 1, 1100, 4, 2, 128
     g = torch.Generator().manual_seed(5)
     q = 0.05 * torch.randn(B, N, Hq, d, generator=g)
@@ -196,13 +196,13 @@ def test_prefill_attn_far_logits_in_the_middle_of_a_long_row(ctx):
 
 
 @pytest.mark.parametrize("B,N,Hq,Hkv,d", [
-    (1, 200, 3, 1, 64), (1, 200, 11, 1, 128),     # heads that do not fill the eight XCDs: padding workgroups, a mark each
-    (16, 250, 32, 2, 64), (16, 250, 32, 2, 128),  # 1024 workgroups: one mark each, every place of the chip redoes blocks in turn
-    (35, 500, 16, 2, 64), (35, 500, 16, 2, 128),  # 2240: five marks a workgroup, several of them set
-    (1376, 300, 8, 1, 64)])                       # 33024: more than 64 marks a workgroup, a second round
+    (1, 200, 3, 1, 64), (1, 200, 11, 1, 128),     # heads that do not fill the eight XCDs: workgroups without a block
+    (16, 250, 32, 2, 64), (16, 250, 32, 2, 128),  # 1024 workgroups, several to a compute unit, some with a second sweep, some without
+    (35, 500, 16, 2, 64), (35, 500, 16, 2, 128),  # 2240: blocks of several tiles in front of the second sweep's
+    (1376, 300, 8, 1, 64)])                       # 33024: many turns of the chip
 def test_prefill_attn_many_far_logits(ctx, B, N, Hq, Hkv, d):
     """Every query block of two sequences out of three sees later logits far beyond the reference of its first tile (natural-log
-    distance 120), so that workgroups of the fallback kernel have several marked blocks to redo, one after the other."""
+    distance 120): its workgroup does it again with the running reference, in the LDS that the first sweep and its output used."""
     g = torch.Generator(device=DEV).manual_seed(N + d)
     q, k, v = (torch.randn(B, N, h, d, generator=g, device=DEV) for h in (Hq, Hkv, Hkv))
     a = (60.0 * d ** 0.5) ** 0.5
@@ -219,6 +219,29 @@ def test_prefill_attn_many_far_logits(ctx, B, N, Hq, Hkv, d):
     o_out, o_lse = O.prefill_attn(f64(q[pick].cpu()), f64(k[pick].cpu()), f64(v[pick].cpu()), dtype="bf16")
     assert rel_err(out[pick].float().cpu(), o_out) < 2e-2
     assert np.abs(lse[pick].cpu().numpy() - o_lse).max() < 1e-5 * np.abs(o_lse).max()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("wave", [0, 1])
+def test_prefill_attn_far_logits_of_one_wave(ctx, d, wave):
+    """Of a block's 128 rows only one wave's 64 see logits far beyond their first tile: the other wave has written its rows by then,
+    and writes them again.  Whole, ragged and single-wave blocks, rows of a wider array beside which nothing is written."""
+    B, N, Hq, Hkv = 3, 450, 5, 1
+    g = torch.Generator().manual_seed(70 + d + wave)
+    q, k, v = (torch.randn(B, N, h, d, generator=g) for h in (Hq, Hkv, Hkv))
+    a = (60.0 * d ** 0.5) ** 0.5
+    far = (torch.arange(N) // 64 % 2 == wave).float()[None, :, None]
+    q, k = 0.05 * q, 0.05 * k
+    q[..., 0] = a * far
+    k[..., 0] = a
+    k[:, :32, :, 0] = -a
+    q, k, v = q.bfloat16(), k.bfloat16(), v.bfloat16()
+    wide = torch.full((B, N, Hq, d + 8), -7.0, dtype=torch.bfloat16, device=DEV)
+    _, lse, _, _ = ctx.prefill_attn(q.to(DEV), k.to(DEV), v.to(DEV), out=wide[..., :d])
+    o_out, o_lse = O.prefill_attn(f64(q), f64(k), f64(v), dtype="bf16")
+    assert rel_err(wide[..., :d].float().cpu(), o_out) < 2e-2
+    assert np.abs(lse.cpu().numpy() - o_lse).max() < 1e-5 * np.abs(o_lse).max()
+    assert bool((wide[..., d:] == -7.0).all())
 
 
 @pytest.mark.parametrize("d,which", [(64, "k"), (128, "v"), (128, "kv")])
@@ -278,11 +301,43 @@ def test_prefill_attn_random_shapes(ctx):
             assert rel_err(sh.cpu(), osh) < 1e-5 and rel_err(sm.cpu(), osm) < 1e-5, case
 
 
-@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
-    (1, 1, 1, 1, 64, True), (2, 15, 4, 4, 64, True), (1, 16, 2, 1, 128, False), (1, 17, 4, 2, 64, True),
-    (1, 97, 3, 1, 128, True), (1, 128, 2, 2, 64, True), (1, 129, 2, 2, 64, False), (2, 161, 4, 1, 128, True),
-    (683, 33, 8, 4, 64, True), (1, 385, 24, 4, 128, True)])       # two 16-row blocks per workgroup; a chip a third full
-def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causal):
+# fp32 calls with the launch their sizes take (tests/test_host_prefill_rules.py holds the library's rule to it): blocks of 16 rows, one or
+# two to a workgroup, or tiles shared by 128 rows; "dealt": causal blocks dealt out to the compute units
+F32_ROW_BLOCKS = [
+    (1, 1, 1, 1, 64, True, "one"), (2, 15, 4, 4, 64, True, "one"), (1, 16, 2, 1, 128, False, "one"), (1, 17, 4, 2, 64, True, "one"),
+    (1, 97, 3, 1, 128, True, "one"), (1, 128, 2, 2, 64, True, "one"), (1, 129, 2, 2, 64, False, "one"),
+    (2, 161, 4, 1, 128, True, "one"), (683, 33, 8, 4, 64, True, "two dealt"), (1, 385, 24, 4, 128, True, "one dealt")]
+F32_WHOLE_TURNS = [
+    (64, 50, 4, 4, 64, True, "shared"), (64, 64, 4, 2, 64, False, "shared"),             # one block, one turn of the chip
+    (32, 125, 8, 4, 64, True, "shared"), (64, 128, 4, 1, 64, False, "shared"),
+    (32, 250, 4, 4, 64, False, "shared"), (64, 640, 4, 4, 64, False, "shared"),          # two blocks, five
+    (64, 250, 4, 2, 64, True, "shared dealt"), (64, 255, 4, 4, 64, True, "shared dealt"),        # causal, beyond one turn: two blocks
+    (32, 500, 4, 4, 64, True, "shared dealt"), (63, 500, 2, 1, 64, True, "shared dealt"),        # four, of 128 heads and of quarters of 126
+    (64, 640, 4, 4, 64, True, "shared dealt"),                                                   # five
+    (32, 250, 4, 4, 64, True, "one dealt"), (16, 510, 4, 4, 64, True, "one dealt"),      # one turn of several causal blocks: not shared
+    (8, 610, 26, 2, 64, True, "one dealt"), (64, 130, 4, 4, 64, True, "one dealt"),      # a last turn of 16, a last block of two rows
+    (64, 1, 4, 4, 128, True, "shared"), (64, 31, 4, 4, 128, False, "shared"), (50, 33, 4, 2, 128, True, "shared"),
+    (32, 129, 4, 1, 128, True, "shared"),                                                # 200 of 256 places; two blocks in one turn
+    (16, 500, 4, 4, 128, False, "shared"), (8, 640, 7, 1, 128, True, "one dealt"),
+    (100, 643, 4, 2, 128, True, "two dealt"),                                            # six blocks: sixteen-row blocks again
+    (683, 33, 8, 4, 64, False, "two"), (205, 128, 10, 2, 128, False, "two")]             # ... a last turn of two
+F32_DEALT = [
+    (1, 1024, 4, 4, 64, True, "one"),               # 256 blocks: the plain grid
+    (1, 1025, 4, 2, 64, True, "one dealt"),         # 260: halves of heads, a turn of an XCD's 32 compute units and one block
+    (1, 4097, 1, 1, 64, True, "one dealt"),         # eighths of one head, 33 levels of which the last is one part's
+    (1, 1377, 3, 1, 128, True, "one dealt"),        # three eighths to an XCD, a turn and one block
+    (3, 1300, 2, 1, 64, True, "one dealt"),         # quarters
+    (5, 700, 5, 1, 64, True, "one dealt"),          # 25 heads of 44 blocks
+    (2, 660, 8, 2, 128, False, "one"),              # whole heads, no mask
+    (64, 129, 5, 1, 64, True, "one dealt"),         # nine blocks to each of 320 heads
+    (16, 500, 8, 2, 64, True, "shared dealt"),      # shared tiles, four blocks of 128 heads
+    (9, 500, 28, 4, 128, True, "shared dealt"),     # ... of 252 heads in halves
+    (27, 700, 4, 2, 64, True, "one dealt"),         # six: blocks of 16 rows, whole turns
+    (16, 512, 4, 4, 64, True, "one dealt")]         # one turn of four blocks: not shared
+
+
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal,form", F32_ROW_BLOCKS)
+def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causal, form):
     fused, split = _qkv(B, N, Hq, Hkv, d, torch.float32, 500 + N, 2.0)
     q, k, v = split(fused)
     out, lse, _, _ = ctx.prefill_attn(*split(fused.to(DEV)), causal=causal)
@@ -291,13 +346,8 @@ def test_prefill_attn_fp32_row_blocks_and_key_tiles(ctx, B, N, Hq, Hkv, d, causa
     assert np.abs(lse.cpu().numpy() - o_lse).max() < 1e-5 * max(1.0, np.abs(o_lse).max())
 
 
-@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
-    (64, 50, 4, 4, 64, True), (64, 64, 4, 2, 64, False), (32, 125, 8, 4, 64, True), (64, 128, 4, 1, 64, False),   # one block, one turn
-    (32, 250, 4, 4, 64, False), (32, 250, 4, 4, 64, True), (16, 510, 4, 4, 64, True), (8, 610, 26, 2, 64, True),  # up to five blocks
-    (64, 1, 4, 4, 128, True), (64, 31, 4, 4, 128, False), (50, 33, 4, 2, 128, True), (32, 129, 4, 1, 128, True),  # 200 of 256 places
-    (16, 500, 4, 4, 128, False), (8, 640, 7, 1, 128, True),
-    (100, 643, 4, 2, 128, True)])                  # six blocks: sixteen-row blocks again, two per workgroup
-def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal):
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal,form", F32_WHOLE_TURNS)
+def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal, form):
     """fp32 launches of whole turns of the chip: the kernel whose four waves share their tiles, at the edges of its rule, of
     its 128-row blocks and of its 32-key tiles.  Sampled sequences against the oracle, every row written."""
     fused, split = _qkv(B, N, Hq, Hkv, d, torch.float32, 700 + N, 2.0)
@@ -311,19 +361,8 @@ def test_prefill_attn_fp32_shared_tiles(ctx, B, N, Hq, Hkv, d, causal):
     assert np.abs(lse[pick].cpu().numpy() - o_lse).max() < 1e-5 * max(1.0, np.abs(o_lse).max())
 
 
-@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal", [
-    (1, 1024, 4, 4, 64, True),          # 256 blocks: the plain grid
-    (1, 1025, 4, 2, 64, True),          # 260: halves of heads, two turns and one block of an XCD's 32 compute units
-    (1, 4097, 1, 1, 64, True),          # eighths of one head, 33 levels of which the last is one part's
-    (1, 1377, 3, 1, 128, True),         # three eighths to an XCD, a turn and one block
-    (3, 1300, 2, 1, 64, True),          # quarters
-    (5, 700, 5, 1, 64, True),           # 25 heads of 44 blocks
-    (2, 660, 8, 2, 128, False),         # whole heads, no mask
-    (64, 129, 5, 1, 64, True),          # shared tiles: two blocks to each of 320 heads
-    (9, 500, 28, 4, 128, True),         # ... four, 252 heads in halves
-    (27, 700, 4, 2, 64, True),          # six: blocks of 16 rows, whole turns
-    (16, 512, 4, 4, 64, True)])         # one turn of four blocks: not shared
-def test_prefill_attn_fp32_blocks_dealt_to_compute_units(ctx, B, N, Hq, Hkv, d, causal):
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,causal,form", F32_DEALT)
+def test_prefill_attn_fp32_blocks_dealt_to_compute_units(ctx, B, N, Hq, Hkv, d, causal, form):
     """Every block of every head is done once, however heads are cut for the XCDs and turns end."""
     fused, split = _qkv(B, N, Hq, Hkv, d, torch.float32, 900 + N, 2.0)
     out = torch.full((B, N, Hq, d), float("nan"), device=DEV)

@@ -56,3 +56,23 @@ def test_launches_of_any_size_fit_their_grid(tmp_path):
     if (prefill_f32_form(d).dealt) return 6;                    // 2^24 workgroups and more
     d.B = 30000;
     if (!prefill_f32_form(d).dealt) return 7;""", HEADER)
+
+
+def test_gpu_tests_take_the_launches_they_name(tmp_path):
+    """The fp32 cases of the GPU tests name the kernel they are for: a rule that moves takes no kernel out of the tests unseen."""
+    from test_gpu_prefill_attn import F32_DEALT, F32_ROW_BLOCKS, F32_WHOLE_TURNS
+    cases = F32_ROW_BLOCKS + F32_WHOLE_TURNS + F32_DEALT
+    assert {(d, form) for _, _, _, _, d, _, form in cases} == {
+        (d, form + dealt) for d in (64, 128) for form in ("one", "two", "shared") for dealt in ("", " dealt")}
+    rows = ", ".join("{%d, %d, %d, %d, %d, %d, %d, %d}" % (*c[:6], ["one", "two", "shared"].index(c[6].split()[0]), "dealt" in c[6])
+                     for c in cases)
+    _run(tmp_path, r"""
+    const int cases[][8] = {%s};
+    int i = 0;
+    for (const auto &c : cases) {
+        lvlm_prefill_desc d{};
+        d.dtype = LVLM_F32; d.B = c[0]; d.N = c[1]; d.Hq = c[2]; d.Hkv = c[3]; d.hd = c[4]; d.causal = c[5];
+        const F32Form f = prefill_f32_form(d);
+        ++i;
+        if ((f.shared ? 2 : f.two ? 1 : 0) != c[6] || (f.dealt != 0) != (c[7] != 0)) return i;
+    }""" % rows, HEADER)
