@@ -569,7 +569,7 @@ SimWs sim_ws(const lvlm_merge_desc &d) {
     w.inv_norm = take(n * 4);
     w.best = take((size_t)d.B * (r > 0 ? r : 1) * 8);
     w.assign = take(n * 4);
-    w.rank2 = take(n * 4);
+    w.rank2 = take(rank_search_form(d.n_img, d.B).parts > 1 ? n * 4 : 0);     // (the order by owner needs ranks only where searches add up in them)
     w.order = take(n * 4);
     w.owner = take(n * 4);
     w.sorted = take(rank_scratch_bytes(d.n_img, d.B));     // sorted blocks of the two rankings, used in turn

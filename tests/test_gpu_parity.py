@@ -1005,13 +1005,14 @@ def test_no_call_writes_past_the_workspace_it_asked_for(ctx):
             dev = [t.to(DEV) for t in _cache(torch.bfloat16, 3, 2, Lmax, 64, lens, 170)]
             c.kv_compress(*dev, len_bound=bound, reserve=reserve, **kw)
         _guarded(compress)
-    # merge: counting ranks and sorted blocks; scoring: the three launch forms
-    for n_img, n_keep, B in ((1333, 400, 3), (9000, 3000, 2)):
-        def merge(c, reserve):
-            hid = _rand((B, n_img + 12, 264), torch.bfloat16, 180).to(DEV)
-            score = torch.rand(B, n_img, generator=torch.Generator().manual_seed(181)).to(DEV)
-            c.merge_compact([hid], score, img_begin=5, n_img=n_img, n_keep=n_keep, reserve=reserve)
-        _guarded(merge)
+    # merges: counting ranks, sorted blocks in all forms of their searches; scoring: the three launch forms
+    for n_img, n_keep, B in ((1333, 400, 3), (9000, 3000, 2), (4097, 30, 9), (33001, 40, 1)):
+        for what in ("merge_compact", "merge_similar"):
+            def merge(c, reserve):
+                hid = _rand((B, n_img + 12, 264), torch.bfloat16, 180).to(DEV)
+                score = torch.rand(B, n_img, generator=torch.Generator().manual_seed(181)).to(DEV)
+                getattr(c, what)([hid], score, img_begin=5, n_img=n_img, n_keep=n_keep, reserve=reserve)
+            _guarded(merge)
     # (two passes, a chunk per workgroup, shared tiles in one launch, shared tiles with the keys in runs)
     for B, N, T, n_img, Hq, Hkv, form in ((1, 5000, 64, 4800, 8, 2, 0), (1, 845, 64, 717, 8, 2, 1), (48, 986, 96, 890, 8, 2, 2),
                                           (4, 2200, 128, 2072, 48, 8, 3)):
