@@ -686,15 +686,18 @@ __device__ __forceinline__ float word(const uint4 &v, int c) {
 struct F32Block {
     int b, h, qb;
 };
+// How a launch's blocks go out: the plain grid, dealt out, or dealt out an XCD's heads in groups.
+enum { kPlain, kDealt, kGrouped };
+template <int DEAL>
 __device__ __forceinline__ bool dealt_to(const PrefillArgs &a, int n_blocks, F32Block &w) {
     int head;
-    const bool any = dealt_block(a.deal, n_blocks, blockIdx.x, head, w.qb);
+    const bool any = dealt_block<DEAL == kGrouped>(a.deal, n_blocks, blockIdx.x, head, w.qb);
     w.b = head / a.Hq;
     w.h = head - w.b * a.Hq;
     return any;
 }
 
-template <int HD, int QB, bool DEALT>
+template <int HD, int QB, int DEAL>
 __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a) {
     constexpr int NW = HD / 16;             // 16-byte words of a row per lane
     constexpr int CPL = HD / 16;            // channels per lane
@@ -707,8 +710,8 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     F32Block blk{(int)blockIdx.z, (int)blockIdx.y, (int)(gridDim.x - 1 - blockIdx.x)};      // longest blocks first
-    if constexpr (DEALT)
-        if (!dealt_to(a, (a.N + 16 * QB - 1) / (16 * QB), blk)) return;
+    if constexpr (DEAL != kPlain)
+        if (!dealt_to<DEAL>(a, (a.N + 16 * QB - 1) / (16 * QB), blk)) return;
     const int h = blk.h, b = blk.b, g = h / a.G;
     const int q0 = blk.qb * 16 * QB;
     const int kmax = a.causal ? min(a.N, q0 + 16 * QB) : a.N;
@@ -863,7 +866,7 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_kernel(PrefillArgs a)
 // are rescaled when it moves).  For O^T += V^T P^T the contraction of one instruction is two keys, one per
 // half-wave: exactly the two keys the two halves hold in the same accumulator register, so register r of the
 // probabilities is the second operand as it stands and the first is V[that key][channel] read from the tile.
-template <int HD, bool DEALT>
+template <int HD, int DEAL>
 __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(PrefillArgs a) {
     constexpr int ROWB = HD * 4;
     constexpr int KP = ROWB + 16;           // tile pitch: odd multiple of 16 bytes
@@ -879,8 +882,8 @@ __global__ __launch_bounds__(256, 1) void prefill_attn_f32_shared_kernel(Prefill
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hf = lane >> 5, l32 = lane & 31;
     F32Block blk{(int)blockIdx.z, (int)blockIdx.y, (int)(gridDim.x - 1 - blockIdx.x)};      // longest blocks first
-    if constexpr (DEALT)
-        if (!dealt_to(a, a.nqb, blk)) return;
+    if constexpr (DEAL != kPlain)
+        if (!dealt_to<DEAL>(a, a.nqb, blk)) return;
     const int h = blk.h, b = blk.b, g = h / a.G;
     const int q0 = blk.qb * 128, blk0 = q0 + 32 * wave;
     const int row = blk0 + l32;
@@ -1061,12 +1064,14 @@ hipError_t launch_prefill_attn(const Prof &prof, const lvlm_prefill_desc &d, con
 #define LVLM_F32(KERNEL, ...)                                                                                              \
     if (d.hd == 128) LVLM_LAUNCH(prof, (KERNEL<128, __VA_ARGS__>), grid, dim3(256), 0, stream, a);                         \
     else LVLM_LAUNCH(prof, (KERNEL<64, __VA_ARGS__>), grid, dim3(256), 0, stream, a)
-        if (f.shared && f.dealt) { LVLM_F32(prefill_attn_f32_shared_kernel, true); }
-        else if (f.shared) { LVLM_F32(prefill_attn_f32_shared_kernel, false); }
-        else if (f.two && f.dealt) { LVLM_F32(prefill_attn_f32_kernel, 2, true); }
-        else if (f.two) { LVLM_F32(prefill_attn_f32_kernel, 2, false); }
-        else if (f.dealt) { LVLM_F32(prefill_attn_f32_kernel, 1, true); }
-        else { LVLM_F32(prefill_attn_f32_kernel, 1, false); }
+        if (f.shared && f.dealt) { LVLM_F32(prefill_attn_f32_shared_kernel, kDealt); }
+        else if (f.shared) { LVLM_F32(prefill_attn_f32_shared_kernel, kPlain); }
+        else if (f.two && f.grouped) { LVLM_F32(prefill_attn_f32_kernel, 2, kGrouped); }
+        else if (f.two && f.dealt) { LVLM_F32(prefill_attn_f32_kernel, 2, kDealt); }
+        else if (f.two) { LVLM_F32(prefill_attn_f32_kernel, 2, kPlain); }
+        else if (f.grouped) { LVLM_F32(prefill_attn_f32_kernel, 1, kGrouped); }
+        else if (f.dealt) { LVLM_F32(prefill_attn_f32_kernel, 1, kDealt); }
+        else { LVLM_F32(prefill_attn_f32_kernel, 1, kPlain); }
 #undef LVLM_F32
     }
     prof.end();

@@ -7,36 +7,67 @@ namespace lvlm {
 
 // ---- causal blocks dealt out to the compute units ----
 // Workgroup number -> (head, block), for blocks that are on the chip beside each other: causal ones are as long as their
-// last row, so what a compute unit is handed adds up to its time.  Heads are cut into parts (every P-th block) until the eight XCDs --
-// workgroups with the same remainder -- get equally many, neighbours in memory order; an XCD takes its parts' blocks longest first in
+// last row, so what a compute unit is handed adds up to its time.  The eight XCDs -- workgroups with the same remainder -- get
+// equally many heads, or parts of heads (every P-th block), neighbours in memory order; an XCD takes its parts' blocks longest first in
 // turns of its 32 compute units, every other turn backwards: the unit with the longest block of one turn has the shortest of the next.
 // Head by head instead, the first units had the longest block of every head (4 heads of 64 channels, 1503 tokens 42.1 -> 32.1 us, 2203
-// 60.6 -> 43.5, 4103 138 -> 109; 16 x 4 heads, 1103 tokens 151 -> 137, 3603 1160 -> 1125).  Up to 256 blocks, one to a unit, take the plain
-// grid: nothing to level, and the divisions here are 0.4 us before the first load (154 tokens 13.7 -> 14.2).
+// 60.6 -> 43.5, 4103 138 -> 109; 16 x 4 heads, 1103 tokens 151 -> 137, 3603 1160 -> 1125).
+// P is the one that leaves the fewest workgroups, idle ones among them: heads may be no multiple of eight, then the last XCD has fewer
+// parts, and blocks none of P, then some parts have a block less.  (Always parts enough for eight equal shares: 1007 heads of two blocks
+// 24.7 us, 12.4 so; 866 heads of 138 tokens, 128 channels, 378 -> 200.)  Of few levels parts mix up the order of lengths, and heads whole are
+// preferred up to a fifteenth more workgroups (306 heads of four blocks, 128 channels 392 -> 288 us).
+// An XCD works on as many parts at a time as have K and V of 6 MB between them, which its 4 MB L2 serves about as well as if they fitted: all of
+// its heads side by side read K and V from memory once for every level (heads x tokens, all heads side by side -> in groups; the plain grid:
+// 506 x 405 220 -> 178 us; 183, 234 x 988 466 -> 357; 371, of 128 channels 303 x 731 828 -> 692; 697.  3 MB and 9 MB: 0.6 % behind on
+// average, at worst 7 and 14 %.)  The kernel that shares its tiles reads them an eighth as often, and groups only disturb its few levels (256
+// heads x 500 95.6 -> 110).
+// The plain grid stays for up to 256 blocks, one to a unit: nothing to level, and the divisions here are 0.4 us before the first load (154
+// tokens 13.7 -> 14.2).  So it does up to 112 tokens, where every wave has one tile of 32 keys at most, but for more than 768 blocks of 64
+// channels (three to a unit at once) of more than 64 tokens (plain -> dealt out, 64 channels: 122 heads x 61 tokens 6.4 -> 6.9, 121 x 88 7.7 ->
+// 8.6, 394 x 112 24.6 -> 22.9; 128 channels: 180 x 106 31.9 -> 33.9).  Else, of 500 shapes timed both ways, dealt out 11 % faster on average
+// and 2.5 % behind at worst (97 and 209 heads).
 // The one grid dimension holds less than 2^32 threads: what does not fit it takes the plain grid too, whose three do.
 struct BlockDeal {
-    int parts_log2, xcd_parts;      // parts of a head (log2), parts per XCD
+    int heads, parts_log2, xcd_parts;      // parts of a head (log2), parts per XCD
+    int group;                             // ... of which it takes so many at a time
 };
-// Returns the workgroups, or 0 for the plain grid.
-inline unsigned deal_blocks(const lvlm_prefill_desc &d, long long blocks, BlockDeal &deal) {
-    const long long heads = (long long)d.B * d.Hq;
+// Returns the workgroups, or 0 for the plain grid.  rows: of a block.
+inline unsigned deal_blocks(const lvlm_prefill_desc &d, int rows, BlockDeal &deal) {
+    const long long heads = (long long)d.B * d.Hq, blocks = (d.N + rows - 1) / rows;
     deal = BlockDeal{};
-    if (!d.causal || blocks <= 1 || blocks * heads <= 256) return 0;          // nothing to level
-    while (deal.parts_log2 < 3 && (heads << deal.parts_log2) % 8) ++deal.parts_log2;
-    deal.xcd_parts = (int)((heads << deal.parts_log2) / 8);
-    const long long grid = 8ll * deal.xcd_parts * (((blocks - 1) >> deal.parts_log2) + 1);
+    if (!d.causal || blocks <= 1 || blocks * heads <= 256) return 0;
+    if (d.N <= 64 || (d.N <= 112 && (d.hd == 128 || blocks * heads <= 768))) return 0;
+    long long grid = 0;
+    for (int log2 = 0; log2 <= 3; ++log2) {
+        const long long parts = ((heads << log2) + 7) / 8, levels = ((blocks - 1) >> log2) + 1, wgs = 8 * parts * levels;
+        if (grid && (levels < 8 ? wgs * 16 >= grid * 15 : wgs >= grid)) continue;
+        grid = wgs;
+        deal = BlockDeal{(int)heads, log2, (int)parts, (int)parts};
+    }
+    const long long kv_bytes = 2ll * d.N * d.hd * sizeof(float), sharing = (long long)(d.Hq / d.Hkv) << deal.parts_log2;
+    int group = 4;
+    while (2 * group * kv_bytes <= sharing * (6 << 20)) group *= 2;
+    if (rows < 128 && 2ll * deal.xcd_parts > 3ll * group) deal.group = group;      // (no small group left over)
     return grid * 256 < 1ll << 32 ? (unsigned)grid : 0;
 }
-// false: no block for this workgroup (its part of the head has one block less than others)
+// false: no block for this workgroup.  GROUPED: group < xcd_parts
+template <bool GROUPED>
 __host__ __device__ __forceinline__ bool dealt_block(const BlockDeal &deal, int n_blocks, unsigned wg, int &head, int &qb) {
     const int P = 1 << deal.parts_log2, xcd = wg & 7, seq = wg >> 3;
-    const int total = deal.xcd_parts * ((n_blocks + P - 1) >> deal.parts_log2);
-    const int turn = seq & ~31, last = min(turn + 31, total - 1);
-    const int rank = (seq & 32) ? turn + last - seq : seq;
-    const int level = rank / deal.xcd_parts, part = xcd * deal.xcd_parts + rank - level * deal.xcd_parts;
+    const int levels = (n_blocks + P - 1) >> deal.parts_log2;
+    int at = seq, first = 0, parts = deal.xcd_parts;
+    if constexpr (GROUPED) {
+        const int g = seq / (deal.group * levels);
+        at = seq - g * deal.group * levels;
+        first = g * deal.group;
+        parts = min(deal.group, parts - first);
+    }
+    const int turn = at & ~31, last = min(turn + 31, parts * levels - 1);
+    const int rank = (at & 32) ? turn + last - at : at;
+    const int level = rank / parts, part = xcd * deal.xcd_parts + first + rank - level * parts;
     head = part >> deal.parts_log2;
     qb = n_blocks - 1 - ((level << deal.parts_log2) + (part & (P - 1)));
-    return qb >= 0;
+    return qb >= 0 && head < deal.heads;
 }
 
 // ---- the kernel that shares its tiles ----
@@ -79,6 +110,7 @@ struct F32Form {
     bool two;             // ... two of them per workgroup
     long long blocks;     // workgroups per head
     unsigned dealt;       // workgroups in all if the blocks are dealt out, else 0
+    bool grouped;         // ... and an XCD's heads taken in groups
     BlockDeal deal;
 };
 inline F32Form prefill_f32_form(const lvlm_prefill_desc &d) {
@@ -89,8 +121,10 @@ inline F32Form prefill_f32_form(const lvlm_prefill_desc &d) {
     // 16000 workgroups on and slower by up to 1.7 times below 4000
     const long long n16 = (d.N + 15) / 16;
     f.two = !f.shared && n16 * d.B * d.Hq >= 16384;
-    f.blocks = f.shared ? (d.N + 127) / 128 : f.two ? (n16 + 1) / 2 : n16;
-    f.dealt = deal_blocks(d, f.blocks, f.deal);
+    const int rows = f.shared ? 128 : f.two ? 32 : 16;
+    f.blocks = (d.N + rows - 1) / rows;
+    f.dealt = deal_blocks(d, rows, f.deal);
+    f.grouped = f.dealt && f.deal.group < f.deal.xcd_parts;
     return f;
 }
 

@@ -302,11 +302,11 @@ def test_prefill_attn_random_shapes(ctx):
 
 
 # fp32 calls with the launch their sizes take (tests/test_host_prefill_rules.py holds the library's rule to it): blocks of 16 rows, one or
-# two to a workgroup, or tiles shared by 128 rows; "dealt": causal blocks dealt out to the compute units
+# two to a workgroup, or tiles shared by 128 rows; "dealt": causal blocks dealt out to the compute units, "grouped": an XCD's heads in groups
 F32_ROW_BLOCKS = [
     (1, 1, 1, 1, 64, True, "one"), (2, 15, 4, 4, 64, True, "one"), (1, 16, 2, 1, 128, False, "one"), (1, 17, 4, 2, 64, True, "one"),
     (1, 97, 3, 1, 128, True, "one"), (1, 128, 2, 2, 64, True, "one"), (1, 129, 2, 2, 64, False, "one"),
-    (2, 161, 4, 1, 128, True, "one"), (683, 33, 8, 4, 64, True, "two dealt"), (1, 385, 24, 4, 128, True, "one dealt")]
+    (2, 161, 4, 1, 128, True, "one"), (683, 33, 8, 4, 64, True, "two"), (1, 385, 24, 4, 128, True, "one dealt")]
 F32_WHOLE_TURNS = [
     (64, 50, 4, 4, 64, True, "shared"), (64, 64, 4, 2, 64, False, "shared"),             # one block, one turn of the chip
     (32, 125, 8, 4, 64, True, "shared"), (64, 128, 4, 1, 64, False, "shared"),
@@ -319,8 +319,13 @@ F32_WHOLE_TURNS = [
     (64, 1, 4, 4, 128, True, "shared"), (64, 31, 4, 4, 128, False, "shared"), (50, 33, 4, 2, 128, True, "shared"),
     (32, 129, 4, 1, 128, True, "shared"),                                                # 200 of 256 places; two blocks in one turn
     (16, 500, 4, 4, 128, False, "shared"), (8, 640, 7, 1, 128, True, "one dealt"),
-    (100, 643, 4, 2, 128, True, "two dealt"),                                            # six blocks: sixteen-row blocks again
-    (683, 33, 8, 4, 64, False, "two"), (205, 128, 10, 2, 128, False, "two")]             # ... a last turn of two
+    (100, 643, 4, 2, 128, True, "two grouped"),                                          # six blocks: sixteen-row blocks again
+    (683, 33, 8, 4, 64, False, "two"), (205, 128, 10, 2, 128, False, "two"),             # ... a last turn of two
+    (100, 700, 4, 2, 64, True, "two grouped"), (100, 700, 4, 1, 64, True, "two dealt"), (50, 643, 8, 1, 128, True, "two dealt"),
+    (23, 194, 9, 3, 128, True, "shared dealt"), (47, 500, 5, 5, 64, True, "shared dealt"),       # heads no multiple of eight: 207, 235
+    (31, 511, 8, 8, 64, True, "shared dealt"), (26, 700, 8, 8, 64, True, "one grouped"),         # 248; heads of an XCD in groups of 16
+    (40, 643, 10, 10, 128, True, "two grouped"), (60, 700, 7, 7, 64, True, "two grouped"),       # ... of 50, eight at a time; of 53
+    (13, 530, 12, 12, 128, True, "one grouped")]
 F32_DEALT = [
     (1, 1024, 4, 4, 64, True, "one"),               # 256 blocks: the plain grid
     (1, 1025, 4, 2, 64, True, "one dealt"),         # 260: halves of heads, a turn of an XCD's 32 compute units and one block
@@ -333,7 +338,11 @@ F32_DEALT = [
     (16, 500, 8, 2, 64, True, "shared dealt"),      # shared tiles, four blocks of 128 heads
     (9, 500, 28, 4, 128, True, "shared dealt"),     # ... of 252 heads in halves
     (27, 700, 4, 2, 64, True, "one dealt"),         # six: blocks of 16 rows, whole turns
-    (16, 512, 4, 4, 64, True, "one dealt")]         # one turn of four blocks: not shared
+    (16, 512, 4, 4, 64, True, "one dealt"),         # one turn of four blocks: not shared
+    (41, 64, 4, 4, 64, True, "one"), (25, 112, 4, 4, 64, True, "one"),                   # too short to level, 700 blocks
+    (29, 112, 4, 4, 64, True, "one dealt"), (16, 113, 3, 1, 64, True, "one dealt"),      # 812; 384, one token more
+    (37, 112, 5, 1, 128, True, "one"), (11, 113, 3, 1, 128, True, "one dealt"),          # of 128 channels
+    (29, 135, 13, 13, 64, True, "one dealt")]       # 377 heads of nine blocks, the last XCD with 41 instead of 48
 
 
 @pytest.mark.parametrize("B,N,Hq,Hkv,d,causal,form", F32_ROW_BLOCKS)
