@@ -118,6 +118,7 @@ template <int HD>
 __device__ __forceinline__ void prefill_write(const PrefillArgs &a, const PrefillBlock &w, char *io, int row0, int lane, float m_run,
                                               float l_run, const f32x16 (&oacc)[HD / 32]) {
     constexpr int P = HD * 2 + 16, UPR = HD / 8, RPI = 64 / UPR;    // row pitch; 16-byte units per row, rows per store
+    if (row0 >= a.N) return;                // (uniform)
     const int hf = lane >> 5, l32 = lane & 31;
     const float l_tot = l_run + other_half(l_run);
     const float inv = 1.f / l_tot;
