@@ -13,8 +13,8 @@ namespace lvlm {
 // Head by head instead, the first units had the longest block of every head (4 heads of 64 channels, 1503 tokens 42.1 -> 32.1 us, 2203
 // 60.6 -> 43.5, 4103 138 -> 109; 16 x 4 heads, 1103 tokens 151 -> 137, 3603 1160 -> 1125).
 // P is the one that leaves the fewest workgroups, idle ones among them: heads may be no multiple of eight, then the last XCD has fewer
-// parts, and blocks none of P, then some parts have a block less.  (Always parts enough for eight equal shares: 1007 heads of two blocks
-// 24.7 us, 12.4 so; 866 heads of 138 tokens, 128 channels, 378 -> 200.)  Of few levels parts mix up the order of lengths, and heads whole are
+// parts, and blocks none of P, then some parts have a block less.  (Always parts enough for eight equal shares: 577 heads of
+// nine blocks 51 us, 44 so; 866 of two blocks, 128 channels, 378 -> 200.)  Of few levels parts mix up the order of lengths, and heads whole are
 // preferred up to a fifteenth more workgroups (306 heads of four blocks, 128 channels 392 -> 288 us).
 // An XCD works on as many parts at a time as have K and V of 6 MB between them, which its 4 MB L2 serves about as well as if they fitted: all of
 // its heads side by side read K and V from memory once for every level (heads x tokens, all heads side by side -> in groups; the plain grid:
@@ -22,9 +22,9 @@ namespace lvlm {
 // average, at worst 7 and 14 %.)  The kernel that shares its tiles reads them an eighth as often, and groups only disturb its few levels (256
 // heads x 500 95.6 -> 110).
 // The plain grid stays for up to 256 blocks, one to a unit: nothing to level, and the divisions here are 0.4 us before the first load (154
-// tokens 13.7 -> 14.2).  So it does up to 112 tokens, where every wave has one tile of 32 keys at most, but for more than 768 blocks of 64
+// tokens 13.7 -> 14.2).  So it does up to 112 tokens, where no wave has more than one tile of 32 keys, but for more than 768 blocks of 64
 // channels (three to a unit at once) of more than 64 tokens (plain -> dealt out, 64 channels: 122 heads x 61 tokens 6.4 -> 6.9, 121 x 88 7.7 ->
-// 8.6, 394 x 112 24.6 -> 22.9; 128 channels: 180 x 106 31.9 -> 33.9).  Else, of 500 shapes timed both ways, dealt out 11 % faster on average
+// 8.6, 394 x 112 24.6 -> 22.9; 128 channels: 180 x 106 31.9 -> 33.9).  Else, of some 400 shapes timed both ways, dealt out is 9 % faster on average
 // and 2.5 % behind at worst (97 and 209 heads).
 // The one grid dimension holds less than 2^32 threads: what does not fit it takes the plain grid too, whose three do.
 struct BlockDeal {
